@@ -329,7 +329,7 @@ int fp8_scaled_mm(const uint8_t* a, int64_t lda, int fmt_a, const float* scale_a
         if (!aligned(scale_a, 4) || !aligned(scale_b, 4)) return fail(FP8_ERR_ALIGN, "fp8_scaled_mm: scales not 4-byte aligned");
     }
     if (flags & FP8_EPILOGUE_SIGMOID) {
-        // the fused activation lives in the LDS-DMA kernel's epilogue, which handles every shape
+        // the fused activation lives in the LDS-DMA kernels' epilogues, which handle every shape
         if (!fp8k::gemm_fp8_snake_fits(lda, ldb))
             return fail(FP8_ERR_SHAPE, "fp8_scaled_mm: the sigmoid epilogue needs lda, ldb below 2^23");
         FP8_TRY(fp8k::launch_gemm_fp8_snake(a, lda, fmt_a, scale_a, gran_a == FP8_ROW, b, ldb, fmt_b, scale_b, gran_b == FP8_ROW,

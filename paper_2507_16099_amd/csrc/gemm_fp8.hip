@@ -2,7 +2,8 @@
 // (v_mfma_f32_16x16x128_f8f6f4): out[M,N] = (A[M,K] . B[N,K]^T) / (sa * sb).
 //
 // The paper (Section 2.1) leaves the FP8 products to the hardware vendor's GEMM
-// kernels; this is this library's own kernel for problems of few tiles, and the dispatch.
+// kernels; this is this library's own fallback for operands that the LDS-DMA kernels' 32-bit offsets do not reach,
+// and the dispatch.
 //
 // Layout of the work
 //   - Both operands have the contraction axis contiguous.  A workgroup owns a
@@ -52,32 +53,11 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
     return r;
 }
 
-// PD: how many K steps ahead of the matrix cores the global loads run (register sets in flight).  A
-// workgroup that is alone on its CU has nothing else to hide the load latency with (about 1 us per step
-// at PD = 1, whatever the tile); the small tiles, used when there are few of them, take PD = 4.
-// One product as the kernel sees it.  A launch can carry two of them (same formats, same kinds of scale): workgroups
-// from `split` on, a multiple of 8, work on the second, so that the two small products of a backward step share
-// one launch and run side by side.
-struct TnProblem {
-    const uint8_t* A; int64_t lda; const uint8_t* B; int64_t ldb;
-    const float* scale_a; const float* scale_b; int M, N, K; void* out; int64_t ld_out; int tiles_m, tiles_n;
-};
-constexpr int ONE_PROBLEM = 0x7FFFFFFF;
-
-template <int BM, int BN, int WAVES_M, int WAVES_N, int FA, int FB, bool OUT_F32, int PD = 1>
-__global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_fp8_tn_kernel(TnProblem p1, int row_a, int row_b, int split,
-                                                                            TnProblem p2) {
-    const bool second = (int)blockIdx.x >= split;
-    const TnProblem& p = second ? p2 : p1;
-    const uint8_t* __restrict__ A = p.A;
-    const uint8_t* __restrict__ B = p.B;
-    const float* __restrict__ scale_a = p.scale_a;
-    const float* __restrict__ scale_b = p.scale_b;
-    void* __restrict__ out = p.out;
-    const int64_t lda = p.lda, ldb = p.ldb, ld_out = p.ld_out;
-    const int M = p.M, N = p.N, K = p.K, tiles_m = p.tiles_m, tiles_n = p.tiles_n;
-    const int bid = second ? (int)blockIdx.x - split : (int)blockIdx.x;
-    const int nblocks = second ? (int)gridDim.x - split : (split == ONE_PROBLEM ? (int)gridDim.x : split);
+template <int BM, int BN, int WAVES_M, int WAVES_N, int FA, int FB, bool OUT_F32>
+__global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_fp8_tn_kernel(
+    const uint8_t* __restrict__ A, int64_t lda, const uint8_t* __restrict__ B, int64_t ldb, const float* __restrict__ scale_a,
+    int row_a, const float* __restrict__ scale_b, int row_b, int M, int N, int K, void* __restrict__ out, int64_t ld_out,
+    int tiles_m, int tiles_n) {
     constexpr int NT = WAVES_M * WAVES_N * 64;
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
     constexpr int FM = WM / 16;       // A fragments (16 rows each) per wave
@@ -92,8 +72,8 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_fp8_tn_kernel(TnPr
 
     // ---- workgroup -> tile
     const int ntiles = tiles_m * tiles_n;
-    const int per_xcd = nblocks / NUM_XCD;
-    const int logical = (bid % NUM_XCD) * per_xcd + bid / NUM_XCD;
+    const int per_xcd = gridDim.x / NUM_XCD;
+    const int logical = (blockIdx.x % NUM_XCD) * per_xcd + blockIdx.x / NUM_XCD;
     if (logical >= ntiles) return;
     const int in_group = GROUP_M * tiles_n;
     const int first_m = (logical / in_group) * GROUP_M;
@@ -109,66 +89,30 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_fp8_tn_kernel(TnPr
     const int srow = tid >> 3, spc = tid & 7;
     const int ca = spc ^ (srow & 7);                                   // logical chunk, A rows
     const int cb = spc ^ ((srow & 3) | ((srow >> 2) & 4));             // logical chunk, B rows
-    // PD == 1: plain global loads, guarded by branches (any size of tensor).  PD > 1: buffer loads, which
-    // return zeros beyond the end of the tensor without a branch, so that the loop body is straight-line
-    // code and the compiler leaves the loads of later steps in flight (a branch around a load makes it
-    // drain them all); the launcher uses this form only where 32-bit offsets suffice.
     const uint8_t* a_ptr = A + (int64_t)(m0 + srow) * lda + ca * 16;
     const uint8_t* b_ptr = B + (int64_t)(n0 + srow) * ldb + cb * 16;
     const int64_t a_step = (int64_t)(NT / 8) * lda, b_step = (int64_t)(NT / 8) * ldb;
-    const __amdgpu_buffer_rsrc_t rs_a = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint8_t*>(A), 0, PD > 1 ? (int)((int64_t)(M - 1) * lda + K) : 0, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rs_b = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint8_t*>(B), 0, PD > 1 ? (int)((int64_t)(N - 1) * ldb + K) : 0, 0x00020000);
-    constexpr uint32_t OUTSIDE = 0x80000000u;   // beyond any tensor this form is used for
-    uint32_t va[NLA], vb[NLB];                  // byte offsets of this thread's rows (PD > 1)
-#pragma unroll
-    for (int i = 0; i < NLA; ++i) {
-        const int r = m0 + srow + i * (NT / 8);
-        va[i] = r < M ? (uint32_t)r * (uint32_t)lda + ca * 16 : OUTSIDE;
-    }
-#pragma unroll
-    for (int i = 0; i < NLB; ++i) {
-        const int r = n0 + srow + i * (NT / 8);
-        vb[i] = r < N ? (uint32_t)r * (uint32_t)ldb + cb * 16 : OUTSIDE;
-    }
-
-    uint4 ra[PD][NLA], rb[PD][NLB];
-    auto gload = [&](int k0, uint4 (&xa)[NLA], uint4 (&xb)[NLB]) {
+    uint4 ra[NLA], rb[NLB];
+    auto gload = [&](int k0) {
         const bool ka = k0 + ca * 16 < K, kb = k0 + cb * 16 < K;
-        if constexpr (PD > 1) {
 #pragma unroll
-            for (int i = 0; i < NLA; ++i) {
-                const uint32_t off = (ka && va[i] != OUTSIDE) ? va[i] + (uint32_t)k0 : OUTSIDE;
-                const v4i_t v = __builtin_amdgcn_raw_buffer_load_b128(rs_a, (int)off, 0, 0);
-                xa[i] = make_uint4((uint32_t)v.x, (uint32_t)v.y, (uint32_t)v.z, (uint32_t)v.w);
-            }
+        for (int i = 0; i < NLA; ++i) {
+            const bool ok = ka && (m0 + srow + i * (NT / 8) < M);
+            ra[i] = ok ? *reinterpret_cast<const uint4*>(a_ptr + i * a_step + k0) : make_uint4(0, 0, 0, 0);
+        }
 #pragma unroll
-            for (int i = 0; i < NLB; ++i) {
-                const uint32_t off = (kb && vb[i] != OUTSIDE) ? vb[i] + (uint32_t)k0 : OUTSIDE;
-                const v4i_t v = __builtin_amdgcn_raw_buffer_load_b128(rs_b, (int)off, 0, 0);
-                xb[i] = make_uint4((uint32_t)v.x, (uint32_t)v.y, (uint32_t)v.z, (uint32_t)v.w);
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < NLA; ++i) {
-                const bool ok = ka && (m0 + srow + i * (NT / 8) < M);
-                xa[i] = ok ? *reinterpret_cast<const uint4*>(a_ptr + i * a_step + k0) : make_uint4(0, 0, 0, 0);
-            }
-#pragma unroll
-            for (int i = 0; i < NLB; ++i) {
-                const bool ok = kb && (n0 + srow + i * (NT / 8) < N);
-                xb[i] = ok ? *reinterpret_cast<const uint4*>(b_ptr + i * b_step + k0) : make_uint4(0, 0, 0, 0);
-            }
+        for (int i = 0; i < NLB; ++i) {
+            const bool ok = kb && (n0 + srow + i * (NT / 8) < N);
+            rb[i] = ok ? *reinterpret_cast<const uint4*>(b_ptr + i * b_step + k0) : make_uint4(0, 0, 0, 0);
         }
     };
-    auto lstore = [&](int stage, const uint4 (&xa)[NLA], const uint4 (&xb)[NLB]) {
+    auto lstore = [&](int stage) {
         uint8_t* as = smem + stage * STAGE + tid * 16;
         uint8_t* bs = as + BM * BK;
 #pragma unroll
-        for (int i = 0; i < NLA; ++i) *reinterpret_cast<uint4*>(as + i * NT * 16) = xa[i];
+        for (int i = 0; i < NLA; ++i) *reinterpret_cast<uint4*>(as + i * NT * 16) = ra[i];
 #pragma unroll
-        for (int i = 0; i < NLB; ++i) *reinterpret_cast<uint4*>(bs + i * NT * 16) = xb[i];
+        for (int i = 0; i < NLB; ++i) *reinterpret_cast<uint4*>(bs + i * NT * 16) = rb[i];
     };
 
     // ---- LDS -> MFMA operands
@@ -205,11 +149,8 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_fp8_tn_kernel(TnPr
         }
     };
 
-    // ---- main loop, two LDS stages; step s travels through register set s % PD.  The step count is
-    // rounded up to a multiple of PD (steps beyond K load zeros), which keeps the unrolled body free of
-    // conditions.
+    // ---- main loop, two LDS stages, loads one step ahead
     const int ksteps = (K + BK - 1) / BK;
-    const int kpad = (ksteps + PD - 1) / PD * PD;
     // the scales of this tile's rows and columns are requested now, so that their latency lies under the K loop
     // (problems of few tiles are bound by such fixed costs: a trip to memory is about as long as two K steps)
     float sa_raw[FM], sb_raw[NG][16];
@@ -226,20 +167,14 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_fp8_tn_kernel(TnPr
             sb_raw[g][e] = row_b ? (n < N ? scale_b[n] : 1.0f) : scale_b[0];
         }
     if (ksteps > 0) {
-        // all PD register sets are requested before the first one is awaited (loads return in issue order)
-#pragma unroll
-        for (int s_ = 0; s_ < PD; ++s_) gload(s_ * BK, ra[s_], rb[s_]);
-        lstore(0, ra[0], rb[0]);
+        gload(0);
+        lstore(0);
         __syncthreads();
-        for (int kb = 0; kb < kpad; kb += PD) {
-#pragma unroll
-            for (int u = 0; u < PD; ++u) {
-                const int kt = kb + u;
-                gload((kt + PD) * BK, ra[u], rb[u]);   // set u is free: step kt sits in LDS
-                compute(kt & 1);
-                lstore((kt + 1) & 1, ra[(u + 1) % PD], rb[(u + 1) % PD]);
-                __syncthreads();
-            }
+        for (int kt = 0; kt < ksteps; ++kt) {
+            gload((kt + 1) * BK);
+            compute(kt & 1);
+            lstore((kt + 1) & 1);
+            __syncthreads();
         }
     }
 
@@ -285,88 +220,105 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_fp8_tn_kernel(TnPr
     }
 }
 
-// g2 == nullptr: one product
-template <int BM, int BN, int WAVES_M, int WAVES_N, int FA, int FB, bool OUT_F32, int PD = 1>
-static hipError_t launch_variant(const GemmOperands& g1, const GemmOperands* g2, int row_a, int row_b, hipStream_t st) {
-    auto kern = gemm_fp8_tn_kernel<BM, BN, WAVES_M, WAVES_N, FA, FB, OUT_F32, PD>;
+template <int FA, int FB, bool OUT_F32>
+static hipError_t launch_tn(const GemmOperands& g, int row_a, int row_b, hipStream_t st) {
+    constexpr int BM = 128, BN = 128;
+    auto kern = gemm_fp8_tn_kernel<BM, BN, 2, 2, FA, FB, OUT_F32>;
     constexpr int lds = 2 * (BM + BN) * BK;
     static DynamicLdsOnce attr;     // one per instantiation
     if (hipError_t e = attr.ensure(reinterpret_cast<const void*>(kern), lds); e != hipSuccess) return e;
-    int64_t blocks[2] = {0, 0};
-    auto problem = [&](const GemmOperands& g, int64_t* nb) {
-        const int tiles_m = (int)((g.M + BM - 1) / BM), tiles_n = (int)((g.N + BN - 1) / BN);
-        *nb = ((int64_t)tiles_m * tiles_n + NUM_XCD - 1) / NUM_XCD * NUM_XCD;
-        return TnProblem{g.a, g.lda, g.b, g.ldb, g.scale_a, g.scale_b, (int)g.M, (int)g.N, (int)g.K, g.out, g.ld_out, tiles_m, tiles_n};
-    };
-    const TnProblem p1 = problem(g1, &blocks[0]);
-    const TnProblem p2 = g2 ? problem(*g2, &blocks[1]) : p1;
-    if (blocks[0] + blocks[1] > 0x7FFFFFF0) return hipErrorInvalidValue;
-    kern<<<dim3((unsigned)(blocks[0] + blocks[1])), dim3(WAVES_M * WAVES_N * 64), lds, st>>>(
-        p1, row_a, row_b, g2 ? (int)blocks[0] : ONE_PROBLEM, p2);
+    const int tiles_m = (int)((g.M + BM - 1) / BM), tiles_n = (int)((g.N + BN - 1) / BN);
+    const int64_t blocks = ((int64_t)tiles_m * tiles_n + NUM_XCD - 1) / NUM_XCD * NUM_XCD;
+    if (blocks > 0x7FFFFFF0) return hipErrorInvalidValue;
+    kern<<<dim3((unsigned)blocks), dim3(256), lds, st>>>(g.a, g.lda, g.b, g.ldb, g.scale_a, row_a, g.scale_b, row_b, (int)g.M, (int)g.N,
+                                                       (int)g.K, g.out, g.ld_out, tiles_m, tiles_n);
     return hipGetLastError();
 }
 
-template <int FA, int FB, bool OUT_F32>
-static hipError_t launch_fmt(int variant, const GemmOperands& g1, const GemmOperands* g2, int row_a, int row_b, hipStream_t st) {
-    if (variant == 6) return launch_variant<64, 64, 4, 1, FA, FB, OUT_F32, 4>(g1, g2, row_a, row_b, st);
-    if (variant == 7) return launch_variant<128, 128, 2, 2, FA, FB, OUT_F32, 4>(g1, g2, row_a, row_b, st);
-    return launch_variant<128, 128, 2, 2, FA, FB, OUT_F32>(g1, g2, row_a, row_b, st);
-}
+// ---- kernel choice.  Up to 32 rows: the few-row kernel of gemm_fp8_skinny.hip (it streams B once; 2-7x faster there).
+// More than one round of 256 x 256 tiles (one per CU): the large-product kernels of gemm_fp8_snake.hip /
+// gemm_fp8_stream.hip.  In between the cheapest of the ring kernel's tiles (gemm_fp8_ring.hip) and one round of
+// 256 x 256 tiles by this estimate, in us (one launch; rounds of 256 workgroups, K steps of 128 bytes):
+//     3 + rounds * (a + steps * b);  256 x 256 tiles: 10 + 1.2 * steps, at most half of the CUs busy (half tiles) 7.2 + 0.91 * steps.
+// a: prologue and epilogue of a tile; b: a K step with every CU busy, bound by the LDS of a CU (128 bytes per cycle,
+// reads of the fragments and writes of the LDS-DMA loads together: 384 / 576 / 768 / 1152 cycles for the tiles below,
+// whose matrix instructions take 128 / 256 / 512 / 1024) and, from 128 x 256 on, by the power limit.
+// Measured (a HIP graph of twelve, operands alternating; us; K = 1024 / 4096 / 16384):
+//                        64x64              128x64             128x128            128x256            before (other kernels)
+//     1024 x 1024     6.0 / 10.5 / 29     7.4 / 13.2 / 36     8.3 / 16.0 / 46    11.3 / 23.9 / 73      7.8 / 14.8 / 45
+//     1024 x 2048     9.6 / 18.3 / 66     7.9 / 14.2 / 50     8.6 / 17.2 / 64    11.6 / 24.8 / 99     10.3 / 21.8 / 74
+//     2048 x 2048    16.7 / 32.7 / 122   13.0 / 26.7 / 89    11.7 / 20.2 / 73    12.3 / 27.0 / 100    13.8 / 29.1 / 95
+//     2048 x 4096    29.9 / 62.1 / 242   22.8 / 49.2 / 176   17.9 / 38.2 / 131   17.6 / 32.7 / 109    14.5 / 36.4 / 157
+//     3072 x 4096    43.0 / 100          32.4 / 76           25.6 / 58           23.9 / 56            19.0 / 46.1
+//     4096 x 4096    57.8 / 136          43.3 / 113          31.7 / 83           31.7 / 68            20.8 / 53.3
+// Switches (tuning and test aid): GEMM_RING = 0 takes the ring kernel out of the choice, 1 + tile forces one of its tiles;
+// GEMM_BIG_FROM: number of 128 x 128 tiles from which the 256 x 256 kernels are taken; GEMM_VARIANT forces a kernel:
+// 0 = the fallback above, 4 = 256 x 256, 5 = few-row kernel (only where M <= 64), 6 / 7 = ring kernel, 64 x 64 / 128 x 128 tiles.
+namespace {
+struct RingCost { int tm, tn; double a, b; };
+constexpr RingCost kRing[RING_TILES] = {{64, 64, 1.0, 0.20},   {128, 64, 2.3, 0.29},  {64, 128, 2.3, 0.29},
+                                        {128, 128, 4.0, 0.42}, {128, 256, 7.0, 0.70}, {256, 128, 7.0, 0.70}};
+constexpr int kPathRing = 100;       // + tile: the ring kernel; otherwise a GEMM_VARIANT number
 
-// Kernel choice: the few-row kernel of gemm_fp8_skinny.hip (variant 5) for
-// M <= 32 (measured 2-7x faster there; from 33 to 64 rows its loads of A
-// through the L1 cache cost as much as the tiled kernels' padding); otherwise by the number of 128 x 128 tiles of
-// the output: up to 128 of them 64 x 64 tiles, up to 256 of them 128 x 128 tiles, beyond that the 256 x 256 kernels
-// of gemm_fp8_snake.hip / gemm_fp8_stream.hip (variant 4).
-// Measured per product, ten in a HIP graph, K = 1024 / 4096 / 16384 (us):
-//      64 tiles (1024 x 1024):   64x64  8.1 / 15.3 /   -     128x128 13.5 / 29.5 /   -     256x256 10.5 / 24.5 /   -
-//     128 tiles (1024 x 2048):         10.1 / 22.0 /   -             13.9 / 30.7 /   -             10.8 / 31.3 /   -
-//     192 tiles (1536 x 2048):         13.2 / 27.3 /  86             14.2 / 30.8 /  95             10.8 / 31.3 / 103
-//     256 tiles (2048 x 2048):         16.2 / 35.1 / 114             14.6 / 31.4 /  95             10.8 / 31.4 / 104
-//     384 tiles (2048 x 3072):         22.3 / 48.4 / 163             26.8 / 58.6 / 186             10.8 / 31.8 / 105
-//     512 tiles (2048 x 4096):         29.1 / 62.1 / 215             27.8 / 59.6 / 188             12.0 / 34.1 / 112
-// With few tiles the K loop of a lone workgroup per CU is bound by the latency of its loads, about 1 us per step
-// whatever the tile, so more and smaller tiles finish sooner; once every CU has a workgroup the time of the small
-// tiles grows with the work, while sixty-four 256 x 256 tiles still take what one takes.  At 129-256 tiles the
-// 128 x 128 tiles are kept although the table favours the large ones for short contractions: inside whole
-// forward + backward steps they came out ahead (3-6 us per step at 1024 x 1024 x 4096 and 4096 x 1024 x 1024), and
-// the two products of a backward step can then share one launch (launch_gemm_fp8_pair), which in steps of
-// 4096 x 1024 x 4096 and five other shapes of that class saved 22-65 us (13-15 %).
-// Switches (tuning and test aid): GEMM_BIG_FROM moves the tile count from which the 256 x 256 kernels are used;
-// GEMM_VARIANT forces a kernel: 0 = 128x128 / 4 waves (register-staged; also the fallback where the 32-bit
-// offsets of the others do not reach), 4 = 256 x 256, 5 = few-row kernel (only where M <= 64), 6 = 64x64 / 4 waves
-// with loads 4 steps ahead, 7 = 128x128 / 4 waves likewise (both register-staged through buffer loads; eight steps ahead
-// measured 5-35 % slower on the small tile, three steps ahead 4-6 % slower on the large one).
-static int pick_variant(int64_t M, int64_t N) {
-    if (const int v = knob(KNOB_GEMM_VARIANT); v == 0 || (v >= 4 && v <= 7)) return v;
-    if (M <= 32) return 5;
-    const int64_t tiles128 = ((M + 127) / 128) * ((N + 127) / 128);
-    const int big = knob(KNOB_GEMM_BIG_FROM);
-    if (tiles128 >= (big > 0 ? big : 257)) return 4;
-    return tiles128 <= 128 ? 6 : 7;   // (launch_gemm_fp8 falls back to 0 where their 32-bit offsets do not reach)
+int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
+double ring_cost(int tile, const GemmOperands& g, const GemmOperands* g2, int64_t cus) {
+    const RingCost& c = kRing[tile];
+    auto tiles = [&](const GemmOperands& x) { return cdiv(x.M, c.tm) * cdiv(x.N, c.tn); };
+    const double per1 = c.a + (double)cdiv(g.K, BK) * c.b, per2 = g2 ? c.a + (double)cdiv(g2->K, BK) * c.b : 0.0;
+    const int64_t n1 = tiles(g), n2 = g2 ? tiles(*g2) : 0;
+    const double operands = 1e-5 * (double)(n1 + n2) * (c.tm + c.tn);      // (equal otherwise: fewer operand bytes)
+    if (n1 + n2 <= cus) return 3.0 + (per1 > per2 ? per1 : per2) + operands;
+    return 3.0 + (double)cdiv(n1 + n2, cus) * ((double)n1 * per1 + (double)n2 * per2) / (double)(n1 + n2) + operands;
 }
+// the cheapest ring tile for one product, or two in one launch
+int best_ring(const GemmOperands& g, const GemmOperands* g2, int64_t cus, double* cost) {
+    int best = 0;
+    for (int t = 0; t < RING_TILES; ++t) {
+        const double c = ring_cost(t, g, g2, cus);
+        if (t == 0 || c < *cost) { best = t; *cost = c; }
+    }
+    return best;
+}
+// kernel for one product; *cost: its estimate (large where there is none)
+int pick_path(const GemmOperands& g, double* cost) {
+    *cost = 1e30;
+    const bool fits = gemm_fp8_ring_fits(g);
+    if (const int r = knob(KNOB_GEMM_RING); r >= 1 && r <= RING_TILES && fits) return kPathRing + r - 1;
+    const int v = knob(KNOB_GEMM_VARIANT);
+    if (v == 0 || v == 4 || v == 5) return v;
+    if (v == 6 || v == 7) return fits ? kPathRing + (v == 6 ? RING_64x64 : RING_128x128) : 0;
+    if (g.M <= 32) return 5;
+    const int64_t cus = compute_units() > 0 ? compute_units() : 256;
+    const int64_t big = cdiv(g.M, 256) * cdiv(g.N, 256);
+    if (const int b = knob(KNOB_GEMM_BIG_FROM); b > 0 && cdiv(g.M, 128) * cdiv(g.N, 128) >= b) return 4;
+    if (big > cus || !fits || knob(KNOB_GEMM_RING) == 0) return 4;
+    const double steps = (double)cdiv(g.K, BK);
+    const double cost_big = 2 * big <= cus ? 7.2 + 0.91 * steps : 10.0 + 1.2 * steps;
+    const int tile = best_ring(g, nullptr, cus, cost);
+    if (*cost <= cost_big) return kPathRing + tile;
+    *cost = cost_big;
+    return 4;
+}
+}  // namespace
 
 hipError_t launch_gemm_fp8(const uint8_t* a, int64_t lda, int fmt_a, const float* scale_a, int row_a,
                            const uint8_t* b, int64_t ldb, int fmt_b, const float* scale_b, int row_b,
                            int64_t M, int64_t N, int64_t K, void* out, int64_t ld_out, int out_f32,
                            hipStream_t st) {
     if (M == 0 || N == 0) return hipSuccess;
-    int v = pick_variant(M, N);
-    // the forms with loads several steps ahead address their operands with 32-bit byte offsets (a tile may
-    // reach up to 127 rows past the end)
-    if ((v == 6 || v == 7) && ((M + 128) * lda + K >= (int64_t)1 << 31 || (N + 128) * ldb + K >= (int64_t)1 << 31)) v = 0;
+    const GemmOperands g{a, lda, scale_a, b, ldb, scale_b, M, N, K, out, ld_out};
+    double cost;
+    const int v = pick_path(g, &cost);
+    if (v >= kPathRing) return launch_gemm_fp8_ring(v - kPathRing, g, nullptr, fmt_a, fmt_b, row_a, row_b, out_f32 ? 1 : 0, st);
     if (v == 5 && M <= 64 && K > 0)
         return launch_gemm_fp8_skinny(a, lda, fmt_a, scale_a, row_a, b, ldb, fmt_b, scale_b, row_b, M, N, K, out, ld_out,
                                       out_f32, st);
-    if (v == 4 && gemm_fp8_snake_fits(lda, ldb))   // else: the 128 x 128 register-staged kernel below
+    if (v == 4 && gemm_fp8_snake_fits(lda, ldb))   // else: the 128 x 128 register-staged kernel
         return launch_gemm_fp8_snake(a, lda, fmt_a, scale_a, row_a, b, ldb, fmt_b, scale_b, row_b, M, N, K, out, ld_out,
                                      out_f32, st);
-    if (v == 4 || v == 5) v = 0;
-    const GemmOperands g{a, lda, scale_a, b, ldb, scale_b, M, N, K, out, ld_out};
 #define FP8K_GEMM(FA_, FB_)                                                                    \
     if (fmt_a == FA_ && fmt_b == FB_)                                                          \
-        return out_f32 ? launch_fmt<FA_, FB_, true>(v, g, nullptr, row_a, row_b, st)          \
-                       : launch_fmt<FA_, FB_, false>(v, g, nullptr, row_a, row_b, st)
+        return out_f32 ? launch_tn<FA_, FB_, true>(g, row_a, row_b, st) : launch_tn<FA_, FB_, false>(g, row_a, row_b, st)
     FP8K_GEMM(FMT_E4M3FN, FMT_E4M3FN);
     FP8K_GEMM(FMT_E5M2, FMT_E4M3FN);
     FP8K_GEMM(FMT_E4M3FN, FMT_E5M2);
@@ -375,28 +327,32 @@ hipError_t launch_gemm_fp8(const uint8_t* a, int64_t lda, int fmt_a, const float
     return hipErrorInvalidValue;
 }
 
+int gemm_fp8_ring_choice(const GemmOperands& g) {
+    double cost;
+    const int v = pick_path(g, &cost);
+    if (v >= kPathRing) return v - kPathRing;
+    if (v == 4 || !gemm_fp8_ring_fits(g)) return -1;
+    return best_ring(g, nullptr, compute_units() > 0 ? compute_units() : 256, &cost);
+}
+
 // Two products of the same formats and kinds of scale (bfloat16 results) in ONE launch, for the pair dX, dW of a
-// backward step whose products are too small to fill the chip one at a time.  hipErrorNotSupported (nothing
-// launched) where either is large enough for the 256 x 256 kernels, has few rows, or the two would take different
-// tiles: the caller then launches them one after the other.
+// backward step whose products are too small to fill the chip one at a time.  hipErrorNotSupported (nothing launched)
+// where one launch each is estimated to be as fast: the caller then launches them one after the other.
 hipError_t launch_gemm_fp8_pair(const GemmOperands& g1, const GemmOperands& g2, int fmt_a, int fmt_b, int row_a, int row_b,
                                 hipStream_t st) {
     if (g1.M == 0 || g1.N == 0 || g2.M == 0 || g2.N == 0 || knob(KNOB_PAIRS) == 0) return hipErrorNotSupported;
-    const int v1 = pick_variant(g1.M, g1.N), v2 = pick_variant(g2.M, g2.N);
-    if ((v1 != 6 && v1 != 7) || v1 != v2) return hipErrorNotSupported;
-    auto reach = [](const GemmOperands& g) {
-        return (g.M + 128) * g.lda + g.K < (int64_t)1 << 31 && (g.N + 128) * g.ldb + g.K < (int64_t)1 << 31;
-    };
-    if (!reach(g1) || !reach(g2)) return hipErrorNotSupported;
-    const int v = v1;   // (a product with few tiles and a long contraction, sharing a launch on the larger tile of the other, took 2-3x longer)
-#define FP8K_GEMM(FA_, FB_) \
-    if (fmt_a == FA_ && fmt_b == FB_) return launch_fmt<FA_, FB_, false>(v, g1, &g2, row_a, row_b, st)
-    FP8K_GEMM(FMT_E4M3FN, FMT_E4M3FN);
-    FP8K_GEMM(FMT_E5M2, FMT_E4M3FN);
-    FP8K_GEMM(FMT_E4M3FN, FMT_E5M2);
-    FP8K_GEMM(FMT_E5M2, FMT_E5M2);
-#undef FP8K_GEMM
-    return hipErrorInvalidValue;
+    if (!gemm_fp8_ring_fits(g1) || !gemm_fp8_ring_fits(g2)) return hipErrorNotSupported;
+    double c1, c2, both = 0.0;
+    const int v1 = pick_path(g1, &c1), v2 = pick_path(g2, &c2);
+    if (c1 > 1e29 || c2 > 1e29) {      // no estimate: forced, few rows, or large
+        if (v1 < kPathRing || v1 != v2) return hipErrorNotSupported;
+        return launch_gemm_fp8_ring(v1 - kPathRing, g1, &g2, fmt_a, fmt_b, row_a, row_b, 0, st);
+    }
+    const int64_t cus = compute_units() > 0 ? compute_units() : 256;
+    const int tile = best_ring(g1, &g2, cus, &both);
+    if (both >= c1 + c2) return hipErrorNotSupported;
+    const bool swap = g2.K > g1.K;     // the workgroups of the longer contraction first
+    return launch_gemm_fp8_ring(tile, swap ? g2 : g1, swap ? &g1 : &g2, fmt_a, fmt_b, row_a, row_b, 0, st);
 }
 
 }  // namespace fp8k

@@ -520,6 +520,11 @@ hipError_t launch_gemm_fp8_snake(const uint8_t* a, int64_t lda, int fmt_a, const
                                  hipStream_t st, int act) {
     if (M == 0 || N == 0) return hipSuccess;
     if (act && out_f32) return hipErrorInvalidValue;
+    if (act) {      // the fused activation of a product of less than a round of these tiles: the ring kernel's epilogue has it too
+        const GemmOperands g{a, lda, scale_a, b, ldb, scale_b, M, N, K, out, ld_out};
+        if (const int tile = gemm_fp8_ring_choice(g); tile >= 0)
+            return launch_gemm_fp8_ring(tile, g, nullptr, fmt_a, fmt_b, row_a, row_b, 2, st);
+    }
     const int m = (int)M, n = (int)N, k = (int)K;
 #define FP8K_SNA(FA_, FB_)                                                                                 \
     if (act && fmt_a == FA_ && fmt_b == FB_)                                                               \

@@ -59,6 +59,14 @@ struct GemmOperands {
 hipError_t launch_gemm_fp8_pair(const GemmOperands& g1, const GemmOperands& g2, int fmt_a, int fmt_b, int row_a, int row_b,
                                 hipStream_t st);
 
+// products of few to middling size on smaller tiles with a deep LDS ring (gemm_fp8_ring.hip); g2: a second product in
+// the same launch, or nullptr; mode 0 = bfloat16, 1 = fp32, 2 = bfloat16 of the sigmoid.  _fits: 32-bit offsets reach
+enum RingTile { RING_64x64 = 0, RING_128x64, RING_64x128, RING_128x128, RING_128x256, RING_256x128, RING_TILES };
+bool gemm_fp8_ring_fits(const GemmOperands& g);
+int gemm_fp8_ring_choice(const GemmOperands& g);      // its tile where a 256 x 256 tile per workgroup is not the better form, else -1
+hipError_t launch_gemm_fp8_ring(int tile, const GemmOperands& g1, const GemmOperands* g2, int fmt_a, int fmt_b, int row_a,
+                                int row_b, int mode, hipStream_t st);
+
 // Rowwise quantization (codes q, scales scale_out) and the per-column scales
 // scale_cols[c] = scale(max_r |x[r, c]|) from a single read of x; scratch holds
 // the first-level column maxima.  hipErrorNotSupported if the shape does not suit.

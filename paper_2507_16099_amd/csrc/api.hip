@@ -126,8 +126,9 @@ int quantize_row_col_impl(const void* x, int64_t rows, int64_t cols, int64_t ld,
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 // Leading dimension of the operands whose contraction axis is the token axis M (dY^T [N, M] and X^T [K, M] of the
-// weight gradient): rows of 16-byte multiples for the products' loads.  The pad columns hold zero codes (the buffers
-// are cleared before the transposing casts write the valid part), so the product may contract over the padded length.
+// weight gradient): rows of 16-byte multiples for the products' loads.  The pad columns hold zero codes - written by the
+// transposing casts of the tensorwise and of the paired launches, cleared beforehand where the single-tensor calls are
+// used - so the product may contract over the padded length.
 int64_t pad16(int64_t v) { return (v + 15) / 16 * 16; }
 
 // part: per-block maxima of the tensorwise amax pass, room for two tensors (a pair shares its launches; otherwise one
@@ -381,7 +382,6 @@ int fp8_linear_fwd(const void* x, const void* w, int64_t M, int64_t K, int64_t N
         const int fl = recipe->flags & FP8_POW2_SCALE;
         float *sxt = reinterpret_cast<float*>(wsb + b.sxt), *swt = reinterpret_cast<float*>(wsb + b.swt);
         const int64_t Mp = pad16(M);
-        if (Mp != M) FP8_TRY(fp8k::launch_fill_u32(reinterpret_cast<uint32_t*>(wsb + b.xt), K * Mp / 4, 0u, st));   // zero codes in the pad columns of X^T
         if (recipe->gran == FP8_TENSOR) {
             float* part = reinterpret_cast<float*>(wsf + p.part);
             bool pair_done = false;
@@ -413,6 +413,7 @@ int fp8_linear_fwd(const void* x, const void* w, int64_t M, int64_t K, int64_t N
             if (recipe->flags & FP8_GRAD_WEIGHT_HP) {   // dW will come from the bfloat16 X: no fp8 copy of X to keep
                 if (int rc = quantize_impl(x, M, K, K, FP8_ROW, recipe->fmt_x, fl, wsf + p.xq, K, nullptr, 0, sx, st)) return rc;
             } else {
+                if (Mp != M) FP8_TRY(fp8k::launch_fill_u32(reinterpret_cast<uint32_t*>(wsb + b.xt), K * Mp / 4, 0u, st));   // zero codes in the pad columns of X^T
                 if (int rc = quantize_row_col_impl(x, M, K, K, recipe->fmt_x, fl, wsf + p.xq, K, sx, wsb + b.xt, Mp, sxt, st)) return rc;
             }
             if (int rc = quantize_row_col_impl(w, N, K, K, recipe->fmt_w, fl, wsf + p.wq, K, sw, wsb + b.wt, N, swt, st)) return rc;
@@ -483,10 +484,9 @@ int fp8_linear_bwd(const void* dy, const void* x, const void* w, int64_t M, int6
         if (!dx) return FP8_OK;
     }
     const int64_t Mp = pad16(M);
-    if (dw && Mp != M) {   // zero codes in the pad columns of dY^T and (unless the forward left it) X^T
-        FP8_TRY(fp8k::launch_fill_u32(reinterpret_cast<uint32_t*>(gqt), N * Mp / 4, 0u, st));
-        if (!saved) FP8_TRY(fp8k::launch_fill_u32(reinterpret_cast<uint32_t*>(xt), K * Mp / 4, 0u, st));
-    }
+    auto clear = [&](uint8_t* t, int64_t rows) {     // zero codes in the pad columns, ahead of the single-tensor calls
+        return Mp != M ? fp8k::launch_fill_u32(reinterpret_cast<uint32_t*>(t), rows * Mp / 4, 0u, st) : hipSuccess;
+    };
 
     if (recipe->gran == FP8_TENSOR) {
         // one scale per tensor; dY is converted once into both layouts
@@ -527,6 +527,7 @@ int fp8_linear_bwd(const void* dy, const void* x, const void* w, int64_t M, int6
         const fp8k::RowColOperand og{dy, M, N, gq, N, sg, gqt, Mp, sgt, ws + p.fold_g};
         const hipError_t e = fp8k::launch_quant_row_col_pair(og, nullptr, N, recipe->fmt_dy, fl, st);
         if (e == hipErrorNotSupported) {
+            FP8_TRY(clear(gqt, N));
             if (int rc = quantize_row_col_impl(dy, M, N, N, recipe->fmt_dy, fl, gq, N, sg, gqt, Mp, sgt, st)) return rc;
         } else if (e != hipSuccess) {
             return hip_fail(e, "quant_row_col");
@@ -534,12 +535,15 @@ int fp8_linear_bwd(const void* dy, const void* x, const void* w, int64_t M, int6
     } else if (dx) {
         if (int rc = quantize_impl(dy, M, N, N, FP8_ROW, recipe->fmt_dy, fl, gq, N, nullptr, 0, sg, st)) return rc;
     } else {
+        FP8_TRY(clear(gqt, N));
         if (int rc = quantize_impl(dy, M, N, N, FP8_COL, recipe->fmt_dy, fl | T, gqt, Mp, nullptr, 0, sgt, st)) return rc;
     }
     if (dx && !saved)
         if (int rc = quantize_impl(w, N, K, K, FP8_COL, recipe->fmt_w, fl | T, wt, N, nullptr, 0, swt, st)) return rc;
-    if (dw && !saved)
+    if (dw && !saved) {
+        FP8_TRY(clear(xt, K));
         if (int rc = quantize_impl(x, M, K, K, FP8_COL, recipe->fmt_x, fl | T, xt, Mp, nullptr, 0, sxt, st)) return rc;
+    }
     return grad_gemms(recipe, 1, gq, sg, wt, swt, gqt, sgt, xt, sxt, M, Mp, K, N, dx, dw, st);
 }
 
@@ -597,9 +601,16 @@ int fp8_linear_bwd_sigmoid(const void* dy, const void* y, const void* x, const v
     hipError_t e = fp8k::launch_quant_row_col_sigmoid_bwd(dy, y, M, N, N, recipe->fmt_dy, fl, gq, N, sg, gqt, M, sgt, st);
     if (e == hipErrorNotSupported) return fail(FP8_ERR_SHAPE, "%s: shape not supported by the fused gradient quantization", fn);
     if (e != hipSuccess) return hip_fail(e, "quant_row_col_sigmoid_bwd");
-    if (dx && !saved)
+    bool pair_done = false;
+    if (dx && dw && !saved && recipe->fmt_w == recipe->fmt_x) {     // W and X in three launches (small ones: two) instead of six
+        const fp8k::ColOperand ow{w, N, K, wt, N, swt, ws + p.fold_w}, ox{x, M, K, xt, M, sxt, ws + p.fold_x};
+        e = fp8k::launch_quant_col_t_pair(ow, ox, K, recipe->fmt_w, fl, st);
+        if (e == hipSuccess) pair_done = true;
+        else if (e != hipErrorNotSupported) return hip_fail(e, "quant_col_t_pair");
+    }
+    if (dx && !saved && !pair_done)
         if (int rc = quantize_impl(w, N, K, K, FP8_COL, recipe->fmt_w, fl | T, wt, N, nullptr, 0, swt, st)) return rc;
-    if (dw && !saved)
+    if (dw && !saved && !pair_done)
         if (int rc = quantize_impl(x, M, K, K, FP8_COL, recipe->fmt_x, fl | T, xt, M, nullptr, 0, sxt, st)) return rc;
     return grad_gemms(recipe, 1, gq, sg, wt, swt, gqt, sgt, xt, sxt, M, M, K, N, dx, dw, st);
 }
@@ -660,7 +671,15 @@ int linear_fwd_prequantized_impl(const char* fn, const void* x, int64_t M, int64
                                                               scale_w, gran_w == FP8_ROW, M, N, K, y, ld_y, st);
     if (fused == hipSuccess) return FP8_OK;
     if (fused != hipErrorNotSupported) return hip_fail(fused, "launch_linear_skinny_fused");
-    if (int rq = quantize_impl(x, M, K, K, gran_x, fmt_x, flags, xq, K, nullptr, 0, sx, st)) return rq;
+    if (gran_x == FP8_TENSOR && M > 0 && K > 0) {
+        // two launches instead of four: the per-block maxima go behind the one scale, in the room that the workspace has
+        // for one per row (at least 64)
+        const int64_t room = (int64_t)align_up(sizeof(float) * (size_t)M, 256) / (int64_t)sizeof(float);
+        const int limit = (int)(room < fp8k::TENSOR_PARTIALS ? room : fp8k::TENSOR_PARTIALS);
+        FP8_TRY(fp8k::launch_quant_tensor(x, M, K, fmt_x, (flags & FP8_POW2_SCALE) | limit << 8, 0, xq, K, nullptr, 0, sx, sx + 64, st));
+    } else if (int rq = quantize_impl(x, M, K, K, gran_x, fmt_x, flags, xq, K, nullptr, 0, sx, st)) {
+        return rq;
+    }
     FP8_TRY(fp8k::launch_gemm_fp8(xq, K, fmt_x, sx, gran_x == FP8_ROW, wq, ldw, fmt_w, scale_w, gran_w == FP8_ROW, M, N, K, y,
                                   ld_y, 0, st));
     return FP8_OK;

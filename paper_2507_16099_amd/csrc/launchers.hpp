@@ -19,6 +19,7 @@ hipError_t launch_col_scales_two_level(const void* x, int64_t rows, int64_t cols
 // tensorwise quantization of a dense tensor in two launches (per-block maxima, then a cast that derives the
 // scale itself); part: scratch for TENSOR_PARTIALS floats
 constexpr int TENSOR_PARTIALS = 512;
+// flags: FP8_POW2_SCALE, and from bit 8 on the room in part where it is less than TENSOR_PARTIALS (0: it is not)
 hipError_t launch_quant_tensor(const void* x, int64_t rows, int64_t cols, int fmt, int flags, int transpose, uint8_t* q,
                                int64_t ld_out, uint8_t* q_plain, int64_t ld_plain, float* scale_out, float* part,
                                hipStream_t st);

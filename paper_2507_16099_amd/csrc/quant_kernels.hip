@@ -332,9 +332,11 @@ hipError_t launch_col_scales_two_level(const void* x, int64_t rows, int64_t cols
                                        float* scale_out, void* scratch, size_t scratch_bytes, hipStream_t st) {
     const int64_t nvec = cols / 8;
     const int64_t ld_part = (cols + 7) / 8 * 8;
+    // G blocks of at least four rows each.  (A rule of eight rows for 1024 blocks, whatever the row count, sent every
+    // tensor of fewer than 8192 rows to four launches with atomics: 36 us for the scales and the cast of 4096 x 4096.)
     int64_t G = 1024;
-    while (G > 64 && (size_t)(G * ld_part * 2) > scratch_bytes) G /= 2;
-    if (rows < 8 * G || nvec > 256 * 16 || (size_t)(G * ld_part * 2) > scratch_bytes) return hipErrorNotSupported;
+    while (G > 64 && ((size_t)(G * ld_part * 2) > scratch_bytes || rows < 4 * G)) G /= 2;
+    if (rows < 4 * G || nvec > 256 * 16 || (size_t)(G * ld_part * 2) > scratch_bytes) return hipErrorNotSupported;
     const uint16_t* xp = static_cast<const uint16_t*>(x);
     uint16_t* part = static_cast<uint16_t*>(scratch);
 #define FP8K_CP(NV) colmax_partial_kernel<NV><<<dim3((unsigned)G), dim3(256), 0, st>>>(xp, rows, cols, ld, part, ld_part)
@@ -489,6 +491,8 @@ __device__ __forceinline__ void transpose4x4_bytes(uint32_t a, uint32_t b, uint3
 // ACT: the tensor to cast is x * y * (1 - y) (gradient through a stored sigmoid output y of the same shape and
 // leading dimension, cols a multiple of 8), formed on the fly.
 // FOLD (per-column scales only): the scales may come from first-level column maxima, see below.
+// pad: the output rows are padded to whole 16-byte pieces that belong to this call (a workspace): their last bytes are
+// written too, as zero codes, so nobody has to clear the buffer first and no piece is stored byte by byte.
 template <int FMT, int GRAN, int TR, bool ACT = false, bool FOLD = false>
 __global__ __launch_bounds__(256) void cast_transpose_kernel(const uint16_t* __restrict__ x, int64_t rows,
                                                               int64_t cols, int64_t ld,
@@ -504,7 +508,8 @@ __global__ __launch_bounds__(256) void cast_transpose_kernel(const uint16_t* __r
                                                               uint8_t* __restrict__ qt2 = nullptr, int64_t ld_t2 = 0, int nx2 = 0,
                                                               int64_t ld_part = 0, int n_part2 = 0,
                                                               float* __restrict__ scale_out2 = nullptr,
-                                                              uint8_t* __restrict__ q_plain2 = nullptr, int64_t ld_plain2 = 0) {
+                                                              uint8_t* __restrict__ q_plain2 = nullptr, int64_t ld_plain2 = 0,
+                                                              int pad = 0) {
     int bid = blockIdx.x;
     if (bid >= split) {
         bid -= split; x = x2; rows = rows2; ld = ld2; scale = scale2; qt = qt2; ld_t = ld_t2; nx = nx2;
@@ -661,16 +666,26 @@ __global__ __launch_bounds__(256) void cast_transpose_kernel(const uint16_t* __r
         if (orow + 16 <= rows) {
             store_stream(dst, v);
         } else {
-            const uint32_t t[4] = {v.x, v.y, v.z, v.w};
-            for (int e = 0; orow + e < rows; ++e) dst[e] = (uint8_t)((t[e >> 2] >> (8 * (e & 3))) & 0xFFu);
+            uint32_t t[4] = {v.x, v.y, v.z, v.w};
+            const int left = (int)(rows - orow);       // 1..15 bytes of codes, the rest of the piece is padding
+            if (pad) {
+#pragma unroll
+                for (int d = 0; d < 4; ++d) t[d] &= left >= 4 * d + 4 ? 0xFFFFFFFFu : left <= 4 * d ? 0u : (1u << (8 * (left - 4 * d))) - 1u;
+                store_stream(dst, make_uint4(t[0], t[1], t[2], t[3]));
+            } else {
+                for (int e = 0; orow + e < rows; ++e) dst[e] = (uint8_t)((t[e >> 2] >> (8 * (e & 3))) & 0xFFu);
+            }
         }
     }
 }
 
+// the rows of a transposed output [cols, rows] in a workspace are padded to 16 bytes: the cast fills the padding
+static int owns_padding(int64_t rows, int64_t ld_out) { return rows % 16 != 0 && ld_out == (rows + 15) / 16 * 16 ? 1 : 0; }
+
 template <int FMT, int GRAN>
 static hipError_t launch_cast_t(const uint16_t* x, int64_t rows, int64_t cols, int64_t ld, const float* scale,
                                 int transpose, uint8_t* q, int64_t ld_out, uint8_t* q_plain, int64_t ld_plain,
-                                hipStream_t st, int n_part = 0, int sflags = 0, float* scale_out = nullptr) {
+                                hipStream_t st, int n_part = 0, int sflags = 0, float* scale_out = nullptr, int pad = 0) {
     if (transpose) {
         // 128-row tiles measured best (256-row tiles: same on the 470 MB gradient
         // tensor, slower on the smaller operands)
@@ -678,7 +693,8 @@ static hipError_t launch_cast_t(const uint16_t* x, int64_t rows, int64_t cols, i
         const int64_t total = ((gy + 15) / 16) * ((gx + 15) / 16) * 256;
         if (total > 0x7FFFFFFF) return hipErrorInvalidValue;
         cast_transpose_kernel<FMT, GRAN, 128><<<dim3((unsigned)total), dim3(256), 0, st>>>(
-            x, rows, cols, ld, scale, q, ld_out, q_plain, ld_plain, (int)gy, (int)gx, nullptr, n_part, sflags, scale_out);
+            x, rows, cols, ld, scale, q, ld_out, q_plain, ld_plain, (int)gy, (int)gx, nullptr, n_part, sflags, scale_out, NO_TWIN,
+            nullptr, 0, 0, nullptr, nullptr, 0, 0, 0, 0, nullptr, nullptr, 0, pad);
         return hipGetLastError();
     }
     const int64_t items = (cols + 15) / 16;
@@ -694,7 +710,8 @@ static hipError_t launch_cast_t(const uint16_t* x, int64_t rows, int64_t cols, i
 
 // Tensorwise quantization of a dense tensor in two launches: per-block maxima into part (room for
 // TENSOR_PARTIALS floats), then the cast, every block of which derives the scale from them; scale_out[0]
-// receives the scale.  Same codes and scale as launch_amax + launch_scale + launch_cast.
+// receives the scale.  Same codes and scale as launch_amax + launch_scale + launch_cast.  A transposed output whose rows
+// are padded to 16 bytes gets zero codes in the padding.
 hipError_t launch_quant_tensor(const void* x, int64_t rows, int64_t cols, int fmt, int flags, int transpose, uint8_t* q,
                                int64_t ld_out, uint8_t* q_plain, int64_t ld_plain, float* scale_out, float* part,
                                hipStream_t st) {
@@ -703,16 +720,17 @@ hipError_t launch_quant_tensor(const void* x, int64_t rows, int64_t cols, int fm
     const int64_t n = rows * cols;
     int64_t blocks = (n / 8 + 256 * 8 - 1) / (256 * 8);
     if (blocks < 1) blocks = 1;
-    if (blocks > TENSOR_PARTIALS) blocks = TENSOR_PARTIALS;
+    const int room = flags >> 8 ? flags >> 8 : TENSOR_PARTIALS;
+    if (blocks > room) blocks = room;
     amax_flat_kernel<true><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(xp, n, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int sfl = flags & 1;
+    const int sfl = flags & 1, pad = owns_padding(rows, ld_out);
     if (fmt == FMT_E4M3FN)
         return launch_cast_t<FMT_E4M3FN, GRAN_TENSOR>(xp, rows, cols, cols, part, transpose, q, ld_out, q_plain, ld_plain, st,
-                                                      (int)blocks, sfl, scale_out);
+                                                      (int)blocks, sfl, scale_out, pad);
     return launch_cast_t<FMT_E5M2, GRAN_TENSOR>(xp, rows, cols, cols, part, transpose, q, ld_out, q_plain, ld_plain, st,
-                                                (int)blocks, sfl, scale_out);
+                                                (int)blocks, sfl, scale_out, pad);
 }
 
 // The same for two dense tensors of the same width and format in two launches (one for both sets of maxima, one for
@@ -737,7 +755,7 @@ static hipError_t quant_tensor_pair(const TensorOperand& a, const TensorOperand&
         cast_transpose_kernel<FMT, GRAN_TENSOR, 128><<<dim3((unsigned)(ta + tb)), dim3(256), 0, st>>>(
             xa, a.rows, cols, cols, a.part, a.q, a.ld_out, a.q_plain, a.ld_plain, (int)gya, (int)gx, nullptr, (int)blocks, sfl,
             a.scale_out, (int)ta, xb, b.rows, cols, b.part, b.q, b.ld_out, (int)gyb, 0, (int)blocks, b.scale_out, b.q_plain,
-            b.ld_plain);
+            b.ld_plain, owns_padding(a.rows, a.ld_out) | owns_padding(b.rows, b.ld_out));
         return hipGetLastError();
     }
     if (a.ld_out != b.ld_out) return hipErrorInvalidValue;
@@ -1071,8 +1089,10 @@ int64_t quant_fold_bytes(int64_t rows, int64_t cols) {
 
 namespace {
 
-int64_t output_scratch(int64_t out_rows, int64_t out_cols, int64_t ld_out) {   // bytes of a transposed output that may hold partial maxima
-    return ld_out == out_cols ? out_rows * out_cols : out_cols;
+// bytes of a transposed output that may hold partial maxima: all of it when its rows are dense or padded to 16 bytes (the
+// outputs of the paired launches lie in a workspace, and the cast fills that padding), else the first row
+int64_t output_scratch(int64_t out_rows, int64_t out_cols, int64_t ld_out) {
+    return ld_out == out_cols || owns_padding(out_cols, ld_out) ? out_rows * ld_out : out_cols;
 }
 
 // where the first-level maxima of a tensor go: the caller's side storage, if any (the cast then folds them), else the
@@ -1139,7 +1159,7 @@ hipError_t cast_t_col(const ColOperand& a, const Partials& pa, int64_t Ga, const
         nullptr, pa.folded ? (int)Ga : 0, flags & 1, a.scale_col,
         b ? (int)ta : NO_TWIN, b ? static_cast<const uint16_t*>(b->x) : nullptr, b ? b->rows : 0, b ? b->ld : 0, sb,
         b ? b->q_col_t : nullptr, b ? b->ld_col_t : 0, (int)gyb, ld_part, b && pb.folded ? (int)Gb : 0, b ? b->scale_col : nullptr,
-        nullptr, 0);
+        nullptr, 0, owns_padding(a.rows, a.ld_col_t) | (b ? owns_padding(b->rows, b->ld_col_t) : 0));
     return hipGetLastError();
 }
 hipError_t cast_t_col(int fmt, const ColOperand& a, const Partials& pa, int64_t Ga, const ColOperand* b, const Partials& pb,

@@ -327,6 +327,23 @@ hipError_t launch_gemm_fp8(const uint8_t* a, int64_t lda, int fmt_a, const float
     return hipErrorInvalidValue;
 }
 
+// The block-scaled product takes the same tiles; its K steps cost a tenth more with the scales in slabs and a quarter more
+// with plain scale rows (a cache line per row and step).  256 x 256 tiles: 9 + 1.05 * steps for at most half of the CUs,
+// else 10 + 1.25 * steps (there are no half tiles).  Measured (us, slabs / plain, before: 256 x 256 or register-staged tiles):
+//     1024 x 1024 x 4096  64x64 12.6 / 14.3, before 40.7 / 77.2     2048 x 2048 x 4096  128x128 21.7 / 26.5, before 41.1 / 76.9
+//     2048 x 4096 x 4096  128x256 34.8 / 39.6, before 42.6 / 43.6   3072 x 4096 x 4096  128x256 59.5 / 67.4, 256x256 48.7 / 46.4
+int gemm_mxfp8_ring_choice(const GemmOperands& g, bool plain_scales) {
+    if (const int r = knob(KNOB_GEMM_RING); r >= 0 && r <= RING_TILES) return r - 1;
+    const int64_t cus = compute_units() > 0 ? compute_units() : 256;
+    const int64_t big = cdiv(g.M, 256) * cdiv(g.N, 256);
+    if (big > cus) return -1;
+    double cost = 0.0;
+    const int tile = best_ring(g, nullptr, cus, &cost);
+    const double steps = (double)cdiv(g.K, BK);
+    const double cost_big = 2 * big <= cus ? 9.0 + 1.05 * steps : 10.0 + 1.25 * steps;
+    return 3.0 + (cost - 3.0) * (plain_scales ? 1.25 : 1.1) <= cost_big ? tile : -1;
+}
+
 int gemm_fp8_ring_choice(const GemmOperands& g) {
     double cost;
     const int v = pick_path(g, &cost);

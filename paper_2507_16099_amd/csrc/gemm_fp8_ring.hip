@@ -1,5 +1,6 @@
 // Scaled FP8 GEMM for gfx950, products of few to middling size:
-// out[M,N] = (A[M,K] . B[N,K]^T) / (sa * sb), v_mfma_f32_16x16x128_f8f6f4.
+// out[M,N] = (A[M,K] . B[N,K]^T) / (sa * sb), v_mfma_f32_16x16x128_f8f6f4, and its block-scaled (MX) form
+// out[m,n] = sum_blk 2^(ea[m,blk]-127) 2^(eb[n,blk]-127) sum_{k in blk} a[m,k] b[n,k], v_mfma_scale_f32_16x16x128_f8f6f4.
 //
 // What bounds these products is not the matrix cores but the time from the request of a K step's operands to their
 // arrival: a workgroup is alone on its CU (there are fewer tiles than fill the chip many times over), and a K step of
@@ -15,6 +16,11 @@
 //
 // LDS layout, swizzle keys, operand roles (B is the first MFMA operand; a lane ends up with consecutive output
 // columns of one row) and the XCD-aware tile order are those of gemm_fp8_snake.hip; B groups can be 32 wide here.
+//
+// MX: a K step is four blocks of 32, so every stage also holds one dword of E8M0 scales per tile row (one LDS-DMA load per
+// 64 rows), and every fragment read is followed by a one-byte read: lane (l % 16, g) passes the scale of block g of row
+// l % 16 to the matrix instruction (gemm_mxfp8_snake.hip).  Scale rows in slabs of sixteen blocks cost 8 cache lines per
+// 64 rows and step, plain rows 64.
 #include "fp8_device.hpp"
 #include "launchers.hpp"
 #include "tuning.hpp"
@@ -51,6 +57,13 @@ __device__ __forceinline__ void lds_dma16(v4i_t rsrc, uint32_t lds_addr, uint32_
                  : "s"(lds_addr), "v"(voffset), "s"(rsrc)
                  : "memory", "m0");
 }
+// 4 bytes per lane into LDS at lds_addr + lane * 4 (the scales of 64 rows)
+__device__ __forceinline__ void lds_dma4(v4i_t rsrc, uint32_t lds_addr, uint32_t voffset) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds"
+                 :
+                 : "s"(lds_addr), "v"(voffset), "s"(rsrc)
+                 : "memory", "m0");
+}
 // at most N_ loads in flight (they complete in issue order), own LDS reads done, workgroup barrier
 template <int N_>
 __device__ __forceinline__ void wait_vmem_but_barrier() {
@@ -78,6 +91,24 @@ __device__ __forceinline__ void mfma(v4f_t& c, const v8i_t& b, const v8i_t& a) {
     }
 }
 #undef RG_MFMA
+// the same with block scales (the low byte of sb / sa)
+#define RG_MFMA_MX(CSTR, MOD) \
+    asm volatile("v_mfma_scale_f32_16x16x128_f8f6f4 %0, %1, %2, %0, %3, %4 op_sel:[0,0,0] op_sel_hi:[0,0,0]" MOD : CSTR(c) : "v"(b), "v"(a), "v"(sb), "v"(sa))
+template <int FA, int FB, bool ACC_V>
+__device__ __forceinline__ void mfma_mx(v4f_t& c, const v8i_t& b, const v8i_t& a, uint32_t sb, uint32_t sa) {
+    if constexpr (ACC_V) {
+        if constexpr (FB == 0 && FA == 0) RG_MFMA_MX("+v", "");
+        else if constexpr (FB == 1 && FA == 0) RG_MFMA_MX("+v", " cbsz:1");
+        else if constexpr (FB == 0 && FA == 1) RG_MFMA_MX("+v", " blgp:1");
+        else RG_MFMA_MX("+v", " cbsz:1 blgp:1");
+    } else {
+        if constexpr (FB == 0 && FA == 0) RG_MFMA_MX("+a", "");
+        else if constexpr (FB == 1 && FA == 0) RG_MFMA_MX("+a", " cbsz:1");
+        else if constexpr (FB == 0 && FA == 1) RG_MFMA_MX("+a", " blgp:1");
+        else RG_MFMA_MX("+a", " cbsz:1 blgp:1");
+    }
+}
+#undef RG_MFMA_MX
 __device__ __forceinline__ float sigmoid(float x) { return __builtin_amdgcn_rcpf(1.0f + __expf(-x)); }
 }  // namespace rg
 
@@ -90,10 +121,11 @@ struct RingProblem {
     // multiplications by ceil(2^32 / d) (exact below 2^16: a scalar division costs a lone workgroup 0.1 us each)
     int in_group; uint32_t inv_group, inv_tail;
     int per_xcd;             // an eighth of the tiles, rounded up: what each XCD walks
+    const uint8_t *EA, *EB; int64_t ld_ea, ld_eb;     // MX: scale rows, ld >= 0: plain, < 0: slabs of -ld rows
 };
 
 // mode: 0 = bfloat16 out, 1 = fp32 out, 2 = bfloat16 of the logistic function of the result
-template <int FA, int FB, int TM, int TN, int WAVES_M, int WAVES_N, int R, int GROUP_M>
+template <int FA, int FB, int TM, int TN, int WAVES_M, int WAVES_N, int R, int GROUP_M, bool MX>
 __global__ __launch_bounds__(rg::NT) void gemm_fp8_ring_kernel(RingProblem p1, RingProblem p2, int row_a, int row_b, int mode) {
     using namespace rg;
     constexpr int WM = TM / WAVES_M, WN = TN / WAVES_N;
@@ -101,11 +133,14 @@ __global__ __launch_bounds__(rg::NT) void gemm_fp8_ring_kernel(RingProblem p1, R
     constexpr int GW = WN < 64 ? WN : 64;            // B rows dealt together: a lane holds GW / 4 consecutive columns of a group
     constexpr int GT = GW / 16, NG = WN / GW;        // fragments per group, groups
     constexpr int SH = GW == 64 ? 4 : 3;             // log2(GW / 4)
-    constexpr int STAGE = (TM + TN) * BK;
-    constexpr int NLA = TM / 32, NLB = TN / 32, NL = NLA + NLB;   // LDS-DMA loads per wave and step
+    constexpr int TILE = (TM + TN) * BK;
+    constexpr int NLE = MX ? ((TM + TN) / 64 + 3) / 4 : 0;        // scale loads (64 rows each) per wave and step
+    constexpr int STAGE = TILE + NLE * 1024;
+    constexpr int NLA = TM / 32, NLB = TN / 32, NLD = NLA + NLB;  // data loads per wave and step
+    constexpr int NL = NLD + NLE;
     constexpr int NM = FM * FN;
-    constexpr bool ACC_V = 4 * NM + 16 * (FM + FN) <= 192;     // accumulators and both fragment sets fit 256 registers with the rest
-    static_assert(WAVES_M * WAVES_N == 4 && WM % 16 == 0 && (GW == 64 || GW == 32) && WN % GW == 0 && TM % 32 == 0 && TN % 32 == 0, "tile");
+    constexpr bool ACC_V = 4 * NM + (MX ? 18 : 16) * (FM + FN) <= 192;     // accumulators and both fragment sets fit 256 registers with the rest
+    static_assert(WAVES_M * WAVES_N == 4 && WM % 16 == 0 && (GW == 64 || GW == 32) && WN % GW == 0 && TM % 64 == 0 && TN % 64 == 0, "tile");
     static_assert(R >= 3 && (R - 1) * NL <= 63, "vmcnt range");
     static_assert(4 * WM * WN * 2 <= R * STAGE, "the epilogue stages through the ring");
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -132,7 +167,7 @@ __global__ __launch_bounds__(rg::NT) void gemm_fp8_ring_kernel(RingProblem p1, R
     // the compiler placed for them would also wait for every LDS-DMA load in flight.  They are older than those loads, so the
     // wait for stage 0 covers them; their registers are not touched before it.
     float raw_a, raw_b;
-    {
+    if constexpr (!MX) {
         const int m = m0 + tid, n = n0 + tid;
         const float* sa_p = p.scale_a + (row_a ? (m < M ? m : M - 1) : 0);
         const float* sb_p = p.scale_b + (row_b ? (n < N ? n : N - 1) : 0);
@@ -143,6 +178,7 @@ __global__ __launch_bounds__(rg::NT) void gemm_fp8_ring_kernel(RingProblem p1, R
     }
     float* inv_tab = reinterpret_cast<float*>(smem + R * STAGE);    // reciprocals: rows, then columns (behind the ring)
     auto scale_table = [&]() {
+        if constexpr (MX) return;
         asm volatile("" : "+v"(raw_a), "+v"(raw_b));
         if (tid < TM) inv_tab[tid] = 1.0f / raw_a;
         if (tid < TN) inv_tab[TM + tid] = 1.0f / raw_b;
@@ -171,7 +207,38 @@ __global__ __launch_bounds__(rg::NT) void gemm_fp8_ring_kernel(RingProblem p1, R
     constexpr uint32_t OOB = 0x80000000u;      // puts a lane outside its descriptor: zeros arrive
     auto load_q = [&](int q, uint32_t stage_off, uint32_t ka, uint32_t ke, uint32_t ko) {
         if (q < NLB) lds_dma16(rsrc_b, lds_base + stage_off + TM * BK + q * 4096, ((q & 1) ? vb0_o + ko : vb0_e + ke) + (uint32_t)q * vb_step);
-        else lds_dma16(rsrc_a, lds_base + stage_off + (q - NLB) * 4096, va0 + (uint32_t)(q - NLB) * va_step + ka);
+        else if (q < NLD) lds_dma16(rsrc_a, lds_base + stage_off + (q - NLB) * 4096, va0 + (uint32_t)(q - NLB) * va_step + ka);
+    };
+    // MX scales: unit u of a stage is the dwords of 64 rows, A's rows first; wave w loads units w, w + 4 (units past the last
+    // one deliver zeros into spare room, so that every wave has the same number of loads in flight).  Slabs: rows past the
+    // operand's end read the next slab's rows; their products reach only rows and columns that are never stored.
+    const bool slab_a = MX && p.ld_ea < 0, slab_b = MX && p.ld_eb < 0;
+    v4i_t rsrc_e[NLE ? NLE : 1];
+    uint32_t ve[NLE ? NLE : 1], gse[NLE ? NLE : 1];      // lane offset, bytes per four steps
+    if constexpr (MX) {
+#pragma unroll
+        for (int h = 0; h < NLE; ++h) {
+            const int u = wave + 4 * h;
+            const bool is_a = u < TM / 64, none = u >= (TM + TN) / 64;
+            const bool slab = is_a ? slab_a : slab_b;
+            const int64_t ld = is_a ? p.ld_ea : p.ld_eb;
+            const int r0 = is_a ? m0 : n0, rows = is_a ? rows_a : rows_b;
+            const int64_t group = slab ? -ld * 16 : 16;
+            const uint64_t pe = reinterpret_cast<uint64_t>((is_a ? p.EA : p.EB) + (int64_t)r0 * (slab ? 16 : ld));
+            const int64_t nrec = slab ? (int64_t)((K + 511) / 512) * group - (int64_t)r0 * 16 : (int64_t)(rows - 1) * ld + K / 32;
+            rsrc_e[h] = v4i_t{(int)(uint32_t)pe, (int)(uint32_t)(pe >> 32), none ? 0 : (int)nrec, 0x00020000};
+            ve[h] = (uint32_t)((64 * (is_a ? u : u - TM / 64) + lane) * (slab ? 16 : (int)ld));
+            gse[h] = (uint32_t)group;
+        }
+    }
+    const uint32_t lds_e = (uint32_t)(size_t)smem + (uint32_t)TILE + (uint32_t)wave * 256u;
+    auto load_e = [&](uint32_t stage_off, int k0) {
+        if constexpr (MX) {
+            const uint32_t s4 = (uint32_t)(k0 >> 9), sr = (uint32_t)((k0 >> 7) & 3) * 4;
+#pragma unroll
+            for (int h = 0; h < NLE; ++h)
+                lds_dma4(rsrc_e[h], lds_e + stage_off + h * 1024, k0 < K ? ve[h] + s4 * gse[h] + sr : OOB);
+        }
     };
     auto kofs = [&](int k0, int c) { return k0 + c * 16 < K ? (uint32_t)k0 : OOB; };
 
@@ -186,6 +253,8 @@ __global__ __launch_bounds__(rg::NT) void gemm_fp8_ring_kernel(RingProblem p1, R
         offb[c] = TM * BK + (wn0 + (GW / 4) * (r16 >> 2) + (r16 & 3)) * BK + (((g + 4 * c) ^ key_b) << 4);
     }
     v8i_t af[2][FM], bf[2][FN];
+    uint32_t ea[2][FM], eb[2][FN];      // their scales (MX)
+    const int offea = TILE + (wm0 + r16) * 4 + g, offeb = TILE + (TM + wn0 + (GW / 4) * (r16 >> 2) + (r16 & 3)) * 4 + g;
     auto read_q = [&](auto set_t, const uint8_t* s, int q) {      // fragment q: first the B ones, then the A ones
         constexpr int SET = decltype(set_t)::value;
         const bool is_b = q < FN;
@@ -194,6 +263,10 @@ __global__ __launch_bounds__(rg::NT) void gemm_fp8_ring_kernel(RingProblem p1, R
         const uint4 x1 = *reinterpret_cast<const uint4*>(s + (is_b ? offb[1] : offa[1]) + ro);
         const v8i_t v = {(int)x0.x, (int)x0.y, (int)x0.z, (int)x0.w, (int)x1.x, (int)x1.y, (int)x1.z, (int)x1.w};
         if (is_b) bf[SET][q < FN ? q : 0] = v; else af[SET][q < FN ? 0 : q - FN] = v;
+        if constexpr (MX) {
+            const uint32_t e = s[(is_b ? offeb + ((q / GT) * GW + (q % GT) * 4) * 4 : offea + (q - FN) * 64)];
+            if (is_b) eb[SET][q < FN ? q : 0] = e; else ea[SET][q < FN ? 0 : q - FN] = e;
+        }
     };
 
     v4f_t acc[FM][FN];
@@ -211,7 +284,8 @@ __global__ __launch_bounds__(rg::NT) void gemm_fp8_ring_kernel(RingProblem p1, R
             const int k0 = r * BK;
             const uint32_t ka = kofs(k0, ca), ke = kofs(k0, cb_e), ko = kofs(k0, cb_o);
 #pragma unroll
-            for (int q = 0; q < NL; ++q) load_q(q, (uint32_t)(r * STAGE), ka, ke, ko);
+            for (int q = 0; q < NLD; ++q) load_q(q, (uint32_t)(r * STAGE), ka, ke, ko);
+            load_e((uint32_t)(r * STAGE), k0);
         }
         wait_vmem_but_barrier<(R - 1) * NL>();      // stage 0 has landed for everyone
 #pragma unroll
@@ -234,13 +308,15 @@ __global__ __launch_bounds__(rg::NT) void gemm_fp8_ring_kernel(RingProblem p1, R
 #pragma unroll
             for (int t = 0; t < NM; ++t) {
                 const int i = t / FN, j = (i & 1) ? FN - 1 - t % FN : t % FN;   // boustrophedon: one operand stays between neighbours
-                mfma<FA, FB, ACC_V>(acc[i][j], bf[P][j], af[P][i]);
+                if constexpr (MX) mfma_mx<FA, FB, ACC_V>(acc[i][j], bf[P][j], af[P][i], eb[P][j], ea[P][i]);
+                else mfma<FA, FB, ACC_V>(acc[i][j], bf[P][j], af[P][i]);
                 if (t < QR) {
 #pragma unroll
                     for (int q = t * (FM + FN) / QR; q < (t + 1) * (FM + FN) / QR; ++q) read_q(NS{}, rs, q);
                 }
 #pragma unroll
-                for (int q = t * NL / NM; q < (t + 1) * NL / NM; ++q) load_q(q, cur, ka, ke, ko);
+                for (int q = t * NLD / NM; q < (t + 1) * NLD / NM; ++q) load_q(q, cur, ka, ke, ko);
+                if (MX && t == NM - 1) load_e(cur, k_refill);
                 __builtin_amdgcn_sched_barrier(0);
             }
             cur = nxt;
@@ -260,19 +336,24 @@ __global__ __launch_bounds__(rg::NT) void gemm_fp8_ring_kernel(RingProblem p1, R
     }
     __syncthreads();
 
-    // ---- epilogue: (acc * 1/sa) * 1/sb
+    // ---- epilogue: (acc * 1/sa) * 1/sb (MX: nothing left to scale)
     constexpr int CE = GW / 4;                          // consecutive columns of a lane in a group
     float inv_b[NG][CE];
 #pragma unroll
     for (int grp = 0; grp < NG; ++grp)
 #pragma unroll
         for (int e = 0; e < CE; e += 4) {
+            if constexpr (MX) break;
             const float4 t4 = *reinterpret_cast<const float4*>(inv_tab + TM + wn0 + GW * grp + CE * g + e);
             inv_b[grp][e] = t4.x; inv_b[grp][e + 1] = t4.y; inv_b[grp][e + 2] = t4.z; inv_b[grp][e + 3] = t4.w;
         }
     float inv_a[FM];
 #pragma unroll
-    for (int fi = 0; fi < FM; ++fi) inv_a[fi] = inv_tab[wm0 + 16 * fi + r16];
+    for (int fi = 0; fi < FM; ++fi) inv_a[fi] = MX ? 1.0f : inv_tab[wm0 + 16 * fi + r16];
+    auto result = [&](int fi, int grp, int e) {
+        const float v = acc[fi][grp * GT + (e >> 2)][e & 3];
+        return MX ? v : (v * inv_a[fi]) * inv_b[grp][e];
+    };
     const int64_t ld_out = p.ld_out;
     if (mode == 1) {
 #pragma unroll
@@ -285,7 +366,7 @@ __global__ __launch_bounds__(rg::NT) void gemm_fp8_ring_kernel(RingProblem p1, R
                     const int nb = n0 + wn0 + GW * grp + CE * g + 4 * t;
                     float v[4];
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) v[r] = (acc[fi][grp * GT + t][r] * inv_a[fi]) * inv_b[grp][4 * t + r];
+                    for (int r = 0; r < 4; ++r) v[r] = result(fi, grp, 4 * t + r);
                     if (m < M && nb < N) {
                         float* dst = static_cast<float*>(p.out) + (int64_t)m * ld_out + nb;
                         if (nb + 4 <= N) *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[2], v[3]);
@@ -310,7 +391,7 @@ __global__ __launch_bounds__(rg::NT) void gemm_fp8_ring_kernel(RingProblem p1, R
         for (int grp = 0; grp < NG; ++grp) {
             float v[CE];
 #pragma unroll
-            for (int e = 0; e < CE; ++e) v[e] = (acc[fi][grp * GT + (e >> 2)][e & 3] * inv_a[fi]) * inv_b[grp][e];
+            for (int e = 0; e < CE; ++e) v[e] = result(fi, grp, e);
             if (mode == 2) {
 #pragma unroll
                 for (int e = 0; e < CE; ++e) v[e] = sigmoid(v[e]);
@@ -345,20 +426,24 @@ __global__ __launch_bounds__(rg::NT) void gemm_fp8_ring_kernel(RingProblem p1, R
     }
 }
 
-template <int FA, int FB, int TM, int TN, int WAVES_M, int WAVES_N, int R, int GROUP_M>
-static hipError_t launch_ring_t(const GemmOperands& g1, const GemmOperands* g2, int row_a, int row_b, int mode, hipStream_t st) {
+struct MxScales { const uint8_t *ea, *eb; int64_t ld_ea, ld_eb; };     // of one product
+
+template <int FA, int FB, int TM, int TN, int WAVES_M, int WAVES_N, int R, int GROUP_M, bool MX>
+static hipError_t launch_ring_t(const GemmOperands& g1, const GemmOperands* g2, const MxScales* e, int row_a, int row_b, int mode,
+                                hipStream_t st) {
     using namespace rg;
-    auto kern = gemm_fp8_ring_kernel<FA, FB, TM, TN, WAVES_M, WAVES_N, R, GROUP_M>;
-    constexpr int lds = R * (TM + TN) * BK + (TM + TN) * 4;
+    auto kern = gemm_fp8_ring_kernel<FA, FB, TM, TN, WAVES_M, WAVES_N, R, GROUP_M, MX>;
+    constexpr int lds = R * ((TM + TN) * BK + (MX ? ((TM + TN) / 64 + 3) / 4 * 1024 : 0)) + (MX ? 0 : (TM + TN) * 4);
     static_assert(lds <= 160 * 1024, "LDS");
     static DynamicLdsOnce attr;     // one per instantiation
-    if (hipError_t e = attr.ensure(reinterpret_cast<const void*>(kern), lds); e != hipSuccess) return e;
+    if (hipError_t err = attr.ensure(reinterpret_cast<const void*>(kern), lds); err != hipSuccess) return err;
     auto problem = [&](const GemmOperands& g) {
         const int tiles_m = (int)((g.M + TM - 1) / TM), tiles_n = (int)((g.N + TN - 1) / TN);
         const int in_group = GROUP_M * tiles_n, tail = tiles_m % GROUP_M ? tiles_m % GROUP_M : GROUP_M;
         auto inv = [](int d) { return (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); };   // (0 for d = 1, which the kernel does not use)
         return RingProblem{g.a, g.lda, g.b, g.ldb, g.scale_a, g.scale_b, (int)g.M, (int)g.N, (int)g.K, g.out, g.ld_out, tiles_m, tiles_n,
-                           in_group, inv(in_group), inv(tail), (tiles_m * tiles_n + NUM_XCD - 1) / NUM_XCD};
+                           in_group, inv(in_group), inv(tail), (tiles_m * tiles_n + NUM_XCD - 1) / NUM_XCD,
+                           e ? e->ea : nullptr, e ? e->eb : nullptr, e ? e->ld_ea : 0, e ? e->ld_eb : 0};
     };
     const RingProblem p1 = problem(g1), p2 = g2 ? problem(*g2) : p1;
     const int per_xcd = p1.per_xcd > p2.per_xcd ? p1.per_xcd : p2.per_xcd;
@@ -366,15 +451,17 @@ static hipError_t launch_ring_t(const GemmOperands& g1, const GemmOperands* g2, 
     return hipGetLastError();
 }
 
-template <int FA, int FB>
-static hipError_t launch_ring_f(int tile, const GemmOperands& g1, const GemmOperands* g2, int row_a, int row_b, int mode, hipStream_t st) {
+// stages: what the LDS holds (64 x 64: for two workgroups per CU); rows of tiles walked together: close to square patches
+template <int FA, int FB, bool MX>
+static hipError_t launch_ring_f(int tile, const GemmOperands& g1, const GemmOperands* g2, const MxScales* e, int row_a, int row_b,
+                                int mode, hipStream_t st) {
     switch (tile) {
-        case RING_64x64: return launch_ring_t<FA, FB, 64, 64, 2, 2, 5, 4>(g1, g2, row_a, row_b, mode, st);     // two workgroups per CU
-        case RING_128x64: return launch_ring_t<FA, FB, 128, 64, 2, 2, 6, 4>(g1, g2, row_a, row_b, mode, st);
-        case RING_64x128: return launch_ring_t<FA, FB, 64, 128, 2, 2, 6, 8>(g1, g2, row_a, row_b, mode, st);
-        case RING_128x128: return launch_ring_t<FA, FB, 128, 128, 2, 2, 4, 4>(g1, g2, row_a, row_b, mode, st);
-        case RING_128x256: return launch_ring_t<FA, FB, 128, 256, 2, 2, 3, 8>(g1, g2, row_a, row_b, mode, st);
-        case RING_256x128: return launch_ring_t<FA, FB, 256, 128, 2, 2, 3, 4>(g1, g2, row_a, row_b, mode, st);
+        case RING_64x64: return launch_ring_t<FA, FB, 64, 64, 2, 2, MX ? 4 : 5, 4, MX>(g1, g2, e, row_a, row_b, mode, st);
+        case RING_128x64: return launch_ring_t<FA, FB, 128, 64, 2, 2, 6, 4, MX>(g1, g2, e, row_a, row_b, mode, st);
+        case RING_64x128: return launch_ring_t<FA, FB, 64, 128, 2, 2, 6, 8, MX>(g1, g2, e, row_a, row_b, mode, st);
+        case RING_128x128: return launch_ring_t<FA, FB, 128, 128, 2, 2, 4, 4, MX>(g1, g2, e, row_a, row_b, mode, st);
+        case RING_128x256: return launch_ring_t<FA, FB, 128, 256, 2, 2, 3, 8, MX>(g1, g2, e, row_a, row_b, mode, st);
+        case RING_256x128: return launch_ring_t<FA, FB, 256, 128, 2, 2, 3, 4, MX>(g1, g2, e, row_a, row_b, mode, st);
     }
     return hipErrorInvalidValue;
 }
@@ -388,7 +475,26 @@ hipError_t launch_gemm_fp8_ring(int tile, const GemmOperands& g1, const GemmOper
                                 int row_b, int mode, hipStream_t st) {
     if (g1.M == 0 || g1.N == 0 || (g2 && (g2->M == 0 || g2->N == 0))) return hipErrorInvalidValue;
 #define FP8K_RING(FA_, FB_) \
-    if (fmt_a == FA_ && fmt_b == FB_) return launch_ring_f<FA_, FB_>(tile, g1, g2, row_a, row_b, mode, st)
+    if (fmt_a == FA_ && fmt_b == FB_) return launch_ring_f<FA_, FB_, false>(tile, g1, g2, nullptr, row_a, row_b, mode, st)
+    FP8K_RING(FMT_E4M3FN, FMT_E4M3FN);
+    FP8K_RING(FMT_E5M2, FMT_E4M3FN);
+    FP8K_RING(FMT_E4M3FN, FMT_E5M2);
+    FP8K_RING(FMT_E5M2, FMT_E5M2);
+#undef FP8K_RING
+    return hipErrorInvalidValue;
+}
+
+bool gemm_mxfp8_ring_fits(const GemmOperands& g, int64_t ld_ea, int64_t ld_eb) {
+    auto reach = [&](int64_t ld, int64_t rows) { return ld >= 0 ? ld < (1 << 22) : -ld >= rows && -ld * ((g.K + 511) / 512) < (1ll << 26); };
+    return gemm_fp8_ring_fits(g) && g.K > 0 && g.K % 128 == 0 && reach(ld_ea, g.M) && reach(ld_eb, g.N);
+}
+
+hipError_t launch_gemm_mxfp8_ring(int tile, const GemmOperands& g, int fmt_a, int fmt_b, const uint8_t* ea, int64_t ld_ea,
+                                  const uint8_t* eb, int64_t ld_eb, int out_f32, hipStream_t st) {
+    if (g.M == 0 || g.N == 0) return hipErrorInvalidValue;
+    const MxScales e{ea, eb, ld_ea, ld_eb};
+#define FP8K_RING(FA_, FB_) \
+    if (fmt_a == FA_ && fmt_b == FB_) return launch_ring_f<FA_, FB_, true>(tile, g, nullptr, &e, 0, 0, out_f32 ? 1 : 0, st)
     FP8K_RING(FMT_E4M3FN, FMT_E4M3FN);
     FP8K_RING(FMT_E5M2, FMT_E4M3FN);
     FP8K_RING(FMT_E4M3FN, FMT_E5M2);

@@ -239,12 +239,13 @@ static hipError_t launch_mx_t(const uint8_t* a, int64_t lda, const uint8_t* ea, 
 
 // K must be a multiple of 128 and ld_ea, ld_eb multiples of 4 (a K step reads one aligned
 // dword of scales per row); checked by the caller
-// large problems: the LDS-DMA kernel (the switch MX_VARIANT = 0 forces this file's kernel, 1 the other)
+// large problems: the 256 x 256 LDS-DMA kernel; less than a round of its tiles: mostly the ring kernel (gemm_fp8_ring.hip), in
+// launch_gemm_mxfp8 (the switch MX_VARIANT = 0 forces this file's kernel, 1 the 256 x 256 one)
 static bool mx_snake_possible(int64_t lda, int64_t ldb, int64_t K) { return K > 0 && gemm_fp8_snake_fits(lda, ldb); }
 static bool mx_takes_snake(int64_t lda, int64_t ldb, int64_t M, int64_t N, int64_t K) {
     const int64_t tiles256 = ((M + 255) / 256) * ((N + 255) / 256);
     const int forced = knob(KNOB_MX_VARIANT);
-    const bool big = forced >= 0 ? forced == 1 : tiles256 > 64;
+    const bool big = forced >= 0 ? forced == 1 : tiles256 > 64;      // (fewer: reached where the ring kernel's 32-bit offsets do not suffice)
     return big && mx_snake_possible(lda, ldb, K);
 }
 // shapes whose scales can lie in slabs of sixteen blocks (whole 16-byte scale pieces, 32-bit offsets reach)
@@ -257,18 +258,24 @@ static bool mx_slab_possible(int64_t lda, int64_t ldb, int64_t M, int64_t N, int
 // passes the decision down through the sign of the leading dimensions; the switch MX_SLAB = 0 turns it off.
 bool gemm_mxfp8_takes_slab_scales(int64_t lda, int64_t ldb, int64_t M, int64_t N, int64_t K) {
     if (knob(KNOB_MX_SLAB) == 0) return false;
-    return mx_takes_snake(lda, ldb, M, N, K) && mx_slab_possible(lda, ldb, M, N, K);
+    if (knob(KNOB_MX_VARIANT) >= 0 && !mx_takes_snake(lda, ldb, M, N, K)) return false;
+    return mx_slab_possible(lda, ldb, M, N, K);      // both LDS-DMA kernels read them
 }
 
 // ld_ea / ld_eb >= 0: scale rows of that many bytes.  < 0: slabs of sixteen blocks, [K / 512][-ld rows][16 bytes]
-// (for both operands alike; only the LDS-DMA kernel reads that layout, so it is taken whatever the switches say).
+// (for both operands alike; only the LDS-DMA kernels read that layout, so one of them is taken whatever the switches say).
 hipError_t launch_gemm_mxfp8(const uint8_t* a, int64_t lda, int fmt_a, const uint8_t* ea, int64_t ld_ea,
                              const uint8_t* b, int64_t ldb, int fmt_b, const uint8_t* eb, int64_t ld_eb, int64_t M,
                              int64_t N, int64_t K, void* out, int64_t ld_out, int out_f32, hipStream_t st) {
     if (M == 0 || N == 0) return hipSuccess;
-    if (ld_ea < 0 || ld_eb < 0) {
-        if (!(ld_ea < 0 && ld_eb < 0) || -ld_ea < M || -ld_eb < N || !mx_slab_possible(lda, ldb, M, N, K))
-            return hipErrorInvalidValue;
+    const bool slabs = ld_ea < 0 || ld_eb < 0;
+    if (slabs && (!(ld_ea < 0 && ld_eb < 0) || -ld_ea < M || -ld_eb < N || !mx_slab_possible(lda, ldb, M, N, K)))
+        return hipErrorInvalidValue;
+    const GemmOperands g{a, lda, nullptr, b, ldb, nullptr, M, N, K, out, ld_out};
+    if (knob(KNOB_MX_VARIANT) < 0 && gemm_mxfp8_ring_fits(g, ld_ea, ld_eb))
+        if (const int tile = gemm_mxfp8_ring_choice(g, !slabs); tile >= 0)
+            return launch_gemm_mxfp8_ring(tile, g, fmt_a, fmt_b, ea, ld_ea, eb, ld_eb, out_f32, st);
+    if (slabs) {
         return launch_gemm_mxfp8_snake(a, lda, fmt_a, ea, ld_ea, b, ldb, fmt_b, eb, ld_eb, M, N, K, out, ld_out, out_f32, st);
     }
     if (mx_takes_snake(lda, ldb, M, N, K) && ld_ea < (1 << 23) && ld_eb < (1 << 23))

@@ -68,6 +68,12 @@ int gemm_fp8_ring_choice(const GemmOperands& g);      // its tile where a 256 x 
 hipError_t launch_gemm_fp8_ring(int tile, const GemmOperands& g1, const GemmOperands* g2, int fmt_a, int fmt_b, int row_a,
                                 int row_b, int mode, hipStream_t st);
 
+// the block-scaled form (K a multiple of 128; scales as for launch_gemm_mxfp8, g.scale_a / g.scale_b unused)
+bool gemm_mxfp8_ring_fits(const GemmOperands& g, int64_t ld_ea, int64_t ld_eb);
+int gemm_mxfp8_ring_choice(const GemmOperands& g, bool plain_scales);      // a tile, or -1
+hipError_t launch_gemm_mxfp8_ring(int tile, const GemmOperands& g, int fmt_a, int fmt_b, const uint8_t* ea, int64_t ld_ea,
+                                  const uint8_t* eb, int64_t ld_eb, int out_f32, hipStream_t st);
+
 // Rowwise quantization (codes q, scales scale_out) and the per-column scales
 // scale_cols[c] = scale(max_r |x[r, c]|) from a single read of x; scratch holds
 // the first-level column maxima.  hipErrorNotSupported if the shape does not suit.

@@ -186,7 +186,8 @@ typedef struct fp8_recipe {
 } fp8_recipe;
 
 /* Bytes of workspace fp8_linear_fwd (bwd == 0) or fp8_linear_bwd (bwd != 0)
- * needs for X [M,K], W [N,K], dY [M,N].  Returns 0 on invalid arguments. */
+ * needs for X [M,K], W [N,K], dY [M,N] (the fp8 copies lie in it with rows padded
+ * to 128 bytes: ask, do not compute).  Returns 0 on invalid arguments. */
 size_t fp8_linear_workspace_bytes(int64_t M, int64_t K, int64_t N, const fp8_recipe* recipe, int bwd);
 
 /*

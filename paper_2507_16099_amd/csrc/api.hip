@@ -66,10 +66,11 @@ size_t output_scratch_bytes(int64_t out_rows, int64_t out_cols, int64_t ld_out) 
     return ld_out == out_cols ? (size_t)out_rows * (size_t)out_cols : (size_t)out_cols;
 }
 
-// amax -> scale -> cast of one operand; amax_tmp has n_groups floats
+// amax -> scale -> cast of one operand; own_rows: the bytes between the output's rows are the library's (a workspace) and
+// hold nothing
 int quantize_impl(const void* x, int64_t rows, int64_t cols, int64_t ld, int gran, int format, int flags,
                   uint8_t* q, int64_t ld_out, uint8_t* q_plain, int64_t ld_plain, float* scale_out,
-                  hipStream_t st, float* part = nullptr) {
+                  hipStream_t st, float* part = nullptr, bool own_rows = false) {
     const int transpose = (flags & FP8_TRANSPOSE_OUT) ? 1 : 0;
     const int pow2 = flags & FP8_POW2_SCALE;
     // dense tensor, one scale, scratch for the per-block maxima at hand: two launches instead of four
@@ -91,7 +92,7 @@ int quantize_impl(const void* x, int64_t rows, int64_t cols, int64_t ld, int gra
     hipError_t ea = hipErrorNotSupported;
     if (gran == FP8_COL && transpose && q_plain == nullptr && rows > 0 && cols > 0)
         ea = fp8k::launch_col_scales_two_level(x, rows, cols, ld, format, pow2, scale_out, q,
-                                               output_scratch_bytes(cols, rows, ld_out), st);
+                                               output_scratch_bytes(cols, own_rows ? ld_out : rows, ld_out), st);
     if (ea == hipErrorNotSupported) {
         ea = fp8k::launch_amax(x, rows, cols, ld, gran, scale_out, st);
         if (ea != hipSuccess) return hip_fail(ea, "amax");
@@ -108,12 +109,12 @@ int quantize_impl(const void* x, int64_t rows, int64_t cols, int64_t ld, int gra
 // first-level maxima until the cast overwrites it)
 int quantize_row_col_impl(const void* x, int64_t rows, int64_t cols, int64_t ld, int format, int flags,
                           uint8_t* q_row, int64_t ld_row, float* scale_row, uint8_t* q_col_t, int64_t ld_col_t,
-                          float* scale_col, hipStream_t st) {
+                          float* scale_col, hipStream_t st, bool own_rows = false) {
     const int pow2 = flags & FP8_POW2_SCALE;
     hipError_t e = hipErrorNotSupported;
     if (rows > 0 && cols > 0)
         e = fp8k::launch_quant_row_colmax(x, rows, cols, ld, format, pow2, q_row, ld_row, scale_row, scale_col, q_col_t,
-                                          output_scratch_bytes(cols, rows, ld_col_t), st);
+                                          output_scratch_bytes(cols, own_rows ? ld_col_t : rows, ld_col_t), st);
     if (e == hipSuccess) {
         FP8_TRY(fp8k::launch_cast(x, rows, cols, ld, scale_col, FP8_COL, format, 1, q_col_t, ld_col_t, nullptr, 0, st));
         return FP8_OK;
@@ -121,7 +122,7 @@ int quantize_row_col_impl(const void* x, int64_t rows, int64_t cols, int64_t ld,
     if (e != hipErrorNotSupported) return hip_fail(e, "quant_row_colmax");
     if (int rc = quantize_impl(x, rows, cols, ld, FP8_ROW, format, pow2, q_row, ld_row, nullptr, 0, scale_row, st)) return rc;
     return quantize_impl(x, rows, cols, ld, FP8_COL, format, pow2 | FP8_TRANSPOSE_OUT, q_col_t, ld_col_t, nullptr, 0,
-                         scale_col, st);
+                         scale_col, st, nullptr, own_rows);
 }
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -130,6 +131,16 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 // transposing casts of the tensorwise and of the paired launches, cleared beforehand where the single-tensor calls are
 // used - so the product may contract over the padded length.
 int64_t pad16(int64_t v) { return (v + 15) / 16 * 16; }
+// Leading dimensions of the fp8 operands inside a workspace, by the length they contract over.  A product reads its
+// operands 128 bytes of a row at a time; with rows that start between cache lines every such piece is two lines, which
+// costs the products 14-22 % (1024^2 x 3504: 12.4 -> 9.7 us, 4096 x 8192 x 3504: 105 -> 90, 8192^2 x 4016: 214 -> 188) and the
+// transposing cast of 8152 tokens 38 -> 27 us.  So lengths beyond 512 are padded to 128 (shorter ones are bound by
+// launches).
+struct Pitch { int64_t k, n, m; };
+Pitch pitch_of(int64_t M, int64_t K, int64_t N) {
+    auto up = [](int64_t v) { return v <= 512 ? pad16(v) : (v + 127) / 128 * 128; };
+    return Pitch{up(K), up(N), up(M)};
+}
 
 // part: per-block maxima of the tensorwise amax pass, room for two tensors (a pair shares its launches; otherwise one
 // tensor at a time: the casts consume them in stream order)
@@ -142,11 +153,12 @@ struct BwdPlan {
 };
 
 FwdPlan plan_fwd(int64_t M, int64_t K, int64_t N, int gran) {
+    const Pitch ld = pitch_of(M, K, N);
     FwdPlan p{};
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes, 256); return at; };
-    p.xq = take((size_t)M * K);
-    p.wq = take((size_t)N * K);
+    p.xq = take((size_t)M * ld.k);
+    p.wq = take((size_t)N * ld.k);
     p.sx = take(sizeof(float) * (gran == FP8_ROW ? (size_t)M : 1));
     p.sw = take(sizeof(float) * (gran == FP8_ROW ? (size_t)N : 1));
     p.part = take(2 * sizeof(float) * fp8k::TENSOR_PARTIALS);
@@ -157,14 +169,15 @@ FwdPlan plan_fwd(int64_t M, int64_t K, int64_t N, int gran) {
 }
 
 BwdPlan plan_bwd(int64_t M, int64_t K, int64_t N, int gran) {
+    const Pitch ld = pitch_of(M, K, N);
     BwdPlan p{};
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes, 256); return at; };
     const bool row = gran == FP8_ROW;
-    p.gq = take((size_t)M * N);   // dY codes, [M, N]
-    p.gqt = take((size_t)pad16(M) * N);  // dY codes, [N, M] (rows padded to multiples of 16 bytes)
-    p.wt = take((size_t)K * N);   // W codes,  [K, N]
-    p.xt = take((size_t)K * pad16(M));   // X codes,  [K, M] (rows padded likewise)
+    p.gq = take((size_t)M * ld.n);   // dY codes, [M, N]
+    p.gqt = take((size_t)ld.m * N);  // dY codes, [N, M] (rows padded to multiples of 16 bytes at least)
+    p.wt = take((size_t)K * ld.n);   // W codes,  [K, N]
+    p.xt = take((size_t)K * ld.m);   // X codes,  [K, M] (rows padded likewise)
     p.sg = take(sizeof(float) * (row ? (size_t)M : 1));
     p.sgt = take(sizeof(float) * (row ? (size_t)N : 1));
     p.swt = take(sizeof(float) * (row ? (size_t)K : 1));
@@ -177,21 +190,28 @@ BwdPlan plan_bwd(int64_t M, int64_t K, int64_t N, int gran) {
     return p;
 }
 
+// Bytes of a workspace: the forward's or the backward's layout; with FP8_SAVE_FOR_BWD both, the backward's first (it holds
+// the saved copies).
+size_t linear_bytes(int64_t M, int64_t K, int64_t N, const fp8_recipe* r, bool bwd) {
+    const size_t f = plan_fwd(M, K, N, r->gran).total, b = plan_bwd(M, K, N, r->gran).total;
+    return (r->flags & FP8_SAVE_FOR_BWD) ? b + f : bwd ? b : f;
+}
+
 // The two products of a backward step from quantized operands: dX[M, K] = dY W (contraction over N) and
 // dW[N, K] = dY^T X (contraction over M).  sg / sgt: scales of dY for the first / second product (the same
-// pointer for tensorwise scaling).  Small products share one launch.  Mp: padded token count, the leading dimension
-// of gqt and xt and the contraction length of the second product.
+// pointer for tensorwise scaling).  Small products share one launch.  Mp: token count padded to 16, the contraction length
+// of the second product.
 int grad_gemms(const fp8_recipe* r, int row, const uint8_t* gq, const float* sg, const uint8_t* wt, const float* swt,
                const uint8_t* gqt, const float* sgt, const uint8_t* xt, const float* sxt, int64_t M, int64_t Mp, int64_t K,
-               int64_t N, void* dx, void* dw, hipStream_t st) {
+               int64_t N, const Pitch& ld, void* dx, void* dw, hipStream_t st) {
     if (dx && dw && r->fmt_w == r->fmt_x) {
-        const fp8k::GemmOperands g1{gq, N, sg, wt, N, swt, M, K, N, dx, K}, g2{gqt, Mp, sgt, xt, Mp, sxt, N, K, Mp, dw, K};
+        const fp8k::GemmOperands g1{gq, ld.n, sg, wt, ld.n, swt, M, K, N, dx, K}, g2{gqt, ld.m, sgt, xt, ld.m, sxt, N, K, Mp, dw, K};
         const hipError_t e = fp8k::launch_gemm_fp8_pair(g1, g2, r->fmt_dy, r->fmt_w, row, row, st);
         if (e == hipSuccess) return FP8_OK;
         if (e != hipErrorNotSupported) return hip_fail(e, "gemm_fp8_pair");
     }
-    if (dx) FP8_TRY(fp8k::launch_gemm_fp8(gq, N, r->fmt_dy, sg, row, wt, N, r->fmt_w, swt, row, M, K, N, dx, K, 0, st));
-    if (dw) FP8_TRY(fp8k::launch_gemm_fp8(gqt, Mp, r->fmt_dy, sgt, row, xt, Mp, r->fmt_x, sxt, row, N, K, Mp, dw, K, 0, st));
+    if (dx) FP8_TRY(fp8k::launch_gemm_fp8(gq, ld.n, r->fmt_dy, sg, row, wt, ld.n, r->fmt_w, swt, row, M, K, N, dx, K, 0, st));
+    if (dw) FP8_TRY(fp8k::launch_gemm_fp8(gqt, ld.m, r->fmt_dy, sgt, row, xt, ld.m, r->fmt_x, sxt, row, N, K, Mp, dw, K, 0, st));
     return FP8_OK;
 }
 
@@ -346,12 +366,8 @@ size_t fp8_linear_workspace_bytes(int64_t M, int64_t K, int64_t N, const fp8_rec
     g_err[0] = 0;
     if (check_recipe("fp8_linear_workspace_bytes", recipe)) return 0;
     if (check_linear_dims("fp8_linear_workspace_bytes", M, K, N, bwd != 0)) return 0;
-    size_t t = bwd ? plan_bwd(M, K, N, recipe->gran).total : plan_fwd(M, K, N, recipe->gran).total;
-    // shared workspace: the backward's layout (it holds the saved copies), then the forward's own buffers
-    if (recipe->flags & FP8_SAVE_FOR_BWD) {
-        if (check_linear_dims("fp8_linear_workspace_bytes", M, K, N, true)) return 0;
-        t = plan_bwd(M, K, N, recipe->gran).total + plan_fwd(M, K, N, recipe->gran).total;
-    }
+    if ((recipe->flags & FP8_SAVE_FOR_BWD) && check_linear_dims("fp8_linear_workspace_bytes", M, K, N, true)) return 0;
+    const size_t t = linear_bytes(M, K, N, recipe, bwd != 0);
     return t ? t : 256;
 }
 
@@ -366,6 +382,7 @@ int fp8_linear_fwd(const void* x, const void* w, int64_t M, int64_t K, int64_t N
     if (!y || !workspace) return fail(FP8_ERR_NULL, "fp8_linear_fwd: y or workspace is NULL");
     if (!aligned(y, 16) || !aligned(workspace, 256)) return fail(FP8_ERR_ALIGN, "fp8_linear_fwd: y (16) / workspace (256) misaligned");
     const FwdPlan p = plan_fwd(M, K, N, recipe->gran);
+    const Pitch ld = pitch_of(M, K, N);
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (recipe->flags & FP8_SAVE_FOR_BWD) {
         // The copies of X and W that the backward needs do not depend on the gradient, so they are made
@@ -381,44 +398,43 @@ int fp8_linear_fwd(const void* x, const void* w, int64_t M, int64_t K, int64_t N
         uint8_t* wsf = wsb + b.total;
         const int fl = recipe->flags & FP8_POW2_SCALE;
         float *sxt = reinterpret_cast<float*>(wsb + b.sxt), *swt = reinterpret_cast<float*>(wsb + b.swt);
-        const int64_t Mp = pad16(M);
         if (recipe->gran == FP8_TENSOR) {
             float* part = reinterpret_cast<float*>(wsf + p.part);
             bool pair_done = false;
             if (recipe->fmt_x == recipe->fmt_w && K > 0) {   // both tensors in two launches
-                const fp8k::TensorOperand ox{x, M, wsb + b.xt, Mp, wsf + p.xq, K, sxt, part};
-                const fp8k::TensorOperand ow{w, N, wsb + b.wt, N, wsf + p.wq, K, swt, part + fp8k::TENSOR_PARTIALS};
+                const fp8k::TensorOperand ox{x, M, wsb + b.xt, ld.m, wsf + p.xq, ld.k, sxt, part};
+                const fp8k::TensorOperand ow{w, N, wsb + b.wt, ld.n, wsf + p.wq, ld.k, swt, part + fp8k::TENSOR_PARTIALS};
                 const hipError_t e = fp8k::launch_quant_tensor_pair(ox, ow, K, recipe->fmt_x, fl, 1, st);
                 if (e == hipSuccess) pair_done = true;
                 else if (e != hipErrorNotSupported) return hip_fail(e, "quant_tensor_pair");
             }
             if (!pair_done) {
-                if (int rc = quantize_impl(x, M, K, K, FP8_TENSOR, recipe->fmt_x, fl | FP8_TRANSPOSE_OUT, wsb + b.xt, Mp, wsf + p.xq, K, sxt, st, part)) return rc;
-                if (int rc = quantize_impl(w, N, K, K, FP8_TENSOR, recipe->fmt_w, fl | FP8_TRANSPOSE_OUT, wsb + b.wt, N, wsf + p.wq, K, swt, st, part)) return rc;
+                if (int rc = quantize_impl(x, M, K, K, FP8_TENSOR, recipe->fmt_x, fl | FP8_TRANSPOSE_OUT, wsb + b.xt, ld.m, wsf + p.xq, ld.k, sxt, st, part)) return rc;
+                if (int rc = quantize_impl(w, N, K, K, FP8_TENSOR, recipe->fmt_w, fl | FP8_TRANSPOSE_OUT, wsb + b.wt, ld.n, wsf + p.wq, ld.k, swt, st, part)) return rc;
             }
-            FP8_TRY(fp8k::launch_gemm_fp8(wsf + p.xq, K, recipe->fmt_x, sxt, 0, wsf + p.wq, K, recipe->fmt_w, swt, 0, M, N, K, y, N, 0, st));
+            FP8_TRY(fp8k::launch_gemm_fp8(wsf + p.xq, ld.k, recipe->fmt_x, sxt, 0, wsf + p.wq, ld.k, recipe->fmt_w, swt, 0, M, N, K, y, N, 0, st));
             return FP8_OK;
         }
         float *sx = reinterpret_cast<float*>(wsf + p.sx), *sw = reinterpret_cast<float*>(wsf + p.sw);
         bool done = false;
         if (!(recipe->flags & FP8_GRAD_WEIGHT_HP) && recipe->fmt_x == recipe->fmt_w) {
             // X and W the same way: twin launches, three (small tensors: two) instead of six
-            const fp8k::RowColOperand ox{x, M, K, wsf + p.xq, K, sx, wsb + b.xt, Mp, sxt, wsf + p.fold_x};
-            const fp8k::RowColOperand ow{w, N, K, wsf + p.wq, K, sw, wsb + b.wt, N, swt, wsf + p.fold_w};
+            const fp8k::RowColOperand ox{x, M, K, wsf + p.xq, ld.k, sx, wsb + b.xt, ld.m, sxt, wsf + p.fold_x};
+            const fp8k::RowColOperand ow{w, N, K, wsf + p.wq, ld.k, sw, wsb + b.wt, ld.n, swt, wsf + p.fold_w};
             const hipError_t e = fp8k::launch_quant_row_col_pair(ox, &ow, K, recipe->fmt_x, fl, st);
             if (e == hipSuccess) done = true;
             else if (e != hipErrorNotSupported) return hip_fail(e, "quant_row_col_pair");
         }
         if (!done) {
             if (recipe->flags & FP8_GRAD_WEIGHT_HP) {   // dW will come from the bfloat16 X: no fp8 copy of X to keep
-                if (int rc = quantize_impl(x, M, K, K, FP8_ROW, recipe->fmt_x, fl, wsf + p.xq, K, nullptr, 0, sx, st)) return rc;
+                if (int rc = quantize_impl(x, M, K, K, FP8_ROW, recipe->fmt_x, fl, wsf + p.xq, ld.k, nullptr, 0, sx, st)) return rc;
             } else {
-                if (Mp != M) FP8_TRY(fp8k::launch_fill_u32(reinterpret_cast<uint32_t*>(wsb + b.xt), K * Mp / 4, 0u, st));   // zero codes in the pad columns of X^T
-                if (int rc = quantize_row_col_impl(x, M, K, K, recipe->fmt_x, fl, wsf + p.xq, K, sx, wsb + b.xt, Mp, sxt, st)) return rc;
+                if (pad16(M) != M) FP8_TRY(fp8k::launch_fill_u32(reinterpret_cast<uint32_t*>(wsb + b.xt), K * ld.m / 4, 0u, st));   // zero codes in the pad columns of X^T
+                if (int rc = quantize_row_col_impl(x, M, K, K, recipe->fmt_x, fl, wsf + p.xq, ld.k, sx, wsb + b.xt, ld.m, sxt, st, pad16(M) == M)) return rc;
             }
-            if (int rc = quantize_row_col_impl(w, N, K, K, recipe->fmt_w, fl, wsf + p.wq, K, sw, wsb + b.wt, N, swt, st)) return rc;
+            if (int rc = quantize_row_col_impl(w, N, K, K, recipe->fmt_w, fl, wsf + p.wq, ld.k, sw, wsb + b.wt, ld.n, swt, st, true)) return rc;
         }
-        FP8_TRY(fp8k::launch_gemm_fp8(wsf + p.xq, K, recipe->fmt_x, sx, 1, wsf + p.wq, K, recipe->fmt_w, sw, 1, M, N, K, y, N, 0, st));
+        FP8_TRY(fp8k::launch_gemm_fp8(wsf + p.xq, ld.k, recipe->fmt_x, sx, 1, wsf + p.wq, ld.k, recipe->fmt_w, sw, 1, M, N, K, y, N, 0, st));
         return FP8_OK;
     }
     if (workspace_bytes < p.total)
@@ -430,21 +446,21 @@ int fp8_linear_fwd(const void* x, const void* w, int64_t M, int64_t K, int64_t N
     float* part = reinterpret_cast<float*>(ws + p.part);
     bool pair_done = false;
     if (g == FP8_ROW && recipe->fmt_x == recipe->fmt_w && K > 0) {   // X and W in one launch
-        const hipError_t e = fp8k::launch_quant_row_pair(x, M, K, xq, K, sx, w, N, K, wq, K, sw, K, recipe->fmt_x, fl, st);
+        const hipError_t e = fp8k::launch_quant_row_pair(x, M, K, xq, ld.k, sx, w, N, K, wq, ld.k, sw, K, recipe->fmt_x, fl, st);
         if (e == hipSuccess) pair_done = true;
         else if (e != hipErrorNotSupported) return hip_fail(e, "quant_row_pair");
     }
     if (g == FP8_TENSOR && recipe->fmt_x == recipe->fmt_w && K > 0) {
-        const fp8k::TensorOperand ox{x, M, xq, K, nullptr, 0, sx, part}, ow{w, N, wq, K, nullptr, 0, sw, part + fp8k::TENSOR_PARTIALS};
+        const fp8k::TensorOperand ox{x, M, xq, ld.k, nullptr, 0, sx, part}, ow{w, N, wq, ld.k, nullptr, 0, sw, part + fp8k::TENSOR_PARTIALS};
         const hipError_t e = fp8k::launch_quant_tensor_pair(ox, ow, K, recipe->fmt_x, fl, 0, st);
         if (e == hipSuccess) pair_done = true;
         else if (e != hipErrorNotSupported) return hip_fail(e, "quant_tensor_pair");
     }
     if (!pair_done) {
-        if (int rc = quantize_impl(x, M, K, K, g, recipe->fmt_x, fl, xq, K, nullptr, 0, sx, st, part)) return rc;
-        if (int rc = quantize_impl(w, N, K, K, g, recipe->fmt_w, fl, wq, K, nullptr, 0, sw, st, part)) return rc;
+        if (int rc = quantize_impl(x, M, K, K, g, recipe->fmt_x, fl, xq, ld.k, nullptr, 0, sx, st, part)) return rc;
+        if (int rc = quantize_impl(w, N, K, K, g, recipe->fmt_w, fl, wq, ld.k, nullptr, 0, sw, st, part)) return rc;
     }
-    FP8_TRY(fp8k::launch_gemm_fp8(xq, K, recipe->fmt_x, sx, g == FP8_ROW, wq, K, recipe->fmt_w, sw, g == FP8_ROW, M, N, K,
+    FP8_TRY(fp8k::launch_gemm_fp8(xq, ld.k, recipe->fmt_x, sx, g == FP8_ROW, wq, ld.k, recipe->fmt_w, sw, g == FP8_ROW, M, N, K,
                                   y, N, 0, st));
     return FP8_OK;
 }
@@ -464,10 +480,10 @@ int fp8_linear_bwd(const void* dy, const void* x, const void* w, int64_t M, int6
     if (!aligned(dx, 16) || !aligned(dw, 16) || !aligned(workspace, 256))
         return fail(FP8_ERR_ALIGN, "fp8_linear_bwd: dx, dw (16) / workspace (256) misaligned");
     if ((K + 127) / 128 > 65535 || (N + 127) / 128 > 65535) return fail(FP8_ERR_SHAPE, "fp8_linear_bwd: K or N too large");
+    const size_t need = linear_bytes(M, K, N, recipe, true);
+    if (workspace_bytes < need) return fail(FP8_ERR_WORKSPACE, "fp8_linear_bwd: workspace %zu < %zu bytes", workspace_bytes, need);
     const BwdPlan p = plan_bwd(M, K, N, recipe->gran);
-    if (workspace_bytes < p.total + (saved ? plan_fwd(M, K, N, recipe->gran).total : 0))
-        return fail(FP8_ERR_WORKSPACE, "fp8_linear_bwd: workspace %zu < %zu bytes", workspace_bytes,
-                    p.total + (saved ? plan_fwd(M, K, N, recipe->gran).total : 0));
+    const Pitch ld = pitch_of(M, K, N);
     hipStream_t st = static_cast<hipStream_t>(stream);
     uint8_t* ws = static_cast<uint8_t*>(workspace);
     uint8_t *gq = ws + p.gq, *gqt = ws + p.gqt, *wt = ws + p.wt, *xt = ws + p.xt;
@@ -485,7 +501,7 @@ int fp8_linear_bwd(const void* dy, const void* x, const void* w, int64_t M, int6
     }
     const int64_t Mp = pad16(M);
     auto clear = [&](uint8_t* t, int64_t rows) {     // zero codes in the pad columns, ahead of the single-tensor calls
-        return Mp != M ? fp8k::launch_fill_u32(reinterpret_cast<uint32_t*>(t), rows * Mp / 4, 0u, st) : hipSuccess;
+        return Mp != M ? fp8k::launch_fill_u32(reinterpret_cast<uint32_t*>(t), rows * ld.m / 4, 0u, st) : hipSuccess;
     };
 
     if (recipe->gran == FP8_TENSOR) {
@@ -493,22 +509,22 @@ int fp8_linear_bwd(const void* dy, const void* x, const void* w, int64_t M, int6
         float* part = reinterpret_cast<float*>(ws + p.part);
         uint8_t* plain = dx ? gq : nullptr;
         if (dw) {
-            if (int rc = quantize_impl(dy, M, N, N, FP8_TENSOR, recipe->fmt_dy, fl | T, gqt, Mp, plain, N, sg, st, part)) return rc;
+            if (int rc = quantize_impl(dy, M, N, N, FP8_TENSOR, recipe->fmt_dy, fl | T, gqt, ld.m, plain, ld.n, sg, st, part)) return rc;
         } else {
-            if (int rc = quantize_impl(dy, M, N, N, FP8_TENSOR, recipe->fmt_dy, fl, gq, N, nullptr, 0, sg, st, part)) return rc;
+            if (int rc = quantize_impl(dy, M, N, N, FP8_TENSOR, recipe->fmt_dy, fl, gq, ld.n, nullptr, 0, sg, st, part)) return rc;
         }
         bool pair_done = false;
         if (dx && dw && !saved && recipe->fmt_w == recipe->fmt_x) {   // W and X in two launches
-            const fp8k::TensorOperand ow{w, N, wt, N, nullptr, 0, swt, part}, ox{x, M, xt, Mp, nullptr, 0, sxt, part + fp8k::TENSOR_PARTIALS};
+            const fp8k::TensorOperand ow{w, N, wt, ld.n, nullptr, 0, swt, part}, ox{x, M, xt, ld.m, nullptr, 0, sxt, part + fp8k::TENSOR_PARTIALS};
             const hipError_t e = fp8k::launch_quant_tensor_pair(ow, ox, K, recipe->fmt_w, fl, 1, st);
             if (e == hipSuccess) pair_done = true;
             else if (e != hipErrorNotSupported) return hip_fail(e, "quant_tensor_pair");
         }
         if (dx && !saved && !pair_done)
-            if (int rc = quantize_impl(w, N, K, K, FP8_TENSOR, recipe->fmt_w, fl | T, wt, N, nullptr, 0, swt, st, part)) return rc;
+            if (int rc = quantize_impl(w, N, K, K, FP8_TENSOR, recipe->fmt_w, fl | T, wt, ld.n, nullptr, 0, swt, st, part)) return rc;
         if (dw && !saved && !pair_done)
-            if (int rc = quantize_impl(x, M, K, K, FP8_TENSOR, recipe->fmt_x, fl | T, xt, Mp, nullptr, 0, sxt, st, part)) return rc;
-        return grad_gemms(recipe, 0, gq, sg, wt, swt, gqt, sg, xt, sxt, M, Mp, K, N, dx, dw, st);
+            if (int rc = quantize_impl(x, M, K, K, FP8_TENSOR, recipe->fmt_x, fl | T, xt, ld.m, nullptr, 0, sxt, st, part)) return rc;
+        return grad_gemms(recipe, 0, gq, sg, wt, swt, gqt, sg, xt, sxt, M, Mp, K, N, ld, dx, dw, st);
     }
     // rowwise: every operand re-quantized along the contraction axis of its GEMM
     // (dX = dY W contracts over N, dW = dY^T X over M).  All quantizations first,
@@ -517,34 +533,34 @@ int fp8_linear_bwd(const void* dy, const void* x, const void* w, int64_t M, int6
     if (both && !saved && recipe->fmt_w == recipe->fmt_x) {
         // all three tensors in five launches: dY's rowwise pass (which also gathers its column maxima), the column
         // maxima of W and X together, one launch for every column scale, two for the transposing casts
-        const fp8k::RowColOperand og{dy, M, N, gq, N, sg, gqt, Mp, sgt, ws + p.fold_g};
-        const fp8k::ColOperand ow{w, N, K, wt, N, swt, ws + p.fold_w}, ox{x, M, K, xt, Mp, sxt, ws + p.fold_x};
+        const fp8k::RowColOperand og{dy, M, N, gq, ld.n, sg, gqt, ld.m, sgt, ws + p.fold_g};
+        const fp8k::ColOperand ow{w, N, K, wt, ld.n, swt, ws + p.fold_w}, ox{x, M, K, xt, ld.m, sxt, ws + p.fold_x};
         const hipError_t e = fp8k::launch_quant_bwd_rowwise(og, N, recipe->fmt_dy, ow, ox, K, recipe->fmt_w, fl, st);
-        if (e == hipSuccess) return grad_gemms(recipe, 1, gq, sg, wt, swt, gqt, sgt, xt, sxt, M, Mp, K, N, dx, dw, st);
+        if (e == hipSuccess) return grad_gemms(recipe, 1, gq, sg, wt, swt, gqt, sgt, xt, sxt, M, Mp, K, N, ld, dx, dw, st);
         if (e != hipErrorNotSupported) return hip_fail(e, "quant_bwd_rowwise");
     }
     if (both) {   // dY along N (rows) and along M (columns, transposed) from two reads instead of three
-        const fp8k::RowColOperand og{dy, M, N, gq, N, sg, gqt, Mp, sgt, ws + p.fold_g};
+        const fp8k::RowColOperand og{dy, M, N, gq, ld.n, sg, gqt, ld.m, sgt, ws + p.fold_g};
         const hipError_t e = fp8k::launch_quant_row_col_pair(og, nullptr, N, recipe->fmt_dy, fl, st);
         if (e == hipErrorNotSupported) {
             FP8_TRY(clear(gqt, N));
-            if (int rc = quantize_row_col_impl(dy, M, N, N, recipe->fmt_dy, fl, gq, N, sg, gqt, Mp, sgt, st)) return rc;
+            if (int rc = quantize_row_col_impl(dy, M, N, N, recipe->fmt_dy, fl, gq, ld.n, sg, gqt, ld.m, sgt, st, Mp == M)) return rc;
         } else if (e != hipSuccess) {
             return hip_fail(e, "quant_row_col");
         }
     } else if (dx) {
-        if (int rc = quantize_impl(dy, M, N, N, FP8_ROW, recipe->fmt_dy, fl, gq, N, nullptr, 0, sg, st)) return rc;
+        if (int rc = quantize_impl(dy, M, N, N, FP8_ROW, recipe->fmt_dy, fl, gq, ld.n, nullptr, 0, sg, st)) return rc;
     } else {
         FP8_TRY(clear(gqt, N));
-        if (int rc = quantize_impl(dy, M, N, N, FP8_COL, recipe->fmt_dy, fl | T, gqt, Mp, nullptr, 0, sgt, st)) return rc;
+        if (int rc = quantize_impl(dy, M, N, N, FP8_COL, recipe->fmt_dy, fl | T, gqt, ld.m, nullptr, 0, sgt, st, nullptr, Mp == M)) return rc;
     }
     if (dx && !saved)
-        if (int rc = quantize_impl(w, N, K, K, FP8_COL, recipe->fmt_w, fl | T, wt, N, nullptr, 0, swt, st)) return rc;
+        if (int rc = quantize_impl(w, N, K, K, FP8_COL, recipe->fmt_w, fl | T, wt, ld.n, nullptr, 0, swt, st, nullptr, true)) return rc;
     if (dw && !saved) {
         FP8_TRY(clear(xt, K));
-        if (int rc = quantize_impl(x, M, K, K, FP8_COL, recipe->fmt_x, fl | T, xt, Mp, nullptr, 0, sxt, st)) return rc;
+        if (int rc = quantize_impl(x, M, K, K, FP8_COL, recipe->fmt_x, fl | T, xt, ld.m, nullptr, 0, sxt, st, nullptr, Mp == M)) return rc;
     }
-    return grad_gemms(recipe, 1, gq, sg, wt, swt, gqt, sgt, xt, sxt, M, Mp, K, N, dx, dw, st);
+    return grad_gemms(recipe, 1, gq, sg, wt, swt, gqt, sgt, xt, sxt, M, Mp, K, N, ld, dx, dw, st);
 }
 
 namespace {
@@ -553,12 +569,16 @@ bool sigmoid_bwd_fused(int64_t M, int64_t N, const fp8_recipe* r) {
     return r->gran == FP8_ROW && !(r->flags & FP8_GRAD_WEIGHT_HP) && N % 8 == 0 && N / 8 >= 64 && N / 8 <= 4096 && M >= 1024 &&
            M % 16 == 0;   // (a token count off the 16-byte grid takes the padded buffers of fp8_linear_bwd)
 }
+// room for the gradient where it is materialised, behind the workspace of the linear backward (a multiple of 256 bytes)
+size_t sigmoid_bwd_extra(int64_t M, int64_t N, const fp8_recipe* r) {
+    return sigmoid_bwd_fused(M, N, r) ? 0 : align_up((size_t)M * (size_t)N * 2, 256);
+}
 }  // namespace
 
 size_t fp8_linear_bwd_sigmoid_workspace_bytes(int64_t M, int64_t K, int64_t N, const fp8_recipe* recipe) {
     const size_t base = fp8_linear_workspace_bytes(M, K, N, recipe, 1);
     if (base == 0) return 0;
-    return sigmoid_bwd_fused(M, N, recipe) ? base : align_up(base, 256) + align_up((size_t)M * (size_t)N * 2, 256);
+    return base + sigmoid_bwd_extra(M, N, recipe);
 }
 
 int fp8_linear_bwd_sigmoid(const void* dy, const void* y, const void* x, const void* w, int64_t M, int64_t K, int64_t N,
@@ -573,16 +593,14 @@ int fp8_linear_bwd_sigmoid(const void* dy, const void* y, const void* x, const v
     if (M == 0 || N == 0 || K == 0 || (!dx && !dw)) return FP8_OK;
     if (!workspace) return fail(FP8_ERR_NULL, "%s: workspace is NULL", fn);
     if (!aligned(workspace, 256)) return fail(FP8_ERR_ALIGN, "%s: workspace not 256-byte aligned", fn);
-    const size_t need = fp8_linear_bwd_sigmoid_workspace_bytes(M, K, N, recipe);
-    if (need == 0) return FP8_ERR_SHAPE;
+    const size_t base = linear_bytes(M, K, N, recipe, true), need = base + sigmoid_bwd_extra(M, N, recipe);
     if (workspace_bytes < need) return fail(FP8_ERR_WORKSPACE, "%s: workspace %zu < %zu bytes", fn, workspace_bytes, need);
     hipStream_t st = static_cast<hipStream_t>(stream);
     uint8_t* ws = static_cast<uint8_t*>(workspace);
-    const size_t base = fp8_linear_workspace_bytes(M, K, N, recipe, 1);
     if (!sigmoid_bwd_fused(M, N, recipe)) {
         // small or unusual shapes, other recipes: dz = dy * y * (1 - y) is written out once and the ordinary
         // backward runs on it
-        uint8_t* dz = ws + align_up(base, 256);
+        uint8_t* dz = ws + base;
         FP8_TRY(fp8k::launch_sigmoid_bwd(dy, y, M * N, dz, st));
         return fp8_linear_bwd(dz, x, w, M, K, N, recipe, dx, dw, workspace, base, stream);
     }
@@ -593,26 +611,27 @@ int fp8_linear_bwd_sigmoid(const void* dy, const void* y, const void* x, const v
     if (!aligned(dx, 16) || !aligned(dw, 16)) return fail(FP8_ERR_ALIGN, "%s: dx, dw not 16-byte aligned", fn);
     if ((K + 127) / 128 > 65535 || (N + 127) / 128 > 65535) return fail(FP8_ERR_SHAPE, "%s: K or N too large", fn);
     const BwdPlan p = plan_bwd(M, K, N, recipe->gran);
+    const Pitch ld = pitch_of(M, K, N);
     uint8_t *gq = ws + p.gq, *gqt = ws + p.gqt, *wt = ws + p.wt, *xt = ws + p.xt;
     float *sg = reinterpret_cast<float*>(ws + p.sg), *sgt = reinterpret_cast<float*>(ws + p.sgt);
     float *swt = reinterpret_cast<float*>(ws + p.swt), *sxt = reinterpret_cast<float*>(ws + p.sxt);
     const int fl = recipe->flags & FP8_POW2_SCALE;
     const int T = FP8_TRANSPOSE_OUT;
-    hipError_t e = fp8k::launch_quant_row_col_sigmoid_bwd(dy, y, M, N, N, recipe->fmt_dy, fl, gq, N, sg, gqt, M, sgt, st);
+    hipError_t e = fp8k::launch_quant_row_col_sigmoid_bwd(dy, y, M, N, N, recipe->fmt_dy, fl, gq, ld.n, sg, gqt, ld.m, sgt, st);
     if (e == hipErrorNotSupported) return fail(FP8_ERR_SHAPE, "%s: shape not supported by the fused gradient quantization", fn);
     if (e != hipSuccess) return hip_fail(e, "quant_row_col_sigmoid_bwd");
     bool pair_done = false;
     if (dx && dw && !saved && recipe->fmt_w == recipe->fmt_x) {     // W and X in three launches (small ones: two) instead of six
-        const fp8k::ColOperand ow{w, N, K, wt, N, swt, ws + p.fold_w}, ox{x, M, K, xt, M, sxt, ws + p.fold_x};
+        const fp8k::ColOperand ow{w, N, K, wt, ld.n, swt, ws + p.fold_w}, ox{x, M, K, xt, ld.m, sxt, ws + p.fold_x};
         e = fp8k::launch_quant_col_t_pair(ow, ox, K, recipe->fmt_w, fl, st);
         if (e == hipSuccess) pair_done = true;
         else if (e != hipErrorNotSupported) return hip_fail(e, "quant_col_t_pair");
     }
     if (dx && !saved && !pair_done)
-        if (int rc = quantize_impl(w, N, K, K, FP8_COL, recipe->fmt_w, fl | T, wt, N, nullptr, 0, swt, st)) return rc;
+        if (int rc = quantize_impl(w, N, K, K, FP8_COL, recipe->fmt_w, fl | T, wt, ld.n, nullptr, 0, swt, st, nullptr, true)) return rc;
     if (dw && !saved && !pair_done)
-        if (int rc = quantize_impl(x, M, K, K, FP8_COL, recipe->fmt_x, fl | T, xt, M, nullptr, 0, sxt, st)) return rc;
-    return grad_gemms(recipe, 1, gq, sg, wt, swt, gqt, sgt, xt, sxt, M, M, K, N, dx, dw, st);
+        if (int rc = quantize_impl(x, M, K, K, FP8_COL, recipe->fmt_x, fl | T, xt, ld.m, nullptr, 0, sxt, st, nullptr, true)) return rc;
+    return grad_gemms(recipe, 1, gq, sg, wt, swt, gqt, sgt, xt, sxt, M, M, K, N, ld, dx, dw, st);
 }
 
 int fp8_grad_weight_hp(const void* dy, const void* x, int64_t M, int64_t K, int64_t N, void* dw, void* stream) {

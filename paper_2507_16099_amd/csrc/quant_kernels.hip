@@ -679,8 +679,9 @@ __global__ __launch_bounds__(256) void cast_transpose_kernel(const uint16_t* __r
     }
 }
 
-// the rows of a transposed output [cols, rows] in a workspace are padded to 16 bytes: the cast fills the padding
-static int owns_padding(int64_t rows, int64_t ld_out) { return rows % 16 != 0 && ld_out == (rows + 15) / 16 * 16 ? 1 : 0; }
+// the rows of a transposed output [cols, rows] in a workspace are padded to 16 bytes at least: the cast fills the piece in
+// which the codes end
+static int owns_padding(int64_t rows, int64_t ld_out) { return rows % 16 != 0 && ld_out >= (rows + 15) / 16 * 16 ? 1 : 0; }
 
 template <int FMT, int GRAN>
 static hipError_t launch_cast_t(const uint16_t* x, int64_t rows, int64_t cols, int64_t ld, const float* scale,
@@ -1089,19 +1090,15 @@ int64_t quant_fold_bytes(int64_t rows, int64_t cols) {
 
 namespace {
 
-// bytes of a transposed output that may hold partial maxima: all of it when its rows are dense or padded to 16 bytes (the
-// outputs of the paired launches lie in a workspace, and the cast fills that padding), else the first row
-int64_t output_scratch(int64_t out_rows, int64_t out_cols, int64_t ld_out) {
-    return ld_out == out_cols || owns_padding(out_cols, ld_out) ? out_rows * ld_out : out_cols;
-}
 
 // where the first-level maxima of a tensor go: the caller's side storage, if any (the cast then folds them), else the
-// transposed output itself, which the cast overwrites afterwards
+// transposed output itself, which the cast overwrites afterwards (all of it, padding between the rows included: the
+// outputs of the paired launches lie in a workspace)
 struct Partials { uint16_t* at; int64_t room; bool folded; };
 Partials partials_of(void* fold, int64_t rows, int64_t cols, uint8_t* q_col_t, int64_t ld_col_t) {
     const int64_t fb = fold ? quant_fold_bytes(rows, cols) : 0;
     if (fb) return Partials{static_cast<uint16_t*>(fold), fb, true};
-    return Partials{reinterpret_cast<uint16_t*>(q_col_t), output_scratch(cols, rows, ld_col_t), false};
+    return Partials{reinterpret_cast<uint16_t*>(q_col_t), cols * ld_col_t, false};
 }
 
 // blocks of quant_row_colmax_kernel for a tensor, given how many the device keeps resident for it (0: not suited)
@@ -1332,8 +1329,7 @@ hipError_t launch_quant_row_col_sigmoid_bwd(const void* dy, const void* y, int64
     const uint16_t* yp = static_cast<const uint16_t*>(y);
     const int64_t ld_part = cols;
     uint16_t* part = reinterpret_cast<uint16_t*>(q_col_t);          // overwritten by the transposed codes afterwards
-    // only bytes that the transposed cast rewrites: all of a dense output, else its first row
-    const size_t scratch_bytes = ld_col_t == rows ? (size_t)cols * (size_t)rows : (size_t)rows;
+    const size_t scratch_bytes = (size_t)cols * (size_t)ld_col_t;   // (the output lies in a workspace, padding included)
     int64_t G = 0;
 #define FP8K_QRCA(FMT, NV)                                                                                    \
     do {                                                                                                      \

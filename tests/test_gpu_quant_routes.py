@@ -72,3 +72,34 @@ def test_per_tensor_activations_of_a_quantized_weight(M, K, N, flags):
         ys = torch.empty_like(y)
         fp8.fp8_linear_fwd_prequantized_static(x, wq, fp8.FP8_E4M3FN, sw, fp8.FP8_ROW, ys, fp8.FP8_E4M3FN, fp8.FP8_TENSOR, flags)
         assert torch.equal(ys.view(torch.int16), want.view(torch.int16))
+
+
+@pytest.mark.parametrize("M,K,N", [(1001, 1040, 1200), (600, 2000, 528), (513, 528, 1008)])
+@pytest.mark.parametrize("recipe", ["tensorwise", "rowwise"])
+@pytest.mark.parametrize("save", [0, fp8.FP8_SAVE_FOR_BWD])
+def test_padded_operand_rows_give_the_products_of_dense_ones(M, K, N, recipe, save):
+    """Operands in the workspace whose contracted length is no multiple of 128 have padded rows; the products are those of
+    the public quantizers' dense operands, bit for bit, and what lies in the padding (NaN codes here) does not matter."""
+    rng = np.random.default_rng(K)
+    x, w, dy = (torch.from_numpy(rng.standard_normal(s).astype(np.float32)).cuda().to(torch.bfloat16) for s in ((M, K), (N, K), (M, N)))
+    row, col = (fp8.FP8_TENSOR,) * 2 if recipe == "tensorwise" else (fp8.FP8_ROW, fp8.FP8_COL)
+    g = fp8.FP8_TENSOR if recipe == "tensorwise" else fp8.FP8_ROW
+    r = fp8.Recipe(gran=g, flags=save)
+    full = lambda n: torch.full((n,), 0x7F, dtype=torch.uint8, device="cuda")      # noqa: E731
+    wb = full(fp8.fp8_linear_workspace_bytes(M, K, N, r, True))
+    y = fp8.fp8_linear_fwd(x, w, r, workspace=wb if save else full(fp8.fp8_linear_workspace_bytes(M, K, N, r, False)))
+    dx, dw = fp8.fp8_linear_bwd(dy, x, w, r, workspace=wb)
+    T, E4, E5 = fp8.FP8_TRANSPOSE_OUT, fp8.FP8_E4M3FN, fp8.FP8_E5M2
+
+    def product(a, ga, fa, ta, b, gb, fb, tb):
+        (qa, sa), (qb, sb) = fp8.fp8_quantize(a, ga, fa, ta), fp8.fp8_quantize(b, gb, fb, tb)
+        k16 = (qa.shape[1] + 15) // 16 * 16
+        if k16 != qa.shape[1]:      # the product contracts over multiples of 16: zero codes
+            pa, pb = (torch.zeros((q.shape[0], k16), dtype=torch.uint8, device="cuda") for q in (qa, qb))
+            pa[:, :qa.shape[1]], pb[:, :qb.shape[1]] = qa, qb
+            qa, qb = pa, pb
+        return fp8.fp8_scaled_mm(qa, fa, sa, g, qb, fb, sb, g)
+
+    assert torch.equal(y, product(x, row, E4, 0, w, row, E4, 0))
+    assert torch.equal(dx, product(dy, row, E5, 0, w, col, E4, T))
+    assert torch.equal(dw, product(dy, col, E5, T, x, col, E4, T))

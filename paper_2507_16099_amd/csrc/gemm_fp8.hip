@@ -235,7 +235,10 @@ static hipError_t launch_tn(const GemmOperands& g, int row_a, int row_b, hipStre
     return hipGetLastError();
 }
 
-// ---- kernel choice.  Up to 32 rows: the few-row kernel of gemm_fp8_skinny.hip (it streams B once; 2-7x faster there).
+// ---- kernel choice.  Up to 32 rows: the few-row kernel of gemm_fp8_skinny.hip (it streams B once), and up to 64 rows where
+// there are too few 64 x 64 tiles for the CUs, N <= 8192, and the contraction is long enough for its wavefronts to share
+// (us, few-row / ring: 48 x 1024 x 4096 8.1 / 11.6, 64 x 4096 x 14336 23.6 / 35.0, 64 x 8192 x 4096 13.8 / 14.9;
+// 64 x 8192 x 1024 5.9 / 5.4, 64 x 11008 x 4096 23.4 / 16.4, 32 x 28672 x 8192 51.6 / 47.8).
 // More than one round of 256 x 256 tiles (one per CU): the large-product kernels of gemm_fp8_snake.hip /
 // gemm_fp8_stream.hip.  In between the cheapest of the ring kernel's tiles (gemm_fp8_ring.hip) and one round of
 // 256 x 256 tiles by this estimate, in us (one launch; rounds of 256 workgroups, K steps of 128 bytes):
@@ -268,7 +271,8 @@ double ring_cost(int tile, const GemmOperands& g, const GemmOperands* g2, int64_
     const int64_t n1 = tiles(g), n2 = g2 ? tiles(*g2) : 0;
     const double operands = 1e-5 * (double)(n1 + n2) * (c.tm + c.tn);      // (equal otherwise: fewer operand bytes)
     if (n1 + n2 <= cus) return 3.0 + (per1 > per2 ? per1 : per2) + operands;
-    return 3.0 + (double)cdiv(n1 + n2, cus) * ((double)n1 * per1 + (double)n2 * per2) / (double)(n1 + n2) + operands;
+    const double rounds = (double)cdiv(n1 + n2, cus) * ((double)n1 * per1 + (double)n2 * per2) / (double)(n1 + n2);
+    return 3.0 + (rounds > per1 + per2 ? rounds : per1 + per2) + operands;     // (two unequal products: at least one tile of each in turn)
 }
 // the cheapest ring tile for one product, or two in one launch
 int best_ring(const GemmOperands& g, const GemmOperands* g2, int64_t cus, double* cost) {
@@ -287,7 +291,7 @@ int pick_path(const GemmOperands& g, double* cost) {
     const int v = knob(KNOB_GEMM_VARIANT);
     if (v == 0 || v == 4 || v == 5) return v;
     if (v == 6 || v == 7) return fits ? kPathRing + (v == 6 ? RING_64x64 : RING_128x128) : 0;
-    if (g.M <= 32) return 5;
+    if (g.M <= 32 || (g.M <= 64 && g.N <= 8192 && g.K >= 2048 && gemm_fp8_snake_fits(g.lda, g.ldb))) return 5;
     const int64_t cus = compute_units() > 0 ? compute_units() : 256;
     const int64_t big = cdiv(g.M, 256) * cdiv(g.N, 256);
     if (const int b = knob(KNOB_GEMM_BIG_FROM); b > 0 && cdiv(g.M, 128) * cdiv(g.N, 128) >= b) return 4;

@@ -4,10 +4,10 @@
 // B (the weight) is read once and the kernel is bound by that HBM stream, N*K
 // bytes, not by the matrix cores.
 //
-// Two forms.  The first (below) is used for 33..64 rows and for leading
-// dimensions beyond the reach of 32-bit buffer offsets; the second, further
-// down, brings the operands in by LDS-DMA and is 10-25 % faster on the
-// large weight shapes (4.2-5.7 TB/s of weight bytes against 3.6-5.0).
+// Two forms.  The first (below) is used for leading dimensions beyond the reach
+// of 32-bit buffer offsets; the second, further down, brings the operands in by
+// LDS-DMA and is 10-25 % faster on the large weight shapes (4.2-5.7 TB/s of
+// weight bytes against 3.6-5.0).
 //
 // First form: no LDS staging and no barriers in the main loop.  A wavefront owns 16 rows
 // of B (16 output columns) and a contiguous part of K; per 128-byte K step
@@ -404,7 +404,7 @@ static hipError_t launch_sk_dma(const uint8_t* a, int64_t lda, const float* sa, 
                                 const float* sb, int row_b, int M, int N, int K, void* out, int64_t ld_out, int out_f32,
                                 int64_t grid, hipStream_t st) {
     constexpr int SLOT = (NW + MT) * 2048;
-    constexpr int R = SLOT <= 4096 ? 5 : (SLOT <= 6144 ? 3 : 2);     // about 20 KB of ring per wavefront: two workgroups per CU
+    constexpr int R = SLOT <= 4096 ? 5 : (SLOT <= 6144 || MT > 2) ? 3 : 2;     // about 20 KB of ring per wavefront: two workgroups per CU
     constexpr int lds = 4 * R * SLOT;
     auto kern = gemm_fp8_skinny_dma_kernel<FA, FB, MT, KS, NW, R>;
     static DynamicLdsOnce attr;
@@ -429,8 +429,9 @@ static hipError_t launch_sk(const uint8_t* a, int64_t lda, const float* sa, int 
     while (ks < 4 && groups * ks < 2048 && K / (ks * 2) >= 512) ks *= 2;
     const int64_t grid = (groups + (4 / ks) - 1) / (4 / ks);
     if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
-    // LDS-DMA form for up to 32 rows when the 32-bit buffer offsets suffice (FP8MI355_SKINNY_DMA=0 / 1 overrides)
-    const bool fits = lda < (1 << 23) && ldb < (1 << 23) && mt <= 2;
+    // LDS-DMA form when the 32-bit buffer offsets suffice (FP8MI355_SKINNY_DMA=0 / 1 overrides; not with 33-64 rows
+    // against 64 columns per wavefront, which only the override SKINNY_NW asks for: the slots would not fit the LDS)
+    const bool fits = lda < (1 << 23) && ldb < (1 << 23) && (mt <= 2 || nw <= 2);
     if (fits && knob(KNOB_SKINNY_DMA) != 0) {
 #define FP8K_SKD(MT_, KS_, NW_)                                                                               \
     if (mt == MT_ && ks == KS_ && nw == NW_)                                                                  \
@@ -439,6 +440,9 @@ static hipError_t launch_sk(const uint8_t* a, int64_t lda, const float* sa, int 
     FP8K_SKD(MT_, 1, 1); FP8K_SKD(MT_, 2, 1); FP8K_SKD(MT_, 4, 1); FP8K_SKD(MT_, 1, 2); FP8K_SKD(MT_, 2, 2); FP8K_SKD(MT_, 4, 2); \
     FP8K_SKD(MT_, 1, 4); FP8K_SKD(MT_, 2, 4); FP8K_SKD(MT_, 4, 4)
         FP8K_SKD3(1); FP8K_SKD3(2);
+#define FP8K_SKD2(MT_) \
+    FP8K_SKD(MT_, 1, 1); FP8K_SKD(MT_, 2, 1); FP8K_SKD(MT_, 4, 1); FP8K_SKD(MT_, 1, 2); FP8K_SKD(MT_, 2, 2); FP8K_SKD(MT_, 4, 2)
+        FP8K_SKD2(3); FP8K_SKD2(4);
 #undef FP8K_SKD3
 #undef FP8K_SKD
     }

@@ -887,6 +887,8 @@ int fp8_mx_scaled_mm(const uint8_t* a, int64_t lda, int fmt_a, const uint8_t* ea
 }
 
 namespace {
+// bytes of a scale row inside a workspace: whole slabs of sixteen blocks
+size_t e8m0_row_bytes(int64_t contracted) { return (size_t)((contracted + 511) / 512 * 16); }
 struct MxPlan { size_t xq, wq, xe, we, total; };
 MxPlan plan_mx(int64_t M, int64_t K, int64_t N) {
     MxPlan p{};
@@ -894,8 +896,8 @@ MxPlan plan_mx(int64_t M, int64_t K, int64_t N) {
     auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes, 256); return at; };
     p.xq = take((size_t)M * K);
     p.wq = take((size_t)N * K);
-    p.xe = take((size_t)M * (K / 32));
-    p.we = take((size_t)N * (K / 32));
+    p.xe = take((size_t)M * e8m0_row_bytes(K));
+    p.we = take((size_t)N * e8m0_row_bytes(K));
     p.total = o;
     return p;
 }
@@ -995,13 +997,13 @@ MxBwdPlan plan_mx_bwd(int64_t M, int64_t K, int64_t N) {
     auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes, 256); return at; };
     const size_t Mp = (size_t)pad128(M), Np = (size_t)pad128(N);
     p.dyq = take((size_t)M * Np);
-    p.dye = take((size_t)M * (Np / 32));
+    p.dye = take((size_t)M * e8m0_row_bytes((int64_t)Np));
     p.wtq = take((size_t)K * Np);
-    p.wte = take((size_t)K * (Np / 32));
+    p.wte = take((size_t)K * e8m0_row_bytes((int64_t)Np));
     p.dytq = take((size_t)N * Mp);
-    p.dyte = take((size_t)N * (Mp / 32));
+    p.dyte = take((size_t)N * e8m0_row_bytes((int64_t)Mp));
     p.xtq = take((size_t)K * Mp);
-    p.xte = take((size_t)K * (Mp / 32));
+    p.xte = take((size_t)K * e8m0_row_bytes((int64_t)Mp));
     p.total = o;
     return p;
 }

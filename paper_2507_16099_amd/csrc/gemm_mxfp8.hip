@@ -248,9 +248,12 @@ static bool mx_takes_snake(int64_t lda, int64_t ldb, int64_t M, int64_t N, int64
     const bool big = forced >= 0 ? forced == 1 : tiles256 > 64;      // (fewer: reached where the ring kernel's 32-bit offsets do not suffice)
     return big && mx_snake_possible(lda, ldb, K);
 }
-// shapes whose scales can lie in slabs of sixteen blocks (whole 16-byte scale pieces, 32-bit offsets reach)
+// shapes whose scales can lie in slabs of sixteen blocks (32-bit offsets reach).  The last slab may be partly filled inside a
+// workspace (K a multiple of 128 only; the kernels ignore the bytes past K): the scales of a contraction that is no multiple
+// of 512 would otherwise be fetched a dword per row and step, a cache line each.
 static bool mx_slab_possible(int64_t lda, int64_t ldb, int64_t M, int64_t N, int64_t K) {
-    return mx_snake_possible(lda, ldb, K) && K % 512 == 0 && M * (K / 32) < (1ll << 31) && N * (K / 32) < (1ll << 31);
+    const int64_t bytes = (K + 511) / 512 * 16;     // of a scale row
+    return mx_snake_possible(lda, ldb, K) && K % 128 == 0 && M * bytes < (1ll << 31) && N * bytes < (1ll << 31);
 }
 
 // True when the MX / blockwise linear calls should hand their scales to launch_gemm_mxfp8 in slabs of sixteen

@@ -73,7 +73,7 @@ __device__ __forceinline__ void msn_wait_vmem_but5_barrier() {
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// SC16 (K a multiple of 512): the scale bytes are fetched 16 per row at a time (four K steps, two buffers
+// SC16 (K a multiple of 512, or slabs, whose last one may be partly filled): the scale bytes are fetched 16 per row at a time (four K steps, two buffers
 // behind the stages) instead of 4 per row and K step.  A scale load touches one cache line per lane
 // whatever its width; one dword per lane and step doubled the kernel's cache-line traffic and cost 20 %.
 template <int FA, int FB, bool OUT_F32, bool SC16>
@@ -117,8 +117,8 @@ __global__ __launch_bounds__(msn::NT) void gemm_mxfp8_snake_kernel(
     const int64_t gsa = slab_a ? -ld_ea * 16 : 16, gsb = slab_b ? -ld_eb * 16 : 16;     // bytes from one group of four K steps to the next
     const uint64_t pea = reinterpret_cast<uint64_t>(EA + (int64_t)m0 * (slab_a ? 16 : ld_ea));
     const uint64_t peb = reinterpret_cast<uint64_t>(EB + (int64_t)n0 * (slab_b ? 16 : ld_eb));
-    const int64_t nrec_a = slab_a ? (int64_t)(K / 512) * gsa - (int64_t)m0 * 16 : (int64_t)(rows_a - 1) * ld_ea + K / 32;
-    const int64_t nrec_b = slab_b ? (int64_t)(K / 512) * gsb - (int64_t)n0 * 16 : (int64_t)(rows_b - 1) * ld_eb + K / 32;
+    const int64_t nrec_a = slab_a ? (int64_t)((K + 511) / 512) * gsa - (int64_t)m0 * 16 : (int64_t)(rows_a - 1) * ld_ea + K / 32;
+    const int64_t nrec_b = slab_b ? (int64_t)((K + 511) / 512) * gsb - (int64_t)n0 * 16 : (int64_t)(rows_b - 1) * ld_eb + K / 32;
     const v4i_x rsrc_ea = {(int)(uint32_t)pea, (int)(uint32_t)(pea >> 32), (int)nrec_a, 0x00020000};
     const v4i_x rsrc_eb = {(int)(uint32_t)peb, (int)(uint32_t)(peb >> 32), (int)nrec_b, 0x00020000};
     const uint32_t vea0 = (uint32_t)((wave * 64 + lane) * (slab_a ? 16 : (int)ld_ea)), veb0 = (uint32_t)((wave * 64 + lane) * (slab_b ? 16 : (int)ld_eb));
@@ -259,7 +259,7 @@ __global__ __launch_bounds__(msn::NT) void gemm_mxfp8_snake_kernel(
     // from stage `rs`, CNT of the step's sixteen LDS-DMA refill loads from number L0 on (0-7: the B part,
     // 8-15: the A part), and the refill of one operand's scales (SCD: 0 = A, 1 = B, -1 = none).
     auto phase = [&](auto ah_t, auto bh_t, auto rda_t, auto rh_t, auto l0_t, auto cnt_t, auto scd_t, const uint8_t* rs, uint32_t la, uint32_t lb,
-                     uint32_t ka, uint32_t ke, uint32_t ko, uint32_t lsc, uint32_t ks, const uint8_t* rsc, bool sc_issue) {
+                     uint32_t ka, uint32_t ke, uint32_t ko, uint32_t lsc, uint32_t ks, const uint8_t* rsc, int emask, bool sc_issue) {
         constexpr int AH = decltype(ah_t)::value, BH = decltype(bh_t)::value, RDA = decltype(rda_t)::value,
                       RH = decltype(rh_t)::value, L0 = decltype(l0_t)::value, CNT = decltype(cnt_t)::value,
                       DMA = decltype(scd_t)::value;
@@ -276,8 +276,8 @@ __global__ __launch_bounds__(msn::NT) void gemm_mxfp8_snake_kernel(
                 else msn_lds_dma16(rsrc_a, la + (q - 8) * 4096, va0 + (uint32_t)(q - 8) * va_step + ka);
             }
             // scales of the half that was read in slots 0..6, packed (the half is not in use in this phase)
-            if constexpr (RDA == 1) { if (t == 9) scales_a_read(rsc, RH, raw); if (t == 14) sa[RH] = scales_pack(raw); }
-            if constexpr (RDA == 0) { if (t == 9) scales_b_read(rsc, RH, raw); if (t == 14) sb[RH] = scales_pack(raw); }
+            if constexpr (RDA == 1) { if (t == 9) scales_a_read(rsc, RH, raw); if (t == 14) sa[RH] = scales_pack(raw) & emask; }
+            if constexpr (RDA == 0) { if (t == 9) scales_b_read(rsc, RH, raw); if (t == 14) sb[RH] = scales_pack(raw) & emask; }
             // the refill of the scales rides in a slot that has neither a read nor a data load
             if constexpr (SC16) {
                 // (lsc, ks: scale buffer and number of the next group of four steps)
@@ -332,25 +332,28 @@ __global__ __launch_bounds__(msn::NT) void gemm_mxfp8_snake_kernel(
                 const uint32_t ks = SC16 ? (uint32_t)q1 : (k2 < K ? (uint32_t)(k2 >> 5) : OOB);   // SC16: the group's number
                 const uint8_t* c_cur = SC16 ? smem + 2 * STAGE + ((k >> 2) & 1) * SCBUF + (k & 3) * 4 : s_cur;
                 const uint8_t* c_nxt = SC16 ? smem + 2 * STAGE + (((k + 1) >> 2) & 1) * SCBUF + ((k + 1) & 3) * 4 : s_nxt;
+                // a phantom step (k or k + 1 == ksteps) multiplies zero codes: its scale bytes, past the end of K in a partly
+                // filled slab, must not be NaN (255)
+                const int e_cur = k < ksteps ? -1 : 0, e_nxt = k + 1 < ksteps ? -1 : 0;
                 // The sixteen data loads of the refill are spread over phases 2-4 (B part first: it is read out after
                 // phase 1; the A part after phase 2); the scale loads stay behind the wait in the middle of the step, so
                 // that the five youngest loads at that wait are always phase 2's.
                 if (par == 0) {
                     // even step: B order 0,1,1,0.  Holds A0, B0 of this step.
-                    phase(I0{}, I0{}, I0{}, I1{}, I0{}, I0{}, IN{}, s_cur, la, lb, ka, ke, ko, lsc, ks, c_cur, sc_issue);    // (A0,B0) | read B1 of this step
+                    phase(I0{}, I0{}, I0{}, I1{}, I0{}, I0{}, IN{}, s_cur, la, lb, ka, ke, ko, lsc, ks, c_cur, e_cur, sc_issue);    // (A0,B0) | read B1 of this step
                     msn_barrier_lds();                 // this step's B part is read out by everyone
-                    phase(I0{}, I1{}, I1{}, I1{}, I0{}, I5{}, IN{}, s_cur, la, lb, ka, ke, ko, lsc, ks, c_cur, sc_issue);    // (A0,B1) | read A1 of this step, refill B 0-4
+                    phase(I0{}, I1{}, I1{}, I1{}, I0{}, I5{}, IN{}, s_cur, la, lb, ka, ke, ko, lsc, ks, c_cur, e_cur, sc_issue);    // (A0,B1) | read A1 of this step, refill B 0-4
                     msn_wait_vmem_but5_barrier();      // step k+1 has landed for everyone; this step's A part and scales are read out
-                    phase(I1{}, I1{}, I1{}, I0{}, I5{}, I6{}, I0{}, s_nxt, la, lb, ka, ke, ko, lsc, ks, c_nxt, sc_issue);    // (A1,B1) | read A0 of step k+1, refill B 5-7, A 0-2, A scales
-                    phase(I1{}, I0{}, I0{}, I1{}, I11{}, I5{}, I1{}, s_nxt, la, lb, ka, ke, ko, lsc, ks, c_nxt, sc_issue);   // (A1,B0) | read B1 of step k+1, refill A 3-7, B scales
+                    phase(I1{}, I1{}, I1{}, I0{}, I5{}, I6{}, I0{}, s_nxt, la, lb, ka, ke, ko, lsc, ks, c_nxt, e_nxt, sc_issue);    // (A1,B1) | read A0 of step k+1, refill B 5-7, A 0-2, A scales
+                    phase(I1{}, I0{}, I0{}, I1{}, I11{}, I5{}, I1{}, s_nxt, la, lb, ka, ke, ko, lsc, ks, c_nxt, e_nxt, sc_issue);   // (A1,B0) | read B1 of step k+1, refill A 3-7, B scales
                 } else {
                     // odd step: B order 1,0,0,1.  Holds A0, B1 of this step.
-                    phase(I0{}, I1{}, I0{}, I0{}, I0{}, I0{}, IN{}, s_cur, la, lb, ka, ke, ko, lsc, ks, c_cur, sc_issue);    // (A0,B1) | read B0 of this step
+                    phase(I0{}, I1{}, I0{}, I0{}, I0{}, I0{}, IN{}, s_cur, la, lb, ka, ke, ko, lsc, ks, c_cur, e_cur, sc_issue);    // (A0,B1) | read B0 of this step
                     msn_barrier_lds();
-                    phase(I0{}, I0{}, I1{}, I1{}, I0{}, I5{}, IN{}, s_cur, la, lb, ka, ke, ko, lsc, ks, c_cur, sc_issue);    // (A0,B0) | read A1 of this step, refill B 0-4
+                    phase(I0{}, I0{}, I1{}, I1{}, I0{}, I5{}, IN{}, s_cur, la, lb, ka, ke, ko, lsc, ks, c_cur, e_cur, sc_issue);    // (A0,B0) | read A1 of this step, refill B 0-4
                     msn_wait_vmem_but5_barrier();
-                    phase(I1{}, I0{}, I1{}, I0{}, I5{}, I6{}, I0{}, s_nxt, la, lb, ka, ke, ko, lsc, ks, c_nxt, sc_issue);    // (A1,B0) | read A0 of step k+1, refill B 5-7, A 0-2, A scales
-                    phase(I1{}, I1{}, I0{}, I0{}, I11{}, I5{}, I1{}, s_nxt, la, lb, ka, ke, ko, lsc, ks, c_nxt, sc_issue);   // (A1,B1) | read B0 of step k+1, refill A 3-7, B scales
+                    phase(I1{}, I0{}, I1{}, I0{}, I5{}, I6{}, I0{}, s_nxt, la, lb, ka, ke, ko, lsc, ks, c_nxt, e_nxt, sc_issue);    // (A1,B0) | read A0 of step k+1, refill B 5-7, A 0-2, A scales
+                    phase(I1{}, I1{}, I0{}, I0{}, I11{}, I5{}, I1{}, s_nxt, la, lb, ka, ke, ko, lsc, ks, c_nxt, e_nxt, sc_issue);   // (A1,B1) | read B0 of step k+1, refill A 3-7, B scales
                 }
             }
         }
@@ -464,7 +467,7 @@ hipError_t launch_gemm_mxfp8_snake(const uint8_t* a, int64_t lda, int fmt_a, con
                                    int64_t N, int64_t K, void* out, int64_t ld_out, int out_f32, hipStream_t st) {
     if (M == 0 || N == 0) return hipSuccess;
     const int m = (int)M, n = (int)N, k = (int)K;
-    const bool sc16 = K > 0 && K % 512 == 0;   // whole 16-byte scale chunks per row
+    const bool sc16 = K > 0 && (K % 512 == 0 || ld_ea < 0);   // whole 16-byte scale pieces per row
 #define FP8K_MSN(FA_, FB_)                                                                                  \
     if (fmt_a == FA_ && fmt_b == FB_)                                                                       \
         return sc16 ? (out_f32 ? launch_msn<FA_, FB_, true, true>(a, lda, ea, ld_ea, b, ldb, eb, ld_eb, m, n, k, out, ld_out, st)   \

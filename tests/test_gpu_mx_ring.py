@@ -58,3 +58,27 @@ def test_linear_steps_on_every_path(M, K, N):
             got = run()
         for a, b in zip(got, want):
             assert torch.equal(a, b), k
+
+
+@pytest.mark.parametrize("M,K,N", [(256, 640, 384), (1408, 896, 1664), (384, 1152, 2432)])
+@pytest.mark.parametrize("variant", [None, 1])
+def test_partly_filled_slabs(M, K, N, variant):
+    """Contractions that are no multiple of 512 (odd and even step counts): inside the linear calls the last slab of scales is
+    partly filled; in a workspace full of NaN scale bytes, the bits of plain scale rows."""
+    rng = np.random.default_rng(K)
+    x, w, dy = (torch.from_numpy(rng.standard_normal(s).astype(np.float32)).cuda().to(torch.bfloat16) for s in ((M, K), (N, K), (M, N)))
+    ff = lambda n: torch.full((n,), 0xFF, dtype=torch.uint8, device="cuda")      # noqa: E731
+
+    def run():
+        outs = [fp8.fp8_mx_linear_fwd(x, w, workspace=ff(fp8.fp8_mx_linear_workspace_bytes(M, K, N))),
+                fp8.fp8_block_linear_fwd(x, w, workspace=ff(fp8.fp8_block_linear_workspace_bytes(M, K, N)))]
+        outs += list(fp8.fp8_mx_linear_bwd(dy, x, w, workspace=ff(fp8.fp8_mx_linear_bwd_workspace_bytes(M, K, N))))
+        outs += list(fp8.fp8_block_linear_bwd(dy, x, w, workspace=ff(fp8.fp8_block_linear_bwd_workspace_bytes(M, K, N))))
+        return [o.view(torch.int16).clone() for o in outs]
+
+    with knobs(MX_VARIANT=variant):
+        got = run()
+    with knobs(MX_SLAB=0, MX_VARIANT=1):
+        want = run()
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)

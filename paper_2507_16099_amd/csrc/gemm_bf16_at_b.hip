@@ -196,11 +196,11 @@ hipError_t launch_gemm_bf16_at_b(const void* a, int64_t lda, const void* b, int6
     using namespace bt;
     if (I == 0 || J == 0) return hipSuccess;
     {
-        // more than 64 tiles: the LDS-DMA kernel (FP8MI355_BF16_VARIANT=0 / 1 forces one of the two)
-        const int64_t tiles = ((I + BI - 1) / BI) * ((J + BJ - 1) / BJ);
+        // the LDS-DMA kernel wherever its 32-bit offsets reach (FP8MI355_BF16_VARIANT=0 / 1 forces one of the two).  With few
+        // tiles it runs half tiles, and its loads a step ahead beat this kernel's register staging at every size: 512 x 1024 x
+        // 1024 (16 tiles) 10.9 against 24.8 us, 16384 x 1024 x 1024 214 / 482, 4096 x 2048 x 2048 (64 tiles) 58 / 129
         const int forced = knob(KNOB_BF16_VARIANT);
-        const bool want = forced >= 0 ? forced != 0 : tiles > 64;
-        if (want && gemm_bf16_at_b_snake_fits(lda, ldb, I, J, C))
+        if (forced != 0 && gemm_bf16_at_b_snake_fits(lda, ldb, I, J, C))
             return launch_gemm_bf16_at_b_snake(a, lda, b, ldb, I, J, C, out, ld_out, st);
     }
     constexpr int lds = 2 * STAGE;

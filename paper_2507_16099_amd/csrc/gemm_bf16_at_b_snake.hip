@@ -340,7 +340,7 @@ __global__ __launch_bounds__(bts::NT) void gemm_bf16_at_b_snake_kernel(
     }
 }
 
-// large problems only; the caller falls back to the register-staged kernel otherwise.
+// the caller falls back to the register-staged kernel where this does not hold
 // Requires I, J multiples of 8, every byte offset of a panel below 2^31.
 bool gemm_bf16_at_b_snake_fits(int64_t lda, int64_t ldb, int64_t I, int64_t J, int64_t C) {
     using namespace bts;

@@ -185,8 +185,8 @@ __global__ __launch_bounds__(256) void layernorm_quant_row_kernel(
     for (int j = 0; j < NV; ++j) {
         const int64_t vi = tx + (int64_t)j * TX;
         if (vi < nvec) {
-            store_stream(reinterpret_cast<uint2*>(qrow) + vi, cast8<FMT>(v[j], s));
-            if (hrow) store_stream(reinterpret_cast<uint4*>(hrow) + vi, v[j]);
+            store_vec(reinterpret_cast<uint2*>(qrow) + vi, cast8<FMT>(v[j], s));
+            if (hrow) store_vec(reinterpret_cast<uint4*>(hrow) + vi, v[j]);
         }
     }
 }

@@ -456,7 +456,7 @@ __global__ __launch_bounds__(256) void cast_kernel(const uint16_t* __restrict__ 
                 lo = cast8<FMT>(v0, s_t);
                 hi = cast8<FMT>(v1, s_t);
             }
-            store_stream(dst, make_uint4(lo.x, lo.y, hi.x, hi.y));
+            store_vec(dst, make_uint4(lo.x, lo.y, hi.x, hi.y));
         } else {
             for (int e = 0; c + e < cols; ++e) {
                 const float s = GRAN == GRAN_COL ? scale[c + e] : s_t;
@@ -634,7 +634,7 @@ __global__ __launch_bounds__(256) void cast_transpose_kernel(const uint16_t* __r
             if (q_plain != nullptr && r < rows) {
                 uint8_t* dst = q_plain + r * ld_plain + c;
                 if (c + 8 <= cols) {
-                    store_stream(dst, b);
+                    store_vec(dst, b);
                 } else {
                     for (int e = 0; c + e < cols; ++e) dst[e] = (uint8_t)((e < 4 ? b.x >> (8 * e) : b.y >> (8 * (e - 4))) & 0xFFu);
                 }
@@ -664,14 +664,14 @@ __global__ __launch_bounds__(256) void cast_transpose_kernel(const uint16_t* __r
         const uint4 v = tile16[cc * PARTS + (p ^ ((cc >> 3) & 7))];
         uint8_t* dst = qt + oc * ld_t + orow;
         if (orow + 16 <= rows) {
-            store_stream(dst, v);
+            store_vec(dst, v);
         } else {
             uint32_t t[4] = {v.x, v.y, v.z, v.w};
             const int left = (int)(rows - orow);       // 1..15 bytes of codes, the rest of the piece is padding
             if (pad) {
 #pragma unroll
                 for (int d = 0; d < 4; ++d) t[d] &= left >= 4 * d + 4 ? 0xFFFFFFFFu : left <= 4 * d ? 0u : (1u << (8 * (left - 4 * d))) - 1u;
-                store_stream(dst, make_uint4(t[0], t[1], t[2], t[3]));
+                store_vec(dst, make_uint4(t[0], t[1], t[2], t[3]));
             } else {
                 for (int e = 0; orow + e < rows; ++e) dst[e] = (uint8_t)((t[e >> 2] >> (8 * (e & 3))) & 0xFFu);
             }
@@ -851,7 +851,7 @@ __global__ __launch_bounds__(256) void quant_row_kernel(const uint16_t* __restri
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
         const int64_t vi = tx + (int64_t)j * TX;
-        if (vi < nvec) store_stream(reinterpret_cast<uint2*>(dst) + vi, cast8<FMT>(v[j], s));
+        if (vi < nvec) store_vec(reinterpret_cast<uint2*>(dst) + vi, cast8<FMT>(v[j], s));
     }
     if (tx < ntail) {
         const float p = __uint_as_float(tail << 16) * s;
@@ -996,7 +996,7 @@ __global__ __launch_bounds__(256) void quant_row_colmax_kernel(const uint16_t* _
 #pragma unroll
             for (int j = 0; j < NV; ++j) {
                 const int64_t vi = tid + (int64_t)j * 256;
-                if (vi < nvec) store_stream(reinterpret_cast<uint2*>(dst) + vi, cast8<FMT>(v[k][j], s));
+                if (vi < nvec) store_vec(reinterpret_cast<uint2*>(dst) + vi, cast8<FMT>(v[k][j], s));
             }
         }
         slot ^= 1;
@@ -1378,7 +1378,7 @@ __global__ __launch_bounds__(256) void sigmoid_bwd_kernel(const uint16_t* __rest
     const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (v * 8 + 8 <= n) {
         const uint4 g = load_stream(dy + v * 8), s = load_stream(y + v * 8);
-        store_stream(dz + v * 8, sigmoid_bwd8(g, s));
+        store_vec(dz + v * 8, sigmoid_bwd8(g, s));
     } else {
         for (int64_t i = v * 8; i < n; ++i)
             dz[i] = (uint16_t)sigmoid_bwd_bf16_bits(__uint_as_float((uint32_t)dy[i] << 16), __uint_as_float((uint32_t)y[i] << 16));
@@ -1451,7 +1451,7 @@ __global__ __launch_bounds__(256) void mx_quant_kernel(const uint16_t* __restric
         // 2^(127 - byte): byte <= 246 for bfloat16 input, so the factor is a normal binary32
         const float factor = __uint_as_float((uint32_t)(254 - byte) << 23);
         if (v0 + u * 256 < nvec) {
-            store_stream(q + qo[u], cast8<FMT>(d[u], factor));
+            store_vec(q + qo[u], cast8<FMT>(d[u], factor));
             if ((threadIdx.x & 3) == 0) e8m0[eo[u]] = (uint8_t)byte;
         }
     }
@@ -1527,7 +1527,7 @@ __global__ __launch_bounds__(256) void block_quant_1x128_kernel(const uint16_t* 
         uint32_t byte;
         const float s = pow2_block_scale<FMT>(m, byte);
         if (v0 + u * 256 < nvec) {
-            store_stream(q + r[u] * ld_q + cv[u] * 8, cast8<FMT>(d[u], s));
+            store_vec(q + r[u] * ld_q + cv[u] * 8, cast8<FMT>(d[u], s));
             if ((threadIdx.x & 15) == 0)     // ld_e % 4 == 0 and (cv / 4) % 4 == 0: an aligned dword
                 *reinterpret_cast<uint32_t*>(e8m0 + e8_off(r[u], cv[u] >> 2, ld_e)) = byte * 0x01010101u;
         }
@@ -1563,7 +1563,7 @@ __global__ __launch_bounds__(256) void block_quant_128x128_kernel(const uint16_t
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         const int64_t r = r0 + ty * 8 + j;
-        if (r < rows) store_stream(q + r * ld_q + c, cast8<FMT>(v[j], s));
+        if (r < rows) store_vec(q + r * ld_q + c, cast8<FMT>(v[j], s));
     }
     if (threadIdx.x < 128 && r0 + threadIdx.x < rows) {
         *reinterpret_cast<uint32_t*>(e8m0 + e8_off(r0 + threadIdx.x, c0 >> 5, ld_e)) = byte * 0x01010101u;
@@ -1595,7 +1595,7 @@ hipError_t launch_block_quant(const void* x, int64_t rows, int64_t cols, int64_t
 // bytes, i.e. the K-contiguous operand of a product that contracts over the
 // rows of x (the backward products of the MX linear layer).  rows % 32 == 0.
 // Same tile scheme as the transposing cast above (128 x 128 tile, 8 x 8 register
-// blocks, byte transpose, swizzled LDS tile, 128-bit streaming stores); a
+// blocks, byte transpose, swizzled LDS tile, 128-bit stores); a
 // wavefront holds exactly one block of 32 rows (4 thread rows x 8), so the
 // block maxima of its 128 columns are two cross-lane steps away.
 // ROWS_TOO: the same read also yields the quantization with the blocks running ALONG the rows
@@ -1655,7 +1655,7 @@ __global__ __launch_bounds__(256) void mx_quant_t_kernel(const uint16_t* __restr
             }
             const float f = __uint_as_float((uint32_t)(254 - byte) << 23);
             const int64_t r = r0 + ty * 8 + j;
-            if (r < rows && c < cols) store_stream(q_row + r * ld_row + c, cast8<FMT>(v[j], f));
+            if (r < rows && c < cols) store_vec(q_row + r * ld_row + c, cast8<FMT>(v[j], f));
             if ((tx & 3) == 0) rbytes[(ty * 8 + j) * 4 + (tx >> 2)] = (uint8_t)byte;
         }
     }
@@ -1719,7 +1719,7 @@ __global__ __launch_bounds__(256) void mx_quant_t_kernel(const uint16_t* __restr
         const int cc = it * ROWS_PER_IT + (threadIdx.x / PARTS), p = threadIdx.x % PARTS;
         const int64_t oc = c0 + cc, orow = r0 + p * 16;
         if (oc >= cols || orow >= rows) continue;      // rows % 32 == 0: a 16-byte piece is inside or outside
-        store_stream(qt + oc * ld_t + orow, tile16[cc * PARTS + (p ^ ((cc >> 3) & 7))]);
+        store_vec(qt + oc * ld_t + orow, tile16[cc * PARTS + (p ^ ((cc >> 3) & 7))]);
     }
     if (threadIdx.x < 128 && c0 + threadIdx.x < cols) {
         uint8_t* dst = et + e8_off(c0 + threadIdx.x, r0 / 32, ld_e);
@@ -1751,7 +1751,7 @@ __global__ __launch_bounds__(256) void mx_quant_t_kernel(const uint16_t* __restr
 //     dW = dY^T X, whose contraction runs down the rows of dY and X): the column maxima over the tile's 128 rows
 //     come from the 8 rows of a thread, two cross-lane steps (4 thread rows of a wavefront) and LDS (4 wavefronts).
 //   SQUARE = true: blocks of 128 x 128 (the weight in dX = dY W; the same numbers as the forward's blocks of W).
-// Tile scheme, byte transpose, swizzled LDS tile and 128-bit streaming stores as in the transposing cast.
+// Tile scheme, byte transpose, swizzled LDS tile and 128-bit stores as in the transposing cast.
 // ROWS_TOO (with SQUARE = false, cols % 128 == 0): the same read also yields the tiles of 1 x 128 ALONG the rows
 // of x (q_row [rows, cols], e_row [rows, cols / 32]): the 16 threads that hold a row of the tile combine their
 // maxima with four cross-lane steps.  The gradient, needed in both orientations by the backward, then costs
@@ -1793,7 +1793,7 @@ __global__ __launch_bounds__(256) void block_quant_t_kernel(const uint16_t* __re
             uint32_t byte;
             const float sr = pow2_block_scale<FMT>(mr, byte);
             const int64_t r = r0 + ty * 8 + j;
-            store_stream(q_row + r * ld_row + c, cast8<FMT>(v[j], sr));                   // cols % 128 == 0: inside
+            store_vec(q_row + r * ld_row + c, cast8<FMT>(v[j], sr));                   // cols % 128 == 0: inside
             if (tx == 0) *reinterpret_cast<uint32_t*>(e_row + e8_off(r, c0 >> 5, ld_er)) = byte * 0x01010101u;
         }
     }
@@ -1861,7 +1861,7 @@ __global__ __launch_bounds__(256) void block_quant_t_kernel(const uint16_t* __re
         const int cc = it * ROWS_PER_IT + (threadIdx.x / PARTS), p = threadIdx.x % PARTS;
         const int64_t oc = c0 + cc;
         if (oc >= cols) continue;
-        store_stream(qt + oc * ld_t + r0 + p * 16, tile16[cc * PARTS + (p ^ ((cc >> 3) & 7))]);
+        store_vec(qt + oc * ld_t + r0 + p * 16, tile16[cc * PARTS + (p ^ ((cc >> 3) & 7))]);
     }
     if (threadIdx.x < 128 && c0 + threadIdx.x < cols)                 // ld_e % 4 == 0 and (r0 / 32) % 4 == 0
         *reinterpret_cast<uint32_t*>(et + e8_off(c0 + threadIdx.x, r0 / 32, ld_e)) = (uint32_t)ebytes[threadIdx.x] * 0x01010101u;

@@ -121,7 +121,9 @@ __global__ __launch_bounds__(256) void amax_flat_kernel(const uint16_t* __restri
 // The tensor's scale from the per-block maxima of amax_flat_kernel<true> (n_part of them, bits of
 // non-negative floats): computed by the first wavefront of every block of the cast that follows, so that
 // neither a zeroing nor a scale kernel sits between the two passes.  Returns the scale to all threads
-// (contains a barrier: call it from uniform control flow).
+// (contains a barrier: call it from uniform control flow).  The maxima are requested at once: one after another their
+// latencies added up to 4 us in every block (777x14336x4096 tensorwise forward 65.2 -> 62.5 us, 8192x4096x6144
+// tensorwise training step 540 -> 532).
 template <int FMT>
 __device__ __forceinline__ float tensor_scale_from_partials(const float* part, int n_part, int sflags, int tid,
                                                             bool writer, float* scale_out) {
@@ -129,9 +131,15 @@ __device__ __forceinline__ float tensor_scale_from_partials(const float* part, i
     if (tid < 64) {
         const uint32_t* pp = reinterpret_cast<const uint32_t*>(part);
         uint32_t m = 0;
-        for (int i = tid; i < n_part; i += 64) {
-            const uint32_t v = pp[i];
-            m = v > m ? v : m;
+        for (int i0 = 0; i0 < n_part; i0 += 512) {   // (one trip: there are at most TENSOR_PARTIALS)
+            uint32_t v[8];                           // requested together; one read twice does not change a maximum
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int k = i0 + 64 * i + tid;
+                v[i] = pp[k < n_part ? k : n_part - 1];
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) m = v[i] > m ? v[i] : m;
         }
         m = wave_max_u32<64>(m);
         const float s = scale_from_amax(__uint_as_float(m), FMT, sflags);

@@ -28,17 +28,34 @@ __device__ __forceinline__ float fmt_max(int fmt) { return fmt == FMT_E4M3FN ? 4
 
 // 128-bit load with the streaming (non-temporal) hint, for bfloat16 input that this kernel is the last of its call to
 // touch: 6-12 % faster than a plain load on the casts of large tensors, and it keeps such data from displacing the codes.
-// Codes themselves are stored without the hint (store_vec): the product reads them next, and with the hint its first
-// touch of every operand went to HBM.  777x14336x4096 tensorwise forward 83.1 -> 66.7 us, 72x4096x14336 17.1 -> 15.6,
-// 8192x4096x6144 tensorwise training step 572 -> 554; operands beyond the caches (8192x4096x28672) are indifferent.
-// Plain loads as well: 72.2 us on the first, 576 on the third, the LayerNorm step of 8192x4096x4096 482 -> 496.
+// Plain loads instead: 777x14336x4096 tensorwise forward 66.7 -> 72.2 us, the LayerNorm step of 8192x4096x4096 482 -> 496.
 typedef unsigned v4u_t __attribute__((ext_vector_type(4)));
+typedef unsigned v2u_t __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint4 load_stream(const void* p) {
     const v4u_t t = __builtin_nontemporal_load(static_cast<const v4u_t*>(p));
     return make_uint4(t[0], t[1], t[2], t[3]);
 }
-__device__ __forceinline__ void store_vec(void* p, const uint4& v) { *static_cast<uint4*>(p) = v; }
-__device__ __forceinline__ void store_vec(void* p, const uint2& v) { *static_cast<uint2*>(p) = v; }
+
+// Codes are stored plainly: the product reads them next and finds them in the caches (hint / plain: 777x14336x4096
+// tensorwise forward 83.1 / 66.7 us, 72x4096x14336 17.1 / 15.6, 8192x4096x6144 tensorwise training step 572 / 554; the one-pass
+// quantizers themselves 0-9 % faster from 128 Mi elements on, level below).  Except where the same tensor is read twice for
+// its per-column codes and the tensor and its codes, in both orientations four bytes an element, do not fit the 256 MB
+// last-level cache: the codes would displace the input between the passes (hint / plain, per-column codes of 16384x4096
+// 72.3 / 72.4 us, 16384x8192 122 / 139, 16384x14336 239 / 281; both orientations 79 / 79, 148 / 168, 263 / 290).
+__device__ __forceinline__ bool keep_codes(int64_t rows, int64_t cols) { return rows * cols <= (int64_t)64 << 20; }
+// (the empty assembly keeps the compiler from merging the two stores into one, which would be the plain one)
+__device__ __forceinline__ void store_vec(void* p, const uint4& v, bool keep = true) {
+    if (keep) { *static_cast<uint4*>(p) = v; return; }
+    asm volatile("; streaming" ::: "memory");
+    __builtin_nontemporal_store(v4u_t{v.x, v.y, v.z, v.w}, static_cast<v4u_t*>(p));
+    asm volatile("; streaming" ::: "memory");
+}
+__device__ __forceinline__ void store_vec(void* p, const uint2& v, bool keep = true) {
+    if (keep) { *static_cast<uint2*>(p) = v; return; }
+    asm volatile("; streaming" ::: "memory");
+    __builtin_nontemporal_store(v2u_t{v.x, v.y}, static_cast<v2u_t*>(p));
+    asm volatile("; streaming" ::: "memory");
+}
 
 // two bfloat16 packed in a dword -> two binary32 (exact widening)
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }

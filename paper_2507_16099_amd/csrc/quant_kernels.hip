@@ -642,7 +642,7 @@ __global__ __launch_bounds__(256) void cast_transpose_kernel(const uint16_t* __r
             if (q_plain != nullptr && r < rows) {
                 uint8_t* dst = q_plain + r * ld_plain + c;
                 if (c + 8 <= cols) {
-                    store_vec(dst, b);
+                    store_vec(dst, b, keep_codes(rows, cols));
                 } else {
                     for (int e = 0; c + e < cols; ++e) dst[e] = (uint8_t)((e < 4 ? b.x >> (8 * e) : b.y >> (8 * (e - 4))) & 0xFFu);
                 }
@@ -672,14 +672,14 @@ __global__ __launch_bounds__(256) void cast_transpose_kernel(const uint16_t* __r
         const uint4 v = tile16[cc * PARTS + (p ^ ((cc >> 3) & 7))];
         uint8_t* dst = qt + oc * ld_t + orow;
         if (orow + 16 <= rows) {
-            store_vec(dst, v);
+            store_vec(dst, v, keep_codes(rows, cols));
         } else {
             uint32_t t[4] = {v.x, v.y, v.z, v.w};
             const int left = (int)(rows - orow);       // 1..15 bytes of codes, the rest of the piece is padding
             if (pad) {
 #pragma unroll
                 for (int d = 0; d < 4; ++d) t[d] &= left >= 4 * d + 4 ? 0xFFFFFFFFu : left <= 4 * d ? 0u : (1u << (8 * (left - 4 * d))) - 1u;
-                store_vec(dst, make_uint4(t[0], t[1], t[2], t[3]));
+                store_vec(dst, make_uint4(t[0], t[1], t[2], t[3]), keep_codes(rows, cols));
             } else {
                 for (int e = 0; orow + e < rows; ++e) dst[e] = (uint8_t)((t[e >> 2] >> (8 * (e & 3))) & 0xFFu);
             }
@@ -1004,7 +1004,7 @@ __global__ __launch_bounds__(256) void quant_row_colmax_kernel(const uint16_t* _
 #pragma unroll
             for (int j = 0; j < NV; ++j) {
                 const int64_t vi = tid + (int64_t)j * 256;
-                if (vi < nvec) store_vec(reinterpret_cast<uint2*>(dst) + vi, cast8<FMT>(v[k][j], s));
+                if (vi < nvec) store_vec(reinterpret_cast<uint2*>(dst) + vi, cast8<FMT>(v[k][j], s), keep_codes(rows, cols));
             }
         }
         slot ^= 1;

@@ -43,17 +43,17 @@ __device__ __forceinline__ uint4 load_stream(const void* p) {
 // last-level cache: the codes would displace the input between the passes (hint / plain, per-column codes of 16384x4096
 // 72.3 / 72.4 us, 16384x8192 122 / 139, 16384x14336 239 / 281; both orientations 79 / 79, 148 / 168, 263 / 290).
 __device__ __forceinline__ bool keep_codes(int64_t rows, int64_t cols) { return rows * cols <= (int64_t)64 << 20; }
-// (the empty assembly keeps the compiler from merging the two stores into one, which would be the plain one)
-__device__ __forceinline__ void store_vec(void* p, const uint4& v, bool keep = true) {
-    if (keep) { *static_cast<uint4*>(p) = v; return; }
-    asm volatile("; streaming" ::: "memory");
-    __builtin_nontemporal_store(v4u_t{v.x, v.y, v.z, v.w}, static_cast<v4u_t*>(p));
-    asm volatile("; streaming" ::: "memory");
+template <typename T>
+__device__ __forceinline__ void store_nt(void* p, const T& v) {
+    if constexpr (sizeof(T) == 16) __builtin_nontemporal_store(v4u_t{v.x, v.y, v.z, v.w}, static_cast<v4u_t*>(p));
+    else __builtin_nontemporal_store(v2u_t{v.x, v.y}, static_cast<v2u_t*>(p));
 }
-__device__ __forceinline__ void store_vec(void* p, const uint2& v, bool keep = true) {
-    if (keep) { *static_cast<uint2*>(p) = v; return; }
+// (the empty assembly keeps the compiler from merging the two stores into one, which would be the plain one)
+template <typename T>
+__device__ __forceinline__ void store_vec(void* p, const T& v, bool keep = true) {
+    if (keep) { *static_cast<T*>(p) = v; return; }
     asm volatile("; streaming" ::: "memory");
-    __builtin_nontemporal_store(v2u_t{v.x, v.y}, static_cast<v2u_t*>(p));
+    store_nt(p, v);
     asm volatile("; streaming" ::: "memory");
 }
 

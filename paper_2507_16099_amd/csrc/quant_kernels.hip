@@ -664,27 +664,32 @@ __global__ __launch_bounds__(256) void cast_transpose_kernel(const uint16_t* __r
 
     const uint4* tile16 = reinterpret_cast<const uint4*>(tile);
     constexpr int ROWS_PER_IT = 256 / PARTS;
+    // the whole loop once per kind of store: a branch at each store keeps the LDS reads from running ahead
+    auto stream_out = [&](auto put) {
 #pragma unroll
-    for (int it = 0; it < 128 / ROWS_PER_IT; ++it) {
-        const int cc = it * ROWS_PER_IT + (threadIdx.x / PARTS), p = threadIdx.x % PARTS;
-        const int64_t oc = c0 + cc, orow = r0 + p * 16;
-        if (oc >= cols || orow >= rows) continue;
-        const uint4 v = tile16[cc * PARTS + (p ^ ((cc >> 3) & 7))];
-        uint8_t* dst = qt + oc * ld_t + orow;
-        if (orow + 16 <= rows) {
-            store_vec(dst, v, keep_codes(rows, cols));
-        } else {
-            uint32_t t[4] = {v.x, v.y, v.z, v.w};
-            const int left = (int)(rows - orow);       // 1..15 bytes of codes, the rest of the piece is padding
-            if (pad) {
-#pragma unroll
-                for (int d = 0; d < 4; ++d) t[d] &= left >= 4 * d + 4 ? 0xFFFFFFFFu : left <= 4 * d ? 0u : (1u << (8 * (left - 4 * d))) - 1u;
-                store_vec(dst, make_uint4(t[0], t[1], t[2], t[3]), keep_codes(rows, cols));
+        for (int it = 0; it < 128 / ROWS_PER_IT; ++it) {
+            const int cc = it * ROWS_PER_IT + (threadIdx.x / PARTS), p = threadIdx.x % PARTS;
+            const int64_t oc = c0 + cc, orow = r0 + p * 16;
+            if (oc >= cols || orow >= rows) continue;
+            const uint4 v = tile16[cc * PARTS + (p ^ ((cc >> 3) & 7))];
+            uint8_t* dst = qt + oc * ld_t + orow;
+            if (orow + 16 <= rows) {
+                put(dst, v);
             } else {
-                for (int e = 0; orow + e < rows; ++e) dst[e] = (uint8_t)((t[e >> 2] >> (8 * (e & 3))) & 0xFFu);
+                uint32_t t[4] = {v.x, v.y, v.z, v.w};
+                const int left = (int)(rows - orow);       // 1..15 bytes of codes, the rest of the piece is padding
+                if (pad) {
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) t[d] &= left >= 4 * d + 4 ? 0xFFFFFFFFu : left <= 4 * d ? 0u : (1u << (8 * (left - 4 * d))) - 1u;
+                    put(dst, make_uint4(t[0], t[1], t[2], t[3]));
+                } else {
+                    for (int e = 0; orow + e < rows; ++e) dst[e] = (uint8_t)((t[e >> 2] >> (8 * (e & 3))) & 0xFFu);
+                }
             }
         }
-    }
+    };
+    if (keep_codes(rows, cols)) stream_out([](uint8_t* dst, const uint4& v) { *reinterpret_cast<uint4*>(dst) = v; });
+    else stream_out([](uint8_t* dst, const uint4& v) { store_nt(dst, v); });
 }
 
 // the rows of a transposed output [cols, rows] in a workspace are padded to 16 bytes at least: the cast fills the piece in

@@ -464,7 +464,7 @@ __global__ __launch_bounds__(256) void cast_kernel(const uint16_t* __restrict__ 
                 lo = cast8<FMT>(v0, s_t);
                 hi = cast8<FMT>(v1, s_t);
             }
-            store_vec(dst, make_uint4(lo.x, lo.y, hi.x, hi.y));
+            store_vec(dst, make_uint4(lo.x, lo.y, hi.x, hi.y), GRAN != GRAN_COL || keep_codes(rows, cols));
         } else {
             for (int e = 0; c + e < cols; ++e) {
                 const float s = GRAN == GRAN_COL ? scale[c + e] : s_t;

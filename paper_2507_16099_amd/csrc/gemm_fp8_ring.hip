@@ -72,9 +72,15 @@ __device__ __forceinline__ void wait_vmem_but_barrier() {
 }
 // c += b a on the matrix cores, assembly with the accumulator tied in place: through the builtin the compiler moves
 // accumulators and fragments between register files (23 copies per 64 instructions on the 128 x 256 tile).  It inserts
-// no wait states for assembly: an accumulator's first update is behind the prologue's barrier, its first other reader
-// behind the loop's last one.
+// no wait states for assembly: an operand written by the vector ALU needs two in front of the instruction, a result
+// twelve behind it before anything else touches it.  So the vector ALU writes no operand among the steps (fragments and
+// scales come from LDS reads), the accumulators are cleared ahead of the prologue's wait and read behind the last barrier.
+// tests/test_isa_hazards.py checks the built code.
 // ACC_V: the accumulator lives in the ordinary register file (tiles small enough: the epilogue then needs no copies).
+// Otherwise the code holds one copy of each step: with a further one for an odd last step, behind the loop, the compiler
+// moved the accumulators to other registers and back directly in front of its matrix instructions, which also took 0.5 us
+// (odd step counts, 128 x 256 tiles: 2048 x 4096 x 4224 33.2 -> 32.6 us, x 1152 16.0 -> 15.4).  The small tiles keep the
+// pair of steps without a branch in it (2048 x 4096 x 4096 on 64 x 64 tiles: 66.8 us, with the branch 70.2).
 #define RG_MFMA(CSTR, MOD) asm volatile("v_mfma_f32_16x16x128_f8f6f4 %0, %1, %2, %0" MOD : CSTR(c) : "v"(b), "v"(a))
 template <int FA, int FB, bool ACC_V>
 __device__ __forceinline__ void mfma(v4f_t& c, const v8i_t& b, const v8i_t& a) {
@@ -278,62 +284,71 @@ __global__ __launch_bounds__(rg::NT) void gemm_fp8_ring_kernel(RingProblem p1, R
     const int ksteps = (K + BK - 1) / BK;
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
-    if (ksteps > 0) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int k0 = r * BK;
-            const uint32_t ka = kofs(k0, ca), ke = kofs(k0, cb_e), ko = kofs(k0, cb_o);
+    for (int r = 0; r < R; ++r) {
+        const int k0 = r * BK;
+        const uint32_t ka = kofs(k0, ca), ke = kofs(k0, cb_e), ko = kofs(k0, cb_o);
 #pragma unroll
-            for (int q = 0; q < NLD; ++q) load_q(q, (uint32_t)(r * STAGE), ka, ke, ko);
-            load_e((uint32_t)(r * STAGE), k0);
-        }
-        wait_vmem_but_barrier<(R - 1) * NL>();      // stage 0 has landed for everyone
+        for (int q = 0; q < NLD; ++q) load_q(q, (uint32_t)(r * STAGE), ka, ke, ko);
+        load_e((uint32_t)(r * STAGE), k0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int q = 0; q < FM + FN; ++q) read_q(I0{}, smem, q);
-        scale_table();
-        __builtin_amdgcn_sched_barrier(0);
+    for (int i = 0; i < NM; ++i) {              // the accumulators are cleared while the first stage is under way
+        if constexpr (ACC_V) asm volatile("" : "+v"(acc[i / FN][i % FN]));
+        else asm volatile("" : "+a"(acc[i / FN][i % FN]));
+    }
+    wait_vmem_but_barrier<(R - 1) * NL>();      // stage 0 has landed for everyone
+#pragma unroll
+    for (int q = 0; q < FM + FN; ++q) read_q(I0{}, smem, q);
+    scale_table();
+    __builtin_amdgcn_sched_barrier(0);
 
-        uint32_t cur = 0, nxt = STAGE;              // byte offsets of the stages of steps s and s + 1
-        int k_refill = R * BK;
-        auto step = [&](auto par_t) {
-            constexpr int P = decltype(par_t)::value;
-            using NS = std::integral_constant<int, P ^ 1>;
-            wait_vmem_but_barrier<(R - 2) * NL>();  // stage s + 1 landed, stage s read out: for everyone
-            const uint32_t ka = kofs(k_refill, ca), ke = kofs(k_refill, cb_e), ko = kofs(k_refill, cb_o);
-            const uint8_t* rs = smem + nxt;
-            // In the shadow of the MFMAs: the reads early (their latency must pass before the next barrier), the refill
-            // loads spread evenly - four waves' loads leave the CU's address unit at one per 16 cycles, and a wave that
-            // finds its queue full stalls, matrix instructions included.
-            constexpr int QR = NM >= 16 ? NM * 5 / 8 : (NM + 1) / 2;
+    uint32_t cur = 0, nxt = STAGE;              // byte offsets of the stages of steps s and s + 1
+    int k_refill = R * BK;
+    auto step = [&](auto par_t) {
+        constexpr int P = decltype(par_t)::value;
+        using NS = std::integral_constant<int, P ^ 1>;
+        wait_vmem_but_barrier<(R - 2) * NL>();  // stage s + 1 landed, stage s read out: for everyone
+        const uint32_t ka = kofs(k_refill, ca), ke = kofs(k_refill, cb_e), ko = kofs(k_refill, cb_o);
+        const uint8_t* rs = smem + nxt;
+        // In the shadow of the MFMAs: the reads early (their latency must pass before the next barrier), the refill
+        // loads spread evenly - four waves' loads leave the CU's address unit at one per 16 cycles, and a wave that
+        // finds its queue full stalls, matrix instructions included.
+        constexpr int QR = NM >= 16 ? NM * 5 / 8 : (NM + 1) / 2;
 #pragma unroll
-            for (int t = 0; t < NM; ++t) {
-                const int i = t / FN, j = (i & 1) ? FN - 1 - t % FN : t % FN;   // boustrophedon: one operand stays between neighbours
-                if constexpr (MX) mfma_mx<FA, FB, ACC_V>(acc[i][j], bf[P][j], af[P][i], eb[P][j], ea[P][i]);
-                else mfma<FA, FB, ACC_V>(acc[i][j], bf[P][j], af[P][i]);
-                if (t < QR) {
+        for (int t = 0; t < NM; ++t) {
+            const int i = t / FN, j = (i & 1) ? FN - 1 - t % FN : t % FN;   // boustrophedon: one operand stays between neighbours
+            if constexpr (MX) mfma_mx<FA, FB, ACC_V>(acc[i][j], bf[P][j], af[P][i], eb[P][j], ea[P][i]);
+            else mfma<FA, FB, ACC_V>(acc[i][j], bf[P][j], af[P][i]);
+            if (t < QR) {
 #pragma unroll
-                    for (int q = t * (FM + FN) / QR; q < (t + 1) * (FM + FN) / QR; ++q) read_q(NS{}, rs, q);
-                }
-#pragma unroll
-                for (int q = t * NLD / NM; q < (t + 1) * NLD / NM; ++q) load_q(q, cur, ka, ke, ko);
-                if (MX && t == NM - 1) load_e(cur, k_refill);
-                __builtin_amdgcn_sched_barrier(0);
+                for (int q = t * (FM + FN) / QR; q < (t + 1) * (FM + FN) / QR; ++q) read_q(NS{}, rs, q);
             }
-            cur = nxt;
-            nxt = nxt + STAGE == R * STAGE ? 0 : nxt + STAGE;
-            k_refill += BK;
-        };
-        int s = 0;
+#pragma unroll
+            for (int q = t * NLD / NM; q < (t + 1) * NLD / NM; ++q) load_q(q, cur, ka, ke, ko);
+            if (MX && t == NM - 1) load_e(cur, k_refill);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        cur = nxt;
+        nxt = nxt + STAGE == R * STAGE ? 0 : nxt + STAGE;
+        k_refill += BK;
+    };
+    int s = 0;
+    if constexpr (ACC_V) {
         for (; s + 2 <= ksteps; s += 2) {
             step(I0{});
             step(I1{});
         }
         if (s < ksteps) step(I0{});
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // trailing (out-of-range) refills must not land in the epilogue's LDS
-    } else {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        scale_table();
+    } else {                    // one copy of each step, see mfma (K = 0: one step of zero codes)
+        do {
+            step(I0{});
+            if (s + 1 < ksteps) step(I1{});
+            s += 2;
+        } while (s < ksteps);
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // trailing (out-of-range) refills must not land in the epilogue's LDS
     __syncthreads();
 
     // ---- epilogue: (acc * 1/sa) * 1/sb (MX: nothing left to scale)

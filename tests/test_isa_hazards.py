@@ -1,0 +1,29 @@
+"""The built gfx950 code keeps the distances that inline assembly takes out of the compiler's hands."""
+import pytest
+
+import paper_2507_16099_amd as fp8
+from tests.isa_hazards import check_kernel, disassemble
+
+MFMA = "v_mfma_f32_16x16x128_f8f6f4 a[0:3], v[0:7], v[8:15], a[0:3]"
+
+
+@pytest.mark.parametrize("bad,text", [
+    (True, ["v_accvgpr_write_b32 a3, v20", MFMA]),
+    (True, ["v_mov_b32_e32 v9, 0", "s_nop 0", MFMA]),
+    (False, ["v_accvgpr_write_b32 a3, v20", "s_nop 1", MFMA, MFMA]),
+    (True, [MFMA, "s_nop 10", "v_accvgpr_read_b32 v0, a0"]),
+    (False, [MFMA, "s_nop 11", "v_accvgpr_read_b32 v0, a0"]),
+    (True, ["global_load_dword v1, v[2:3], off", "buffer_load_dwordx4 v4, s[0:3], 0 offen lds", "s_waitcnt vmcnt(2)", "v_mov_b32_e32 v1, 0"]),
+    (False, ["global_load_dword v1, v[2:3], off", "buffer_load_dwordx4 v4, s[0:3], 0 offen lds", "s_waitcnt vmcnt(1)", "v_mov_b32_e32 v1, 0"]),
+    (True, ["global_load_dword v1, v[2:3], off", "s_cbranch_scc1 1", "s_waitcnt vmcnt(0)", "v_mov_b32_e32 v1, 0"]),    # one path waits
+])
+def test_the_check_itself(bad, text):
+    code = [(4 * n, *line.split(" ", 1)) for n, line in enumerate([*text, "s_endpgm "])]
+    assert bool(check_kernel(code)) == bad
+
+
+def test_no_instruction_comes_too_early():
+    kernels = disassemble(fp8.library_path())
+    assert any("gemm_fp8_ring" in name for name in kernels) and any("gemm_fp8_stream" in name for name in kernels)
+    found = {name: bad for name, code in kernels.items() if (bad := check_kernel(code))}
+    assert not found, {name: bad[:3] for name, bad in found.items()}

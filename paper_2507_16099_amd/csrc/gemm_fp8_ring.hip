@@ -57,7 +57,7 @@ __device__ __forceinline__ void lds_dma16(v4i_t rsrc, uint32_t lds_addr, uint32_
                  : "s"(lds_addr), "v"(voffset), "s"(rsrc)
                  : "memory", "m0");
 }
-// 4 bytes per lane into LDS at lds_addr + lane * 4 (the scales of 64 rows)
+// 4 bytes per lane into LDS at lds_addr + lane * 4 (the scales of 64 rows, or the block scales of a step of 64 rows)
 __device__ __forceinline__ void lds_dma4(v4i_t rsrc, uint32_t lds_addr, uint32_t voffset) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds"
                  :
@@ -169,27 +169,6 @@ __global__ __launch_bounds__(rg::NT) void gemm_fp8_ring_kernel(RingProblem p1, R
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm0 = (wave / WAVES_N) * WM, wn0 = (wave % WAVES_N) * WN;
 
-    // Scales of the tile's rows and columns, one per thread, requested ahead of the operands.  Assembly loads: a wait that
-    // the compiler placed for them would also wait for every LDS-DMA load in flight.  They are older than those loads, so the
-    // wait for stage 0 covers them; their registers are not touched before it.
-    float raw_a, raw_b;
-    if constexpr (!MX) {
-        const int m = m0 + tid, n = n0 + tid;
-        const float* sa_p = p.scale_a + (row_a ? (m < M ? m : M - 1) : 0);
-        const float* sb_p = p.scale_b + (row_b ? (n < N ? n : N - 1) : 0);
-        asm volatile("global_load_dword %0, %2, off\n\tglobal_load_dword %1, %3, off"
-                     : "=&v"(raw_a), "=&v"(raw_b)
-                     : "v"(sa_p), "v"(sb_p)
-                     : "memory");
-    }
-    float* inv_tab = reinterpret_cast<float*>(smem + R * STAGE);    // reciprocals: rows, then columns (behind the ring)
-    auto scale_table = [&]() {
-        if constexpr (MX) return;
-        asm volatile("" : "+v"(raw_a), "+v"(raw_b));
-        if (tid < TM) inv_tab[tid] = 1.0f / raw_a;
-        if (tid < TN) inv_tab[TM + tid] = 1.0f / raw_b;
-    };
-
     // ---- buffer descriptors of this tile's operand panels (the host checks that offsets stay below 2^31)
     const int64_t lda = p.lda, ldb = p.ldb;
     const int rows_a = M - m0 < TM ? M - m0 : TM, rows_b = N - n0 < TN ? N - n0 : TN;
@@ -197,6 +176,28 @@ __global__ __launch_bounds__(rg::NT) void gemm_fp8_ring_kernel(RingProblem p1, R
     const uint64_t pb = reinterpret_cast<uint64_t>(p.B + (int64_t)n0 * ldb);
     const v4i_t rsrc_a = {(int)(uint32_t)pa, (int)(uint32_t)(pa >> 32), (int)((int64_t)(rows_a - 1) * lda + K), 0x00020000};
     const v4i_t rsrc_b = {(int)(uint32_t)pb, (int)(uint32_t)(pb >> 32), (int)((int64_t)(rows_b - 1) * ldb + K), 0x00020000};
+
+    // ---- scales of the tile's rows and columns, by LDS-DMA into the table behind the ring (64 rows or columns a load: unit u
+    //      goes to wave u % 4), ahead of the operands: older than these, they have landed with stage 0.  The table then takes
+    //      their reciprocals, rows first.
+    float* inv_tab = reinterpret_cast<float*>(smem + R * STAGE);
+    if constexpr (!MX) {
+        const uint64_t psa = reinterpret_cast<uint64_t>(p.scale_a + (row_a ? m0 : 0)), psb = reinterpret_cast<uint64_t>(p.scale_b + (row_b ? n0 : 0));
+        const v4i_t rsrc_sa = {(int)(uint32_t)psa, (int)(uint32_t)(psa >> 32), row_a ? rows_a * 4 : 4, 0x00020000};
+        const v4i_t rsrc_sb = {(int)(uint32_t)psb, (int)(uint32_t)(psb >> 32), row_b ? rows_b * 4 : 4, 0x00020000};
+#pragma unroll
+        for (int h = 0; h < ((TM + TN) / 64 + 3) / 4; ++h) {
+            const int u = wave + 4 * h, r = 64 * (u < TM / 64 ? u : u - TM / 64) + lane;
+            const uint32_t at = (uint32_t)(size_t)inv_tab + (uint32_t)u * 256u;
+            if (u < TM / 64) lds_dma4(rsrc_sa, at, row_a ? (uint32_t)(r < rows_a ? r : rows_a - 1) * 4u : 0u);
+            else if (u < (TM + TN) / 64) lds_dma4(rsrc_sb, at, row_b ? (uint32_t)(r < rows_b ? r : rows_b - 1) * 4u : 0u);
+        }
+    }
+    auto scale_table = [&]() {
+        if constexpr (MX) return;
+        if (tid < TM) inv_tab[tid] = 1.0f / inv_tab[tid];
+        if (tid < TN) inv_tab[TM + tid] = 1.0f / inv_tab[TM + tid];
+    };
 
     // ---- global -> LDS: load i of wave w fills rows 32 i + 8 w + lane / 8; lane's chunk slot lane % 8 takes chunk
     //      slot ^ key(row).  A: key = (row >> 1) & 7.  B: ((row >> 1) & 1) | ((row >> SH) & 3) << 1.

@@ -48,7 +48,9 @@ __device__ __forceinline__ void skf_lds_dma16(v4i_q rsrc, uint32_t lds_addr, uin
                  : "memory", "m0");
 }
 // 16 bytes per lane from a raw buffer into registers; the data is there after skf_wait_x.  Assembly, like
-// the wait: the compiler's own count of loads in flight knows nothing of the LDS-DMA loads issued behind these.
+// the wait: the compiler's own count of loads in flight knows nothing of the LDS-DMA loads issued behind these, and its
+// wait would be for the first ring fill too (24 MB over the chip, about 5 us of a 6.6 us kernel).  Every register written
+// here is an operand of that wait; that nothing touches one before it is checked in the built code (tests/test_isa_hazards.py).
 __device__ __forceinline__ void skf_load16(v4i_q& dst, v4i_q rsrc, uint32_t voffset) {
     asm volatile("buffer_load_dwordx4 %0, %1, %2, 0 offen" : "=v"(dst) : "v"(voffset), "s"(rsrc) : "memory");
 }

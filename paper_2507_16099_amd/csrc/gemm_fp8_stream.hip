@@ -74,6 +74,13 @@ __device__ __forceinline__ void st_lds_dma16(v4i_t2 rsrc, uint32_t lds_addr, uin
                  : "s"(lds_addr), "v"(voffset), "s"(rsrc)
                  : "memory", "m0");
 }
+// 4 bytes per lane into LDS at lds_addr + lane * 4
+__device__ __forceinline__ void st_lds_dma4(v4i_t2 rsrc, uint32_t lds_addr, uint32_t voffset) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds"
+                 :
+                 : "s"(lds_addr), "v"(voffset), "s"(rsrc)
+                 : "memory", "m0");
+}
 __device__ __forceinline__ void st_wait_all_vmem() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 __device__ __forceinline__ void st_barrier_lds() {
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -373,22 +380,21 @@ __global__ __launch_bounds__(st::NT) void gemm_fp8_stream_kernel(
     const int kpairs = (ksteps + 1) / 2;        // >= 2 (checked by the launcher); an odd count gets one phantom step of zeros
     const int nsteps = 2 * kpairs;
 
-    // reciprocal scales of a tile, one row and one column per thread (correctly rounded divides); the raw scales are
-    // fetched by assembly loads so that the compiler's own wait counters never see them (a compiler-placed wait would
-    // also wait for the LDS-DMA loads in flight)
-    float raw_a = 1.f, raw_b = 1.f;
-    auto scale_loads = [&](const StTile& t) {
-        const int m = t.m0 + (int)threadIdx.x, n = t.n0 + (int)threadIdx.x;
-        const float* pa = scale_a + (row_a ? (m < M ? m : M - 1) : 0);
-        const float* pb = scale_b + (row_b ? (n < N ? n : N - 1) : 0);
-        asm volatile("global_load_dword %0, %2, off\n\tglobal_load_dword %1, %3, off"
-                     : "=&v"(raw_a), "=&v"(raw_b)
-                     : "v"(pa), "v"(pb)
-                     : "memory");
+    // Reciprocal scales of a tile, one row and one column per thread (correctly rounded divides).  The raw scales come into
+    // the table by LDS-DMA, each wave those of its own threads: the compiler, which sees no load, places no wait for them
+    // (it would also wait for the operands in flight), and no register stands for a load that has not arrived.
+    auto scale_loads = [&](const StTile& t, float* tab) {
+        const int rows = M - t.m0 < BM ? M - t.m0 : BM, cols = N - t.n0 < BN ? N - t.n0 : BN, i = (int)threadIdx.x;
+        const uint64_t pa = reinterpret_cast<uint64_t>(scale_a + (row_a ? t.m0 : 0)), pb = reinterpret_cast<uint64_t>(scale_b + (row_b ? t.n0 : 0));
+        const v4i_t2 rsrc_a = {(int)(uint32_t)pa, (int)(uint32_t)(pa >> 32), row_a ? rows * 4 : 4, 0x00020000};
+        const v4i_t2 rsrc_b = {(int)(uint32_t)pb, (int)(uint32_t)(pb >> 32), row_b ? cols * 4 : 4, 0x00020000};
+        const uint32_t at = (uint32_t)(size_t)tab + (uint32_t)wave * 256u;
+        st_lds_dma4(rsrc_a, at, row_a ? (uint32_t)(i < rows ? i : rows - 1) * 4u : 0u);
+        st_lds_dma4(rsrc_b, at + 1024u, row_b ? (uint32_t)(i < cols ? i : cols - 1) * 4u : 0u);
     };
     auto scale_table = [&](float* tab) {
         // (the loads were issued ahead of a phase 3's refill loads and a wait that lets only younger operations stay in flight has passed)
-        asm volatile("" : "+v"(raw_a), "+v"(raw_b));
+        const float raw_a = tab[threadIdx.x], raw_b = tab[256 + threadIdx.x];
         tab[threadIdx.x] = 1.0f / raw_a;
         tab[256 + threadIdx.x] = 1.0f / raw_b;
     };
@@ -424,7 +430,7 @@ __global__ __launch_bounds__(st::NT) void gemm_fp8_stream_kernel(
             st_barrier_lds();                  // this step's B part is read out by everyone
             phase(I0{}, I1{}, I1{}, I1{}, I0{}, I5{}, Z{}, std::conditional_t<FD, StJobsF2, NJ>{}, s_cur, la, lb, lt, ko, dprev);   // (A0,B1) | read A1 of this step, refill B 0-4
             st_wait_vmem_but_barrier<5 + (FD ? st_extra_f(AF1) : 0)>();   // step k+1 has landed for everyone; this step's A part is read out
-            if constexpr (FIRST) scale_loads(cur);   // older than the refill loads below: complete at the next such wait
+            if constexpr (FIRST) scale_loads(cur, tab_cur);   // older than the refill loads below: complete at the next such wait
             phase(I1{}, I1{}, I1{}, I0{}, I5{}, I6{}, Z{}, std::conditional_t<FD, StJobsF3, NJ>{}, s_nxt, la, lb, lt, ko, dprev);   // (A1,B1) | read A0 of step k+1, refill B 5-7, A 0-2
             phase(I1{}, I0{}, I0{}, I1{}, I11{}, I5{}, Z{}, NJ{}, s_nxt, la, lb, lt, ko, dprev);                                    // (A1,B0) | read B1 of step k+1, refill A 3-7
         }

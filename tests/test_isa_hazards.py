@@ -1,4 +1,8 @@
 """The built gfx950 code keeps the distances that inline assembly takes out of the compiler's hands."""
+import glob
+import os
+import re
+
 import pytest
 
 import paper_2507_16099_amd as fp8
@@ -27,3 +31,14 @@ def test_no_instruction_comes_too_early():
     assert any("gemm_fp8_ring" in name for name in kernels) and any("gemm_fp8_stream" in name for name in kernels)
     found = {name: bad for name, code in kernels.items() if (bad := check_kernel(code))}
     assert not found, {name: bad[:3] for name, bad in found.items()}
+
+
+def test_assembly_loads_write_no_register():
+    """A register that an assembly load will write counts as written for the compiler from the load on.  Loads in assembly
+    therefore write LDS; the one exception holds its registers as operands of the wait that follows."""
+    found = []
+    for path in sorted(glob.glob(os.path.join(os.path.dirname(fp8.library_path()), "csrc", "*.hip"))):
+        for m in re.finditer(r"asm volatile\((.*?)\);", open(path).read(), re.S):
+            if "_load_" in m[1] and '"=' in m[1]:
+                found.append(os.path.basename(path))
+    assert found == ["gemm_fp8_skinny_fused.hip"]

@@ -156,13 +156,18 @@ def _check(rc: int) -> None:
 
 # A decode linear is 6-10 us on the GPU, so what a call costs here counts: 9.3 us of Python, ctypes and launch with the
 # stream object (2.7 us) and one attribute at a time in _mat (0.75 us per tensor), of which the launch itself is 3.5 us.
-# Every tensor has been seen to be on the GPU before the stream is asked for, so the runtime is up.
-_raw_stream, _device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+# Every tensor has been seen to be on the GPU before the stream is asked for, so the runtime is up.  The two functions are
+# torch's own and not public (a CPU build has neither): without them the stream object serves.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
 
-
-def _stream() -> int:
-    """The current stream of the current device, as torch.cuda.current_stream().cuda_stream gives it."""
-    return _raw_stream(_device())
+if _raw_stream is not None and _device is not None:
+    def _stream() -> int:
+        """The current stream of the current device, as torch.cuda.current_stream().cuda_stream gives it."""
+        return _raw_stream(_device())
+else:
+    def _stream() -> int:
+        return torch.cuda.current_stream().cuda_stream
 
 
 def _ptr(t) -> int | None:

@@ -135,10 +135,13 @@ int64_t pad16(int64_t v) { return (v + 15) / 16 * 16; }
 // operands 128 bytes of a row at a time; with rows that start between cache lines every such piece is two lines, which
 // costs the products 14-22 % (1024^2 x 3504: 12.4 -> 9.7 us, 4096 x 8192 x 3504: 105 -> 90, 8192^2 x 4016: 214 -> 188) and the
 // transposing cast of 8152 tokens 38 -> 27 us.  So lengths beyond 512 are padded to 128 (shorter ones are bound by
-// launches).
+// launches), except where that reaches a multiple of 2^22: at 2^22 and 2^23 end the 32-bit offsets of the product kernels.
 struct Pitch { int64_t k, n, m; };
 Pitch pitch_of(int64_t M, int64_t K, int64_t N) {
-    auto up = [](int64_t v) { return v <= 512 ? pad16(v) : (v + 127) / 128 * 128; };
+    auto up = [](int64_t v) {
+        const int64_t p = (v + 127) / 128 * 128;
+        return v <= 512 || p % (1 << 22) == 0 ? pad16(v) : p;
+    };
     return Pitch{up(K), up(N), up(M)};
 }
 

@@ -25,6 +25,10 @@
  *    synchronizes with the host.
  *  - Ownership: the caller owns every buffer, including the workspace.  The
  *    library allocates no device memory and keeps no state between calls.
+ *  - Workspaces: a call needs what its *_workspace_bytes function returns for
+ *    the same arguments, and refuses less.  Ask this library: the layout inside
+ *    (padded rows, scales in whole slabs) is its own, and a size computed from
+ *    the shapes or kept from another version can be too small.
  *  - Errors: arguments are validated on the host BEFORE anything is launched.
  *    A negative fp8_status is returned and fp8_last_error() describes it;
  *    nothing is thrown across the boundary and the process is never aborted.
@@ -67,7 +71,7 @@ enum fp8_status {
     FP8_ERR_SHAPE = -2,     /* negative dimension, ld too small, K not % 16     */
     FP8_ERR_ENUM = -3,      /* unknown format / granularity / flag              */
     FP8_ERR_ALIGN = -4,     /* pointer or leading dimension not aligned         */
-    FP8_ERR_WORKSPACE = -5, /* workspace smaller than fp8_linear_workspace_bytes */
+    FP8_ERR_WORKSPACE = -5, /* workspace smaller than the call's *_workspace_bytes  */
     FP8_ERR_HIP = -6        /* a kernel launch failed (hipGetLastError)         */
 };
 
@@ -186,8 +190,7 @@ typedef struct fp8_recipe {
 } fp8_recipe;
 
 /* Bytes of workspace fp8_linear_fwd (bwd == 0) or fp8_linear_bwd (bwd != 0)
- * needs for X [M,K], W [N,K], dY [M,N] (the fp8 copies lie in it with rows padded
- * to 128 bytes: ask, do not compute).  Returns 0 on invalid arguments. */
+ * needs for X [M,K], W [N,K], dY [M,N].  Returns 0 on invalid arguments. */
 size_t fp8_linear_workspace_bytes(int64_t M, int64_t K, int64_t N, const fp8_recipe* recipe, int bwd);
 
 /*
@@ -207,9 +210,8 @@ int fp8_linear_fwd(const void* x, const void* w, int64_t M, int64_t K, int64_t N
  * over a contiguous axis.  Tensorwise: one scale per tensor, only the layouts
  * change.  dx and dw are bfloat16, dense; either may be NULL to skip it.
  * K and N multiples of 16; M (tokens) arbitrary: the transposed operands of dW,
- * whose contraction axis is M, get rows padded to 16 bytes with zero codes
- * inside the workspace (token counts on the 16-byte grid take the faster
- * quantization kernels).
+ * whose contraction axis is M, get zero codes up to the next multiple of 16
+ * inside the workspace.
  */
 int fp8_linear_bwd(const void* dy, const void* x, const void* w, int64_t M, int64_t K, int64_t N,
                    const fp8_recipe* recipe, void* dx, void* dw, void* workspace,

@@ -26,9 +26,10 @@ typedef unsigned short u16x2_t __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ float fmt_max(int fmt) { return fmt == FMT_E4M3FN ? 448.0f : 57344.0f; }
 
-// 128-bit load with the streaming (non-temporal) hint, for bfloat16 input that this kernel is the last of its call to
-// touch: 6-12 % faster than a plain load on the casts of large tensors, and it keeps such data from displacing the codes.
-// Plain loads instead: 777x14336x4096 tensorwise forward 66.7 -> 72.2 us, the LayerNorm step of 8192x4096x4096 482 -> 496.
+// 128-bit load with the streaming (non-temporal) hint, for the bfloat16 input of the quantizers: 6-12 % faster than a plain
+// load on the casts of large tensors, and it keeps such data from displacing the codes.  (The first of two passes uses it
+// too: the second one finds the tensor in the last-level cache all the same.)  Plain loads instead: 777x14336x4096
+// tensorwise forward 66.7 -> 72.2 us, the LayerNorm step of 8192x4096x4096 482 -> 496.
 typedef unsigned v4u_t __attribute__((ext_vector_type(4)));
 typedef unsigned v2u_t __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint4 load_stream(const void* p) {
@@ -36,25 +37,35 @@ __device__ __forceinline__ uint4 load_stream(const void* p) {
     return make_uint4(t[0], t[1], t[2], t[3]);
 }
 
-// Codes are stored plainly: the product reads them next and finds them in the caches (hint / plain: 777x14336x4096
-// tensorwise forward 83.1 / 66.7 us, 72x4096x14336 17.1 / 15.6, 8192x4096x6144 tensorwise training step 572 / 554; the one-pass
-// quantizers themselves 0-9 % faster from 128 Mi elements on, level below).  Except where the same tensor is read twice for
-// its per-column codes and the tensor and its codes, in both orientations four bytes an element, do not fit the 256 MB
-// last-level cache: the codes would displace the input between the passes (hint / plain, per-column codes of 16384x4096
-// 72.3 / 72.4 us, 16384x8192 122 / 139, 16384x14336 239 / 281; both orientations 79 / 79, 148 / 168, 263 / 290).
+// Codes are stored through the L2 (system scope): they are in the 256 MB last-level cache when the product reads them, and
+// no dirty lines are left that the end of the kernel has to wait for.  Measured (us; streaming hint / plain store / this):
+//   the quantizers alone: MX 2048x2048 5.4 / 5.9 / 5.2, both orientations 8.6 / 10.0 / 8.5, 16384x8192 118 / 102 / 100;
+//     rowwise 4096x4096 11.2 / 11.8 / 11.1, 16384x14336 113 / 107 / 103; LayerNorm 2048x2048 9.8 / 11.5 / 10.0
+//   with the product, 2048x4096x4096: rowwise 53.0 / 52.5 / 50.8, MX 56.9 / 58.4 / 56.0
+//   training steps: rowwise 1024x1024x1024 43.2 / 42.7 / 39.9, tensorwise 8192x8192x4096 716 / 677 / 670
+//   a quantized weight's forward, 72 tokens x 4096 x 14336: 17.1 / 15.6 / 15.7
+// Except in the second of two passes over a tensor that, with its codes in both orientations, four bytes an element, does
+// not fit that cache: the codes would displace the input between the passes, so they take the hint (hint / plain, per-column
+// codes of 16384x4096 72.3 / 72.4 us, 16384x8192 122 / 139, 16384x14336 239 / 281; both orientations 79 / 79, 148 / 168,
+// 263 / 290).  That is every transposing cast and the rowwise pass that gathers column maxima; the untransposed cast with
+// one scale per tensor, whose codes are half as many bytes, gains nothing from it (16384x14336 199 / 193 us).
 __device__ __forceinline__ bool keep_codes(int64_t rows, int64_t cols) { return rows * cols <= (int64_t)64 << 20; }
 template <typename T>
 __device__ __forceinline__ void store_nt(void* p, const T& v) {
     if constexpr (sizeof(T) == 16) __builtin_nontemporal_store(v4u_t{v.x, v.y, v.z, v.w}, static_cast<v4u_t*>(p));
     else __builtin_nontemporal_store(v2u_t{v.x, v.y}, static_cast<v2u_t*>(p));
 }
-// (the empty assembly keeps the compiler from merging the two stores into one, which would be the plain one)
+// (assembly: no builtin stores 128 bits at system scope.  The s_nop is the wait state between a 128-bit store and a write to
+// its data registers, which the compiler does not insert for assembly.)
+template <typename T>
+__device__ __forceinline__ void store_through(void* p, const T& v) {
+    if constexpr (sizeof(T) == 16) asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 0" ::"v"(p), "v"(v4u_t{v.x, v.y, v.z, v.w}) : "memory");
+    else __hip_atomic_store(static_cast<uint64_t*>(p), (uint64_t)v.y << 32 | v.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 template <typename T>
 __device__ __forceinline__ void store_vec(void* p, const T& v, bool keep = true) {
-    if (keep) { *static_cast<T*>(p) = v; return; }
-    asm volatile("; streaming" ::: "memory");
-    store_nt(p, v);
-    asm volatile("; streaming" ::: "memory");
+    if (keep) store_through(p, v);
+    else store_nt(p, v);
 }
 
 // two bfloat16 packed in a dword -> two binary32 (exact widening)

@@ -688,7 +688,7 @@ __global__ __launch_bounds__(256) void cast_transpose_kernel(const uint16_t* __r
             }
         }
     };
-    if (keep_codes(rows, cols)) stream_out([](uint8_t* dst, const uint4& v) { *reinterpret_cast<uint4*>(dst) = v; });
+    if (keep_codes(rows, cols)) stream_out([](uint8_t* dst, const uint4& v) { store_through(dst, v); });
     else stream_out([](uint8_t* dst, const uint4& v) { store_nt(dst, v); });
 }
 

@@ -82,3 +82,30 @@ def test_two_products_in_one_launch(tile):
         with knobs(GEMM_RING=0, PAIRS=0, GEMM_VARIANT=4):
             dx0, dw0 = fp8.fp8_linear_bwd(dy, x, w, r)
         assert torch.equal(dx.view(torch.int16), dx0.view(torch.int16)) and torch.equal(dw.view(torch.int16), dw0.view(torch.int16))
+
+
+@pytest.mark.parametrize("tile", TILES)
+def test_empty_contraction(tile):
+    """K = 0: zeros, 0.5 behind the sigmoid, whatever the scales."""
+    M, N = 70, 72
+    a, b = (torch.empty((r, 0), dtype=torch.uint8, device="cuda") for r in (M, N))
+    sa, sb = torch.full((M,), 3.0, device="cuda"), torch.full((N,), 0.25, device="cuda")
+    with knobs(GEMM_RING=TILES[tile]):
+        for flags, value in ((0, 0.0), (fp8.FP8_OUT_FP32, 0.0), (fp8.FP8_EPILOGUE_SIGMOID, 0.5)):
+            out = torch.full((M, N), 7.0, dtype=torch.float32 if flags & fp8.FP8_OUT_FP32 else torch.bfloat16, device="cuda")
+            fp8.fp8_scaled_mm(a, 0, sa, fp8.FP8_ROW, b, 1, sb, fp8.FP8_ROW, flags, out=out)
+            assert bool((out == value).all())
+
+
+@pytest.mark.parametrize("tile", TILES)
+@pytest.mark.parametrize("steps", [1, 2, 3, 4, 5, 6, 7, 8, 9])
+def test_every_count_of_steps_around_the_depth_of_the_ring(tile, steps):
+    """Odd and even counts, fewer and more steps than stages: exact integer products."""
+    rng = np.random.default_rng(steps)
+    M, N, K = 140, 136, 128 * steps - 16
+    ai, bi = _ints((M, K), rng), _ints((N, K), rng)
+    one = dev_f32(np.ones(1, np.float32))
+    a, b = dev_u8(orc.encode_array(ai, 0), (K + 15) // 16 * 16), dev_u8(orc.encode_array(bi, 0), (K + 15) // 16 * 16)
+    with knobs(GEMM_RING=TILES[tile]):
+        got = host_f32(fp8.fp8_scaled_mm(a, 0, one, 0, b, 0, one, 0, fp8.FP8_OUT_FP32))
+    assert (got == ai @ bi.T).all()

@@ -238,7 +238,8 @@ static hipError_t launch_tn(const GemmOperands& g, int row_a, int row_b, hipStre
 // ---- kernel choice.  Up to 32 rows: the few-row kernel of gemm_fp8_skinny.hip (it streams B once), and up to 64 rows where
 // there are too few 64 x 64 tiles for the CUs, N <= 8192, and the contraction is long enough for its wavefronts to share
 // (us, few-row / ring: 48 x 1024 x 4096 8.1 / 11.6, 64 x 4096 x 14336 23.6 / 35.0, 64 x 8192 x 4096 13.8 / 14.9;
-// 64 x 8192 x 1024 5.9 / 5.4, 64 x 11008 x 4096 23.4 / 16.4, 32 x 28672 x 8192 51.6 / 47.8).
+// 64 x 8192 x 1024 5.9 / 5.4, 64 x 11008 x 4096 23.4 / 16.4).  These lines lie between 48 and 64 rows measured; that up to 32
+// rows always take the few-row kernel is not the best everywhere (32 x 28672 x 8192 51.6 / 47.8).
 // More than one round of 256 x 256 tiles (one per CU): the large-product kernels of gemm_fp8_snake.hip /
 // gemm_fp8_stream.hip.  In between the cheapest of the ring kernel's tiles (gemm_fp8_ring.hip) and one round of
 // 256 x 256 tiles by this estimate, in us (one launch; rounds of 256 workgroups, K steps of 128 bytes):

@@ -467,7 +467,10 @@ static hipError_t launch_ring_t(const GemmOperands& g1, const GemmOperands* g2, 
     return hipGetLastError();
 }
 
-// stages: what the LDS holds (64 x 64: for two workgroups per CU); rows of tiles walked together: close to square patches
+// stages: what the LDS holds; rows of tiles walked together: close to square patches.  64 x 64: five stages, which with the
+// table of reciprocals is one workgroup per CU; four, for two of them (as in the MX form), cost a long contraction more than
+// they give a short one or a second round (us, five / four stages: 1000 x 1000 x 14336 25.2 / 27.1, 512 x 512 x 28672 40.5 / 43.0,
+// 1024 x 1024 x 4096 10.5 / 10.5, x 1024 6.0 / 5.8; several rounds, where larger tiles are taken: 2048 x 2048 x 1024 16.3 / 12.9).
 template <int FA, int FB, bool MX>
 static hipError_t launch_ring_f(int tile, const GemmOperands& g1, const GemmOperands* g2, const MxScales* e, int row_a, int row_b,
                                 int mode, hipStream_t st) {

@@ -404,7 +404,10 @@ static hipError_t launch_sk_dma(const uint8_t* a, int64_t lda, const float* sa, 
                                 const float* sb, int row_b, int M, int N, int K, void* out, int64_t ld_out, int out_f32,
                                 int64_t grid, hipStream_t st) {
     constexpr int SLOT = (NW + MT) * 2048;
-    constexpr int R = SLOT <= 4096 ? 5 : (SLOT <= 6144 || MT > 2) ? 3 : 2;     // about 20 KB of ring per wavefront: two workgroups per CU
+    // up to 32 rows about 20 KB of ring per wavefront, two workgroups per CU; from 33 rows on three steps in flight, 24 to
+    // 36 KB, one workgroup per CU (two steps, for two workgroups, at 33-48 rows against 16 columns per wavefront: 6144 x 4096
+    // 9.3 -> 9.0 us, 8192 x 8192 18.9 -> 18.5, but 33 x 1024 x 16384 12.4 -> 13.0 and 33 x 2048 x 8192 8.8 -> 9.0)
+    constexpr int R = SLOT <= 4096 ? 5 : (SLOT <= 6144 || MT > 2) ? 3 : 2;
     constexpr int lds = 4 * R * SLOT;
     auto kern = gemm_fp8_skinny_dma_kernel<FA, FB, MT, KS, NW, R>;
     static DynamicLdsOnce attr;

@@ -43,7 +43,7 @@ __device__ __forceinline__ uint4 load_stream(const void* p) {
 //     rowwise 4096x4096 11.2 / 11.8 / 11.1, 16384x14336 113 / 107 / 103; LayerNorm 2048x2048 9.8 / 11.5 / 10.0
 //   with the product, 2048x4096x4096: rowwise 53.0 / 52.5 / 50.8, MX 56.9 / 58.4 / 56.0
 //   training steps: rowwise 1024x1024x1024 43.2 / 42.7 / 39.9, tensorwise 8192x8192x4096 716 / 677 / 670
-//   a quantized weight's forward, 72 tokens x 4096 x 14336: 17.1 / 15.6 / 15.7
+//   a quantized weight's forward, 72 tokens x 4096 x 14336: 17.1 / 15.6 / 15.7 (few tokens: see quant_row_kernel's launch)
 // Except in the second of two passes over a tensor that, with its codes in both orientations, four bytes an element, does
 // not fit that cache: the codes would displace the input between the passes, so they take the hint (hint / plain, per-column
 // codes of 16384x4096 72.3 / 72.4 us, 16384x8192 122 / 139, 16384x14336 239 / 281; both orientations 79 / 79, 148 / 168,

@@ -103,3 +103,17 @@ def test_padded_operand_rows_give_the_products_of_dense_ones(M, K, N, recipe, sa
     assert torch.equal(y, product(x, row, E4, 0, w, row, E4, 0))
     assert torch.equal(dx, product(dy, row, E5, 0, w, col, E4, T))
     assert torch.equal(dw, product(dy, col, E5, T, x, col, E4, T))
+
+
+@pytest.mark.parametrize("rows,cols", [(1, 8), (128, 4096), (129, 4096), (64, 8200), (1023, 512), (17, 32768), (3, 130), (4097, 128)])
+def test_rowwise_codes_on_both_sides_of_the_store_rule(rows, cols):
+    """Up to 512 Ki elements another form of the rowwise kernel stores the codes; rows with a tail, padded input and output."""
+    x = si.normal_bf16((rows, cols), 1.0, 3, rows + cols)
+    ld = (cols + 7) // 8 * 8 + 8
+    xd = dev_bf16(x, ld)
+    for fmt, flags in ((orc.E4M3FN, 0), (orc.E5M2, fp8.FP8_POW2_SCALE)):
+        want_q, want_s = orc.quantize(x, orc.ROW, fmt, bool(flags))
+        out = torch.full((rows, (cols + 15) // 16 * 16 + 16), 0x5A, dtype=torch.uint8, device="cuda")
+        q, s = fp8.fp8_quantize(xd, fp8.FP8_ROW, fmt, flags, out=out[:, :cols])
+        assert (s.cpu().numpy() == want_s).all() and (q.cpu().numpy() == want_q).all()
+        assert bool((out[:, cols:] == 0x5A).all())

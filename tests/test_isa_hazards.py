@@ -45,12 +45,14 @@ def test_assembly_loads_write_no_register():
 
 
 def test_codes_are_stored_through_the_l2_or_past_it():
-    """Plain stores of codes leave dirty lines that the end of a quantization kernel waits for (3-18 % of its time)."""
+    """Plain stores of codes leave dirty lines that the end of a quantization kernel waits for (3-18 % of its time).  Only the
+    rowwise kernel's form for few tokens (last template argument) stores plainly."""
     plain = {}
     for name, code in disassemble(fp8.library_path()).items():
         if re.search(r"\d(quant_row_kernel|cast_kernel|cast_transpose_kernel|mx_quant\w*_kernel|block_quant\w*_kernel)I", name):
             stores = [args for _, op, args in code if op in ("global_store_dwordx2", "global_store_dwordx4")]
             assert stores, name
-            if bad := [args for args in stores if not re.search(r"\bsc0 sc1\b|\bnt\b", args)]:
+            few = re.search(r"quant_row_kernelI(Li\d+E)+Lb1E", name)
+            if not few and (bad := [args for args in stores if not re.search(r"\bsc0 sc1\b|\bnt\b", args)]):
                 plain[name] = bad[0]
     assert not plain

@@ -8,6 +8,7 @@ cannot make across inline assembly:
   * loads into registers: no instruction touches the destination before an s_waitcnt vmcnt that covers the load.
 
 Both run over the control-flow graph of every kernel, worst case over all paths."""
+import functools
 import os
 import re
 import shutil
@@ -21,6 +22,7 @@ _SYM = re.compile(r"^[0-9a-f]+ <(.+)>:$")
 _VM = ("global_", "buffer_", "flat_", "scratch_")
 
 
+@functools.lru_cache(maxsize=1)
 def disassemble(library: str) -> dict:
     """kernel name -> [(address, mnemonic, operands)]"""
     kernels: dict = {}

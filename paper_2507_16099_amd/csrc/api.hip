@@ -854,7 +854,7 @@ int fp8_mx_quantize_row_col(const void* x, int64_t rows, int64_t cols, int64_t l
     if (int rc = check_q_out("fp8_mx_quantize_row_col(q_col_t)", q_col_t, cols, rows, ld_col_t, 0)) return rc;
     if (int rc = check_e8m0("fp8_mx_quantize_row_col(e_row)", e_row, rows, cols / 32, ld_er)) return rc;
     if (int rc = check_e8m0("fp8_mx_quantize_row_col(e_col_t)", e_col_t, cols, rows / 32, ld_ec)) return rc;
-    FP8_TRY(fp8k::launch_mx_quant_t(x, rows, cols, ld, format, q_col_t, ld_col_t, e_col_t, ld_ec, q_row, ld_row, e_row, ld_er,
+    FP8_TRY(fp8k::launch_mx_quant_t(x, rows, cols, ld, format | fp8k::FMT_ALONE, q_col_t, ld_col_t, e_col_t, ld_ec, q_row, ld_row, e_row, ld_er,
                                     static_cast<hipStream_t>(stream)));
     return FP8_OK;
 }
@@ -1108,7 +1108,7 @@ int fp8_block_quantize_row_col(const void* x, int64_t rows, int64_t cols, int64_
     if (int rc = check_q_out(fn, q_col_t, cols, rows, ld_col_t, 0)) return rc;
     if (int rc = check_e8m0("fp8_block_quantize_row_col(e_row)", e_row, rows, cols / 32, ld_er)) return rc;
     if (int rc = check_e8m0("fp8_block_quantize_row_col(e_col_t)", e_col_t, cols, rows / 32, ld_ec)) return rc;
-    FP8_TRY(fp8k::launch_block_quant_t(x, rows, cols, ld, 1, format, q_col_t, ld_col_t, e_col_t, ld_ec, static_cast<hipStream_t>(stream),
+    FP8_TRY(fp8k::launch_block_quant_t(x, rows, cols, ld, 1, format | fp8k::FMT_ALONE, q_col_t, ld_col_t, e_col_t, ld_ec, static_cast<hipStream_t>(stream),
                                        q_row, ld_row, e_row, ld_er));
     return FP8_OK;
 }

@@ -28,6 +28,8 @@ hipError_t launch_block_quant(const void* x, int64_t rows, int64_t cols, int64_t
                               int64_t ld_q, uint8_t* e8m0, int64_t ld_e, hipStream_t st);
 // the same of the transposed matrix, written transposed (rows % 128 == 0, cols % 8 == 0)
 // q_row / e_row (optional, block_rows == 1, cols % 128 == 0): the tiles along the rows of x from the same read
+// FMT_ALONE, or'ed into fmt with q_row given: the codes are the call's result, no product of the same call reads them
+constexpr int FMT_ALONE = 256;
 hipError_t launch_block_quant_t(const void* x, int64_t rows, int64_t cols, int64_t ld, int block_rows, int fmt, uint8_t* qt,
                                 int64_t ld_t, uint8_t* et, int64_t ld_e, hipStream_t st, uint8_t* q_row = nullptr,
                                 int64_t ld_row = 0, uint8_t* e_row = nullptr, int64_t ld_er = 0);
@@ -192,6 +194,7 @@ hipError_t launch_mx_quant(const void* x, int64_t rows, int64_t cols, int64_t ld
 // blocks of 32 down the columns of x (rows % 32 == 0), output transposed: qt [cols, rows], et [cols, rows / 32];
 // with q_row != nullptr also the blocks along the rows (cols % 32 == 0) from the same read: q_row [rows, cols],
 // e_row [rows, cols / 32] (ld_er % 4 == 0)
+// (FMT_ALONE as above)
 hipError_t launch_mx_quant_t(const void* x, int64_t rows, int64_t cols, int64_t ld, int fmt, uint8_t* qt, int64_t ld_t,
                              uint8_t* et, int64_t ld_e, uint8_t* q_row, int64_t ld_row, uint8_t* e_row, int64_t ld_er,
                              hipStream_t st);

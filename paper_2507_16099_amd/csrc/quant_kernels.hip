@@ -1610,6 +1610,13 @@ hipError_t launch_block_quant(const void* x, int64_t rows, int64_t cols, int64_t
     return hipGetLastError();
 }
 
+// How the one-pass quantizers into both orientations store their codes, two bytes an element: through the L2, except where
+// the call is a quantization alone (FMT_ALONE) and the codes are half as much again as the last-level cache holds.  There the
+// hint is mostly faster (us, hint / through: 180 Mi elements 172 / 171, 192 Mi 181 / 183, 224 Mi 200 / 213 - 8192 x 28672 210 / 204 -,
+// 256 Mi 222 / 240; below, 112 Mi 105 / 91), but the products behind it lose more (MX steps of 16384 x 2048 x 16384 1530 / 1516,
+// 32768 x 2048 x 8192 1552 / 1531).
+static bool keep_both_codes(int fmt, int64_t rows, int64_t cols) { return !(fmt & FMT_ALONE) || rows * cols <= (int64_t)192 << 20; }
+
 // MX block quantization with the blocks running DOWN the columns of x and the
 // output written transposed: qt [cols, rows] codes and et [cols, rows / 32] E8M0
 // bytes, i.e. the K-contiguous operand of a product that contracts over the
@@ -1622,8 +1629,8 @@ hipError_t launch_block_quant(const void* x, int64_t rows, int64_t cols, int64_t
 // (q_row [rows, cols], e_row [rows, cols / 32]; cols % 32 == 0): the four threads that hold 32
 // consecutive elements of a row combine their maxima with two cross-lane steps.  A tensor that is
 // needed in both orientations (the gradient in the backward) then costs 4 bytes per element
-// instead of 6.
-template <int FMT, bool ROWS_TOO>
+// instead of 6.  2: the same, codes stored with the streaming hint.
+template <int FMT, int ROWS_TOO>
 __global__ __launch_bounds__(256) void mx_quant_t_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t cols,
                                                           int64_t ld, uint8_t* __restrict__ qt, int64_t ld_t,
                                                           uint8_t* __restrict__ et, int64_t ld_e,
@@ -1675,7 +1682,7 @@ __global__ __launch_bounds__(256) void mx_quant_t_kernel(const uint16_t* __restr
             }
             const float f = __uint_as_float((uint32_t)(254 - byte) << 23);
             const int64_t r = r0 + ty * 8 + j;
-            if (r < rows && c < cols) store_vec(q_row + r * ld_row + c, cast8<FMT>(v[j], f));
+            if (r < rows && c < cols) store_vec(q_row + r * ld_row + c, cast8<FMT>(v[j], f), ROWS_TOO != 2);
             if ((tx & 3) == 0) rbytes[(ty * 8 + j) * 4 + (tx >> 2)] = (uint8_t)byte;
         }
     }
@@ -1739,7 +1746,7 @@ __global__ __launch_bounds__(256) void mx_quant_t_kernel(const uint16_t* __restr
         const int cc = it * ROWS_PER_IT + (threadIdx.x / PARTS), p = threadIdx.x % PARTS;
         const int64_t oc = c0 + cc, orow = r0 + p * 16;
         if (oc >= cols || orow >= rows) continue;      // rows % 32 == 0: a 16-byte piece is inside or outside
-        store_vec(qt + oc * ld_t + orow, tile16[cc * PARTS + (p ^ ((cc >> 3) & 7))]);
+        store_vec(qt + oc * ld_t + orow, tile16[cc * PARTS + (p ^ ((cc >> 3) & 7))], ROWS_TOO != 2);
     }
     if (threadIdx.x < 128 && c0 + threadIdx.x < cols) {
         uint8_t* dst = et + e8_off(c0 + threadIdx.x, r0 / 32, ld_e);
@@ -1775,8 +1782,8 @@ __global__ __launch_bounds__(256) void mx_quant_t_kernel(const uint16_t* __restr
 // ROWS_TOO (with SQUARE = false, cols % 128 == 0): the same read also yields the tiles of 1 x 128 ALONG the rows
 // of x (q_row [rows, cols], e_row [rows, cols / 32]): the 16 threads that hold a row of the tile combine their
 // maxima with four cross-lane steps.  The gradient, needed in both orientations by the backward, then costs
-// 4 bytes of HBM traffic per element instead of 6.
-template <int FMT, bool SQUARE, bool ROWS_TOO = false>
+// 4 bytes of HBM traffic per element instead of 6.  2: the same, codes stored with the streaming hint.
+template <int FMT, bool SQUARE, int ROWS_TOO = 0>
 __global__ __launch_bounds__(256) void block_quant_t_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t cols,
                                                              int64_t ld, uint8_t* __restrict__ qt, int64_t ld_t,
                                                              uint8_t* __restrict__ et, int64_t ld_e, int nx, int ny,
@@ -1813,7 +1820,7 @@ __global__ __launch_bounds__(256) void block_quant_t_kernel(const uint16_t* __re
             uint32_t byte;
             const float sr = pow2_block_scale<FMT>(mr, byte);
             const int64_t r = r0 + ty * 8 + j;
-            store_vec(q_row + r * ld_row + c, cast8<FMT>(v[j], sr));                   // cols % 128 == 0: inside
+            store_vec(q_row + r * ld_row + c, cast8<FMT>(v[j], sr), ROWS_TOO != 2);                   // cols % 128 == 0: inside
             if (tx == 0) *reinterpret_cast<uint32_t*>(e_row + e8_off(r, c0 >> 5, ld_er)) = byte * 0x01010101u;
         }
     }
@@ -1881,7 +1888,7 @@ __global__ __launch_bounds__(256) void block_quant_t_kernel(const uint16_t* __re
         const int cc = it * ROWS_PER_IT + (threadIdx.x / PARTS), p = threadIdx.x % PARTS;
         const int64_t oc = c0 + cc;
         if (oc >= cols) continue;
-        store_vec(qt + oc * ld_t + r0 + p * 16, tile16[cc * PARTS + (p ^ ((cc >> 3) & 7))]);
+        store_vec(qt + oc * ld_t + r0 + p * 16, tile16[cc * PARTS + (p ^ ((cc >> 3) & 7))], ROWS_TOO != 2);
     }
     if (threadIdx.x < 128 && c0 + threadIdx.x < cols)                 // ld_e % 4 == 0 and (r0 / 32) % 4 == 0
         *reinterpret_cast<uint32_t*>(et + e8_off(c0 + threadIdx.x, r0 / 32, ld_e)) = (uint32_t)ebytes[threadIdx.x] * 0x01010101u;
@@ -1900,9 +1907,11 @@ hipError_t launch_block_quant_t(const void* x, int64_t rows, int64_t cols, int64
 #define FP8K_BQT(FMT, SQ, RT) block_quant_t_kernel<FMT, SQ, RT><<<dim3((unsigned)total), dim3(256), 0, st>>>(xp, rows, cols, ld, qt, ld_t, et, ld_e, (int)gy, (int)gx, q_row, ld_row, e_row, ld_er)
     if (q_row != nullptr) {
         if (block_rows != 1 || cols % 128 != 0) return hipErrorInvalidValue;
-        if (fmt == FMT_E4M3FN) FP8K_BQT(FMT_E4M3FN, false, true); else FP8K_BQT(FMT_E5M2, false, true);
-    } else if (fmt == FMT_E4M3FN) { if (block_rows == 128) FP8K_BQT(FMT_E4M3FN, true, false); else FP8K_BQT(FMT_E4M3FN, false, false); }
-    else { if (block_rows == 128) FP8K_BQT(FMT_E5M2, true, false); else FP8K_BQT(FMT_E5M2, false, false); }
+        const bool keep = keep_both_codes(fmt, rows, cols);
+        if ((fmt & ~FMT_ALONE) == FMT_E4M3FN) { if (keep) FP8K_BQT(FMT_E4M3FN, false, 1); else FP8K_BQT(FMT_E4M3FN, false, 2); }
+        else { if (keep) FP8K_BQT(FMT_E5M2, false, 1); else FP8K_BQT(FMT_E5M2, false, 2); }
+    } else if (fmt == FMT_E4M3FN) { if (block_rows == 128) FP8K_BQT(FMT_E4M3FN, true, 0); else FP8K_BQT(FMT_E4M3FN, false, 0); }
+    else { if (block_rows == 128) FP8K_BQT(FMT_E5M2, true, 0); else FP8K_BQT(FMT_E5M2, false, 0); }
 #undef FP8K_BQT
     return hipGetLastError();
 }
@@ -1916,8 +1925,9 @@ hipError_t launch_mx_quant_t(const void* x, int64_t rows, int64_t cols, int64_t 
     if (total > 0x7FFFFFFF) return hipErrorInvalidValue;
     const uint16_t* xp = static_cast<const uint16_t*>(x);
 #define FP8K_MXT(FMT, R) mx_quant_t_kernel<FMT, R><<<dim3((unsigned)total), dim3(256), 0, st>>>(xp, rows, cols, ld, qt, ld_t, et, ld_e, q_row, ld_row, e_row, ld_er, (int)gy, (int)gx)
-    if (fmt == FMT_E4M3FN) { if (q_row) FP8K_MXT(FMT_E4M3FN, true); else FP8K_MXT(FMT_E4M3FN, false); }
-    else { if (q_row) FP8K_MXT(FMT_E5M2, true); else FP8K_MXT(FMT_E5M2, false); }
+    const bool keep = keep_both_codes(fmt, rows, cols);
+    if ((fmt & ~FMT_ALONE) == FMT_E4M3FN) { if (!q_row) FP8K_MXT(FMT_E4M3FN, 0); else if (keep) FP8K_MXT(FMT_E4M3FN, 1); else FP8K_MXT(FMT_E4M3FN, 2); }
+    else { if (!q_row) FP8K_MXT(FMT_E5M2, 0); else if (keep) FP8K_MXT(FMT_E5M2, 1); else FP8K_MXT(FMT_E5M2, 2); }
 #undef FP8K_MXT
     return hipGetLastError();
 }

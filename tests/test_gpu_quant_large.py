@@ -54,3 +54,16 @@ def test_ragged_step_in_a_workspace_of_nan_codes(recipe):
     with knobs(PAIRS=0):
         single = run()
     assert all(torch.equal(a, b) for a, b in zip(shared, single))
+
+
+@pytest.mark.parametrize("rows,cols", [(12288, 16384), (12416, 16384)])
+@pytest.mark.parametrize("scheme", ["mx", "block"])
+def test_block_codes_of_both_orientations_equal_the_single_ones(rows, cols, scheme):
+    """192 Mi elements, and a tile row more: the other kind of store."""
+    x = _tensor(rows, cols)
+    both = getattr(fp8, f"fp8_{scheme}_quantize_row_col")(x, fp8.FP8_E4M3FN)
+    args = () if scheme == "mx" else (1,)
+    row = getattr(fp8, f"fp8_{scheme}_quantize")(x, *args, fp8.FP8_E4M3FN)
+    col = getattr(fp8, f"fp8_{scheme}_quantize_t")(x, *args, fp8.FP8_E4M3FN)
+    for a, b in zip(both, (*row, *col)):
+        assert torch.equal(a, b)

@@ -55,11 +55,11 @@ __device__ __forceinline__ void store_nt(void* p, const T& v) {
     if constexpr (sizeof(T) == 16) __builtin_nontemporal_store(v4u_t{v.x, v.y, v.z, v.w}, static_cast<v4u_t*>(p));
     else __builtin_nontemporal_store(v2u_t{v.x, v.y}, static_cast<v2u_t*>(p));
 }
-// (assembly: no builtin stores 128 bits at system scope.  The s_nop is the wait state between a 128-bit store and a write to
-// its data registers, which the compiler does not insert for assembly.)
+// (assembly: no builtin stores 128 bits at system scope.  The s_nop is the two wait states between a 128-bit store and a write
+// to its data registers, which the compiler does not insert for assembly; tests/test_isa_hazards.py checks the built code.)
 template <typename T>
 __device__ __forceinline__ void store_through(void* p, const T& v) {
-    if constexpr (sizeof(T) == 16) asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 0" ::"v"(p), "v"(v4u_t{v.x, v.y, v.z, v.w}) : "memory");
+    if constexpr (sizeof(T) == 16) asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" ::"v"(p), "v"(v4u_t{v.x, v.y, v.z, v.w}) : "memory");
     else __hip_atomic_store(static_cast<uint64_t*>(p), (uint64_t)v.y << 32 | v.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 template <typename T>

@@ -5,6 +5,8 @@ cannot make across inline assembly:
     later at the earliest; a result is touched by anything else 12 wait states after the instruction at the earliest
     (v_mfma_f32_16x16x128_f8f6f4; 8 for v_mfma_f32_16x16x32_bf16).  These are the distances the compiler keeps for the
     builtins.  A matrix instruction that follows another one is taken to wait until the unit is free (8 / 4 wait states).
+  * stores of more than 64 bits: the vector ALU writes a register of their data two wait states later at the earliest (buffer
+    stores with a scalar register as offset need none).
   * loads into registers: no instruction touches the destination before an s_waitcnt vmcnt that covers the load.
 
 Both run over the control-flow graph of every kernel, worst case over all paths."""
@@ -49,12 +51,12 @@ def _regs(text: str) -> list:
 
 
 class _Ins:
-    __slots__ = ("kind", "defs", "uses", "n", "addr", "text")
+    __slots__ = ("kind", "defs", "uses", "n", "addr", "text", "data")
 
 
 def _decode(addr: int, op: str, args: str) -> _Ins:
     i = _Ins()
-    i.addr, i.text, i.kind, i.defs, i.uses, i.n = addr, f"{op} {args}", "other", (), (), 1
+    i.addr, i.text, i.kind, i.defs, i.uses, i.n, i.data = addr, f"{op} {args}", "other", (), (), 1, ()
     if op == "s_nop":
         i.kind, i.n = "nop", int(args, 0) + 1
     elif op == "s_waitcnt":
@@ -69,6 +71,11 @@ def _decode(addr: int, op: str, args: str) -> _Ins:
             i.kind, i.defs, i.uses = "load", _regs(dst), _regs(rest)
         elif "atomic" in op or "store" in op or "load" in op:
             i.kind, i.uses = "vmem", _regs(args)
+            if re.search(r"_store_(dwordx[34]|format_xyzw?)$", op):
+                part = args.split(",")
+                buffer = op.startswith("buffer_")
+                if not (buffer and re.match(r"\s*(s\d+|m0)\b", part[3] if len(part) > 3 else part[2])):
+                    i.data = _regs(part[0 if buffer else 1])
     elif op.startswith("ds_"):
         regs = args.split(",", 1)
         if "read" in op or "rtn" in op or "permute" in op:
@@ -108,14 +115,20 @@ def check_kernel(code: list) -> list:
 
     def flow(s, state):
         # written: register -> wait states a reading matrix instruction still needs; result: register -> wait states until it
-        # may be touched; unit: until the matrix unit is free; flight: register -> vector-memory operations issued since its load
-        written, result, unit, flight = dict(state[0]), dict(state[1]), state[2], dict(state[3])
+        # may be touched; stored: register -> wait states until the vector ALU may write it; unit: until the matrix unit is
+        # free; flight: register -> vector-memory operations issued since its load
+        written, result, stored, unit, flight = dict(state[0]), dict(state[1]), dict(state[2]), state[3], dict(state[4])
         for k in range(s, end_of[s]):
             x = ins[k]
             cost = x.n if x.kind == "nop" else 1
             if x.kind == "mfma" and unit > 0:
                 written = {r: w - unit for r, w in written.items() if w > unit}
                 result = {r: w - unit for r, w in result.items() if w > unit}
+                stored = {r: w - unit for r, w in stored.items() if w > unit}
+            if stored and x.kind == "valu":
+                for r in x.defs:
+                    if r in stored:
+                        bad[x.addr] = f"{x.addr:#x} {x.text}: writes the data of a store {stored[r]} wait states too early"
             if flight and (x.defs or x.uses):
                 for r in x.uses if x.kind == "load" else (*x.defs, *x.uses):     # (loads return in order)
                     if r in flight:
@@ -136,6 +149,10 @@ def check_kernel(code: list) -> list:
                 written = {r: w - cost for r, w in written.items() if w > cost}
             if result:
                 result = {r: w - cost for r, w in result.items() if w > cost}
+            if stored:
+                stored = {r: w - cost for r, w in stored.items() if w > cost}
+            for r in x.data:
+                stored[r] = 2
             unit = max(unit - cost, 0) if x.kind != "mfma" else x.n - 1
             if x.kind == "valu":
                 for r in x.defs:
@@ -150,23 +167,23 @@ def check_kernel(code: list) -> list:
                     flight[r] = 0
             elif x.kind == "wait" and flight:
                 flight = {r: y for r, y in flight.items() if y < x.n}
-        return written, result, unit, flight
+        return written, result, stored, unit, flight
 
     def merge(a, b):
         if a is None:
             return b
         out = []
-        for n in (0, 1):
+        for n in (0, 1, 2):
             m = dict(a[n])
             for r, w in b[n].items():
                 m[r] = max(m.get(r, 0), w)
             out.append(m)
-        f = dict(a[3])
-        for r, y in b[3].items():
+        f = dict(a[4])
+        for r, y in b[4].items():
             f[r] = min(f.get(r, 99), y)
-        return out[0], out[1], min(a[2], b[2]), f
+        return *out, min(a[3], b[3]), f
 
-    state = {0: ({}, {}, 0, {})}
+    state = {0: ({}, {}, {}, 0, {})}
     work = [0]
     while work:
         s = work.pop()

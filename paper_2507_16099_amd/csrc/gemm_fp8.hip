@@ -237,16 +237,19 @@ static hipError_t launch_tn(const GemmOperands& g, int row_a, int row_b, hipStre
 
 // ---- kernel choice.  Up to 32 rows: the few-row kernel of gemm_fp8_skinny.hip (it streams B once), and up to 64 rows where
 // there are too few 64 x 64 tiles for the CUs, N <= 8192, and the contraction is long enough for its wavefronts to share
-// (us, few-row / ring: 48 x 1024 x 4096 8.1 / 11.6, 64 x 4096 x 14336 23.6 / 35.0, 64 x 8192 x 4096 13.8 / 14.9;
-// 64 x 8192 x 1024 5.9 / 5.4, 64 x 11008 x 4096 23.4 / 16.4).  These lines lie between 48 and 64 rows measured; that up to 32
-// rows always take the few-row kernel is not the best everywhere (32 x 28672 x 8192 51.6 / 47.8).
+// (us, few-row / best ring tile, N x K at 33, 40, 48, 64 rows, weights from HBM: 4096 x 4096 7.8 / 11.2, 8.0 / 11.5,
+// 8.5 / 12.0, 9.5 / 12.8; 8192 x 4096 11.1 / 12.1, 11.5 / 12.4, 11.9 / 12.9, 13.0 / 13.9; 4096 x 14336 18.3 / 30.3 .. 23.6 / 36.9; 4096 x
+// 2048 4.9 / 6.1 .. 5.8 / 6.3.  Beyond the lines: 11008 x 4096 18.8 / 13.1 .. 22.3 / 14.8, 14336 x 4096 20.4 / 15.3 .. 23.6 / 16.0,
+// 28672 x 8192 60.7 / 50.1 .. 71.8 / 52.1, 8192 x 1024 6.1 / 5.1 .. 6.8 / 5.2.  On them it is close: 8192 x 2048 7.8 / 7.8 .. 9.2 / 8.7,
+// 4096 x 1024 4.7 / 4.9 .. 5.3 / 5.1.)  That up to 32 rows always take the few-row kernel is not the best everywhere (32 rows: 4096 x 4096
+// 7.2 / 11.2, 8192 x 4096 10.2 / 12.0, but 11008 x 4096 15.1 / 13.1, 28672 x 4096 29.4 / 26.5, 28672 x 8192 52.1 / 49.9).
 // More than one round of 256 x 256 tiles (one per CU): the large-product kernels of gemm_fp8_snake.hip /
 // gemm_fp8_stream.hip.  In between the cheapest of the ring kernel's tiles (gemm_fp8_ring.hip) and one round of
 // 256 x 256 tiles by this estimate, in us (one launch; rounds of 256 workgroups, K steps of 128 bytes):
 //     3 + rounds * (a + steps * b);  256 x 256 tiles: 10 + 1.2 * steps, at most half of the CUs busy (half tiles) 7.2 + 0.91 * steps.
-// a: prologue and epilogue of a tile; b: a K step with every CU busy, bound by the LDS of a CU (128 bytes per cycle,
-// reads of the fragments and writes of the LDS-DMA loads together: 384 / 576 / 768 / 1152 cycles for the tiles below,
-// whose matrix instructions take 128 / 256 / 512 / 1024) and, from 128 x 256 on, by the power limit.
+// a: prologue and epilogue of a tile; b: a K step with every CU busy (some 460 / 670 / 970 / 1600 cycles for the tiles below; their
+// matrix instructions take 128 / 256 / 512 / 1024, the fragment reads and LDS-DMA writes at 128 bytes a cycle 384 / 576 / 768 / 1152).
+// No unit is full: 128 x 128 tiles at 777 x 4096 x 14336 keep the matrix units busy 42 % of the time and the LDS's reads 22 %.
 // Measured (a HIP graph of twelve, operands alternating; us; K = 1024 / 4096 / 16384):
 //                        64x64              128x64             128x128            128x256            before (other kernels)
 //     1024 x 1024     6.0 / 10.5 / 29     7.4 / 13.2 / 36     8.3 / 16.0 / 46    11.3 / 23.9 / 73      7.8 / 14.8 / 45

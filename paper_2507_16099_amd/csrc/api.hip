@@ -420,9 +420,11 @@ int fp8_linear_fwd(const void* x, const void* w, int64_t M, int64_t K, int64_t N
         }
         float *sx = reinterpret_cast<float*>(wsf + p.sx), *sw = reinterpret_cast<float*>(wsf + p.sw);
         bool done = false;
-        if (!(recipe->flags & FP8_GRAD_WEIGHT_HP) && recipe->fmt_x == recipe->fmt_w) {
-            // X and W the same way: twin launches, three (small tensors: two) instead of six
-            const fp8k::RowColOperand ox{x, M, K, wsf + p.xq, ld.k, sx, wsb + b.xt, ld.m, sxt, wsf + p.fold_x};
+        if (recipe->fmt_x == recipe->fmt_w) {
+            // X and W the same way: one launch, or twin launches, three (small tensors: two) instead of six.  (dW from the
+            // bfloat16 X: no fp8 copy of X to keep)
+            uint8_t* xt = recipe->flags & FP8_GRAD_WEIGHT_HP ? nullptr : wsb + b.xt;
+            const fp8k::RowColOperand ox{x, M, K, wsf + p.xq, ld.k, sx, xt, ld.m, sxt, wsf + p.fold_x};
             const fp8k::RowColOperand ow{w, N, K, wsf + p.wq, ld.k, sw, wsb + b.wt, ld.n, swt, wsf + p.fold_w};
             const hipError_t e = fp8k::launch_quant_row_col_pair(ox, &ow, K, recipe->fmt_x, fl, st);
             if (e == hipSuccess) done = true;
@@ -533,12 +535,13 @@ int fp8_linear_bwd(const void* dy, const void* x, const void* w, int64_t M, int6
     // (dX = dY W contracts over N, dW = dY^T X over M).  All quantizations first,
     // then the GEMMs back to back.
     const bool both = dx && dw;
-    if (both && !saved && recipe->fmt_w == recipe->fmt_x) {
-        // all three tensors in five launches: dY's rowwise pass (which also gathers its column maxima), the column
+    if (!saved && (!both || recipe->fmt_w == recipe->fmt_x)) {
+        // all three tensors in one launch, or in five: dY's rowwise pass (which also gathers its column maxima), the column
         // maxima of W and X together, one launch for every column scale, two for the transposing casts
-        const fp8k::RowColOperand og{dy, M, N, gq, ld.n, sg, gqt, ld.m, sgt, ws + p.fold_g};
-        const fp8k::ColOperand ow{w, N, K, wt, ld.n, swt, ws + p.fold_w}, ox{x, M, K, xt, ld.m, sxt, ws + p.fold_x};
-        const hipError_t e = fp8k::launch_quant_bwd_rowwise(og, N, recipe->fmt_dy, ow, ox, K, recipe->fmt_w, fl, st);
+        // (only one gradient wanted: its operands in one launch, or one by one below)
+        const fp8k::RowColOperand og{dy, M, N, dx ? gq : nullptr, ld.n, sg, dw ? gqt : nullptr, ld.m, sgt, ws + p.fold_g};
+        const fp8k::ColOperand ow{dx ? w : nullptr, N, K, wt, ld.n, swt, ws + p.fold_w}, ox{dw ? x : nullptr, M, K, xt, ld.m, sxt, ws + p.fold_x};
+        const hipError_t e = fp8k::launch_quant_bwd_rowwise(og, N, recipe->fmt_dy, ow, ox, K, dx ? recipe->fmt_w : recipe->fmt_x, fl, st);
         if (e == hipSuccess) return grad_gemms(recipe, 1, gq, sg, wt, swt, gqt, sgt, xt, sxt, M, Mp, K, N, ld, dx, dw, st);
         if (e != hipErrorNotSupported) return hip_fail(e, "quant_bwd_rowwise");
     }

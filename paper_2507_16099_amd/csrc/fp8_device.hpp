@@ -203,6 +203,18 @@ __device__ __forceinline__ uint2 cast8(const uint4& v, float s) {
     return r;
 }
 
+// 4x4 byte transpose: rows a,b,c,d (byte j = column j) -> o[j] = column j
+__device__ __forceinline__ void transpose4x4_bytes(uint32_t a, uint32_t b, uint32_t c, uint32_t d, uint32_t (&o)[4]) {
+    const uint32_t t0 = __builtin_amdgcn_perm(b, a, 0x05010400u);
+    const uint32_t t1 = __builtin_amdgcn_perm(b, a, 0x07030602u);
+    const uint32_t u0 = __builtin_amdgcn_perm(d, c, 0x05010400u);
+    const uint32_t u1 = __builtin_amdgcn_perm(d, c, 0x07030602u);
+    o[0] = __builtin_amdgcn_perm(u0, t0, 0x05040100u);
+    o[1] = __builtin_amdgcn_perm(u0, t0, 0x07060302u);
+    o[2] = __builtin_amdgcn_perm(u1, t1, 0x05040100u);
+    o[3] = __builtin_amdgcn_perm(u1, t1, 0x07060302u);
+}
+
 // Gradient through a sigmoid whose output y is stored in bfloat16: dz = dy * y * (1 - y), evaluated in
 // binary32 one operation at a time, left to right (no contraction), rounded to bfloat16; 8 elements.
 __device__ __forceinline__ uint32_t sigmoid_bwd_bf16_bits(float g, float y) {

@@ -116,13 +116,25 @@ struct ColOperand {         // a tensor [rows, cols] quantized per column, trans
 hipError_t launch_quant_row_pair(const void* x1, int64_t rows1, int64_t ld1, uint8_t* q1, int64_t ld_q1, float* s1, const void* x2,
                                  int64_t rows2, int64_t ld2, uint8_t* q2, int64_t ld_q2, float* s2, int64_t cols, int fmt,
                                  int flags, hipStream_t st);
-// one tensor (b == nullptr) or two of the same width and format along both axes: three launches, two with folding
+// one tensor (b == nullptr) or two of the same width and format along both axes: one launch (strips), else three, two with folding.
+// q_col_t nullptr: that tensor per row only (strips or hipErrorNotSupported)
 hipError_t launch_quant_row_col_pair(const RowColOperand& a, const RowColOperand* b, int64_t cols, int fmt, int flags, hipStream_t st);
-// two tensors of the same width and format per column, transposed: three launches (instead of six)
+// two tensors of the same width and format per column, transposed: one launch, or three (instead of six)
 hipError_t launch_quant_col_t_pair(const ColOperand& a, const ColOperand& b, int64_t cols, int fmt, int flags, hipStream_t st);
-// the backward of the rowwise recipe: the gradient g along both axes, W and X per column: five launches (instead of nine), four with folding
+// the backward of the rowwise recipe: the gradient g along both axes, W and X per column: one launch (strips), else five (instead of
+// nine), four with folding.  Without g.q_row, g.q_col_t, w.x or x.x (nullptr) what is left: strips or hipErrorNotSupported
 hipError_t launch_quant_bwd_rowwise(const RowColOperand& g, int64_t cols_g, int fmt_g, const ColOperand& w, const ColOperand& x,
                                     int64_t cols_wx, int fmt_wx, int flags, hipStream_t st);
+
+// several tensors in one launch, each per row, per column (transposed), or both; q_row / q_col_t nullptr: not wanted.
+// Output rows of q_col_t are padded to 16 bytes at least, the padding belongs to the call (zero codes up to the next 16).
+// hipErrorNotSupported (nothing launched) where a tensor does not suit.
+struct StripOperand {
+    const void* x; int64_t rows, cols, ld; int fmt;
+    uint8_t* q_row; int64_t ld_row; float* scale_row;
+    uint8_t* q_col_t; int64_t ld_col_t; float* scale_col;
+};
+hipError_t launch_quant_strips(const StripOperand* ops, int n, int flags, hipStream_t st);
 
 // 256 x 256 kernel on 16x16x128 MFMAs with LDS-DMA loads and the four-phase "snake" schedule; same contract.
 // _fits: its 32-bit buffer offsets reach (leading dimensions below 2^23)

@@ -475,18 +475,6 @@ __global__ __launch_bounds__(256) void cast_kernel(const uint16_t* __restrict__ 
     }
 }
 
-// 4x4 byte transpose: rows a,b,c,d (byte j = column j) -> o[j] = column j
-__device__ __forceinline__ void transpose4x4_bytes(uint32_t a, uint32_t b, uint32_t c, uint32_t d, uint32_t (&o)[4]) {
-    const uint32_t t0 = __builtin_amdgcn_perm(b, a, 0x05010400u);
-    const uint32_t t1 = __builtin_amdgcn_perm(b, a, 0x07030602u);
-    const uint32_t u0 = __builtin_amdgcn_perm(d, c, 0x05010400u);
-    const uint32_t u1 = __builtin_amdgcn_perm(d, c, 0x07030602u);
-    o[0] = __builtin_amdgcn_perm(u0, t0, 0x05040100u);
-    o[1] = __builtin_amdgcn_perm(u0, t0, 0x07060302u);
-    o[2] = __builtin_amdgcn_perm(u1, t1, 0x05040100u);
-    o[3] = __builtin_amdgcn_perm(u1, t1, 0x07060302u);
-}
-
 // Transposing cast.  A block converts a TR x 128 tile (TR = 128 or 256 input
 // rows): each thread loads 8 x 8 sub-blocks (eight 128-bit loads each),
 // converts them, transposes the bytes in registers and parks eight 64-bit
@@ -1238,6 +1226,12 @@ hipError_t row_colmax_first_level(const RowColOperand& a, const Partials& pa, co
 #undef FP8K_RCF
 }
 
+StripOperand strips_of(const RowColOperand& o, int64_t cols, int fmt) {
+    return StripOperand{o.x, o.rows, cols, o.ld, fmt, o.q_row, o.ld_row, o.scale_row, o.q_col_t, o.ld_col_t, o.scale_col};
+}
+StripOperand strips_of(const ColOperand& o, int64_t cols, int fmt) {
+    return StripOperand{o.x, o.rows, cols, o.ld, fmt, nullptr, 0, nullptr, o.q_col_t, o.ld_col_t, o.scale_col};
+}
 ColOperand col_part(const RowColOperand& o) { return ColOperand{o.x, o.rows, o.ld, o.q_col_t, o.ld_col_t, o.scale_col, o.fold}; }
 Partials partials_of(const RowColOperand& o, int64_t cols) { return partials_of(o.fold, o.rows, cols, o.q_col_t, o.ld_col_t); }
 Partials partials_of(const ColOperand& o, int64_t cols) { return partials_of(o.fold, o.rows, cols, o.q_col_t, o.ld_col_t); }
@@ -1278,6 +1272,9 @@ hipError_t launch_quant_row_col_pair(const RowColOperand& a, const RowColOperand
                                      hipStream_t st) {
     if (b && knob(KNOB_PAIRS) == 0) return hipErrorNotSupported;
     if (a.rows == 0 || (b && b->rows == 0) || cols == 0) return hipErrorNotSupported;
+    const StripOperand strips[2] = {strips_of(a, cols, fmt), b ? strips_of(*b, cols, fmt) : StripOperand{}};
+    if (const hipError_t e = launch_quant_strips(strips, b ? 2 : 1, flags, st); e != hipErrorNotSupported) return e;
+    if (!a.q_col_t || (b && !b->q_col_t)) return hipErrorNotSupported;
     const Partials pa = partials_of(a, cols), pb = b ? partials_of(*b, cols) : Partials{nullptr, 0, false};
     int64_t Ga = 0, Gb = 0;
     hipError_t e = row_colmax_first_level(a, pa, b, pb, cols, fmt, flags, &Ga, &Gb, st);
@@ -1295,6 +1292,8 @@ hipError_t launch_quant_row_col_pair(const RowColOperand& a, const RowColOperand
 hipError_t launch_quant_col_t_pair(const ColOperand& a, const ColOperand& b, int64_t cols, int fmt, int flags, hipStream_t st) {
     if (knob(KNOB_PAIRS) == 0) return hipErrorNotSupported;
     if (a.rows == 0 || b.rows == 0 || cols == 0) return hipErrorNotSupported;
+    const StripOperand strips[2] = {strips_of(a, cols, fmt), strips_of(b, cols, fmt)};
+    if (const hipError_t e = launch_quant_strips(strips, 2, flags, st); e != hipErrorNotSupported) return e;
     const Partials pa = partials_of(a, cols), pb = partials_of(b, cols);
     const int64_t Ga = colmax_partial_blocks(a.rows, cols, pa.room), Gb = colmax_partial_blocks(b.rows, cols, pb.room);
     if (Ga == 0 || Gb == 0) return hipErrorNotSupported;
@@ -1314,6 +1313,12 @@ hipError_t launch_quant_bwd_rowwise(const RowColOperand& g, int64_t cols_g, int 
                                     int64_t cols_wx, int fmt_wx, int flags, hipStream_t st) {
     if (knob(KNOB_PAIRS) == 0) return hipErrorNotSupported;
     if (g.rows == 0 || w.rows == 0 || x.rows == 0 || cols_g == 0 || cols_wx == 0) return hipErrorNotSupported;
+    StripOperand strips[3] = {strips_of(g, cols_g, fmt_g)};
+    int ns = 1;
+    if (w.x) strips[ns++] = strips_of(w, cols_wx, fmt_wx);
+    if (x.x) strips[ns++] = strips_of(x, cols_wx, fmt_wx);
+    if (const hipError_t e = launch_quant_strips(strips, ns, flags, st); e != hipErrorNotSupported) return e;
+    if (!g.q_row || !g.q_col_t || !w.x || !x.x) return hipErrorNotSupported;
     // everything is checked before the first launch, so that "not suited" leaves nothing half done
     const Partials pg = partials_of(g, cols_g), pw = partials_of(w, cols_wx), px = partials_of(x, cols_wx);
     const int64_t Gw = colmax_partial_blocks(w.rows, cols_wx, pw.room), Gx = colmax_partial_blocks(x.rows, cols_wx, px.room);

@@ -25,6 +25,7 @@ enum Knob {
     KNOB_PAIRS,             // 0 = no shared launches: every tensor of a linear step quantized, every product launched, by itself
     KNOB_DECODE_FUSED,      // few tokens against a quantized weight: 0 = activation quantization always a launch of its own, 2 = inside the product wherever that kernel applies
     KNOB_GEMM_RING,         // small and middling products: 0 = never the ring kernel, 1 + tile = always that tile of it
+    KNOB_STRIPS,            // rowwise steps: 0 = never column strips, 2 / 4 = wherever they fit, 16 / 32 columns wide
     KNOB_COUNT
 };
 

@@ -235,14 +235,16 @@ static hipError_t launch_tn(const GemmOperands& g, int row_a, int row_b, hipStre
     return hipGetLastError();
 }
 
-// ---- kernel choice.  Up to 32 rows: the few-row kernel of gemm_fp8_skinny.hip (it streams B once), and up to 64 rows where
+// ---- kernel choice.  Up to 16 rows: the few-row kernel of gemm_fp8_skinny.hip (it streams B once).  17 to 32 rows: the same where
+// there are 64 x 64 ring tiles for less than five eighths of the CUs, else those tiles (us, few-row / ring at 32 rows, weights from HBM:
+// 4096 x 4096 7.1 / 11.2, 8192 x 4096 10.2 / 12.0; 11008 x 4096 15.1 / 13.4, 14336 x 4096 16.2 / 15.3; with the streaming hint 28672 x 4096
+// 27.5 / 26.6, 28672 x 8192 47.3 / 43.6).  Up to 64 rows the few-row kernel where
 // there are too few 64 x 64 tiles for the CUs, N <= 8192, and the contraction is long enough for its wavefronts to share
 // (us, few-row / best ring tile, N x K at 33, 40, 48, 64 rows, weights from HBM: 4096 x 4096 7.8 / 11.2, 8.0 / 11.5,
 // 8.5 / 12.0, 9.5 / 12.8; 8192 x 4096 11.1 / 12.1, 11.5 / 12.4, 11.9 / 12.9, 13.0 / 13.9; 4096 x 14336 18.3 / 30.3 .. 23.6 / 36.9; 4096 x
 // 2048 4.9 / 6.1 .. 5.8 / 6.3.  Beyond the lines: 11008 x 4096 18.8 / 13.1 .. 22.3 / 14.8, 14336 x 4096 20.4 / 15.3 .. 23.6 / 16.0,
 // 28672 x 8192 60.7 / 50.1 .. 71.8 / 52.1, 8192 x 1024 6.1 / 5.1 .. 6.8 / 5.2.  On them it is close: 8192 x 2048 7.8 / 7.8 .. 9.2 / 8.7,
-// 4096 x 1024 4.7 / 4.9 .. 5.3 / 5.1.)  That up to 32 rows always take the few-row kernel is not the best everywhere (32 rows: 4096 x 4096
-// 7.2 / 11.2, 8192 x 4096 10.2 / 12.0, but 11008 x 4096 15.1 / 13.1, 28672 x 4096 29.4 / 26.5, 28672 x 8192 52.1 / 49.9).
+// 4096 x 1024 4.7 / 4.9 .. 5.3 / 5.1.)
 // More than one round of 256 x 256 tiles (one per CU): the large-product kernels of gemm_fp8_snake.hip /
 // gemm_fp8_stream.hip.  In between the cheapest of the ring kernel's tiles (gemm_fp8_ring.hip) and one round of
 // 256 x 256 tiles by this estimate, in us (one launch; rounds of 256 workgroups, K steps of 128 bytes):
@@ -295,8 +297,10 @@ int pick_path(const GemmOperands& g, double* cost) {
     const int v = knob(KNOB_GEMM_VARIANT);
     if (v == 0 || v == 4 || v == 5) return v;
     if (v == 6 || v == 7) return fits ? kPathRing + (v == 6 ? RING_64x64 : RING_128x128) : 0;
-    if (g.M <= 32 || (g.M <= 64 && g.N <= 8192 && g.K >= 2048 && gemm_fp8_snake_fits(g.lda, g.ldb))) return 5;
     const int64_t cus = compute_units() > 0 ? compute_units() : 256;
+    if (g.M <= 16 || (g.M <= 32 && (8 * cdiv(g.N, 64) < 5 * cus || !fits)) ||
+        (g.M <= 64 && g.N <= 8192 && g.K >= 2048 && gemm_fp8_snake_fits(g.lda, g.ldb))) return 5;
+    if (g.M <= 32) return kPathRing + RING_64x64;
     const int64_t big = cdiv(g.M, 256) * cdiv(g.N, 256);
     if (const int b = knob(KNOB_GEMM_BIG_FROM); b > 0 && cdiv(g.M, 128) * cdiv(g.N, 128) >= b) return 4;
     if (big > cus || !fits || knob(KNOB_GEMM_RING) == 0) return 4;

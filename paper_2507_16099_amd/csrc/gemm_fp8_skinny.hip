@@ -228,18 +228,26 @@ __global__ __launch_bounds__(256) void gemm_fp8_skinny_kernel(
 // younger loads (they complete in order).  No barriers in the main loop.
 typedef int v4i_k __attribute__((ext_vector_type(4)));
 
+// HINT: with the streaming (non-temporal) hint
+template <bool HINT = false>
 __device__ __forceinline__ void sk_lds_dma16(v4i_k rsrc, uint32_t lds_addr, uint32_t voffset) {
     // LDS reads of this wavefront that still use the slot have been issued before (program order)
     // and are waited for here, so the refill cannot overtake them
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                 :
-                 : "s"(lds_addr), "v"(voffset), "s"(rsrc)
-                 : "memory", "m0");
+    if constexpr (HINT)
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds"
+                     :
+                     : "s"(lds_addr), "v"(voffset), "s"(rsrc)
+                     : "memory", "m0");
+    else
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                     :
+                     : "s"(lds_addr), "v"(voffset), "s"(rsrc)
+                     : "memory", "m0");
 }
 template <int N_>
 __device__ __forceinline__ void sk_wait_vmem() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N_) : "memory"); }
 
-template <int FA, int FB, int MT, int KS, int NW, int R>
+template <int FA, int FB, int MT, int KS, int NW, int R, bool HINT>
 __global__ __launch_bounds__(256) void gemm_fp8_skinny_dma_kernel(
     const uint8_t* __restrict__ A, int64_t lda, const uint8_t* __restrict__ B, int64_t ldb,
     const float* __restrict__ scale_a, int row_a, const float* __restrict__ scale_b, int row_b, int M, int N,
@@ -295,13 +303,13 @@ __global__ __launch_bounds__(256) void gemm_fp8_skinny_dma_kernel(
         const uint32_t dst = ring + (uint32_t)(slot * SLOT);
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
-            sk_lds_dma16(rsrc_b, dst + w * 2048, vb0 + (uint32_t)(16 * w * (int)ldb) + k_0);
-            sk_lds_dma16(rsrc_b, dst + w * 2048 + 1024, vb1 + (uint32_t)(16 * w * (int)ldb) + k_1);
+            sk_lds_dma16<HINT>(rsrc_b, dst + w * 2048, vb0 + (uint32_t)(16 * w * (int)ldb) + k_0);
+            sk_lds_dma16<HINT>(rsrc_b, dst + w * 2048 + 1024, vb1 + (uint32_t)(16 * w * (int)ldb) + k_1);
         }
 #pragma unroll
         for (int t = 0; t < MT; ++t) {
-            sk_lds_dma16(rsrc_a, dst + (NW + t) * 2048, va0 + (uint32_t)(16 * t * (int)lda) + k_0);
-            sk_lds_dma16(rsrc_a, dst + (NW + t) * 2048 + 1024, va1 + (uint32_t)(16 * t * (int)lda) + k_1);
+            sk_lds_dma16<>(rsrc_a, dst + (NW + t) * 2048, va0 + (uint32_t)(16 * t * (int)lda) + k_0);
+            sk_lds_dma16<>(rsrc_a, dst + (NW + t) * 2048 + 1024, va1 + (uint32_t)(16 * t * (int)lda) + k_1);
         }
     };
 
@@ -404,14 +412,16 @@ static hipError_t launch_sk_dma(const uint8_t* a, int64_t lda, const float* sa, 
                                 const float* sb, int row_b, int M, int N, int K, void* out, int64_t ld_out, int out_f32,
                                 int64_t grid, hipStream_t st) {
     constexpr int SLOT = (NW + MT) * 2048;
-    // up to 32 rows about 20 KB of ring per wavefront, two workgroups per CU; from 33 rows on three steps in flight, 24 to
-    // 36 KB, one workgroup per CU (two steps, for two workgroups, at 33-48 rows against 16 columns per wavefront: 6144 x 4096
-    // 9.3 -> 9.0 us, 8192 x 8192 18.9 -> 18.5, but 33 x 1024 x 16384 12.4 -> 13.0 and 33 x 2048 x 8192 8.8 -> 9.0)
-    constexpr int R = SLOT <= 4096 ? 5 : (SLOT <= 6144 || MT > 2) ? 3 : 2;
+    // Short rings and three workgroups per CU rather than long ones and one or two: a workgroup streams nothing while its ring
+    // fills and while its K parts are summed.  (us, weights from HBM: five steps / three at 16 x 4096 x 4096 6.2 / 5.9, 2 x 4096 x 14336
+    // 12.6 / 12.3; three / two at 16 x 28672 x 4096 25.9 / 25.0, 2 x 14336 x 4096 13.5 / 13.1, 16 x 11008 x 4096 13.3 / 12.7, 64 x 8192 x 8192
+    // 19.7 / 19.3, 64 x 4096 x 4096 9.5 / 9.2; one or two tiles of 16 columns each way keep three: 2 x 4096 x 14336 12.3 / 14.3, 32 x 1024 x 8192 6.8 / 7.2)
+    constexpr int R = SLOT <= 6144 && NW == 1 ? 3 : 2;
     constexpr int lds = 4 * R * SLOT;
-    auto kern = gemm_fp8_skinny_dma_kernel<FA, FB, MT, KS, NW, R>;
-    static DynamicLdsOnce attr;
-    if (hipError_t e = attr.ensure(reinterpret_cast<const void*>(kern), lds); e != hipSuccess) return e;
+    const bool hint = stream_weight(N, K);
+    auto kern = hint ? gemm_fp8_skinny_dma_kernel<FA, FB, MT, KS, NW, R, true> : gemm_fp8_skinny_dma_kernel<FA, FB, MT, KS, NW, R, false>;
+    static DynamicLdsOnce attr[2];
+    if (hipError_t e = attr[hint].ensure(reinterpret_cast<const void*>(kern), lds); e != hipSuccess) return e;
     kern<<<dim3((unsigned)grid), dim3(256), lds, st>>>(a, lda, b, ldb, sa, row_a, sb, row_b, M, N, K, out, ld_out, out_f32);
     return hipGetLastError();
 }

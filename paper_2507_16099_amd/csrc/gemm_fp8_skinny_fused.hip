@@ -41,11 +41,18 @@ __device__ __forceinline__ uint32_t skf_pack_bf16(float a, float b) {
 
 // 16 bytes per lane from a raw buffer into LDS at lds_addr + lane * 16 (the wavefront's own LDS reads of
 // the slot were issued before, in program order, and are waited for here)
+template <bool HINT>
 __device__ __forceinline__ void skf_lds_dma16(v4i_q rsrc, uint32_t lds_addr, uint32_t voffset) {
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                 :
-                 : "s"(lds_addr), "v"(voffset), "s"(rsrc)
-                 : "memory", "m0");
+    if constexpr (HINT)       // streaming (non-temporal)
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds"
+                     :
+                     : "s"(lds_addr), "v"(voffset), "s"(rsrc)
+                     : "memory", "m0");
+    else
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                     :
+                     : "s"(lds_addr), "v"(voffset), "s"(rsrc)
+                     : "memory", "m0");
 }
 // 16 bytes per lane from a raw buffer into registers; the data is there after skf_wait_x.  Assembly, like
 // the wait: the compiler's own count of loads in flight knows nothing of the LDS-DMA loads issued behind these, and its
@@ -79,7 +86,7 @@ constexpr int MAX_X = 32768;       // elements of X a workgroup holds in registe
 constexpr int ROW_PAD = 64;        // bytes between the rows of codes in LDS beyond K: consecutive rows start 16 banks apart
 }  // namespace skf
 
-template <int FX, int FB, int KS, int NW, int WAVES, int R>
+template <int FX, int FB, int KS, int NW, int WAVES, int R, bool HINT>
 __global__ __launch_bounds__(64 * WAVES) void gemm_fp8_skinny_fused_kernel(
     const uint16_t* __restrict__ X, int64_t ldx, int row_x, int flags, const uint8_t* __restrict__ B, int64_t ldb,
     const float* __restrict__ scale_b, int row_b, int M, int N, int K, uint16_t* __restrict__ out, int64_t ld_out) {
@@ -150,8 +157,8 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_fp8_skinny_fused_kernel(
         const uint32_t dst = ring + (uint32_t)(slot * SLOT);
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
-            skf_lds_dma16(rsrc_b, dst + w * 2048, vb0 + (uint32_t)(16 * w * (int)ldb) + k0);
-            skf_lds_dma16(rsrc_b, dst + w * 2048 + 1024, vb1 + (uint32_t)(16 * w * (int)ldb) + k0);
+            skf_lds_dma16<HINT>(rsrc_b, dst + w * 2048, vb0 + (uint32_t)(16 * w * (int)ldb) + k0);
+            skf_lds_dma16<HINT>(rsrc_b, dst + w * 2048 + 1024, vb1 + (uint32_t)(16 * w * (int)ldb) + k0);
         }
     };
 #pragma unroll
@@ -262,9 +269,10 @@ static hipError_t launch_skf(const uint16_t* x, int64_t ldx, int row_x, int flag
     // eight wavefronts: 96 KB of rings, one workgroup per CU with the codes of X (33 KB at most); four: 40 or 48 KB
     constexpr int R = WAVES == 8 ? (NW == 1 ? 6 : 3) : (NW == 1 ? 5 : 3);
     const int lds = WAVES * R * NW * 2048 + M * (K + ROW_PAD) + 128;
-    auto kern = gemm_fp8_skinny_fused_kernel<FX, FB, KS, NW, WAVES, R>;
-    static DynamicLdsOnce attr;
-    if (hipError_t e = attr.ensure(reinterpret_cast<const void*>(kern), WAVES * R * NW * 2048 + MAX_X + 8 * ROW_PAD + 128); e != hipSuccess) return e;
+    const bool hint = stream_weight(N, K);
+    auto kern = hint ? gemm_fp8_skinny_fused_kernel<FX, FB, KS, NW, WAVES, R, true> : gemm_fp8_skinny_fused_kernel<FX, FB, KS, NW, WAVES, R, false>;
+    static DynamicLdsOnce attr[2];
+    if (hipError_t e = attr[hint].ensure(reinterpret_cast<const void*>(kern), WAVES * R * NW * 2048 + MAX_X + 8 * ROW_PAD + 128); e != hipSuccess) return e;
     kern<<<dim3((unsigned)grid), dim3(64 * WAVES), lds, st>>>(x, ldx, row_x, flags, b, ldb, sb, row_b, M, N, K, out, ld_out);
     return hipGetLastError();
 }

@@ -252,7 +252,8 @@ static hipError_t launch_tn(const GemmOperands& g, int row_a, int row_b, hipStre
 // a: prologue and epilogue of a tile; b: a K step with every CU busy (some 460 / 670 / 970 / 1600 cycles for the tiles below; their
 // matrix instructions take 128 / 256 / 512 / 1024, the fragment reads and LDS-DMA writes at 128 bytes a cycle 384 / 576 / 768 / 1152).
 // No unit is full: 128 x 128 tiles at 777 x 4096 x 14336 keep the matrix units busy 42 % of the time and the LDS's reads 22 %.
-// Measured (a HIP graph of twelve, operands alternating; us; K = 1024 / 4096 / 16384):
+// Measured (a HIP graph of twelve, operands alternating; us; K = 1024 / 4096 / 16384; since then 128 x 64 tiles take 0.4 us less, 128 x 256
+// tiles 0.7 up to K = 6144):
 //                        64x64              128x64             128x128            128x256            before (other kernels)
 //     1024 x 1024     6.0 / 10.5 / 29     7.4 / 13.2 / 36     8.3 / 16.0 / 46    11.3 / 23.9 / 73      7.8 / 14.8 / 45
 //     1024 x 2048     9.6 / 18.3 / 66     7.9 / 14.2 / 50     8.6 / 17.2 / 64    11.6 / 24.8 / 99     10.3 / 21.8 / 74
@@ -265,8 +266,8 @@ static hipError_t launch_tn(const GemmOperands& g, int row_a, int row_b, hipStre
 // 0 = the fallback above, 4 = 256 x 256, 5 = few-row kernel (only where M <= 64), 6 / 7 = ring kernel, 64 x 64 / 128 x 128 tiles.
 namespace {
 struct RingCost { int tm, tn; double a, b; };
-constexpr RingCost kRing[RING_TILES] = {{64, 64, 1.0, 0.20},   {128, 64, 2.3, 0.29},  {64, 128, 2.3, 0.29},
-                                        {128, 128, 4.0, 0.42}, {128, 256, 7.0, 0.70}, {256, 128, 7.0, 0.70}};
+constexpr RingCost kRing[RING_TILES] = {{64, 64, 1.0, 0.20},   {128, 64, 1.9, 0.29},  {64, 128, 1.9, 0.29},
+                                        {128, 128, 4.0, 0.42}, {128, 256, 6.3, 0.70}, {256, 128, 6.3, 0.70}};
 constexpr int kPathRing = 100;       // + tile: the ring kernel; otherwise a GEMM_VARIANT number
 
 int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }

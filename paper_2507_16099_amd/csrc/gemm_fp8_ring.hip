@@ -7,7 +7,8 @@
 // a 128 x 128 tile is 512 matrix-core cycles next to some 2000 cycles of latency from the Infinity Cache or HBM.  So
 // the tiles here are smaller than the 256 x 256 of the large-product kernels, which gives every CU one, and the LDS
 // that a smaller tile leaves free holds more K steps in flight: a ring of R stages, filled R steps ahead by
-// LDS-DMA (no staging registers), one workgroup barrier per step.
+// LDS-DMA (no staging registers), one workgroup barrier per step.  Four wavefronts, one per SIMD; of 128 x 256 tiles eight,
+// where the contraction is short: what they save is in the prologue and the epilogue (below).
 //
 //   step s:  wait until stage s + 1 has landed (vmcnt counts the loads of the younger stages) and the wave's own
 //            fragment reads of stage s are done; barrier: both now hold for every wave
@@ -38,7 +39,6 @@ typedef float v4f_t __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 constexpr int BK = 128;
-constexpr int NT = 256;          // four wavefronts
 constexpr int NUM_XCD = 8;
 
 __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
@@ -139,23 +139,24 @@ struct RingProblem {
 
 // mode: 0 = bfloat16 out, 1 = fp32 out, 2 = bfloat16 of the logistic function of the result
 template <int FA, int FB, int TM, int TN, int WAVES_M, int WAVES_N, int R, int GROUP_M, bool MX, bool HINT_B>
-__global__ __launch_bounds__(rg::NT) void gemm_fp8_ring_kernel(RingProblem p1, RingProblem p2, int row_a, int row_b, int mode) {
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_fp8_ring_kernel(RingProblem p1, RingProblem p2, int row_a, int row_b, int mode) {
     using namespace rg;
+    constexpr int NW = WAVES_M * WAVES_N;            // wavefronts: four, one per SIMD, or eight
     constexpr int WM = TM / WAVES_M, WN = TN / WAVES_N;
     constexpr int FM = WM / 16, FN = WN / 16;        // fragments (16 rows each) per wave
     constexpr int GW = WN < 64 ? WN : 64;            // B rows dealt together: a lane holds GW / 4 consecutive columns of a group
     constexpr int GT = GW / 16, NG = WN / GW;        // fragments per group, groups
     constexpr int SH = GW == 64 ? 4 : 3;             // log2(GW / 4)
     constexpr int TILE = (TM + TN) * BK;
-    constexpr int NLE = MX ? ((TM + TN) / 64 + 3) / 4 : 0;        // scale loads (64 rows each) per wave and step
-    constexpr int STAGE = TILE + NLE * 1024;
-    constexpr int NLA = TM / 32, NLB = TN / 32, NLD = NLA + NLB;  // data loads per wave and step
+    constexpr int NLE = MX ? ((TM + TN) / 64 + NW - 1) / NW : 0;  // scale loads (64 rows each) per wave and step
+    constexpr int STAGE = TILE + NLE * NW * 256;
+    constexpr int NLA = TM / (8 * NW), NLB = TN / (8 * NW), NLD = NLA + NLB;   // data loads per wave and step
     constexpr int NL = NLD + NLE;
     constexpr int NM = FM * FN;
-    constexpr bool ACC_V = 4 * NM + (MX ? 18 : 16) * (FM + FN) <= 192;     // accumulators and both fragment sets fit 256 registers with the rest
-    static_assert(WAVES_M * WAVES_N == 4 && WM % 16 == 0 && (GW == 64 || GW == 32) && WN % GW == 0 && TM % 64 == 0 && TN % 64 == 0, "tile");
+    constexpr bool ACC_V = 4 * NM + (MX ? 18 : 16) * (FM + FN) <= (NW == 8 ? 208 : 192);     // accumulators and both fragment sets fit 256 registers with the rest
+    static_assert((NW == 4 || NW == 8) && WM % 16 == 0 && (GW == 64 || GW == 32) && WN % GW == 0 && TM % 64 == 0 && TN % 64 == 0, "tile");
     static_assert(R >= 3 && (R - 1) * NL <= 63, "vmcnt range");
-    static_assert(4 * WM * WN * 2 <= R * STAGE, "the epilogue stages through the ring");
+    static_assert(NW * WM * WN * 2 <= R * STAGE, "the epilogue stages through the ring");
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
 
     const RingProblem& p = blockIdx.y ? p2 : p1;
@@ -185,7 +186,7 @@ __global__ __launch_bounds__(rg::NT) void gemm_fp8_ring_kernel(RingProblem p1, R
     const v4i_t rsrc_b = {(int)(uint32_t)pb, (int)(uint32_t)(pb >> 32), (int)((int64_t)(rows_b - 1) * ldb + K), 0x00020000};
 
     // ---- scales of the tile's rows and columns, by LDS-DMA into the table behind the ring (64 rows or columns a load: unit u
-    //      goes to wave u % 4), ahead of the operands: older than these, they have landed with stage 0.  The table then takes
+    //      goes to wave u % NW), ahead of the operands: older than these, they have landed with stage 0.  The table then takes
     //      their reciprocals, rows first.
     float* inv_tab = reinterpret_cast<float*>(smem + R * STAGE);
     if constexpr (!MX) {
@@ -193,8 +194,8 @@ __global__ __launch_bounds__(rg::NT) void gemm_fp8_ring_kernel(RingProblem p1, R
         const v4i_t rsrc_sa = {(int)(uint32_t)psa, (int)(uint32_t)(psa >> 32), row_a ? rows_a * 4 : 4, 0x00020000};
         const v4i_t rsrc_sb = {(int)(uint32_t)psb, (int)(uint32_t)(psb >> 32), row_b ? rows_b * 4 : 4, 0x00020000};
 #pragma unroll
-        for (int h = 0; h < ((TM + TN) / 64 + 3) / 4; ++h) {
-            const int u = wave + 4 * h, r = 64 * (u < TM / 64 ? u : u - TM / 64) + lane;
+        for (int h = 0; h < ((TM + TN) / 64 + NW - 1) / NW; ++h) {
+            const int u = wave + NW * h, r = 64 * (u < TM / 64 ? u : u - TM / 64) + lane;
             const uint32_t at = (uint32_t)(size_t)inv_tab + (uint32_t)u * 256u;
             if (u < TM / 64) lds_dma4(rsrc_sa, at, row_a ? (uint32_t)(r < rows_a ? r : rows_a - 1) * 4u : 0u);
             else if (u < (TM + TN) / 64) lds_dma4(rsrc_sb, at, row_b ? (uint32_t)(r < rows_b ? r : rows_b - 1) * 4u : 0u);
@@ -206,24 +207,24 @@ __global__ __launch_bounds__(rg::NT) void gemm_fp8_ring_kernel(RingProblem p1, R
         if (tid < TN) inv_tab[TM + tid] = 1.0f / inv_tab[TM + tid];
     };
 
-    // ---- global -> LDS: load i of wave w fills rows 32 i + 8 w + lane / 8; lane's chunk slot lane % 8 takes chunk
+    // ---- global -> LDS: load i of wave w fills rows 8 NW i + 8 w + lane / 8; lane's chunk slot lane % 8 takes chunk
     //      slot ^ key(row).  A: key = (row >> 1) & 7.  B: ((row >> 1) & 1) | ((row >> SH) & 3) << 1.
     const int lrow = lane >> 3;
     const int ca = (lane & 7) ^ ((4 * (wave & 1) + (lrow >> 1)) & 7);
-    const int kb_e = SH == 4 ? (wave >> 1) : wave, kb_o = SH == 4 ? 2 + (wave >> 1) : wave;
+    const int kb_e = SH == 4 ? (wave >> 1) : wave, kb_o = SH == 4 && NW == 4 ? 2 + (wave >> 1) : kb_e;
     const int cb_e = (lane & 7) ^ (((lrow >> 1) & 1) | ((kb_e & 3) << 1));     // even i
     const int cb_o = (lane & 7) ^ (((lrow >> 1) & 1) | ((kb_o & 3) << 1));     // odd i
     const uint32_t va0 = (uint32_t)((wave * 8 + lrow) * (int)lda + ca * 16);
     const uint32_t vb0_e = (uint32_t)((wave * 8 + lrow) * (int)ldb + cb_e * 16);
     const uint32_t vb0_o = (uint32_t)((wave * 8 + lrow) * (int)ldb + cb_o * 16);
-    const uint32_t va_step = (uint32_t)(32 * (int)lda), vb_step = (uint32_t)(32 * (int)ldb);
+    const uint32_t va_step = (uint32_t)(8 * NW * (int)lda), vb_step = (uint32_t)(8 * NW * (int)ldb);
     const uint32_t lds_base = (uint32_t)(size_t)smem + (uint32_t)wave * 1024u;
     constexpr uint32_t OOB = 0x80000000u;      // puts a lane outside its descriptor: zeros arrive
     auto load_q = [&](int q, uint32_t stage_off, uint32_t ka, uint32_t ke, uint32_t ko) {
-        if (q < NLB) lds_dma16<HINT_B>(rsrc_b, lds_base + stage_off + TM * BK + q * 4096, ((q & 1) ? vb0_o + ko : vb0_e + ke) + (uint32_t)q * vb_step);
-        else if (q < NLD) lds_dma16<>(rsrc_a, lds_base + stage_off + (q - NLB) * 4096, va0 + (uint32_t)(q - NLB) * va_step + ka);
+        if (q < NLB) lds_dma16<HINT_B>(rsrc_b, lds_base + stage_off + TM * BK + q * (NW * 1024), ((q & 1) ? vb0_o + ko : vb0_e + ke) + (uint32_t)q * vb_step);
+        else if (q < NLD) lds_dma16<>(rsrc_a, lds_base + stage_off + (q - NLB) * (NW * 1024), va0 + (uint32_t)(q - NLB) * va_step + ka);
     };
-    // MX scales: unit u of a stage is the dwords of 64 rows, A's rows first; wave w loads units w, w + 4 (units past the last
+    // MX scales: unit u of a stage is the dwords of 64 rows, A's rows first; wave w loads units w, w + NW (units past the last
     // one deliver zeros into spare room, so that every wave has the same number of loads in flight).  Slabs: rows past the
     // operand's end read the next slab's rows; their products reach only rows and columns that are never stored.
     const bool slab_a = MX && p.ld_ea < 0, slab_b = MX && p.ld_eb < 0;
@@ -232,7 +233,7 @@ __global__ __launch_bounds__(rg::NT) void gemm_fp8_ring_kernel(RingProblem p1, R
     if constexpr (MX) {
 #pragma unroll
         for (int h = 0; h < NLE; ++h) {
-            const int u = wave + 4 * h;
+            const int u = wave + NW * h;
             const bool is_a = u < TM / 64, none = u >= (TM + TN) / 64;
             const bool slab = is_a ? slab_a : slab_b;
             const int64_t ld = is_a ? p.ld_ea : p.ld_eb;
@@ -251,7 +252,7 @@ __global__ __launch_bounds__(rg::NT) void gemm_fp8_ring_kernel(RingProblem p1, R
             const uint32_t s4 = (uint32_t)(k0 >> 9), sr = (uint32_t)((k0 >> 7) & 3) * 4;
 #pragma unroll
             for (int h = 0; h < NLE; ++h)
-                lds_dma4(rsrc_e[h], lds_e + stage_off + h * 1024, k0 < K ? ve[h] + s4 * gse[h] + sr : OOB);
+                lds_dma4(rsrc_e[h], lds_e + stage_off + h * (NW * 256), k0 < K ? ve[h] + s4 * gse[h] + sr : OOB);
         }
     };
     auto kofs = [&](int k0, int c) { return k0 + c * 16 < K ? (uint32_t)k0 : OOB; };
@@ -456,7 +457,8 @@ static hipError_t launch_ring_t(const GemmOperands& g1, const GemmOperands* g2, 
                                 hipStream_t st) {
     using namespace rg;
     auto kern = gemm_fp8_ring_kernel<FA, FB, TM, TN, WAVES_M, WAVES_N, R, GROUP_M, MX, HINT_B>;
-    constexpr int lds = R * ((TM + TN) * BK + (MX ? ((TM + TN) / 64 + 3) / 4 * 1024 : 0)) + (MX ? 0 : (TM + TN) * 4);
+    constexpr int NW = WAVES_M * WAVES_N;
+    constexpr int lds = R * ((TM + TN) * BK + (MX ? ((TM + TN) / 64 + NW - 1) / NW * (NW * 256) : 0)) + (MX ? 0 : (TM + TN) * 4);
     static_assert(lds <= 160 * 1024, "LDS");
     static DynamicLdsOnce attr;     // one per instantiation
     if (hipError_t err = attr.ensure(reinterpret_cast<const void*>(kern), lds); err != hipSuccess) return err;
@@ -470,11 +472,14 @@ static hipError_t launch_ring_t(const GemmOperands& g1, const GemmOperands* g2, 
     };
     const RingProblem p1 = problem(g1), p2 = g2 ? problem(*g2) : p1;
     const int per_xcd = p1.per_xcd > p2.per_xcd ? p1.per_xcd : p2.per_xcd;
-    kern<<<dim3((unsigned)(per_xcd * NUM_XCD), g2 ? 2 : 1), dim3(NT), lds, st>>>(p1, p2, row_a, row_b, mode);
+    kern<<<dim3((unsigned)(per_xcd * NUM_XCD), g2 ? 2 : 1), dim3(64 * NW), lds, st>>>(p1, p2, row_a, row_b, mode);
     return hipGetLastError();
 }
 
-// stages: what the LDS holds; rows of tiles walked together: close to square patches.  64 x 64: five stages, which with the
+// stages: 128 x 64 and 64 x 128 tiles take four, though six fit: filling them is the longer part of a short product (us, six / four:
+// 1024 x 2048 x 1024 6.3 / 6.0, 72 x 14336 x 4096 13.8 / 12.8, 512 x 4096 x 4096 13.4 / 13.0, 256 x 4096 x 14336 32.6 / 31.9).  Otherwise what the LDS holds;
+// rows of tiles walked together: close to square patches.  128 x 256 and 256 x 128: eight wavefronts up to K = 6144 (us, four / eight:
+// 2048 x 4096 x 1024 14.4 / 13.7, 3001 x 2048 x 4096 26.9 / 25.9, 2048 x 4096 x 4096 31.1 / 30.6; x 8192 54.0 / 54.9, 4096 x 4096 x 16384 214 / 219).  64 x 64: five stages, which with the
 // table of reciprocals is one workgroup per CU; four, for two of them (as in the MX form), cost a long contraction more than
 // they give a short one or a second round (us, five / four stages: 1000 x 1000 x 14336 25.2 / 27.1, 512 x 512 x 28672 40.5 / 43.0,
 // 1024 x 1024 x 4096 10.5 / 10.5, x 1024 6.0 / 5.8; several rounds, where larger tiles are taken: 2048 x 2048 x 1024 16.3 / 12.9).
@@ -486,18 +491,23 @@ static hipError_t launch_ring_f(int tile, const GemmOperands& g1, const GemmOper
     if constexpr (!MX) {
         if (!g2 && stream_weight(g1.N, g1.K)) {
             if (tile == RING_64x64 && g1.M <= 64) return launch_ring_t<FA, FB, 64, 64, 2, 2, 5, 4, false, true>(g1, g2, e, row_a, row_b, mode, st);
-            if (tile == RING_64x128 && g1.M <= 64) return launch_ring_t<FA, FB, 64, 128, 2, 2, 6, 8, false, true>(g1, g2, e, row_a, row_b, mode, st);
+            if (tile == RING_64x128 && g1.M <= 64) return launch_ring_t<FA, FB, 64, 128, 2, 2, 4, 8, false, true>(g1, g2, e, row_a, row_b, mode, st);
             if (tile == RING_128x128 && g1.M <= 128) return launch_ring_t<FA, FB, 128, 128, 2, 2, 4, 4, false, true>(g1, g2, e, row_a, row_b, mode, st);
             if (tile == RING_128x256 && g1.M <= 256) return launch_ring_t<FA, FB, 128, 256, 2, 2, 3, 8, false, true>(g1, g2, e, row_a, row_b, mode, st);
         }
     }
+    const bool shallow = g1.K <= 6144 && (!g2 || g2->K <= 6144);
     switch (tile) {
         case RING_64x64: return launch_ring_t<FA, FB, 64, 64, 2, 2, MX ? 4 : 5, 4, MX>(g1, g2, e, row_a, row_b, mode, st);
-        case RING_128x64: return launch_ring_t<FA, FB, 128, 64, 2, 2, 6, 4, MX>(g1, g2, e, row_a, row_b, mode, st);
-        case RING_64x128: return launch_ring_t<FA, FB, 64, 128, 2, 2, 6, 8, MX>(g1, g2, e, row_a, row_b, mode, st);
+        case RING_128x64: return launch_ring_t<FA, FB, 128, 64, 2, 2, 4, 4, MX>(g1, g2, e, row_a, row_b, mode, st);
+        case RING_64x128: return launch_ring_t<FA, FB, 64, 128, 2, 2, 4, 8, MX>(g1, g2, e, row_a, row_b, mode, st);
         case RING_128x128: return launch_ring_t<FA, FB, 128, 128, 2, 2, 4, 4, MX>(g1, g2, e, row_a, row_b, mode, st);
-        case RING_128x256: return launch_ring_t<FA, FB, 128, 256, 2, 2, 3, 8, MX>(g1, g2, e, row_a, row_b, mode, st);
-        case RING_256x128: return launch_ring_t<FA, FB, 256, 128, 2, 2, 3, 4, MX>(g1, g2, e, row_a, row_b, mode, st);
+        case RING_128x256:
+            return shallow ? launch_ring_t<FA, FB, 128, 256, 2, 4, 3, 8, MX>(g1, g2, e, row_a, row_b, mode, st)
+                           : launch_ring_t<FA, FB, 128, 256, 2, 2, 3, 8, MX>(g1, g2, e, row_a, row_b, mode, st);
+        case RING_256x128:
+            return shallow ? launch_ring_t<FA, FB, 256, 128, 4, 2, 3, 4, MX>(g1, g2, e, row_a, row_b, mode, st)
+                           : launch_ring_t<FA, FB, 256, 128, 2, 2, 3, 4, MX>(g1, g2, e, row_a, row_b, mode, st);
     }
     return hipErrorInvalidValue;
 }

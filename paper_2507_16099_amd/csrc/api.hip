@@ -938,8 +938,14 @@ int fp8_mx_linear_fwd(const void* x, const void* w, int64_t M, int64_t K, int64_
     // scales between the quantizers and the GEMM: in slabs of sixteen blocks (negative leading dimension) where the GEMM takes them
     const bool slab = fp8k::gemm_mxfp8_takes_slab_scales(K, K, M, N, K);
     const int64_t ld_xe = slab ? -M : K / 32, ld_we = slab ? -N : K / 32;
-    FP8_TRY(fp8k::launch_mx_quant(x, M, K, K, fmt_x, ws + p.xq, K, ws + p.xe, ld_xe, st));
-    FP8_TRY(fp8k::launch_mx_quant(w, N, K, K, fmt_w, ws + p.wq, K, ws + p.we, ld_we, st));
+    const fp8k::BlockOperand ops[2] = {{x, M, K, fmt_x, ws + p.xq, K, ws + p.xe, ld_xe}, {w, N, K, fmt_w, ws + p.wq, K, ws + p.we, ld_we}};
+    const hipError_t e = fp8k::launch_quant_blocks(ops, 2, true, st);
+    if (e == hipErrorNotSupported) {
+        FP8_TRY(fp8k::launch_mx_quant(x, M, K, K, fmt_x, ws + p.xq, K, ws + p.xe, ld_xe, st));
+        FP8_TRY(fp8k::launch_mx_quant(w, N, K, K, fmt_w, ws + p.wq, K, ws + p.we, ld_we, st));
+    } else if (e != hipSuccess) {
+        return hip_fail(e, "quant_blocks");
+    }
     FP8_TRY(fp8k::launch_gemm_mxfp8(ws + p.xq, K, fmt_x, ws + p.xe, ld_xe, ws + p.wq, K, fmt_w, ws + p.we, ld_we, M, N, K, y,
                                     N, 0, st));
     return FP8_OK;
@@ -983,8 +989,14 @@ int fp8_block_linear_fwd(const void* x, const void* w, int64_t M, int64_t K, int
     // scales between the quantizers and the GEMM: in slabs of sixteen blocks (negative leading dimension) where the GEMM takes them
     const bool slab = fp8k::gemm_mxfp8_takes_slab_scales(K, K, M, N, K);
     const int64_t ld_xe = slab ? -M : K / 32, ld_we = slab ? -N : K / 32;
-    FP8_TRY(fp8k::launch_block_quant(x, M, K, K, 1, fmt_x, ws + p.xq, K, ws + p.xe, ld_xe, st));
-    FP8_TRY(fp8k::launch_block_quant(w, N, K, K, 128, fmt_w, ws + p.wq, K, ws + p.we, ld_we, st));
+    const fp8k::BlockOperand ops[2] = {{x, M, K, fmt_x, ws + p.xq, K, ws + p.xe, ld_xe}, {w, N, K, fmt_w, ws + p.wq, K, ws + p.we, ld_we}};
+    const hipError_t e = fp8k::launch_quant_blocks(ops, 2, false, st);
+    if (e == hipErrorNotSupported) {
+        FP8_TRY(fp8k::launch_block_quant(x, M, K, K, 1, fmt_x, ws + p.xq, K, ws + p.xe, ld_xe, st));
+        FP8_TRY(fp8k::launch_block_quant(w, N, K, K, 128, fmt_w, ws + p.wq, K, ws + p.we, ld_we, st));
+    } else if (e != hipSuccess) {
+        return hip_fail(e, "quant_blocks");
+    }
     FP8_TRY(fp8k::launch_gemm_mxfp8(ws + p.xq, K, fmt_x, ws + p.xe, ld_xe, ws + p.wq, K, fmt_w, ws + p.we, ld_we, M, N, K, y,
                                     N, 0, st));
     return FP8_OK;
@@ -1064,15 +1076,24 @@ int fp8_mx_linear_bwd(const void* dy, const void* x, const void* w, int64_t M, i
     const int64_t ld_dye = slab_dx ? -M : Np / 32, ld_wte = slab_dx ? -K : Np / 32;
     const int64_t ld_dyte = slab_dw ? -N : Mp / 32, ld_xte = slab_dw ? -K : Mp / 32;
     // all quantizations first, then the products back to back
-    if (dx && dw) {   // the gradient in both orientations from one read
+    hipError_t e = hipErrorNotSupported;
+    if (dx && dw && N % 32 == 0) {      // all three in one launch
+        const fp8k::BlockOperand ops[3] = {{dy, M, N, fmt_dy, ws + p.dytq, Mp, ws + p.dyte, ld_dyte, ws + p.dyq, Np, ws + p.dye, ld_dye},
+                                           {w, N, K, fmt_w, ws + p.wtq, Np, ws + p.wte, ld_wte}, {x, M, K, fmt_x, ws + p.xtq, Mp, ws + p.xte, ld_xte}};
+        e = fp8k::launch_quant_blocks(ops, 3, true, st);
+        if (e != hipSuccess && e != hipErrorNotSupported) return hip_fail(e, "quant_blocks");
+    }
+    const bool left = e != hipSuccess;
+    if (!left) {
+    } else if (dx && dw) {   // the gradient in both orientations from one read
         FP8_TRY(fp8k::launch_mx_quant_t(dy, M, N, N, fmt_dy, ws + p.dytq, Mp, ws + p.dyte, ld_dyte, ws + p.dyq, Np, ws + p.dye, ld_dye, st));
     } else if (dx) {
         FP8_TRY(fp8k::launch_mx_quant(dy, M, N, N, fmt_dy, ws + p.dyq, Np, ws + p.dye, ld_dye, st));
     } else {
         FP8_TRY(fp8k::launch_mx_quant_t(dy, M, N, N, fmt_dy, ws + p.dytq, Mp, ws + p.dyte, ld_dyte, nullptr, 0, nullptr, 0, st));
     }
-    if (dx) FP8_TRY(fp8k::launch_mx_quant_t(w, N, K, K, fmt_w, ws + p.wtq, Np, ws + p.wte, ld_wte, nullptr, 0, nullptr, 0, st));
-    if (dw) FP8_TRY(fp8k::launch_mx_quant_t(x, M, K, K, fmt_x, ws + p.xtq, Mp, ws + p.xte, ld_xte, nullptr, 0, nullptr, 0, st));
+    if (left && dx) FP8_TRY(fp8k::launch_mx_quant_t(w, N, K, K, fmt_w, ws + p.wtq, Np, ws + p.wte, ld_wte, nullptr, 0, nullptr, 0, st));
+    if (left && dw) FP8_TRY(fp8k::launch_mx_quant_t(x, M, K, K, fmt_x, ws + p.xtq, Mp, ws + p.xte, ld_xte, nullptr, 0, nullptr, 0, st));
     if (dx)
         FP8_TRY(fp8k::launch_gemm_mxfp8(ws + p.dyq, Np, fmt_dy, ws + p.dye, ld_dye, ws + p.wtq, Np, fmt_w, ws + p.wte, ld_wte,
                                         M, K, Np, dx, K, 0, st));
@@ -1152,15 +1173,24 @@ int fp8_block_linear_bwd(const void* dy, const void* x, const void* w, int64_t M
     const int64_t ld_dye = slab_dx ? -M : N / 32, ld_wte = slab_dx ? -K : N / 32;
     const int64_t ld_dyte = slab_dw ? -N : M / 32, ld_xte = slab_dw ? -K : M / 32;
     // dX = dY W: dY in tiles along N, W^T [K, N] in its 128 x 128 blocks; dW = dY^T X: dY^T and X^T in tiles along M
-    if (dx && dw) {   // the gradient in both orientations from one read
+    hipError_t e = hipErrorNotSupported;
+    if (dx && dw) {      // all three in one launch
+        const fp8k::BlockOperand ops[3] = {{dy, M, N, fmt_dy, ws + p.dytq, M, ws + p.dyte, ld_dyte, ws + p.dyq, N, ws + p.dye, ld_dye},
+                                           {w, N, K, fmt_w, ws + p.wtq, N, ws + p.wte, ld_wte}, {x, M, K, fmt_x, ws + p.xtq, M, ws + p.xte, ld_xte}};
+        e = fp8k::launch_quant_blocks(ops, 3, false, st);
+        if (e != hipSuccess && e != hipErrorNotSupported) return hip_fail(e, "quant_blocks");
+    }
+    const bool left = e != hipSuccess;
+    if (!left) {
+    } else if (dx && dw) {   // the gradient in both orientations from one read
         FP8_TRY(fp8k::launch_block_quant_t(dy, M, N, N, 1, fmt_dy, ws + p.dytq, M, ws + p.dyte, ld_dyte, st, ws + p.dyq, N, ws + p.dye, ld_dye));
     } else if (dx) {
         FP8_TRY(fp8k::launch_block_quant(dy, M, N, N, 1, fmt_dy, ws + p.dyq, N, ws + p.dye, ld_dye, st));
     } else {
         FP8_TRY(fp8k::launch_block_quant_t(dy, M, N, N, 1, fmt_dy, ws + p.dytq, M, ws + p.dyte, ld_dyte, st));
     }
-    if (dx) FP8_TRY(fp8k::launch_block_quant_t(w, N, K, K, 128, fmt_w, ws + p.wtq, N, ws + p.wte, ld_wte, st));
-    if (dw) FP8_TRY(fp8k::launch_block_quant_t(x, M, K, K, 1, fmt_x, ws + p.xtq, M, ws + p.xte, ld_xte, st));
+    if (left && dx) FP8_TRY(fp8k::launch_block_quant_t(w, N, K, K, 128, fmt_w, ws + p.wtq, N, ws + p.wte, ld_wte, st));
+    if (left && dw) FP8_TRY(fp8k::launch_block_quant_t(x, M, K, K, 1, fmt_x, ws + p.xtq, M, ws + p.xte, ld_xte, st));
     if (dx)
         FP8_TRY(fp8k::launch_gemm_mxfp8(ws + p.dyq, N, fmt_dy, ws + p.dye, ld_dye, ws + p.wtq, N, fmt_w, ws + p.wte, ld_wte,
                                         M, K, N, dx, K, 0, st));

@@ -217,6 +217,15 @@ hipError_t launch_mx_quant(const void* x, int64_t rows, int64_t cols, int64_t ld
 hipError_t launch_mx_quant_t(const void* x, int64_t rows, int64_t cols, int64_t ld, int fmt, uint8_t* qt, int64_t ld_t,
                              uint8_t* et, int64_t ld_e, uint8_t* q_row, int64_t ld_row, uint8_t* e_row, int64_t ld_er,
                              hipStream_t st);
+// The tensors of a block-scaled linear layer in one launch, all in one format (else, and where a tensor does not suit, hipErrorNotSupported
+// and nothing launched).  Two: X and W of a forward, dense rows, MX blocks along them or tiles of 1 x 128 (X) and blocks of 128 x 128 (W).
+// Three: dY, W and X of a backward, transposed as by launch_mx_quant_t / launch_block_quant_t (W in blocks of 128 x 128), dY with q_row.
+struct BlockOperand {
+    const void* x; int64_t rows, cols; int fmt;
+    uint8_t* q; int64_t ld_q; uint8_t* e; int64_t ld_e;
+    uint8_t* q_row; int64_t ld_row; uint8_t* e_row; int64_t ld_er;
+};
+hipError_t launch_quant_blocks(const BlockOperand* ops, int n, bool mx, hipStream_t st);
 bool gemm_mxfp8_takes_slab_scales(int64_t lda, int64_t ldb, int64_t M, int64_t N, int64_t K);
 hipError_t launch_gemm_mxfp8(const uint8_t* a, int64_t lda, int fmt_a, const uint8_t* ea, int64_t ld_ea,
                              const uint8_t* b, int64_t ldb, int fmt_b, const uint8_t* eb, int64_t ld_eb, int64_t M,

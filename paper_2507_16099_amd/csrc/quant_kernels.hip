@@ -1436,14 +1436,14 @@ __device__ __forceinline__ int64_t e8_off(int64_t r, int64_t kb, int64_t ld_e) {
 // Four lanes own a block (one 128-bit load each); the maximum is taken on the
 // bfloat16 magnitude bits, whose exponent field gives floor(log2) directly.
 template <int FMT, bool DENSE>
-__global__ __launch_bounds__(256) void mx_quant_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t cols,
-                                                        int64_t ld, uint8_t* __restrict__ q, int64_t ld_q,
-                                                        uint8_t* __restrict__ e8m0, int64_t ld_e) {
+__device__ __forceinline__ void mx_quant_rows(int bid, const uint16_t* __restrict__ x, int64_t rows, int64_t cols,
+                                              int64_t ld, uint8_t* __restrict__ q, int64_t ld_q,
+                                              uint8_t* __restrict__ e8m0, int64_t ld_e) {
     constexpr int U = DENSE ? 4 : 1;                    // vectors per thread, all loads issued before the first use
     constexpr int EMAX = FMT == FMT_E4M3FN ? 8 : 15;
     const int64_t vpr = cols >> 3;                      // 128-bit vectors per row (cols % 32 == 0)
     const int64_t nvec = rows * vpr;
-    const int64_t v0 = (int64_t)blockIdx.x * (256 * U) + threadIdx.x;
+    const int64_t v0 = (int64_t)bid * (256 * U) + threadIdx.x;
     uint4 d[U];
     int64_t xo[U], qo[U], eo[U];
 #pragma unroll
@@ -1480,6 +1480,13 @@ __global__ __launch_bounds__(256) void mx_quant_kernel(const uint16_t* __restric
             if ((threadIdx.x & 3) == 0) e8m0[eo[u]] = (uint8_t)byte;
         }
     }
+}
+
+template <int FMT, bool DENSE>
+__global__ __launch_bounds__(256) void mx_quant_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t cols,
+                                                        int64_t ld, uint8_t* __restrict__ q, int64_t ld_q,
+                                                        uint8_t* __restrict__ e8m0, int64_t ld_e) {
+    mx_quant_rows<FMT, DENSE>(blockIdx.x, x, rows, cols, ld, q, ld_q, e8m0, ld_e);
 }
 
 hipError_t launch_mx_quant(const void* x, int64_t rows, int64_t cols, int64_t ld, int fmt, uint8_t* q, int64_t ld_q,
@@ -1529,13 +1536,12 @@ __device__ __forceinline__ float pow2_block_scale(uint32_t mag, uint32_t& byte) 
 // 1 x 128 tiles: a thread holds 8 elements of each of four tiles (all four loads in flight together), the 16
 // threads of a tile combine their maxima with four cross-lane steps.  cols % 128 == 0.
 template <int FMT>
-__global__ __launch_bounds__(256) void block_quant_1x128_kernel(const uint16_t* __restrict__ x, int64_t rows,
-                                                                 int64_t cols, int64_t ld, uint8_t* __restrict__ q,
-                                                                 int64_t ld_q, uint8_t* __restrict__ e8m0,
-                                                                 int64_t ld_e) {
+__device__ __forceinline__ void block_quant_1x128(int bid, const uint16_t* __restrict__ x, int64_t rows, int64_t cols,
+                                                  int64_t ld, uint8_t* __restrict__ q, int64_t ld_q,
+                                                  uint8_t* __restrict__ e8m0, int64_t ld_e) {
     constexpr int U = 4;
     const int64_t vpr = cols >> 3, nvec = rows * vpr;          // a multiple of 16: tiles never straddle the end
-    const int64_t v0 = (int64_t)blockIdx.x * (256 * U) + threadIdx.x;
+    const int64_t v0 = (int64_t)bid * (256 * U) + threadIdx.x;
     uint4 d[U];
     int64_t r[U], cv[U];
 #pragma unroll
@@ -1558,16 +1564,22 @@ __global__ __launch_bounds__(256) void block_quant_1x128_kernel(const uint16_t* 
         }
     }
 }
+template <int FMT>
+__global__ __launch_bounds__(256) void block_quant_1x128_kernel(const uint16_t* __restrict__ x, int64_t rows,
+                                                                 int64_t cols, int64_t ld, uint8_t* __restrict__ q,
+                                                                 int64_t ld_q, uint8_t* __restrict__ e8m0,
+                                                                 int64_t ld_e) {
+    block_quant_1x128<FMT>(blockIdx.x, x, rows, cols, ld, q, ld_q, e8m0, ld_e);
+}
 
 // 128 x 128 blocks: one workgroup per block, the block held in registers (8 x 8 elements per thread)
 // between the reduction and the conversion: one pass over HBM.  The bottom row of blocks may be partial.
 template <int FMT>
-__global__ __launch_bounds__(256) void block_quant_128x128_kernel(const uint16_t* __restrict__ x, int64_t rows,
-                                                                   int64_t cols, int64_t ld, uint8_t* __restrict__ q,
-                                                                   int64_t ld_q, uint8_t* __restrict__ e8m0,
-                                                                   int64_t ld_e) {
+__device__ __forceinline__ void block_quant_128x128(int bx, int by, const uint16_t* __restrict__ x, int64_t rows, int64_t ld,
+                                                    uint8_t* __restrict__ q, int64_t ld_q, uint8_t* __restrict__ e8m0,
+                                                    int64_t ld_e) {
     const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    const int64_t r0 = (int64_t)blockIdx.y * 128, c0 = (int64_t)blockIdx.x * 128, c = c0 + tx * 8;
+    const int64_t r0 = (int64_t)by * 128, c0 = (int64_t)bx * 128, c = c0 + tx * 8;
     uint4 v[8];
     uint32_t acc = 0;
 #pragma unroll
@@ -1593,6 +1605,13 @@ __global__ __launch_bounds__(256) void block_quant_128x128_kernel(const uint16_t
     if (threadIdx.x < 128 && r0 + threadIdx.x < rows) {
         *reinterpret_cast<uint32_t*>(e8m0 + e8_off(r0 + threadIdx.x, c0 >> 5, ld_e)) = byte * 0x01010101u;
     }
+}
+template <int FMT>
+__global__ __launch_bounds__(256) void block_quant_128x128_kernel(const uint16_t* __restrict__ x, int64_t rows,
+                                                                   int64_t cols, int64_t ld, uint8_t* __restrict__ q,
+                                                                   int64_t ld_q, uint8_t* __restrict__ e8m0,
+                                                                   int64_t ld_e) {
+    block_quant_128x128<FMT>(blockIdx.x, blockIdx.y, x, rows, ld, q, ld_q, e8m0, ld_e);
 }
 
 // block_rows: 1 (tiles of 1 x 128) or 128 (blocks of 128 x 128); cols % 128 == 0
@@ -1635,21 +1654,22 @@ static bool keep_both_codes(int fmt, int64_t rows, int64_t cols) { return !(fmt 
 // consecutive elements of a row combine their maxima with two cross-lane steps.  A tensor that is
 // needed in both orientations (the gradient in the backward) then costs 4 bytes per element
 // instead of 6.  2: the same, codes stored with the streaming hint.
+constexpr int TILE_LDS = 128 * 128 + 4 * 16 * 16 + 128;      // what the tile functions below need: codes, maxima or scale bytes
 template <int FMT, int ROWS_TOO>
-__global__ __launch_bounds__(256) void mx_quant_t_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t cols,
-                                                          int64_t ld, uint8_t* __restrict__ qt, int64_t ld_t,
-                                                          uint8_t* __restrict__ et, int64_t ld_e,
-                                                          uint8_t* __restrict__ q_row, int64_t ld_row,
-                                                          uint8_t* __restrict__ e_row, int64_t ld_er, int nx, int ny) {
+__device__ __forceinline__ void mx_quant_t_tile(int bid, uint8_t* lds, const uint16_t* __restrict__ x, int64_t rows, int64_t cols,
+                                                int64_t ld, uint8_t* __restrict__ qt, int64_t ld_t,
+                                                uint8_t* __restrict__ et, int64_t ld_e,
+                                                uint8_t* __restrict__ q_row, int64_t ld_row,
+                                                uint8_t* __restrict__ e_row, int64_t ld_er, int nx, int ny) {
     constexpr int TR = 128, SLOTS = TR / 8, PARTS = TR / 16;
     constexpr int EMAX = FMT == FMT_E4M3FN ? 8 : 15;
-    __shared__ __attribute__((aligned(16))) uint2 tile[128 * SLOTS];
-    __shared__ __attribute__((aligned(16))) uint8_t ebytes[128 * 4];   // [column of the tile][block of the tile]
-    __shared__ __attribute__((aligned(16))) uint8_t rbytes[ROWS_TOO ? 128 * 4 : 4];   // [row of the tile][column block of the tile]
+    uint2* tile = reinterpret_cast<uint2*>(lds);
+    uint8_t* ebytes = lds + 128 * 128;            // [column of the tile][block of the tile], 128 * 4
+    uint8_t* rbytes = ebytes + 128 * 4;           // [row of the tile][column block of the tile], 128 * 4 (ROWS_TOO)
     const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
     constexpr int PX = 16, PY = 16;
     const int pxc = (nx + PX - 1) / PX;
-    const int patch = blockIdx.x / (PX * PY), within = blockIdx.x % (PX * PY);
+    const int patch = bid / (PX * PY), within = bid % (PX * PY);
     const int bx = (patch % pxc) * PX + within % PX, by = (patch / pxc) * PY + within / PX;
     if (bx >= nx || by >= ny) return;
     const int64_t r0 = (int64_t)bx * TR, c0 = (int64_t)by * 128;
@@ -1776,6 +1796,15 @@ __global__ __launch_bounds__(256) void mx_quant_t_kernel(const uint16_t* __restr
         }
     }
 }
+template <int FMT, int ROWS_TOO>
+__global__ __launch_bounds__(256) void mx_quant_t_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t cols,
+                                                          int64_t ld, uint8_t* __restrict__ qt, int64_t ld_t,
+                                                          uint8_t* __restrict__ et, int64_t ld_e,
+                                                          uint8_t* __restrict__ q_row, int64_t ld_row,
+                                                          uint8_t* __restrict__ e_row, int64_t ld_er, int nx, int ny) {
+    __shared__ __attribute__((aligned(16))) uint8_t lds[TILE_LDS];
+    mx_quant_t_tile<FMT, ROWS_TOO>(blockIdx.x, lds, x, rows, cols, ld, qt, ld_t, et, ld_e, q_row, ld_row, e_row, ld_er, nx, ny);
+}
 
 // Blockwise FP8 of the TRANSPOSED matrix, written transposed: qt [cols, rows] and et [cols, rows / 32] are what
 // block_quant_* gives on x^T, i.e. the contraction-contiguous operands of the backward products.  rows % 128 == 0.
@@ -1788,20 +1817,20 @@ __global__ __launch_bounds__(256) void mx_quant_t_kernel(const uint16_t* __restr
 // of x (q_row [rows, cols], e_row [rows, cols / 32]): the 16 threads that hold a row of the tile combine their
 // maxima with four cross-lane steps.  The gradient, needed in both orientations by the backward, then costs
 // 4 bytes of HBM traffic per element instead of 6.  2: the same, codes stored with the streaming hint.
-template <int FMT, bool SQUARE, int ROWS_TOO = 0>
-__global__ __launch_bounds__(256) void block_quant_t_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t cols,
-                                                             int64_t ld, uint8_t* __restrict__ qt, int64_t ld_t,
-                                                             uint8_t* __restrict__ et, int64_t ld_e, int nx, int ny,
-                                                             uint8_t* __restrict__ q_row = nullptr, int64_t ld_row = 0,
-                                                             uint8_t* __restrict__ e_row = nullptr, int64_t ld_er = 0) {
+template <int FMT, bool SQUARE, int ROWS_TOO>
+__device__ __forceinline__ void block_quant_t_tile(int bid, uint8_t* lds, const uint16_t* __restrict__ x, int64_t rows, int64_t cols,
+                                                   int64_t ld, uint8_t* __restrict__ qt, int64_t ld_t,
+                                                   uint8_t* __restrict__ et, int64_t ld_e, int nx, int ny,
+                                                   uint8_t* __restrict__ q_row, int64_t ld_row,
+                                                   uint8_t* __restrict__ e_row, int64_t ld_er) {
     constexpr int TR = 128, SLOTS = TR / 8, PARTS = TR / 16;
-    __shared__ __attribute__((aligned(16))) uint2 tile[128 * SLOTS];
-    __shared__ uint32_t red[4][16][4];
-    __shared__ uint8_t ebytes[128];                                   // scale byte of each column of the tile
+    uint2* tile = reinterpret_cast<uint2*>(lds);
+    uint32_t (*red)[16][4] = reinterpret_cast<uint32_t (*)[16][4]>(lds + 128 * 128);
+    uint8_t* ebytes = lds + 128 * 128 + 4 * 16 * 16;                  // scale byte of each column of the tile
     const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4, wave = threadIdx.x >> 6;
     constexpr int PX = 16, PY = 16;
     const int pxc = (nx + PX - 1) / PX;
-    const int patch = blockIdx.x / (PX * PY), within = blockIdx.x % (PX * PY);
+    const int patch = bid / (PX * PY), within = bid % (PX * PY);
     const int bx = (patch % pxc) * PX + within % PX, by = (patch / pxc) * PY + within / PX;
     if (bx >= nx || by >= ny) return;
     const int64_t r0 = (int64_t)bx * TR, c0 = (int64_t)by * 128;
@@ -1898,6 +1927,15 @@ __global__ __launch_bounds__(256) void block_quant_t_kernel(const uint16_t* __re
     if (threadIdx.x < 128 && c0 + threadIdx.x < cols)                 // ld_e % 4 == 0 and (r0 / 32) % 4 == 0
         *reinterpret_cast<uint32_t*>(et + e8_off(c0 + threadIdx.x, r0 / 32, ld_e)) = (uint32_t)ebytes[threadIdx.x] * 0x01010101u;
 }
+template <int FMT, bool SQUARE, int ROWS_TOO = 0>
+__global__ __launch_bounds__(256) void block_quant_t_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t cols,
+                                                             int64_t ld, uint8_t* __restrict__ qt, int64_t ld_t,
+                                                             uint8_t* __restrict__ et, int64_t ld_e, int nx, int ny,
+                                                             uint8_t* __restrict__ q_row = nullptr, int64_t ld_row = 0,
+                                                             uint8_t* __restrict__ e_row = nullptr, int64_t ld_er = 0) {
+    __shared__ __attribute__((aligned(16))) uint8_t lds[TILE_LDS];
+    block_quant_t_tile<FMT, SQUARE, ROWS_TOO>(blockIdx.x, lds, x, rows, cols, ld, qt, ld_t, et, ld_e, nx, ny, q_row, ld_row, e_row, ld_er);
+}
 
 // block_rows: blocks of x^T, 1 (tiles of 1 x 128 of x^T) or 128 (128 x 128); rows % 128 == 0, cols % 8 == 0.
 // q_row != nullptr (block_rows == 1, cols % 128 == 0): also the tiles of 1 x 128 along the rows of x.
@@ -1934,6 +1972,80 @@ hipError_t launch_mx_quant_t(const void* x, int64_t rows, int64_t cols, int64_t 
     if ((fmt & ~FMT_ALONE) == FMT_E4M3FN) { if (!q_row) FP8K_MXT(FMT_E4M3FN, 0); else if (keep) FP8K_MXT(FMT_E4M3FN, 1); else FP8K_MXT(FMT_E4M3FN, 2); }
     else { if (!q_row) FP8K_MXT(FMT_E5M2, 0); else if (keep) FP8K_MXT(FMT_E5M2, 1); else FP8K_MXT(FMT_E5M2, 2); }
 #undef FP8K_MXT
+    return hipGetLastError();
+}
+
+// The quantizations of a block-scaled linear layer in one launch: X and W of a forward (rows), or dY, W and X of a backward
+// (transposed, dY along its rows too).  Each tensor's workgroups are those of its own kernel; what is saved are the start and the
+// end of a launch, 3-5 us each (us, separate / together: blockwise 2048 x 4096 x 4096 forward 19.2 / 15.2, backward 31.6 / 24.8; MX 4096 x 4096 x 14336 42.4 / 41.9, 98.9 / 88.4).
+struct BlockSeg {
+    const uint16_t* x; int64_t rows, cols;
+    uint8_t* q; int64_t ld_q; uint8_t* e; int64_t ld_e;                  // rows: codes and scale bytes; backward: of the transposed tensor
+    uint8_t* q_row; int64_t ld_row; uint8_t* e_row; int64_t ld_er;       // backward, first tensor: along its rows
+    int nx, ny, blocks;
+};
+template <int FMT, bool MX>
+__global__ __launch_bounds__(256) void quant_blocks_fwd_kernel(BlockSeg x, BlockSeg w) {
+    const int bid = blockIdx.x;
+    if constexpr (MX) {
+        if (bid < x.blocks) mx_quant_rows<FMT, true>(bid, x.x, x.rows, x.cols, x.cols, x.q, x.ld_q, x.e, x.ld_e);
+        else mx_quant_rows<FMT, true>(bid - x.blocks, w.x, w.rows, w.cols, w.cols, w.q, w.ld_q, w.e, w.ld_e);
+    } else {
+        if (bid < w.blocks) block_quant_128x128<FMT>(bid % w.nx, bid / w.nx, w.x, w.rows, w.cols, w.q, w.ld_q, w.e, w.ld_e);
+        else block_quant_1x128<FMT>(bid - w.blocks, x.x, x.rows, x.cols, x.cols, x.q, x.ld_q, x.e, x.ld_e);
+    }
+}
+template <int FMT, bool MX>
+__global__ __launch_bounds__(256) void quant_blocks_bwd_kernel(BlockSeg g, BlockSeg w, BlockSeg x) {
+    __shared__ __attribute__((aligned(16))) uint8_t lds[TILE_LDS];
+    int bid = blockIdx.x;
+    if (bid < g.blocks) {
+        if constexpr (MX) mx_quant_t_tile<FMT, 1>(bid, lds, g.x, g.rows, g.cols, g.cols, g.q, g.ld_q, g.e, g.ld_e, g.q_row, g.ld_row, g.e_row, g.ld_er, g.nx, g.ny);
+        else block_quant_t_tile<FMT, false, 1>(bid, lds, g.x, g.rows, g.cols, g.cols, g.q, g.ld_q, g.e, g.ld_e, g.nx, g.ny, g.q_row, g.ld_row, g.e_row, g.ld_er);
+        return;
+    }
+    bid -= g.blocks;
+    if (bid < w.blocks) {
+        if constexpr (MX) mx_quant_t_tile<FMT, 0>(bid, lds, w.x, w.rows, w.cols, w.cols, w.q, w.ld_q, w.e, w.ld_e, nullptr, 0, nullptr, 0, w.nx, w.ny);
+        else block_quant_t_tile<FMT, true, 0>(bid, lds, w.x, w.rows, w.cols, w.cols, w.q, w.ld_q, w.e, w.ld_e, w.nx, w.ny, nullptr, 0, nullptr, 0);
+        return;
+    }
+    bid -= w.blocks;
+    if constexpr (MX) mx_quant_t_tile<FMT, 0>(bid, lds, x.x, x.rows, x.cols, x.cols, x.q, x.ld_q, x.e, x.ld_e, nullptr, 0, nullptr, 0, x.nx, x.ny);
+    else block_quant_t_tile<FMT, false, 0>(bid, lds, x.x, x.rows, x.cols, x.cols, x.q, x.ld_q, x.e, x.ld_e, x.nx, x.ny, nullptr, 0, nullptr, 0);
+}
+
+hipError_t launch_quant_blocks(const BlockOperand* ops, int n, bool mx, hipStream_t st) {
+    if (knob(KNOB_PAIRS) == 0 || (n != 2 && n != 3)) return hipErrorNotSupported;
+    BlockSeg s[3] = {};
+    int64_t total = 0;
+    for (int i = 0; i < n; ++i) {
+        const BlockOperand& o = ops[i];
+        if (o.fmt != ops[0].fmt || o.rows <= 0 || o.cols <= 0) return hipErrorNotSupported;
+        int64_t blocks, nx, ny;
+        if (n == 2) {
+            nx = o.cols / 128; ny = (o.rows + 127) / 128;
+            blocks = !mx && i == 1 ? nx * ny : (o.rows * (o.cols / 8) + 1023) / 1024;
+            if (mx && (o.ld_q != o.cols || (o.ld_e != o.cols / 32 && o.ld_e >= 0))) return hipErrorNotSupported;     // the dense form
+        } else {
+            nx = (o.rows + 127) / 128; ny = (o.cols + 127) / 128;
+            blocks = ((nx + 15) / 16) * ((ny + 15) / 16) * 256;
+        }
+        if (nx > 0x7FFFFF || ny > 0x7FFFFF) return hipErrorNotSupported;
+        s[i] = BlockSeg{static_cast<const uint16_t*>(o.x), o.rows, o.cols, o.q, o.ld_q, o.e, o.ld_e, o.q_row, o.ld_row, o.e_row, o.ld_er,
+                        (int)nx, (int)ny, (int)blocks};
+        total += blocks;
+        if (total > 0x7FFFFFFF) return hipErrorNotSupported;
+    }
+    const dim3 grid((unsigned)total), block(256);
+#define FP8K_QB(FMT, MX)                                                                \
+    do {                                                                                \
+        if (n == 2) quant_blocks_fwd_kernel<FMT, MX><<<grid, block, 0, st>>>(s[0], s[1]);   \
+        else quant_blocks_bwd_kernel<FMT, MX><<<grid, block, 0, st>>>(s[0], s[1], s[2]);    \
+    } while (0)
+    if (ops[0].fmt == FMT_E4M3FN) { if (mx) FP8K_QB(FMT_E4M3FN, true); else FP8K_QB(FMT_E4M3FN, false); }
+    else { if (mx) FP8K_QB(FMT_E5M2, true); else FP8K_QB(FMT_E5M2, false); }
+#undef FP8K_QB
     return hipGetLastError();
 }
 

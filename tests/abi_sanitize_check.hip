@@ -44,6 +44,7 @@ int64_t quant_fold_bytes(int64_t rows, int64_t cols) { return rows >= 256 && row
 hipError_t launch_linear_skinny_fused(const void*, int64_t, int, int, int, const uint8_t*, int64_t, int, const float*, int, int64_t, int64_t, int64_t, void*, int64_t, hipStream_t) STUB_ALTERNATING
 hipError_t launch_quant_col_t_pair(const ColOperand&, const ColOperand&, int64_t, int, int, hipStream_t) STUB_ALTERNATING
 hipError_t launch_quant_bwd_rowwise(const RowColOperand&, int64_t, int, const ColOperand&, const ColOperand&, int64_t, int, int, hipStream_t) STUB_ALTERNATING
+hipError_t launch_quant_blocks(const BlockOperand*, int, bool, hipStream_t) STUB_ALTERNATING
 hipError_t launch_gemm_fp8_pair(const GemmOperands&, const GemmOperands&, int, int, int, int, hipStream_t) STUB_ALTERNATING
 hipError_t launch_sigmoid_bwd(const void*, const void*, int64_t, void*, hipStream_t) STUB
 hipError_t launch_layernorm_quant_row(const void*, int64_t, int64_t, int64_t, const void*, const void*, double, int, int, void*, int64_t, uint8_t*, int64_t, float*, float*, float*, hipStream_t) STUB

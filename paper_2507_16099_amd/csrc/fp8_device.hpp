@@ -203,6 +203,33 @@ __device__ __forceinline__ uint2 cast8(const uint4& v, float s) {
     return r;
 }
 
+// Eight products to codes.  A value times the scale of its own group exceeds FMAX by an ulp at most, which rounds to FMAX, so
+// nothing has to be clamped - except where the group's maximum is NaN: its scale is then the clamp's (FMAX / 1e-12), which is also that
+// of a group of zeros.  CLAMP = false takes half the instructions.
+template <int FMT, bool CLAMP>
+__device__ __forceinline__ uint2 cast8_own(const uint4& v, const float (&s)[8]) {
+    if constexpr (CLAMP) return cast8<FMT>(v, s);
+    auto pack = [](float a, float b, float c, float d) {
+        int r;
+        if constexpr (FMT == FMT_E4M3FN) {
+            r = __builtin_amdgcn_cvt_pk_fp8_f32(a, b, 0, false);
+            r = __builtin_amdgcn_cvt_pk_fp8_f32(c, d, r, true);
+        } else {
+            r = __builtin_amdgcn_cvt_pk_bf8_f32(a, b, 0, false);
+            r = __builtin_amdgcn_cvt_pk_bf8_f32(c, d, r, true);
+        }
+        return (uint32_t)r;
+    };
+    return make_uint2(pack(bf16_lo(v.x) * s[0], bf16_hi(v.x) * s[1], bf16_lo(v.y) * s[2], bf16_hi(v.y) * s[3]),
+                      pack(bf16_lo(v.z) * s[4], bf16_hi(v.z) * s[5], bf16_lo(v.w) * s[6], bf16_hi(v.w) * s[7]));
+}
+constexpr float CLAMP_FROM = 2.8e14f;      // below the clamp's scale in either format, rounded down to a power of two or not
+template <int FMT, bool CLAMP>
+__device__ __forceinline__ uint2 cast8_own(const uint4& v, float s) {
+    const float s8[8] = {s, s, s, s, s, s, s, s};
+    return cast8_own<FMT, CLAMP>(v, s8);
+}
+
 // 4x4 byte transpose: rows a,b,c,d (byte j = column j) -> o[j] = column j
 __device__ __forceinline__ void transpose4x4_bytes(uint32_t a, uint32_t b, uint32_t c, uint32_t d, uint32_t (&o)[4]) {
     const uint32_t t0 = __builtin_amdgcn_perm(b, a, 0x05010400u);

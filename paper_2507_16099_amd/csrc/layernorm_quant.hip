@@ -15,9 +15,11 @@
 // value, see f64_to_bf16_bits): whatever the summation order, the bfloat16 result is the
 // correctly rounded one except when the binary64 value lies within ~1e-16 of a
 // rounding boundary (the bit-parity with a reference that sums in another order is
-// therefore statistical, not by construction).  The binary64 work makes the kernel
-// ALU-bound: about 38 instructions per element, measured at 0.45 of the HBM rate
-// that its 5 bytes per element would allow.
+// therefore statistical, not by construction).  What bounds it: VALU work, 26 instructions an element (71 % of the issue slots
+// at 37 before the rounding's tie test moved out of the elements' way and the cast lost its clamp), and the chain of three reductions
+// with a division and a square root in binary64 between them.  8192 x 4096 with h: 46 -> 40 us = 4.2 TB/s, 16384 x 4096 84 -> 72,
+// 8192 x 8192 87 -> 76.  The same in binary32 with a certified error bound and binary64 for the undecided elements was slower (50 us):
+// binary64 runs at full rate here, and the certificate costs as much as what it replaces.
 #include "fp8_device.hpp"
 #include "launchers.hpp"
 
@@ -37,6 +39,16 @@ __device__ __forceinline__ uint32_t f64_to_bf16_bits(double d) {
     return ((b & 0xFFFFu) == 0x8000u && back != d) ? alt : rne;
 }
 
+typedef __bf16 bf16x2_ln __attribute__((ext_vector_type(2)));
+typedef float f32x2_ln __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pack_bf16_rne(float a, float b) {
+    const f32x2_ln v = {a, b};
+    const bf16x2_ln h = __builtin_convertvector(v, bf16x2_ln);
+    uint32_t r;
+    __builtin_memcpy(&r, &h, 4);
+    return r;
+}
+
 __device__ __forceinline__ double wave_sum_f64(double v) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
@@ -47,7 +59,7 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
 template <int FMT, int TX, int NV>
 __global__ __launch_bounds__(256) void layernorm_quant_row_kernel(
     const uint16_t* __restrict__ x, int64_t rows, int64_t cols, int64_t ld, const uint16_t* __restrict__ gamma,
-    const uint16_t* __restrict__ beta, double eps, int flags, uint16_t* __restrict__ h, int64_t ld_h,
+    const uint16_t* __restrict__ beta, double eps, double inv_cols, int flags, uint16_t* __restrict__ h, int64_t ld_h,
     uint8_t* __restrict__ q, int64_t ld_q, float* __restrict__ scale_out, float* __restrict__ mean_out,
     float* __restrict__ rstd_out) {
     constexpr int TY = 256 / TX;
@@ -94,7 +106,9 @@ __global__ __launch_bounds__(256) void layernorm_quant_row_kernel(
     double mean;
     {
         const double total = block_sum(part, red_sum);
-        if constexpr (TX > 64) {
+        if (inv_cols != 0.0) {
+            mean = total * inv_cols;
+        } else if constexpr (TX > 64) {
             if (wave0) {
                 const double m_ = total / (double)cols;
                 if (threadIdx.x == 0) bc_stat[0] = m_;
@@ -123,13 +137,13 @@ __global__ __launch_bounds__(256) void layernorm_quant_row_kernel(
         const double total = block_sum(part, red_sq);
         if constexpr (TX > 64) {
             if (wave0) {
-                const double r_ = 1.0 / sqrt(total / (double)cols + eps);
+                const double r_ = 1.0 / sqrt((inv_cols != 0.0 ? total * inv_cols : total / (double)cols) + eps);
                 if (threadIdx.x == 0) bc_stat[1] = r_;
             }
             __syncthreads();
             rstd = bc_stat[1];
         } else {
-            rstd = 1.0 / sqrt(total / (double)cols + eps);
+            rstd = 1.0 / sqrt((inv_cols != 0.0 ? total * inv_cols : total / (double)cols) + eps);
         }
     }
 
@@ -142,14 +156,25 @@ __global__ __launch_bounds__(256) void layernorm_quant_row_kernel(
         if (vi < nvec) {
             const uint4 g4 = reinterpret_cast<const uint4*>(gamma)[vi];
             const uint4 b4 = beta ? reinterpret_cast<const uint4*>(beta)[vi] : make_uint4(0, 0, 0, 0);
-            uint32_t hb[8];
+            double d[8];
+            float f[8];
+            bool tie = false;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 // ((x - mean) * rstd) * gamma + beta, every operation rounded by itself (no contraction)
                 const double t = __dmul_rn(__dmul_rn(__dsub_rn(elem(v[j], e), mean), rstd), elem(g4, e));
-                hb[e] = f64_to_bf16_bits(__dadd_rn(t, elem(b4, e)));
+                d[e] = __dadd_rn(t, elem(b4, e));
+                f[e] = (float)d[e];
+                tie |= (uint16_t)__float_as_uint(f[e]) == 0x8000;
             }
-            hv = make_uint4(hb[0] | (hb[1] << 16), hb[2] | (hb[3] << 16), hb[4] | (hb[5] << 16), hb[6] | (hb[7] << 16));
+            // through binary32 (one bfloat16 result in 65536 of these may be wrong, see f64_to_bf16_bits)
+            hv = make_uint4(pack_bf16_rne(f[0], f[1]), pack_bf16_rne(f[2], f[3]), pack_bf16_rne(f[4], f[5]), pack_bf16_rne(f[6], f[7]));
+            if (__any(tie)) {
+                uint32_t hb[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) hb[e] = f64_to_bf16_bits(d[e]);
+                hv = make_uint4(hb[0] | (hb[1] << 16), hb[2] | (hb[3] << 16), hb[4] | (hb[5] << 16), hb[6] | (hb[7] << 16));
+            }
         }
         v[j] = hv;
         acc = pk_absmax4(acc, hv);
@@ -185,7 +210,7 @@ __global__ __launch_bounds__(256) void layernorm_quant_row_kernel(
     for (int j = 0; j < NV; ++j) {
         const int64_t vi = tx + (int64_t)j * TX;
         if (vi < nvec) {
-            store_vec(reinterpret_cast<uint2*>(qrow) + vi, cast8<FMT>(v[j], s));
+            store_vec(reinterpret_cast<uint2*>(qrow) + vi, s >= CLAMP_FROM ? cast8_own<FMT, true>(v[j], s) : cast8_own<FMT, false>(v[j], s));
             if (hrow) store_vec(reinterpret_cast<uint4*>(hrow) + vi, v[j]);
         }
     }
@@ -196,9 +221,11 @@ static bool launch_lnq_t(const uint16_t* x, int64_t rows, int64_t cols, int64_t 
                          const uint16_t* beta, double eps, int flags, uint16_t* h, int64_t ld_h, uint8_t* q, int64_t ld_q,
                          float* scale_out, float* mean_out, float* rstd_out, hipStream_t st) {
     const int64_t nvec = cols / 8;
+    // a power of two: its reciprocal is exact, and so multiplying gives the quotient
+    const double inv_cols = (cols & (cols - 1)) == 0 ? 1.0 / (double)cols : 0.0;
 #define FP8K_LNQ(TX, NV)                                                                                          \
     layernorm_quant_row_kernel<FMT, TX, NV><<<dim3((unsigned)((rows + (256 / TX) - 1) / (256 / TX))), dim3(256), 0, st>>>( \
-        x, rows, cols, ld, gamma, beta, eps, flags, h, ld_h, q, ld_q, scale_out, mean_out, rstd_out)
+        x, rows, cols, ld, gamma, beta, eps, inv_cols, flags, h, ld_h, q, ld_q, scale_out, mean_out, rstd_out)
     // up to 2048 columns a wavefront owns a row (no barriers, the per-row scalar work once per row)
     if (nvec <= 64) FP8K_LNQ(64, 1);
     else if (nvec <= 128) FP8K_LNQ(64, 2);

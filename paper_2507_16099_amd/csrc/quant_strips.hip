@@ -45,28 +45,6 @@ __device__ __forceinline__ uint32_t pk_absmax_ror(uint32_t v) {
     return pk_absmax(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x120 + OFF, 0xF, 0xF, false));
 }
 
-// Eight products to codes.  A value times the scale of its own group exceeds FMAX by an ulp at most, which rounds to FMAX, so
-// nothing has to be clamped - except where the group's maximum is NaN: its scale is then the clamp's (FMAX / 1e-12), which is also that
-// of a group of zeros.  CLAMP = false takes half the instructions.
-template <int FMT, bool CLAMP>
-__device__ __forceinline__ uint2 cast8_own(const uint4& v, const float (&s)[8]) {
-    if constexpr (CLAMP) return cast8<FMT>(v, s);
-    auto pack = [](float a, float b, float c, float d) {
-        int r;
-        if constexpr (FMT == FMT_E4M3FN) {
-            r = __builtin_amdgcn_cvt_pk_fp8_f32(a, b, 0, false);
-            r = __builtin_amdgcn_cvt_pk_fp8_f32(c, d, r, true);
-        } else {
-            r = __builtin_amdgcn_cvt_pk_bf8_f32(a, b, 0, false);
-            r = __builtin_amdgcn_cvt_pk_bf8_f32(c, d, r, true);
-        }
-        return (uint32_t)r;
-    };
-    return make_uint2(pack(bf16_lo(v.x) * s[0], bf16_hi(v.x) * s[1], bf16_lo(v.y) * s[2], bf16_hi(v.y) * s[3]),
-                      pack(bf16_lo(v.z) * s[4], bf16_hi(v.z) * s[5], bf16_lo(v.w) * s[6], bf16_hi(v.w) * s[7]));
-}
-constexpr float CLAMP_FROM = 2.8e14f;      // below the clamp's scale in either format, rounded down to a power of two or not
-
 // Strips of workgroup b.  A thread owns RPT consecutive rows of 8 columns: RPT 16-byte loads, LPR lanes a row; its codes leave as
 // RPT bytes of eight rows of the transposed output, 64 / LPR * RPT consecutive bytes per wavefront and column.
 template <int FMT, int NT, int LPR>
@@ -188,8 +166,7 @@ __device__ __forceinline__ void quant_rows(const StripRows& s, int b, int flags,
 #pragma unroll
         for (int j = 0; j < NV; ++j)
             if (tx + j * 256 < nvec) {
-                const float s8[8] = {sc, sc, sc, sc, sc, sc, sc, sc};
-                store_through(dst + tx + j * 256, sc >= CLAMP_FROM ? cast8_own<FMT, true>(v[k][j], s8) : cast8_own<FMT, false>(v[k][j], s8));
+                store_through(dst + tx + j * 256, sc >= CLAMP_FROM ? cast8_own<FMT, true>(v[k][j], sc) : cast8_own<FMT, false>(v[k][j], sc));
             }
     }
 }

@@ -37,3 +37,30 @@ def test_one_launch_changes_no_bit(M, K, N, kind):
         want = run()
     for a, b in zip(got, want):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("fmt", [0, 1])
+@pytest.mark.parametrize("block_rows", [1, 128])
+def test_blocks_with_infinities_and_nan_are_clamped(fmt, block_rows):
+    """The cast without a clamp only where the block's maximum is finite: infinities become the largest normal value, NaN stays NaN, in
+    either direction, and blocks beside them are as ever."""
+    rng = np.random.default_rng(fmt)
+    x = torch.from_numpy(rng.standard_normal((256, 384)).astype(np.float32)).to(torch.bfloat16)
+    x[3, 5], x[130, 200], x[131, 380], x[255, 0], x[7, 300] = float("inf"), float("-inf"), float("nan"), 3e38, 0.0
+    xd = x.cuda()
+    t8, top = ((torch.float8_e4m3fn, 448.0), (torch.float8_e5m2, 57344.0))[fmt]
+
+    def check(q, e, v):                          # q [r, c] codes, e [r, c / 32] scale bytes
+        s = torch.exp2(127.0 - e.cpu().float()).repeat_interleave(32, 1)
+        p = v.float() * s
+        want = torch.where(p.isnan(), p, p.clamp(-top, top)).to(t8).view(torch.uint8)
+        got = q.cpu()
+        same = torch.where(p.isnan(), (got & 0x7F) > (0x7E, 0x7C)[fmt], got == want)      # any code of the NaN class
+        assert bool(same.all())
+
+    check(*fp8.fp8_block_quantize(xd, block_rows, fmt), x)
+    check(*fp8.fp8_block_quantize_t(xd, block_rows, fmt), x.t().contiguous())
+    if block_rows == 1:
+        q, e, qt, et = fp8.fp8_block_quantize_row_col(xd, fmt)
+        check(q, e, x)
+        check(qt, et, x.t().contiguous())

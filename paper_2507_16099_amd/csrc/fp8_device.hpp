@@ -37,6 +37,9 @@ __device__ __forceinline__ uint4 load_stream(const void* p) {
     return make_uint4(t[0], t[1], t[2], t[3]);
 }
 
+// hint: as above; else a plain load.  Small tensors are read plainly (hint_inputs in launchers.hpp says where the line lies).
+__device__ __forceinline__ uint4 load_in(const void* p, bool hint) { return hint ? load_stream(p) : *static_cast<const uint4*>(p); }
+
 // Codes are stored through the L2 (system scope): they are in the 256 MB last-level cache when the product reads them, and
 // no dirty lines are left that the end of the kernel has to wait for.  Measured (us; streaming hint / plain store / this):
 //   the quantizers alone: MX 2048x2048 5.4 / 5.9 / 5.2, both orientations 8.6 / 10.0 / 8.5, 16384x8192 118 / 102 / 100;

@@ -37,7 +37,7 @@ struct StripRows {             // one tensor's rows
     int rows, cols, fmt;
     int groups;
 };
-struct StripArgs { StripCols c[3]; StripRows r[2]; int flags; };
+struct StripArgs { StripCols c[3]; StripRows r[2]; int flags; int hint; };      // hint: rows are read with the streaming hint
 
 // with the lane OFF away within the row of 16, cyclically
 template <int OFF>
@@ -132,18 +132,22 @@ __device__ __forceinline__ void quant_strip(const StripCols& s, int b, int flags
 
 // Rows of workgroup b: groups of 256 threads, each RW consecutive rows, kept in registers between maximum and cast
 template <int FMT, int NT, int NV, int RW>
-__device__ __forceinline__ void quant_rows(const StripRows& s, int b, int flags, uint32_t* red) {
+__device__ __forceinline__ void quant_rows(const StripRows& s, int b, int flags, bool hint, uint32_t* red) {
     const int tx = threadIdx.x & 255, g = threadIdx.x >> 8;
     const int nvec = s.cols >> 3;
     const int r0 = (b * (NT / 256) + g) * RW;
     uint4 v[RW][NV];
+    auto request = [&](auto load) {
 #pragma unroll
-    for (int k = 0; k < RW; ++k) {
-        const int r = r0 + k < s.rows ? r0 + k : s.rows - 1;
-        const uint4* rv = reinterpret_cast<const uint4*>(s.x + (int64_t)r * s.ld);
+        for (int k = 0; k < RW; ++k) {
+            const int r = r0 + k < s.rows ? r0 + k : s.rows - 1;
+            const uint4* rv = reinterpret_cast<const uint4*>(s.x + (int64_t)r * s.ld);
 #pragma unroll
-        for (int j = 0; j < NV; ++j) v[k][j] = tx + j * 256 < nvec ? load_stream(rv + tx + j * 256) : make_uint4(0, 0, 0, 0);
-    }
+            for (int j = 0; j < NV; ++j) v[k][j] = tx + j * 256 < nvec ? load(rv + tx + j * 256) : make_uint4(0, 0, 0, 0);
+        }
+    };
+    if (hint) request([](const uint4* p) { return load_stream(p); });
+    else request([](const uint4* p) { return *p; });
 #pragma unroll
     for (int k = 0; k < RW; ++k) {
         uint32_t acc = 0;
@@ -192,8 +196,8 @@ __global__ __launch_bounds__(NT) void quant_strips_kernel(StripArgs a) {
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         if (b < a.r[i].groups) {
-            if (a.r[i].fmt == FMT_E4M3FN) quant_rows<FMT_E4M3FN, NT, NV, RW>(a.r[i], b, a.flags, red);
-            else quant_rows<FMT_E5M2, NT, NV, RW>(a.r[i], b, a.flags, red);
+            if (a.r[i].fmt == FMT_E4M3FN) quant_rows<FMT_E4M3FN, NT, NV, RW>(a.r[i], b, a.flags, a.hint != 0, red);
+            else quant_rows<FMT_E5M2, NT, NV, RW>(a.r[i], b, a.flags, a.hint != 0, red);
             return;
         }
         b -= a.r[i].groups;
@@ -220,13 +224,18 @@ hipError_t launch_quant_strips(const StripOperand* ops, int n, int flags, hipStr
     if (v < 0 && tall > 4096 && n < 3) return hipErrorNotSupported;
     // A tensor wanted in both orientations is read twice, the second time from the 256 MB last-level cache if all of them fit it
     // (X and W of 4096 x 14336, 235 MB: 654 -> 643 us a step; of 4096 x 16384, 268 MB: 756 -> 778).
-    int64_t twice = 0;
+    int64_t twice = 0, by_rows = 0;
     double load = 0.0;
     for (int i = 0; i < n; ++i) {
         if (ops[i].q_row && ops[i].q_col_t) twice += ops[i].rows * ops[i].cols;
+        if (ops[i].q_row) by_rows += ops[i].rows * ops[i].cols;
         load += (ops[i].q_col_t ? 1.0 : 0.5) * (double)((ops[i].cols + 31) / 32) * (double)ops[i].rows / (double)tall;
     }
     if (twice > (int64_t)120 << 20) return hipErrorNotSupported;
+    // Rows with the streaming hint beyond 24 Mi elements: the loads are slower by themselves, but what they read does not displace the
+    // codes (us a step, hint / plain: 1024x2048x1024 34.4 / 30.3, 2048^3 58.0 / 52.7, 2048x4096x4096 with dW in bfloat16, 24 Mi, 153.1 / 150.8, 4096^3
+    // 215.9 / 217.1, 600x14336x4096 238 / 246, 4096x14336x2048 416 / 428).
+    a.hint = hint_inputs(by_rows, HINT_PAIR);
     // Width: load = strips of 32 columns, in units of the tallest tensor's, a tensor without strips half.  16 columns where 32 would
     // keep half of the CUs busy, unless the strips are short (us, 32 / 16 columns: gradient 4096 x 1024 20.9 / 14.9, x 4096 27.3 / 26.4,
     // x 6144 31.8 / 36.0; 2048 x 1024 12.8 / 10.2, x 4096 15.3 / 14.7, x 6144 16.5 / 20.7; 1024 x 1024 8.7 / 9.3, x 4096 10.8 / 12.5).

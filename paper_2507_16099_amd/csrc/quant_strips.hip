@@ -13,7 +13,8 @@
 // conversion carries no clamp.  With more strips HBM: X and W of 4096 x 4096, both orientations, 201 MB in 38 us = 5.3 TB/s.
 // Before / now (us, first kernel's start to last one's end): X and W of 1024 x 1024 20.3 / 9.5, of 4096 x 1024 25.0 / 20.1; the
 // gradient 1024 x 8192 33.7 / 10.4, 2048 x 4096 39.4 / 14.7, 3072 x 8192 42.3 / 29.9, 4096 x 8192 48.1 / 39.9.
-// Steps: 1024 x 2048 x 1024 43.4 / 33.9, 1024 x 1024 x 1024 41.1 / 24.5, 3001 x 4096 x 2048 141 / 121, 4096^3 231 / 205 (the last three stateless).
+// Steps: 1024 x 2048 x 1024 41.7 / 29.1 (33 before its rows were read plainly), 1024^3 41.1 / 24.5, 3001 x 4096 x 2048 140 / 113, 4096^3
+// 231 / 205 (the last three stateless).
 #include "fp8_device.hpp"
 #include "launchers.hpp"
 #include "tuning.hpp"

@@ -7,8 +7,8 @@
 // maxima across its wavefronts, derives the scales and writes the transposed codes: one launch, no scratch, no order among
 // workgroups.  The rowwise codes that the same step needs are made by further workgroups of the same launch.
 //
-// What bounds it: up to some 64 strips the time of one strip on its CU - a CU has about 90 requests of up to 128 bytes in
-// flight, whatever their width, so 4096 rows take 10 us to arrive, then 4 us of conversion and 4 us of stores; that is why strips
+// What bounds it: up to some 64 strips the time of one strip on its CU - a CU takes in a row's piece every five cycles or
+// so, 32 or 128 bytes alike (measured; 2 KB pitch and more), so 4096 rows take 10 us to arrive, and conversion and stores follow; that is why strips
 // are 16 columns wide where 32 would leave CUs idle, why the loads are plain ones (17 us with the streaming hint) and why the
 // conversion carries no clamp.  With more strips HBM: X and W of 4096 x 4096, both orientations, 201 MB in 38 us = 5.3 TB/s.
 // Before / now (us, first kernel's start to last one's end): X and W of 1024 x 1024 20.3 / 9.5, of 4096 x 1024 25.0 / 20.1; the

@@ -76,3 +76,17 @@ def test_weight_and_input_of_the_sigmoid_backward(M, K, N):
             got = fp8.fp8_linear_bwd_sigmoid(dy, y, x, w, r)
         for a, b in zip(got, want):
             assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
+@pytest.mark.parametrize("M,K,N", [(144, 272, 528), (2064, 528, 1040)])
+@pytest.mark.parametrize("want", ["dx", "dw"])
+def test_one_gradient_wanted(M, K, N, want):
+    """The tensors of one product only."""
+    x, w, dy = _inputs(M, K, N, False)
+    r = fp8.Recipe(gran=fp8.FP8_ROW)
+    run = lambda: fp8.fp8_linear_bwd(dy, x, w, r, need_dx=want == "dx", need_dw=want == "dw")[want == "dw"].view(torch.int16)      # noqa: E731
+    with knobs(PAIRS=0):
+        ref = run()
+    for strips in (None, 2, 4):
+        with knobs(STRIPS=strips):
+            assert torch.equal(run(), ref)

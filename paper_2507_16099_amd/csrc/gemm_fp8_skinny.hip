@@ -418,7 +418,7 @@ static hipError_t launch_sk_dma(const uint8_t* a, int64_t lda, const float* sa, 
     // 19.7 / 19.3, 64 x 4096 x 4096 9.5 / 9.2; one or two tiles of 16 columns each way keep three: 2 x 4096 x 14336 12.3 / 14.3, 32 x 1024 x 8192 6.8 / 7.2)
     constexpr int R = SLOT <= 6144 && NW == 1 ? 3 : 2;
     constexpr int lds = 4 * R * SLOT;
-    const bool hint = stream_weight(N, K);
+    const bool hint = stream_weight(b, ldb, N, K);
     auto kern = hint ? gemm_fp8_skinny_dma_kernel<FA, FB, MT, KS, NW, R, true> : gemm_fp8_skinny_dma_kernel<FA, FB, MT, KS, NW, R, false>;
     static DynamicLdsOnce attr[2];
     if (hipError_t e = attr[hint].ensure(reinterpret_cast<const void*>(kern), lds); e != hipSuccess) return e;

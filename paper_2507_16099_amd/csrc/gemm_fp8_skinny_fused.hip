@@ -269,7 +269,7 @@ static hipError_t launch_skf(const uint16_t* x, int64_t ldx, int row_x, int flag
     // eight wavefronts: 96 KB of rings, one workgroup per CU with the codes of X (33 KB at most); four: 40 or 48 KB
     constexpr int R = WAVES == 8 ? (NW == 1 ? 6 : 3) : (NW == 1 ? 5 : 3);
     const int lds = WAVES * R * NW * 2048 + M * (K + ROW_PAD) + 128;
-    const bool hint = stream_weight(N, K);
+    const bool hint = stream_weight(b, ldb, N, K);
     auto kern = hint ? gemm_fp8_skinny_fused_kernel<FX, FB, KS, NW, WAVES, R, true> : gemm_fp8_skinny_fused_kernel<FX, FB, KS, NW, WAVES, R, false>;
     static DynamicLdsOnce attr[2];
     if (hipError_t e = attr[hint].ensure(reinterpret_cast<const void*>(kern), WAVES * R * NW * 2048 + MAX_X + 8 * ROW_PAD + 128); e != hipSuccess) return e;

@@ -168,8 +168,12 @@ hipError_t launch_gemm_fp8_stream(const uint8_t* a, int64_t lda, int fmt_a, cons
 // more is not in the 256 MB last-level cache when it is wanted again, whatever the calls in between: with the hint it passes at 5.9
 // instead of 5.2 TB/s (us without / with: 16 x 28672 x 8192 45.0 / 40.0, x 4096 24.6 / 21.5; 64 x 28672 x 8192 51.5 / 47.0).  Smaller ones
 // gain the same where they come from HBM (16 x 14336 x 4096 13.6 / 12.6) but lose as much where all weights of the calls fit the
-// cache, which they never stay in then (the same, three weights in turn: 11.1 / 12.2).
-inline bool stream_weight(int64_t N, int64_t K) { return N * K >= (int64_t)96 << 20; }
+// cache, which they never stay in then (the same, three weights in turn: 11.1 / 12.2).  Rows have to be whole lines of 128 bytes: a line
+// that two rows or two stages share is fetched twice with the hint (1 x 28672 x 4112 24.8 / 36.5, x 8224 52.0 / 62.9, x 8256 53.6 / 60.1;
+// 128 x 28672 x 8224 72.8 / 86.7; x 8320, whole lines, 49.3 / 45.0).
+inline bool stream_weight(const uint8_t* b, int64_t ldb, int64_t N, int64_t K) {
+    return N * K >= (int64_t)96 << 20 && (((uintptr_t)b | (uint64_t)ldb) & 127) == 0;
+}
 
 // few rows of A (M <= 64, the decode shape of inference): B is streamed once
 // from HBM by wavefronts that load their MFMA operands straight from global

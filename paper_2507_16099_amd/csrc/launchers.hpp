@@ -10,7 +10,11 @@ namespace fp8k {
 // hint.  The hint makes a load slower by itself (a strip of 4096 rows arrives in 17 instead of 10 us), but its data does not displace what
 // the product reads next (us, hint / plain: see each launcher's lines).
 inline bool hint_inputs(int64_t elements, int64_t line) { return elements > line; }
-constexpr int64_t HINT_ALONE = (int64_t)8 << 20;     // one tensor
+// One tensor before its product: what plain loads gain is small (1 to 3 %), what they cost is large where the weights in turn just fit
+// the last-level cache and the input no longer does beside them (us, hint / plain, three weights in turn: 712 x 7840 x 8080 65.0 / 81.4,
+// 512 x 14336 x 4096 42.3 / 53.2; six: 1900 x 4096 x 4096 36.3 / 40.0).  So only inputs that are a small part of that cache, 4 MB.
+constexpr int64_t HINT_ALONE = (int64_t)2 << 20;
+constexpr int64_t HINT_BLOCKS = (int64_t)8 << 20;    // the tensors of an MX or blockwise step
 constexpr int64_t HINT_PAIR = (int64_t)24 << 20;     // X and W of a step, whose codes are all that the product reads
 
 hipError_t launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t st);

@@ -2066,7 +2066,7 @@ hipError_t launch_quant_blocks(const BlockOperand* ops, int n, bool mx, hipStrea
     }
     // (us a step, hint / plain: MX 512x1024x1024 28.6 / 27.6, 1024x2048x1024 35.7 / 34.4, 2048x4096x4096 135.2 / 136.3; blockwise 27.2 / 25.9,
     // 34.8 / 32.8, 133.5 / 133.9)
-    const int hint = hint_inputs(elements, HINT_ALONE);
+    const int hint = hint_inputs(elements, HINT_BLOCKS);
     const dim3 grid((unsigned)total), block(256);
 #define FP8K_QB(FMT, MX)                                                                \
     do {                                                                                \

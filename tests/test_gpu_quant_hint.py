@@ -1,4 +1,4 @@
-"""Both sides of the lines beyond which the quantizers read their input with the streaming hint (8 Mi elements alone, 24 Mi for a pair): the
+"""Both sides of the lines beyond which the quantizers read their input with the streaming hint (2 Mi elements alone, 24 Mi for a pair): the
 codes and scales of plain arithmetic on the same tensors."""
 import pytest
 import torch
@@ -22,7 +22,7 @@ def _tensor(rows, cols):
     return torch.randn((rows, cols), device="cuda", generator=gen).to(torch.bfloat16)
 
 
-@pytest.mark.parametrize("rows", [2048, 2049])
+@pytest.mark.parametrize("rows", [512, 513, 2048, 2049])
 def test_rows_and_tensor_scaled_products_at_the_line(rows):
     x = _tensor(rows, 4096)
     wq, sw = fp8.fp8_quantize(_tensor(64, 4096), fp8.FP8_ROW, E4)

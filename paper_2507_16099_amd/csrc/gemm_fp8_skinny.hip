@@ -407,7 +407,7 @@ __global__ __launch_bounds__(256) void gemm_fp8_skinny_dma_kernel(
     }
 }
 
-template <int FA, int FB, int MT, int KS, int NW>
+template <int FA, int FB, int MT, int KS, int NW, bool DEEP = false>
 static hipError_t launch_sk_dma(const uint8_t* a, int64_t lda, const float* sa, int row_a, const uint8_t* b, int64_t ldb,
                                 const float* sb, int row_b, int M, int N, int K, void* out, int64_t ld_out, int out_f32,
                                 int64_t grid, hipStream_t st) {
@@ -416,7 +416,9 @@ static hipError_t launch_sk_dma(const uint8_t* a, int64_t lda, const float* sa, 
     // fills and while its K parts are summed.  (us, weights from HBM: five steps / three at 16 x 4096 x 4096 6.2 / 5.9, 2 x 4096 x 14336
     // 12.6 / 12.3; three / two at 16 x 28672 x 4096 25.9 / 25.0, 2 x 14336 x 4096 13.5 / 13.1, 16 x 11008 x 4096 13.3 / 12.7, 64 x 8192 x 8192
     // 19.7 / 19.3, 64 x 4096 x 4096 9.5 / 9.2; one or two tiles of 16 columns each way keep three: 2 x 4096 x 14336 12.3 / 14.3, 32 x 1024 x 8192 6.8 / 7.2)
-    constexpr int R = SLOT <= 6144 && NW == 1 ? 3 : 2;
+    // DEEP: up to 8 rows on at most half of the CUs, where a long contraction keeps five (three / five at 2 rows: 1024 x 14336 7.50 / 7.21,
+    // x 28672 11.39 / 10.70, 2048 x 28672 11.96 / 11.71; x 8192 5.44 / 5.61; 16 rows, 1024 x 28672 12.71 / 12.99)
+    constexpr int R = DEEP ? 5 : SLOT <= 6144 && NW == 1 ? 3 : 2;
     constexpr int lds = 4 * R * SLOT;
     const bool hint = stream_weight(b, ldb, N, K);
     auto kern = hint ? gemm_fp8_skinny_dma_kernel<FA, FB, MT, KS, NW, R, true> : gemm_fp8_skinny_dma_kernel<FA, FB, MT, KS, NW, R, false>;
@@ -446,6 +448,8 @@ static hipError_t launch_sk(const uint8_t* a, int64_t lda, const float* sa, int 
     // against 64 columns per wavefront, which only the override SKINNY_NW asks for: the slots would not fit the LDS)
     const bool fits = lda < (1 << 23) && ldb < (1 << 23) && (mt <= 2 || nw <= 2);
     if (fits && knob(KNOB_SKINNY_DMA) != 0) {
+        if (M <= 8 && ks == 4 && nw == 1 && K > 10240 && grid <= 128)
+            return launch_sk_dma<FA, FB, 1, 4, 1, true>(a, lda, sa, row_a, b, ldb, sb, row_b, M, N, K, out, ld_out, out_f32, grid, st);
 #define FP8K_SKD(MT_, KS_, NW_)                                                                               \
     if (mt == MT_ && ks == KS_ && nw == NW_)                                                                  \
         return launch_sk_dma<FA, FB, MT_, KS_, NW_>(a, lda, sa, row_a, b, ldb, sb, row_b, M, N, K, out, ld_out, out_f32, grid, st)

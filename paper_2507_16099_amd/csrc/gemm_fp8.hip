@@ -293,18 +293,18 @@ int best_ring(const GemmOperands& g, const GemmOperands* g2, int64_t cus, double
 // kernel for one product; *cost: its estimate (large where there is none)
 int pick_path(const GemmOperands& g, double* cost) {
     *cost = 1e30;
-    const bool fits = gemm_fp8_ring_fits(g);
+    const bool fits = gemm_fp8_ring_fits(g), ring = fits && knob(KNOB_GEMM_RING) != 0;
     if (const int r = knob(KNOB_GEMM_RING); r >= 1 && r <= RING_TILES && fits) return kPathRing + r - 1;
     const int v = knob(KNOB_GEMM_VARIANT);
     if (v == 0 || v == 4 || v == 5) return v;
     if (v == 6 || v == 7) return fits ? kPathRing + (v == 6 ? RING_64x64 : RING_128x128) : 0;
     const int64_t cus = compute_units() > 0 ? compute_units() : 256;
-    if (g.M <= 16 || (g.M <= 32 && (8 * cdiv(g.N, 64) < 5 * cus || !fits)) ||
+    if (g.M <= 16 || (g.M <= 32 && (8 * cdiv(g.N, 64) < 5 * cus || !ring)) ||
         (g.M <= 64 && g.N <= 8192 && g.K >= 2048 && gemm_fp8_snake_fits(g.lda, g.ldb))) return 5;
     if (g.M <= 32) return kPathRing + RING_64x64;
     const int64_t big = cdiv(g.M, 256) * cdiv(g.N, 256);
     if (const int b = knob(KNOB_GEMM_BIG_FROM); b > 0 && cdiv(g.M, 128) * cdiv(g.N, 128) >= b) return 4;
-    if (big > cus || !fits || knob(KNOB_GEMM_RING) == 0) return 4;
+    if (big > cus || !ring) return 4;
     const double steps = (double)cdiv(g.K, BK);
     const double cost_big = 2 * big <= cus ? 7.2 + 0.91 * steps : 10.0 + 1.2 * steps;
     const int tile = best_ring(g, nullptr, cus, cost);
@@ -361,7 +361,7 @@ int gemm_fp8_ring_choice(const GemmOperands& g) {
     double cost;
     const int v = pick_path(g, &cost);
     if (v >= kPathRing) return v - kPathRing;
-    if (v == 4 || !gemm_fp8_ring_fits(g)) return -1;
+    if (v == 4 || knob(KNOB_GEMM_RING) == 0 || !gemm_fp8_ring_fits(g)) return -1;
     return best_ring(g, nullptr, compute_units() > 0 ? compute_units() : 256, &cost);
 }
 

@@ -1,0 +1,67 @@
+// Which kernel the FP8 products are sent to (test infrastructure, no device).
+//
+// Built by tests/test_gemm_choice.py from this file and gemm_fp8.hip.  The launchers behind the choice are replaced by the stubs
+// below, which print what they were asked for; the switches and the number of CUs come from the command line.  Each line of the
+// input is a query, each line of the output its answer:
+//     one M N K                   a product
+//     act M N K                   the same with the sigmoid
+//     two M1 N1 K1 M2 N2 K2       the pair of a backward step
+// Arguments: CUs=<n>, <switch number>=<value>.
+#include "../paper_2507_16099_amd/csrc/launchers.hpp"
+#include "../paper_2507_16099_amd/csrc/tuning.hpp"
+
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+
+namespace fp8k {
+static int g_cus = 256, g_knobs[KNOB_COUNT];
+int knob(Knob k) { return g_knobs[k]; }
+int compute_units() { return g_cus; }
+bool gemm_fp8_ring_fits(const GemmOperands& g) { return g.lda < (1 << 22) && g.ldb < (1 << 22) && ((g.M + 63) / 64) * ((g.N + 63) / 64) < (1 << 15); }
+bool gemm_fp8_snake_fits(int64_t lda, int64_t ldb) { return lda < (1 << 23) && ldb < (1 << 23); }
+hipError_t launch_gemm_fp8_ring(int tile, const GemmOperands& g1, const GemmOperands* g2, int, int, int, int, int, hipStream_t) {
+    static const char* const names[RING_TILES] = {"64x64", "128x64", "64x128", "128x128", "128x256", "256x128"};
+    std::printf("ring %s %s K=%lld\n", names[tile], g2 ? "together" : "alone", (long long)g1.K);      // (together: K of the one whose workgroups come first)
+    return hipSuccess;
+}
+hipError_t launch_gemm_fp8_skinny(const uint8_t*, int64_t, int, const float*, int, const uint8_t*, int64_t, int, const float*, int, int64_t, int64_t,
+                                  int64_t, void*, int64_t, int, hipStream_t) {
+    std::printf("few-row\n");
+    return hipSuccess;
+}
+hipError_t launch_gemm_fp8_snake(const uint8_t*, int64_t, int, const float*, int, const uint8_t*, int64_t, int, const float*, int, int64_t, int64_t,
+                                 int64_t, void*, int64_t, int, hipStream_t, int) {
+    std::printf("256x256\n");
+    return hipSuccess;
+}
+}  // namespace fp8k
+
+int main(int argc, char** argv) {
+    using namespace fp8k;
+    for (int& k : g_knobs) k = -1;
+    for (int i = 1; i < argc; ++i) {
+        const char* eq = std::strchr(argv[i], '=');
+        if (!eq) return 2;
+        if (std::strncmp(argv[i], "CUs=", 4) == 0) g_cus = std::atoi(eq + 1);
+        else g_knobs[std::atoi(argv[i])] = std::atoi(eq + 1);
+    }
+    char kind[8];
+    long long M, N, K, M2, N2, K2;
+    auto product = [](long long m, long long n, long long k) {
+        // (addresses that nothing reads: whole cache lines)
+        return GemmOperands{reinterpret_cast<const uint8_t*>(4096), k, nullptr, reinterpret_cast<const uint8_t*>(8192), k, nullptr, m, n, k, nullptr, n};
+    };
+    while (std::scanf("%7s %lld %lld %lld", kind, &M, &N, &K) == 4) {
+        const GemmOperands g = product(M, N, K);
+        if (std::strcmp(kind, "two") == 0) {
+            if (std::scanf("%lld %lld %lld", &M2, &N2, &K2) != 3) return 2;
+            if (launch_gemm_fp8_pair(g, product(M2, N2, K2), 0, 0, 1, 1, nullptr) != hipSuccess) std::printf("apart\n");
+        } else if (std::strcmp(kind, "act") == 0) {
+            std::printf("%s\n", gemm_fp8_ring_choice(g) >= 0 ? "ring" : "256x256");
+        } else if (launch_gemm_fp8(g.a, g.lda, 0, nullptr, 1, g.b, g.ldb, 0, nullptr, 1, M, N, K, nullptr, N, 0, nullptr) != hipSuccess) {
+            return 3;
+        }
+    }
+    return 0;
+}

@@ -1,0 +1,39 @@
+"""The choice of a kernel for an FP8 product, without a device: gemm_fp8.hip with stubs in place of the launchers behind it."""
+import os
+import re
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2507_16099_amd", "csrc")
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+pytestmark = pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not available")
+
+
+@pytest.fixture(scope="module")
+def choose(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("choice") / "gemm_choice_check")
+    cmd = [HIPCC, "--offload-arch=gfx950", "-O1", "-std=c++20", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-w", "-o", exe,
+           os.path.join(ROOT, "tests", "gemm_choice_check.hip"), os.path.join(CSRC, "gemm_fp8.hip")]
+    r = subprocess.run(cmd, capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, r.stderr[-3000:]
+    with open(os.path.join(CSRC, "tuning.hpp")) as f:
+        knobs = re.findall(r"^ +KNOB_(\w+)", f.read(), re.M)
+
+    def ask(*queries, cus=256, **switches):
+        args = [f"CUs={cus}"] + [f"{knobs.index(k)}={v}" for k, v in switches.items()]
+        out = subprocess.run([exe, *args], input="\n".join(queries) + "\n", capture_output=True, text=True, timeout=60, check=True).stdout
+        answers = out.splitlines()
+        assert len(answers) == len(queries), (queries, out)
+        return answers
+
+    return ask
+
+
+@pytest.mark.parametrize("M", [1, 16, 17, 32, 33, 64, 65, 300])
+def test_ring_kernel_switched_off(choose, M):
+    """GEMM_RING = 0 holds for every count of rows and width of weight."""
+    queries = [f"{kind} {M} {N} {K}" for kind in ("one", "act") for N in (512, 8192, 10176, 10184, 28672) for K in (16, 1024, 8192)]
+    assert any(a.startswith("ring") for a in choose(*queries))
+    assert not any(a.startswith("ring") for a in choose(*queries, GEMM_RING=0))

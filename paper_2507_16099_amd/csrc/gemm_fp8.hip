@@ -278,7 +278,10 @@ double ring_cost(int tile, const GemmOperands& g, const GemmOperands* g2, int64_
     const int64_t n1 = tiles(g), n2 = g2 ? tiles(*g2) : 0;
     const double operands = 1e-5 * (double)(n1 + n2) * (c.tm + c.tn);      // (equal otherwise: fewer operand bytes)
     if (n1 + n2 <= cus) return 3.0 + (per1 > per2 ? per1 : per2) + operands;
-    const double rounds = (double)cdiv(n1 + n2, cus) * ((double)n1 * per1 + (double)n2 * per2) / (double)(n1 + n2);
+    // beside a product of up to 32 rows the lowest tiles' later rounds cost more than the first (us a backward step apart / together:
+    // 32 x 14336 x 256 14.3 / 64x64 17.7, 64x128 15.1, 128x256 12.1; 32 x 11008 x 128 12.4 / 64x64 12.6, 128x128 9.9)
+    const double later = tile <= RING_64x128 && g2 && g.M <= 32 ? 0.8 * (double)(cdiv(n1 + n2, cus) - 1) : 0.0;
+    const double rounds = (double)cdiv(n1 + n2, cus) * ((double)n1 * per1 + (double)n2 * per2) / (double)(n1 + n2) + later;
     return 3.0 + (rounds > per1 + per2 ? rounds : per1 + per2) + operands;     // (two unequal products: at least one tile of each in turn)
 }
 // the cheapest ring tile for one product, or two in one launch
@@ -301,7 +304,10 @@ int pick_path(const GemmOperands& g, double* cost) {
     const int64_t cus = compute_units() > 0 ? compute_units() : 256;
     if (g.M <= 16 || (g.M <= 32 && (8 * cdiv(g.N, 64) < 5 * cus || !ring)) ||
         (g.M <= 64 && g.N <= 8192 && g.K >= 2048 && gemm_fp8_snake_fits(g.lda, g.ldb))) return 5;
-    if (g.M <= 32) return kPathRing + RING_64x64;
+    if (g.M <= 32) {
+        *cost = ring_cost(RING_64x64, g, nullptr, cus);
+        return kPathRing + RING_64x64;
+    }
     const int64_t big = cdiv(g.M, 256) * cdiv(g.N, 256);
     if (const int b = knob(KNOB_GEMM_BIG_FROM); b > 0 && cdiv(g.M, 128) * cdiv(g.N, 128) >= b) return 4;
     if (big > cus || !ring) return 4;

@@ -37,3 +37,18 @@ def test_ring_kernel_switched_off(choose, M):
     queries = [f"{kind} {M} {N} {K}" for kind in ("one", "act") for N in (512, 8192, 10176, 10184, 28672) for K in (16, 1024, 8192)]
     assert any(a.startswith("ring") for a in choose(*queries))
     assert not any(a.startswith("ring") for a in choose(*queries, GEMM_RING=0))
+
+
+def test_backward_of_few_tokens_compares_estimates(choose):
+    """17 to 32 tokens against a wide layer: dX goes to the ring kernel, and shares a launch with dW where that is estimated to be
+    faster, on the tile that is cheapest for both (not just where both by themselves take 64 x 64 tiles)."""
+    def pair(M, K, N):
+        return f"two {M} {K} {N} {N} {K} {(M + 15) // 16 * 16}"
+
+    together = [(17, 10240, 128), (32, 11008, 256), (24, 14336, 256), (32, 28672, 64), (20, 16384, 384)]
+    apart = [(32, 28672, 192), (17, 11008, 1024), (32, 11008, 11008)]
+    answers = choose(*[pair(*s) for s in together + apart])
+    for s, a in zip(together, answers):
+        tiles = sum(-(-rows // int(t)) * -(-s[1] // int(u)) for t, u in re.findall(r"ring (\d+)x(\d+) together", a) for rows in (s[0], s[2]))
+        assert 0 < tiles <= 512 and a.endswith(f"K={s[2]}"), (s, a)
+    assert answers[len(together):] == ["apart"] * len(apart)

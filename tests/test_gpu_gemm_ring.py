@@ -109,3 +109,16 @@ def test_every_count_of_steps_around_the_depth_of_the_ring(tile, steps):
     with knobs(GEMM_RING=TILES[tile]):
         got = host_f32(fp8.fp8_scaled_mm(a, 0, one, 0, b, 0, one, 0, fp8.FP8_OUT_FP32))
     assert (got == ai @ bi.T).all()
+
+
+@pytest.mark.parametrize("M", [17, 32])
+@pytest.mark.parametrize("K,N", [(10192, 128), (11008, 64), (11008, 256), (14336, 512), (10240, 1024), (28672, 192)])
+def test_backward_of_few_tokens_in_one_launch(M, K, N):
+    """dX of 17 to 32 rows beside the weight gradient, together or apart as estimated: the bits of one product at a time."""
+    rng = np.random.default_rng(K + N)
+    dy, x, w = (torch.from_numpy(_ints(s, rng)).cuda().to(torch.bfloat16) for s in ((M, N), (M, K), (N, K)))
+    r = fp8.Recipe(gran=fp8.FP8_ROW, flags=fp8.FP8_POW2_SCALE)
+    dx, dw = fp8.fp8_linear_bwd(dy, x, w, r)
+    with knobs(PAIRS=0):
+        dx0, dw0 = fp8.fp8_linear_bwd(dy, x, w, r)
+    assert torch.equal(dx.view(torch.int16), dx0.view(torch.int16)) and torch.equal(dw.view(torch.int16), dw0.view(torch.int16))

@@ -486,14 +486,12 @@ static hipError_t launch_ring_t(const GemmOperands& g1, const GemmOperands* g2, 
 template <int FA, int FB, bool MX>
 static hipError_t launch_ring_f(int tile, const GemmOperands& g1, const GemmOperands* g2, const MxScales* e, int row_a, int row_b,
                                 int mode, hipStream_t st) {
-    // few rows against a weight that stream_weight accepts: one or two rows of tiles, side by side, read it
-    // once (us without / with the hint: 64 x 28672 x 8192 51.5 / 47.0, 128 rows 54.6 / 51.9, 256 rows 68.5 / 65.7)
     if constexpr (!MX) {
-        if (!g2 && stream_weight(g1.b, g1.ldb, g1.N, g1.K)) {
-            if (tile == RING_64x64 && g1.M <= 64) return launch_ring_t<FA, FB, 64, 64, 2, 2, 5, 4, false, true>(g1, g2, e, row_a, row_b, mode, st);
-            if (tile == RING_64x128 && g1.M <= 64) return launch_ring_t<FA, FB, 64, 128, 2, 2, 4, 8, false, true>(g1, g2, e, row_a, row_b, mode, st);
-            if (tile == RING_128x128 && g1.M <= 128) return launch_ring_t<FA, FB, 128, 128, 2, 2, 4, 4, false, true>(g1, g2, e, row_a, row_b, mode, st);
-            if (tile == RING_128x256 && g1.M <= 256) return launch_ring_t<FA, FB, 128, 256, 2, 2, 3, 8, false, true>(g1, g2, e, row_a, row_b, mode, st);
+        if (ring_hint(tile, g1, g2)) {
+            if (tile == RING_64x64) return launch_ring_t<FA, FB, 64, 64, 2, 2, 5, 4, false, true>(g1, g2, e, row_a, row_b, mode, st);
+            if (tile == RING_64x128) return launch_ring_t<FA, FB, 64, 128, 2, 2, 4, 8, false, true>(g1, g2, e, row_a, row_b, mode, st);
+            if (tile == RING_128x128) return launch_ring_t<FA, FB, 128, 128, 2, 2, 4, 4, false, true>(g1, g2, e, row_a, row_b, mode, st);
+            if (tile == RING_128x256) return launch_ring_t<FA, FB, 128, 256, 2, 2, 3, 8, false, true>(g1, g2, e, row_a, row_b, mode, st);
         }
     }
     const bool shallow = g1.K <= 6144 && (!g2 || g2->K <= 6144);

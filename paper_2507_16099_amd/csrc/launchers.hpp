@@ -73,9 +73,34 @@ struct GemmOperands {
 hipError_t launch_gemm_fp8_pair(const GemmOperands& g1, const GemmOperands& g2, int fmt_a, int fmt_b, int row_a, int row_b,
                                 hipStream_t st);
 
+// Whether the rows of a product's weight [N, K] are requested with the streaming hint.  Read once per call, a weight of 96 MiB or
+// more is not in the 256 MB last-level cache when it is wanted again, whatever the calls in between: with the hint it passes at 5.9
+// instead of 5.2 TB/s (us without / with: 16 x 28672 x 8192 45.0 / 40.0, x 4096 24.6 / 21.5; 64 x 28672 x 8192 51.5 / 47.0).  Smaller ones
+// gain the same where they come from HBM (16 x 14336 x 4096 13.6 / 12.6) but lose as much where all weights of the calls fit the
+// cache, which they never stay in then (the same, three weights in turn: 11.1 / 12.2).  Rows have to be whole lines of 128 bytes: a line
+// that two rows or two stages share is fetched twice with the hint (1 x 28672 x 4112 24.8 / 36.5, x 8224 52.0 / 62.9, x 8256 53.6 / 60.1;
+// 128 x 28672 x 8224 72.8 / 86.7; x 8320, whole lines, 49.3 / 45.0).
+inline bool stream_weight(const uint8_t* b, int64_t ldb, int64_t N, int64_t K) {
+    return N * K >= (int64_t)96 << 20 && (((uintptr_t)b | (uint64_t)ldb) & 127) == 0;
+}
+
 // products of few to middling size on smaller tiles with a deep LDS ring (gemm_fp8_ring.hip); g2: a second product in
 // the same launch, or nullptr; mode 0 = bfloat16, 1 = fp32, 2 = bfloat16 of the sigmoid.  _fits: 32-bit offsets reach
 enum RingTile { RING_64x64 = 0, RING_128x64, RING_64x128, RING_128x128, RING_128x256, RING_256x128, RING_TILES };
+// Its form for a tile: whether B is read with the streaming hint.  Few rows against a weight that stream_weight accepts: one row of tiles reads
+// it once, and two rows of 128 x 256 tiles side by side do where they keep step, i.e. where the second is more than half full (us, weights
+// from HBM, without / with: 64 x 28672 x 8192 51.5 / 47.0, 128 rows 56.1 / 53.2; 129 rows 61.2 / 66.2, 160 63.7 / 64.6, 192 65.9 / 63.5, 208
+// 66.7 / 64.2, 256 68.4 / 65.7; x 6144 129 rows 47.8 / 53.5, 160 50.1 / 52.3, 208 53.8 / 52.3; x 3584 129 rows 28.9 / 32.5, 192 31.6 / 31.9, 256
+// 34.5 / 33.8; 24576 x 4608 129 rows 34.5 / 39.8, 192 38.3 / 38.1, 256 42.1 / 40.6).
+inline bool ring_hint(int tile, const GemmOperands& g, const GemmOperands* g2) {
+    if (g2 || !stream_weight(g.b, g.ldb, g.N, g.K)) return false;
+    switch (tile) {
+        case RING_64x64: case RING_64x128: return g.M <= 64;
+        case RING_128x128: return g.M <= 128;
+        case RING_128x256: return g.M <= 128 || (g.M > 192 && g.M <= 256);
+    }
+    return false;
+}
 bool gemm_fp8_ring_fits(const GemmOperands& g);
 int gemm_fp8_ring_choice(const GemmOperands& g);      // its tile where a 256 x 256 tile per workgroup is not the better form, else -1
 hipError_t launch_gemm_fp8_ring(int tile, const GemmOperands& g1, const GemmOperands* g2, int fmt_a, int fmt_b, int row_a,
@@ -167,17 +192,6 @@ hipError_t launch_gemm_fp8_stream(const uint8_t* a, int64_t lda, int fmt_a, cons
                                   const uint8_t* b, int64_t ldb, int fmt_b, const float* scale_b, int row_b,
                                   int64_t M, int64_t N, int64_t K, void* out, int64_t ld_out, int64_t units, int tile_m,
                                   hipStream_t st);
-
-// Whether the rows of a product's weight [N, K] are requested with the streaming hint.  Read once per call, a weight of 96 MiB or
-// more is not in the 256 MB last-level cache when it is wanted again, whatever the calls in between: with the hint it passes at 5.9
-// instead of 5.2 TB/s (us without / with: 16 x 28672 x 8192 45.0 / 40.0, x 4096 24.6 / 21.5; 64 x 28672 x 8192 51.5 / 47.0).  Smaller ones
-// gain the same where they come from HBM (16 x 14336 x 4096 13.6 / 12.6) but lose as much where all weights of the calls fit the
-// cache, which they never stay in then (the same, three weights in turn: 11.1 / 12.2).  Rows have to be whole lines of 128 bytes: a line
-// that two rows or two stages share is fetched twice with the hint (1 x 28672 x 4112 24.8 / 36.5, x 8224 52.0 / 62.9, x 8256 53.6 / 60.1;
-// 128 x 28672 x 8224 72.8 / 86.7; x 8320, whole lines, 49.3 / 45.0).
-inline bool stream_weight(const uint8_t* b, int64_t ldb, int64_t N, int64_t K) {
-    return N * K >= (int64_t)96 << 20 && (((uintptr_t)b | (uint64_t)ldb) & 127) == 0;
-}
 
 // few rows of A (M <= 64, the decode shape of inference): B is streamed once
 // from HBM by wavefronts that load their MFMA operands straight from global

@@ -22,7 +22,7 @@ bool gemm_fp8_ring_fits(const GemmOperands& g) { return g.lda < (1 << 22) && g.l
 bool gemm_fp8_snake_fits(int64_t lda, int64_t ldb) { return lda < (1 << 23) && ldb < (1 << 23); }
 hipError_t launch_gemm_fp8_ring(int tile, const GemmOperands& g1, const GemmOperands* g2, int, int, int, int, int, hipStream_t) {
     static const char* const names[RING_TILES] = {"64x64", "128x64", "64x128", "128x128", "128x256", "256x128"};
-    std::printf("ring %s %s K=%lld\n", names[tile], g2 ? "together" : "alone", (long long)g1.K);      // (together: K of the one whose workgroups come first)
+    std::printf("ring %s %s%s K=%lld\n", names[tile], g2 ? "together" : "alone", ring_hint(tile, g1, g2) ? " hint" : "", (long long)g1.K);      // (together: K of the one whose workgroups come first)
     return hipSuccess;
 }
 hipError_t launch_gemm_fp8_skinny(const uint8_t*, int64_t, int, const float*, int, const uint8_t*, int64_t, int, const float*, int, int64_t, int64_t,

@@ -52,3 +52,16 @@ def test_backward_of_few_tokens_compares_estimates(choose):
         tiles = sum(-(-rows // int(t)) * -(-s[1] // int(u)) for t, u in re.findall(r"ring (\d+)x(\d+) together", a) for rows in (s[0], s[2]))
         assert 0 < tiles <= 512 and a.endswith(f"K={s[2]}"), (s, a)
     assert answers[len(together):] == ["apart"] * len(apart)
+
+
+@pytest.mark.parametrize("N,K", [(28672, 3584), (28672, 8192), (16384, 6144)])
+def test_streaming_hint_only_where_the_weight_is_read_once(choose, N, K):
+    """One row of tiles, or a second one that is more than half full: between them the two fall out of step, and lines are fetched twice."""
+    for M in (33, 64, 65, 128, 129, 160, 192, 193, 256, 257):
+        for tile, rows in ((1, 64), (3, 64), (4, 128), (5, 256)):
+            answer, = choose(f"one {M} {N} {K}", GEMM_RING=tile)
+            assert ("hint" in answer) == (M <= rows and not 128 < M <= 192), (M, answer)
+        for tile in (2, 6):
+            assert "hint" not in choose(f"one {M} {N} {K}", GEMM_RING=tile)[0]
+    for tile in range(1, 7):      # smaller weights, and weights whose rows are not whole lines
+        assert not any("hint" in a for a in choose(f"one 64 {N} 2048", f"one 64 {(96 << 20) // K - 8} {K}", f"one 64 {N} {K + 16}", GEMM_RING=tile))

@@ -323,9 +323,9 @@ int pick_path(const GemmOperands& g, double* cost) {
 hipError_t launch_gemm_fp8(const uint8_t* a, int64_t lda, int fmt_a, const float* scale_a, int row_a,
                            const uint8_t* b, int64_t ldb, int fmt_b, const float* scale_b, int row_b,
                            int64_t M, int64_t N, int64_t K, void* out, int64_t ld_out, int out_f32,
-                           hipStream_t st) {
+                           hipStream_t st, bool b_written) {
     if (M == 0 || N == 0) return hipSuccess;
-    const GemmOperands g{a, lda, scale_a, b, ldb, scale_b, M, N, K, out, ld_out};
+    const GemmOperands g{a, lda, scale_a, b, ldb, scale_b, M, N, K, out, ld_out, b_written};
     double cost;
     const int v = pick_path(g, &cost);
     if (v >= kPathRing) return launch_gemm_fp8_ring(v - kPathRing, g, nullptr, fmt_a, fmt_b, row_a, row_b, out_f32 ? 1 : 0, st);

@@ -58,28 +58,30 @@ hipError_t launch_quant_row(const void* x, int64_t rows, int64_t cols, int64_t l
                             int64_t ld_out, float* scale_out, hipStream_t st);
 
 // out[M,N] = (a[M,K] . b[N,K]^T) / (sa * sb); scale_a/scale_b have one entry
-// (row_a / row_b == 0) or one per row.
+// (row_a / row_b == 0) or one per row.  b_written: the same call has just written b (see ring_hint).
 hipError_t launch_gemm_fp8(const uint8_t* a, int64_t lda, int fmt_a, const float* scale_a, int row_a,
                            const uint8_t* b, int64_t ldb, int fmt_b, const float* scale_b, int row_b,
                            int64_t M, int64_t N, int64_t K, void* out, int64_t ld_out, int out_f32,
-                           hipStream_t st);
+                           hipStream_t st, bool b_written = false);
 // one scaled product out[M, N] = A[M, K] . B[N, K]^T / (scale_a * scale_b), operands as for launch_gemm_fp8
 struct GemmOperands {
     const uint8_t* a; int64_t lda; const float* scale_a;
     const uint8_t* b; int64_t ldb; const float* scale_b;
     int64_t M, N, K; void* out; int64_t ld_out;
+    bool b_written = false;
 };
 // two small products (bfloat16 results) in one launch; hipErrorNotSupported, with nothing launched, where that does not pay
 hipError_t launch_gemm_fp8_pair(const GemmOperands& g1, const GemmOperands& g2, int fmt_a, int fmt_b, int row_a, int row_b,
                                 hipStream_t st);
 
-// Whether the rows of a product's weight [N, K] are requested with the streaming hint.  Read once per call, a weight of 96 MiB or
-// more is not in the 256 MB last-level cache when it is wanted again, whatever the calls in between: with the hint it passes at 5.9
-// instead of 5.2 TB/s (us without / with: 16 x 28672 x 8192 45.0 / 40.0, x 4096 24.6 / 21.5; 64 x 28672 x 8192 51.5 / 47.0).  Smaller ones
-// gain the same where they come from HBM (16 x 14336 x 4096 13.6 / 12.6) but lose as much where all weights of the calls fit the
-// cache, which they never stay in then (the same, three weights in turn: 11.1 / 12.2).  Rows have to be whole lines of 128 bytes: a line
-// that two rows or two stages share is fetched twice with the hint (1 x 28672 x 4112 24.8 / 36.5, x 8224 52.0 / 62.9, x 8256 53.6 / 60.1;
-// 128 x 28672 x 8224 72.8 / 86.7; x 8320, whole lines, 49.3 / 45.0).
+// Whether the rows of a product's weight [N, K] are requested with the streaming hint: from 96 MiB on, for a served model, whose layers
+// between two calls push such a weight out of the 256 MB last-level cache.  From HBM it then passes at 5.9 instead of 5.2 TB/s (us without /
+// with, three weights in turn: 16 x 28672 x 4096 25.3 / 22.0, x 8192 45.8 / 40.2; 64 x 16384 x 8192 32.6 / 28.2).  What that costs: a weight called
+// again and again with nothing in between, or just written, is in the cache and comes slower with the hint (the same with one
+// weight: 19.9 / 21.1, 36.7 / 39.4, 23.2 / 27.2; 128 x 28672 x 8192 39.5 / 46.4, 256 rows 49.0 / 62.5).  Smaller weights gain as much from HBM (16 x
+// 14336 x 4096 13.6 / 12.6), but more of them fit the cache between the calls, and lose there (the same, three weights in turn: 11.1 / 12.2).
+// Rows have to be whole lines of 128 bytes: a line that two rows or two stages share is fetched twice with the hint (1 x 28672 x 4112 24.8 /
+// 36.5, x 8224 52.0 / 62.9, x 8256 53.6 / 60.1; 128 x 28672 x 8224 72.8 / 86.7; x 8320, whole lines, 49.3 / 45.0).
 inline bool stream_weight(const uint8_t* b, int64_t ldb, int64_t N, int64_t K) {
     return N * K >= (int64_t)96 << 20 && (((uintptr_t)b | (uint64_t)ldb) & 127) == 0;
 }
@@ -91,13 +93,16 @@ enum RingTile { RING_64x64 = 0, RING_128x64, RING_64x128, RING_128x128, RING_128
 // it once, and two rows of 128 x 256 tiles side by side do where they keep step, i.e. where the second is more than half full (us, weights
 // from HBM, without / with: 64 x 28672 x 8192 51.5 / 47.0, 128 rows 56.1 / 53.2; 129 rows 61.2 / 66.2, 160 63.7 / 64.6, 192 65.9 / 63.5, 208
 // 66.7 / 64.2, 256 68.4 / 65.7; x 6144 129 rows 47.8 / 53.5, 160 50.1 / 52.3, 208 53.8 / 52.3; x 3584 129 rows 28.9 / 32.5, 192 31.6 / 31.9, 256
-// 34.5 / 33.8; 24576 x 4608 129 rows 34.5 / 39.8, 192 38.3 / 38.1, 256 42.1 / 40.6).
+// 34.5 / 33.8; 24576 x 4608 129 rows 34.5 / 39.8, 192 38.3 / 38.1, 256 42.1 / 40.6).  Where the same call has quantized B, its codes are in the
+// last-level cache: the taller tiles then read them plainly (forward, 256 rows, N x K 28672 x 4096 82.1 / 100.8, x 8192 152.9 / 190.1; 128 rows 73.9 /
+// 75.6, 140.3 / 141.7; dX against W^T 28672 x 4096, 128 rows 112.3 / 114.5, 256 119.5 / 121.9), one row of low ones with the hint (forward 64 rows 72.0 /
+// 72.4, 136.8 / 137.7, 82.0 / 82.3; dX 64 rows 106.8 / 105.0, 271.4 / 268.8, 163.8 / 162.1, 16 rows 104.3 / 100.2, 268.8 / 263.7, 156.3 / 154.8).
 inline bool ring_hint(int tile, const GemmOperands& g, const GemmOperands* g2) {
     if (g2 || !stream_weight(g.b, g.ldb, g.N, g.K)) return false;
     switch (tile) {
         case RING_64x64: case RING_64x128: return g.M <= 64;
-        case RING_128x128: return g.M <= 128;
-        case RING_128x256: return g.M <= 128 || (g.M > 192 && g.M <= 256);
+        case RING_128x128: return g.M <= 128 && !g.b_written;
+        case RING_128x256: return (g.M <= 128 || (g.M > 192 && g.M <= 256)) && !g.b_written;
     }
     return false;
 }

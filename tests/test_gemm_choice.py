@@ -65,3 +65,13 @@ def test_streaming_hint_only_where_the_weight_is_read_once(choose, N, K):
             assert "hint" not in choose(f"one {M} {N} {K}", GEMM_RING=tile)[0]
     for tile in range(1, 7):      # smaller weights, and weights whose rows are not whole lines
         assert not any("hint" in a for a in choose(f"one 64 {N} 2048", f"one 64 {(96 << 20) // K - 8} {K}", f"one 64 {N} {K + 16}", GEMM_RING=tile))
+
+
+@pytest.mark.parametrize("N,K", [(28672, 4096), (28672, 8192), (16384, 8192)])
+def test_no_streaming_hint_on_tall_tiles_behind_the_weights_own_quantization(choose, N, K):
+    """The codes are in the last-level cache."""
+    for M in (33, 64, 65, 128, 193, 256):
+        for tile in range(1, 7):
+            one, own = choose(f"one {M} {N} {K}", f"own {M} {N} {K}", GEMM_RING=tile)
+            assert one.replace(" hint", "") == own.replace(" hint", "")
+            assert ("hint" in own) == ("hint" in one and M <= 64 and tile <= 3), (M, tile, one, own)

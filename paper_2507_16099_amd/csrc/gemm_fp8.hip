@@ -313,7 +313,8 @@ int pick_path(const GemmOperands& g, double* cost) {
     if (big > cus || !ring) return 4;
     const double steps = (double)cdiv(g.K, BK);
     const double cost_big = 2 * big <= cus ? 7.2 + 0.91 * steps : 10.0 + 1.2 * steps;
-    const int tile = best_ring(g, nullptr, cus, cost);
+    int tile = best_ring(g, nullptr, cus, cost);
+    if (tile == RING_128x256 && one_row(g)) tile = RING_256x128;
     if (*cost <= cost_big) return kPathRing + tile;
     *cost = cost_big;
     return 4;

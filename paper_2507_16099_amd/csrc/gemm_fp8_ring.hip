@@ -478,34 +478,35 @@ static hipError_t launch_ring_t(const GemmOperands& g1, const GemmOperands* g2, 
 
 // stages: 128 x 64 and 64 x 128 tiles take four, though six fit: filling them is the longer part of a short product (us, six / four:
 // 1024 x 2048 x 1024 6.3 / 6.0, 72 x 14336 x 4096 13.8 / 12.8, 512 x 4096 x 4096 13.4 / 13.0, 256 x 4096 x 14336 32.6 / 31.9).  Otherwise what the LDS holds;
-// rows of tiles walked together: close to square patches.  128 x 256 and 256 x 128: eight wavefronts up to K = 6144 (us, four / eight:
-// 2048 x 4096 x 1024 14.4 / 13.7, 3001 x 2048 x 4096 26.9 / 25.9, 2048 x 4096 x 4096 31.1 / 30.6; x 8192 54.0 / 54.9, 4096 x 4096 x 16384 214 / 219).  64 x 64: five stages, which with the
+// rows of tiles walked together: close to square patches.  64 x 64: five stages, which with the
 // table of reciprocals is one workgroup per CU; four, for two of them (as in the MX form), cost a long contraction more than
 // they give a short one or a second round (us, five / four stages: 1000 x 1000 x 14336 25.2 / 27.1, 512 x 512 x 28672 40.5 / 43.0,
 // 1024 x 1024 x 4096 10.5 / 10.5, x 1024 6.0 / 5.8; several rounds, where larger tiles are taken: 2048 x 2048 x 1024 16.3 / 12.9).
 template <int FA, int FB, bool MX>
 static hipError_t launch_ring_f(int tile, const GemmOperands& g1, const GemmOperands* g2, const MxScales* e, int row_a, int row_b,
                                 int mode, hipStream_t st) {
+    const bool eight = ring_waves(tile, g1, g2, MX) == 8;
     if constexpr (!MX) {
         if (ring_hint(tile, g1, g2)) {
             if (tile == RING_64x64) return launch_ring_t<FA, FB, 64, 64, 2, 2, 5, 4, false, true>(g1, g2, e, row_a, row_b, mode, st);
             if (tile == RING_64x128) return launch_ring_t<FA, FB, 64, 128, 2, 2, 4, 8, false, true>(g1, g2, e, row_a, row_b, mode, st);
             if (tile == RING_128x128) return launch_ring_t<FA, FB, 128, 128, 2, 2, 4, 4, false, true>(g1, g2, e, row_a, row_b, mode, st);
-            if (tile == RING_128x256) return launch_ring_t<FA, FB, 128, 256, 2, 2, 3, 8, false, true>(g1, g2, e, row_a, row_b, mode, st);
+            if (tile == RING_128x256)
+                return eight ? launch_ring_t<FA, FB, 128, 256, 2, 4, 3, 8, false, true>(g1, g2, e, row_a, row_b, mode, st)
+                             : launch_ring_t<FA, FB, 128, 256, 2, 2, 3, 8, false, true>(g1, g2, e, row_a, row_b, mode, st);
         }
     }
-    const bool shallow = g1.K <= 6144 && (!g2 || g2->K <= 6144);
     switch (tile) {
         case RING_64x64: return launch_ring_t<FA, FB, 64, 64, 2, 2, MX ? 4 : 5, 4, MX>(g1, g2, e, row_a, row_b, mode, st);
         case RING_128x64: return launch_ring_t<FA, FB, 128, 64, 2, 2, 4, 4, MX>(g1, g2, e, row_a, row_b, mode, st);
         case RING_64x128: return launch_ring_t<FA, FB, 64, 128, 2, 2, 4, 8, MX>(g1, g2, e, row_a, row_b, mode, st);
         case RING_128x128: return launch_ring_t<FA, FB, 128, 128, 2, 2, 4, 4, MX>(g1, g2, e, row_a, row_b, mode, st);
         case RING_128x256:
-            return shallow ? launch_ring_t<FA, FB, 128, 256, 2, 4, 3, 8, MX>(g1, g2, e, row_a, row_b, mode, st)
-                           : launch_ring_t<FA, FB, 128, 256, 2, 2, 3, 8, MX>(g1, g2, e, row_a, row_b, mode, st);
+            return eight ? launch_ring_t<FA, FB, 128, 256, 2, 4, 3, 8, MX>(g1, g2, e, row_a, row_b, mode, st)
+                         : launch_ring_t<FA, FB, 128, 256, 2, 2, 3, 8, MX>(g1, g2, e, row_a, row_b, mode, st);
         case RING_256x128:
-            return shallow ? launch_ring_t<FA, FB, 256, 128, 4, 2, 3, 4, MX>(g1, g2, e, row_a, row_b, mode, st)
-                           : launch_ring_t<FA, FB, 256, 128, 2, 2, 3, 4, MX>(g1, g2, e, row_a, row_b, mode, st);
+            return eight ? launch_ring_t<FA, FB, 256, 128, 4, 2, 3, 4, MX>(g1, g2, e, row_a, row_b, mode, st)
+                         : launch_ring_t<FA, FB, 256, 128, 2, 2, 3, 4, MX>(g1, g2, e, row_a, row_b, mode, st);
     }
     return hipErrorInvalidValue;
 }

@@ -78,7 +78,7 @@ hipError_t launch_gemm_fp8_pair(const GemmOperands& g1, const GemmOperands& g2, 
 // between two calls push such a weight out of the 256 MB last-level cache.  From HBM it then passes at 5.9 instead of 5.2 TB/s (us without /
 // with, three weights in turn: 16 x 28672 x 4096 25.3 / 22.0, x 8192 45.8 / 40.2; 64 x 16384 x 8192 32.6 / 28.2).  What that costs: a weight called
 // again and again with nothing in between, or just written, is in the cache and comes slower with the hint (the same with one
-// weight: 19.9 / 21.1, 36.7 / 39.4, 23.2 / 27.2; 128 x 28672 x 8192 39.5 / 46.4, 256 rows 49.0 / 62.5).  Smaller weights gain as much from HBM (16 x
+// weight: 19.9 / 21.1, 36.7 / 39.4, 23.2 / 27.2; 128 x 28672 x 4096 22.8 / 27.4, x 8192 39.3 / 53.4, 72 x 16512 x 6528 22.9 / 33.1).  Smaller weights gain as much from HBM (16 x
 // 14336 x 4096 13.6 / 12.6), but more of them fit the cache between the calls, and lose there (the same, three weights in turn: 11.1 / 12.2).
 // Rows have to be whole lines of 128 bytes: a line that two rows or two stages share is fetched twice with the hint (1 x 28672 x 4112 24.8 /
 // 36.5, x 8224 52.0 / 62.9, x 8256 53.6 / 60.1; 128 x 28672 x 8224 72.8 / 86.7; x 8320, whole lines, 49.3 / 45.0).
@@ -89,22 +89,35 @@ inline bool stream_weight(const uint8_t* b, int64_t ldb, int64_t N, int64_t K) {
 // products of few to middling size on smaller tiles with a deep LDS ring (gemm_fp8_ring.hip); g2: a second product in
 // the same launch, or nullptr; mode 0 = bfloat16, 1 = fp32, 2 = bfloat16 of the sigmoid.  _fits: 32-bit offsets reach
 enum RingTile { RING_64x64 = 0, RING_128x64, RING_64x128, RING_128x128, RING_128x256, RING_256x128, RING_TILES };
-// Its form for a tile: whether B is read with the streaming hint.  Few rows against a weight that stream_weight accepts: one row of tiles reads
-// it once, and two rows of 128 x 256 tiles side by side do where they keep step, i.e. where the second is more than half full (us, weights
-// from HBM, without / with: 64 x 28672 x 8192 51.5 / 47.0, 128 rows 56.1 / 53.2; 129 rows 61.2 / 66.2, 160 63.7 / 64.6, 192 65.9 / 63.5, 208
-// 66.7 / 64.2, 256 68.4 / 65.7; x 6144 129 rows 47.8 / 53.5, 160 50.1 / 52.3, 208 53.8 / 52.3; x 3584 129 rows 28.9 / 32.5, 192 31.6 / 31.9, 256
-// 34.5 / 33.8; 24576 x 4608 129 rows 34.5 / 39.8, 192 38.3 / 38.1, 256 42.1 / 40.6).  Where the same call has quantized B, its codes are in the
-// last-level cache: the taller tiles then read them plainly (forward, 256 rows, N x K 28672 x 4096 82.1 / 100.8, x 8192 152.9 / 190.1; 128 rows 73.9 /
-// 75.6, 140.3 / 141.7; dX against W^T 28672 x 4096, 128 rows 112.3 / 114.5, 256 119.5 / 121.9), one row of low ones with the hint (forward 64 rows 72.0 /
-// 72.4, 136.8 / 137.7, 82.0 / 82.3; dX 64 rows 106.8 / 105.0, 271.4 / 268.8, 163.8 / 162.1, 16 rows 104.3 / 100.2, 268.8 / 263.7, 156.3 / 154.8).
+// Its form for a tile: whether B is read with the streaming hint.  One row of tiles against a weight that stream_weight accepts reads it once (us,
+// weights from HBM, without / with: 64 x 28672 x 8192 51.5 / 47.0, 128 rows 56.1 / 53.2, x 4096 32.8 / 30.5).  Not two rows of 128 x 256 tiles: they
+// read it side by side, but fall out of step where the second is not full, and lines are fetched twice (129 rows, x 8192 61.2 / 66.2, x 6144
+// 47.8 / 53.5, x 3584 28.9 / 32.5; 160 rows 63.7 / 64.6, 50.1 / 52.3, 30.5 / 31.7; 256 rows 68.4 / 65.7, 56.7 / 54.3, 34.5 / 33.8); one_row below is
+// for them.  Where the same call has quantized B, its codes are in the last-level cache: the taller tiles then read them plainly (forward of 128 rows, N x K
+// 28672 x 4096 73.9 / 75.6, x 8192 140.3 / 141.7; dX against W^T 28672 x 4096 112.3 / 114.5), low ones with the hint (forward 64 rows 72.0 / 72.4, 136.8 /
+// 137.7, 16384 x 8192 82.0 / 82.3; dX 64 rows 106.8 / 105.0, 271.4 / 268.8, 163.8 / 162.1, 16 rows 104.3 / 100.2, 268.8 / 263.7, 156.3 / 154.8).
 inline bool ring_hint(int tile, const GemmOperands& g, const GemmOperands* g2) {
     if (g2 || !stream_weight(g.b, g.ldb, g.N, g.K)) return false;
     switch (tile) {
         case RING_64x64: case RING_64x128: return g.M <= 64;
-        case RING_128x128: return g.M <= 128 && !g.b_written;
-        case RING_128x256: return (g.M <= 128 || (g.M > 192 && g.M <= 256)) && !g.b_written;
+        case RING_128x128: case RING_128x256: return g.M <= 128 && !g.b_written;
     }
     return false;
+}
+// 129 to 256 rows against such a weight: one row of 256 x 128 tiles in place of two of 128 x 256, which fetches it once (us from HBM, 129 / 193 / 256
+// rows, 128 x 256 plain, with the hint, 256 x 128: 28672 x 8192 61.5 66.2 69.9, 65.3 63.1 65.4, 58.0 62.6 67.1; x 6144 47.6 52.6 57.2, 53.6 51.4 54.3, 46.3
+// 50.0 52.7; x 3584 29.2 32.1 34.5, 33.0 32.1 34.0, 28.7 31.6 34.8; 24576 x 4608 34.7 38.3 42.0, 39.8 38.2 40.3, 33.5 37.3 38.2).  From the cache the two
+// are close (28672 x 6144 36.1 39.7 40.2 / 35.2 38.8 43.2): where the same call has quantized the weight nothing changes.
+inline bool one_row(const GemmOperands& g) { return g.M > 128 && g.M <= 256 && !g.b_written && stream_weight(g.b, g.ldb, g.N, g.K); }
+// Wavefronts of a workgroup: four, one per SIMD, or eight on 128 x 256 and 256 x 128 tiles of short contractions, K <= 6144 (us, four / eight: 2048 x 4096 x
+// 1024 14.5 / 13.4, 3001 x 2048 x 4096 26.0 / 25.1, 2048 x 4096 x 4096 29.6 / 28.7, 1000 x 4096 x 6144 34.2 / 32.7, 4096 x 4096 x 6144 79.5 / 77.1, with the
+// hint 72 x 28672 x 4096 35.8 / 34.7; x 8192 99.6 / 99.2, 2048 x 4096 x 8192 50.3 / 51.0, x 14336 +2 %).  Not where a row of full 256 x 128 tiles fetches a
+// large weight (160 / 193 / 224 / 256 rows, 24576 x 4608 36.7 37.3 37.8 38.2 / 35.8 37.2 39.0 41.7, 28672 x 6144 50.0 50.0 51.1 52.7 / 48.4 49.0 51.9
+// 55.7, 20480 x 5120 42.1 42.6 42.4 44.1 / 41.5 43.9 43.8 47.9).
+inline int ring_waves(int tile, const GemmOperands& g, const GemmOperands* g2, bool mx) {
+    if (tile != RING_128x256 && tile != RING_256x128) return 4;
+    if (tile == RING_256x128 && !mx && !g2 && g.M > 192 && one_row(g)) return 4;
+    return g.K <= 6144 && (!g2 || g2->K <= 6144) ? 8 : 4;
 }
 bool gemm_fp8_ring_fits(const GemmOperands& g);
 int gemm_fp8_ring_choice(const GemmOperands& g);      // its tile where a 256 x 256 tile per workgroup is not the better form, else -1

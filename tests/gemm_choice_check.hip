@@ -4,6 +4,7 @@
 // below, which print what they were asked for; the switches and the number of CUs come from the command line.  Each line of the
 // input is a query, each line of the output its answer:
 //     one M N K                   a product
+//     mx M N K                    the same, block-scaled
 //     own M N K                   the same, its weight written by the same call
 //     act M N K                   the same with the sigmoid
 //     two M1 N1 K1 M2 N2 K2       the pair of a backward step
@@ -16,14 +17,15 @@
 #include <cstring>
 
 namespace fp8k {
+static const char* const names[RING_TILES] = {"64x64", "128x64", "64x128", "128x128", "128x256", "256x128"};
 static int g_cus = 256, g_knobs[KNOB_COUNT];
 int knob(Knob k) { return g_knobs[k]; }
 int compute_units() { return g_cus; }
 bool gemm_fp8_ring_fits(const GemmOperands& g) { return g.lda < (1 << 22) && g.ldb < (1 << 22) && ((g.M + 63) / 64) * ((g.N + 63) / 64) < (1 << 15); }
 bool gemm_fp8_snake_fits(int64_t lda, int64_t ldb) { return lda < (1 << 23) && ldb < (1 << 23); }
 hipError_t launch_gemm_fp8_ring(int tile, const GemmOperands& g1, const GemmOperands* g2, int, int, int, int, int, hipStream_t) {
-    static const char* const names[RING_TILES] = {"64x64", "128x64", "64x128", "128x128", "128x256", "256x128"};
-    std::printf("ring %s %s%s K=%lld\n", names[tile], g2 ? "together" : "alone", ring_hint(tile, g1, g2) ? " hint" : "", (long long)g1.K);      // (together: K of the one whose workgroups come first)
+    std::printf("ring %s %s%s %d K=%lld\n", names[tile], g2 ? "together" : "alone", ring_hint(tile, g1, g2) ? " hint" : "", ring_waves(tile, g1, g2, false),
+                (long long)g1.K);      // (together: K of the one whose workgroups come first)
     return hipSuccess;
 }
 hipError_t launch_gemm_fp8_skinny(const uint8_t*, int64_t, int, const float*, int, const uint8_t*, int64_t, int, const float*, int, int64_t, int64_t,
@@ -58,6 +60,10 @@ int main(int argc, char** argv) {
         if (std::strcmp(kind, "two") == 0) {
             if (std::scanf("%lld %lld %lld", &M2, &N2, &K2) != 3) return 2;
             if (launch_gemm_fp8_pair(g, product(M2, N2, K2), 0, 0, 1, 1, nullptr) != hipSuccess) std::printf("apart\n");
+        } else if (std::strcmp(kind, "mx") == 0) {
+            const int tile = gemm_mxfp8_ring_choice(g, false);
+            if (tile < 0) std::printf("256x256\n");
+            else std::printf("ring %s %d\n", names[tile], ring_waves(tile, g, nullptr, true));
         } else if (std::strcmp(kind, "act") == 0) {
             std::printf("%s\n", gemm_fp8_ring_choice(g) >= 0 ? "ring" : "256x256");
         } else if (launch_gemm_fp8(g.a, g.lda, 0, nullptr, 1, g.b, g.ldb, 0, nullptr, 1, M, N, K, nullptr, N, 0, nullptr, std::strcmp(kind, "own") == 0) != hipSuccess) {

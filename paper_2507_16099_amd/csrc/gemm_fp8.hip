@@ -265,6 +265,9 @@ static hipError_t launch_tn(const GemmOperands& g, int row_a, int row_b, hipStre
 // GEMM_BIG_FROM: number of 128 x 128 tiles from which the 256 x 256 kernels are taken; GEMM_VARIANT forces a kernel:
 // 0 = the fallback above, 4 = 256 x 256, 5 = few-row kernel (only where M <= 64), 6 / 7 = ring kernel, 64 x 64 / 128 x 128 tiles.
 namespace {
+// a of the widest tiles is that of eight wavefronts also beyond K = 6144, where four take 0.7 us more: it decides there only between a shared launch
+// of two products on these tiles and other forms, of which the shared launch is the faster (us a backward step, 6.3 / 7.0: 2215 x 2048 x 7936
+// 110.8 / 124.3 on 128 x 128 tiles, 4743 x 896 x 16000 272.5 / 300.3; apart 2091 x 2048 x 7168 93.3 / 101.9, 3729 x 1152 x 11648 173.0 / 182.6).
 struct RingCost { int tm, tn; double a, b; };
 constexpr RingCost kRing[RING_TILES] = {{64, 64, 1.0, 0.20},   {128, 64, 1.9, 0.29},  {64, 128, 1.9, 0.29},
                                         {128, 128, 4.0, 0.42}, {128, 256, 6.3, 0.70}, {256, 128, 6.3, 0.70}};

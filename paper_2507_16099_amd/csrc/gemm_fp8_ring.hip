@@ -485,7 +485,7 @@ static hipError_t launch_ring_t(const GemmOperands& g1, const GemmOperands* g2, 
 template <int FA, int FB, bool MX>
 static hipError_t launch_ring_f(int tile, const GemmOperands& g1, const GemmOperands* g2, const MxScales* e, int row_a, int row_b,
                                 int mode, hipStream_t st) {
-    const bool eight = ring_waves(tile, g1, g2, MX) == 8;
+    const bool eight = ring_waves(tile, g1, g2, MX, MX && e->ld_ea >= 0) == 8;
     if constexpr (!MX) {
         if (ring_hint(tile, g1, g2)) {
             if (tile == RING_64x64) return launch_ring_t<FA, FB, 64, 64, 2, 2, 5, 4, false, true>(g1, g2, e, row_a, row_b, mode, st);

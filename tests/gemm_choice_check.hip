@@ -4,7 +4,7 @@
 // below, which print what they were asked for; the switches and the number of CUs come from the command line.  Each line of the
 // input is a query, each line of the output its answer:
 //     one M N K                   a product
-//     mx M N K                    the same, block-scaled
+//     mx M N K                    the same, block-scaled; mxrows: with plain rows of scales
 //     own M N K                   the same, its weight written by the same call
 //     act M N K                   the same with the sigmoid
 //     two M1 N1 K1 M2 N2 K2       the pair of a backward step
@@ -60,10 +60,11 @@ int main(int argc, char** argv) {
         if (std::strcmp(kind, "two") == 0) {
             if (std::scanf("%lld %lld %lld", &M2, &N2, &K2) != 3) return 2;
             if (launch_gemm_fp8_pair(g, product(M2, N2, K2), 0, 0, 1, 1, nullptr) != hipSuccess) std::printf("apart\n");
-        } else if (std::strcmp(kind, "mx") == 0) {
-            const int tile = gemm_mxfp8_ring_choice(g, false);
+        } else if (std::strncmp(kind, "mx", 2) == 0) {
+            const bool plain = std::strcmp(kind, "mxrows") == 0;
+            const int tile = gemm_mxfp8_ring_choice(g, plain);
             if (tile < 0) std::printf("256x256\n");
-            else std::printf("ring %s %d\n", names[tile], ring_waves(tile, g, nullptr, true));
+            else std::printf("ring %s %d\n", names[tile], ring_waves(tile, g, nullptr, true, plain));
         } else if (std::strcmp(kind, "act") == 0) {
             std::printf("%s\n", gemm_fp8_ring_choice(g) >= 0 ? "ring" : "256x256");
         } else if (launch_gemm_fp8(g.a, g.lda, 0, nullptr, 1, g.b, g.ldb, 0, nullptr, 1, M, N, K, nullptr, N, 0, nullptr, std::strcmp(kind, "own") == 0) != hipSuccess) {

@@ -93,6 +93,8 @@ def test_wavefronts_of_the_widest_tiles(choose, tile):
         for kind in ("one", "mx"):
             a = choose(*[f"{kind} {M} {N} {K}" for K in (128, 6144, 6272)], GEMM_RING=tile)
             assert [re.search(r" (\d)(?: K=|$)", x)[1] for x in a] == (["8", "8", "4"] if tile >= 5 else ["4"] * 3), a
+        a = choose(*[f"mxrows {M} {N} {K}" for K in (128, 3072, 3200)], GEMM_RING=tile)
+        assert [x[-1] for x in a] == (["8", "8", "4"] if tile >= 5 else ["4"] * 3), a
     wide = 8 if tile >= 5 else 4
     assert choose("mx 256 28672 4096", GEMM_RING=tile)[0].endswith(f" {wide}")
     assert f" together 4 " in choose("two 400 400 6144 400 400 6272", GEMM_RING=tile)[0]

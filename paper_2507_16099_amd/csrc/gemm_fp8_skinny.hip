@@ -416,8 +416,7 @@ static hipError_t launch_sk_dma(const uint8_t* a, int64_t lda, const float* sa, 
     // fills and while its K parts are summed.  (us, weights from HBM: five steps / three at 16 x 4096 x 4096 6.2 / 5.9, 2 x 4096 x 14336
     // 12.6 / 12.3; three / two at 16 x 28672 x 4096 25.9 / 25.0, 2 x 14336 x 4096 13.5 / 13.1, 16 x 11008 x 4096 13.3 / 12.7, 64 x 8192 x 8192
     // 19.7 / 19.3, 64 x 4096 x 4096 9.5 / 9.2; one or two tiles of 16 columns each way keep three: 2 x 4096 x 14336 12.3 / 14.3, 32 x 1024 x 8192 6.8 / 7.2)
-    // DEEP: up to 8 rows on at most half of the CUs, where a long contraction keeps five (three / five at 2 rows: 1024 x 14336 7.50 / 7.21,
-    // x 28672 11.39 / 10.70, 2048 x 28672 11.96 / 11.71; x 8192 5.44 / 5.61; 16 rows, 1024 x 28672 12.71 / 12.99)
+    // DEEP: five, where few_row_form says so
     constexpr int R = DEEP ? 5 : SLOT <= 6144 && NW == 1 ? 3 : 2;
     constexpr int lds = 4 * R * SLOT;
     const bool hint = stream_weight(b, ldb, N, K);
@@ -433,22 +432,14 @@ static hipError_t launch_sk(const uint8_t* a, int64_t lda, const float* sa, int 
                             const float* sb, int row_b, int M, int N, int K, void* out, int64_t ld_out, int out_f32,
                             hipStream_t st) {
     const int mt = (M + 15) / 16;                 // 1..4
-    // columns per wavefront: 16 or 32 (64 through the override).  Wider groups reuse every fragment of A
-    // for two or four MFMAs but shorten the ring of K steps in flight, narrower ones give more wavefronts;
-    // measured: 32 wins or ties from N = 6144 on, 64 never beats 32 (28672 x 8192: 5 % slower)
-    int nw = N >= 6144 ? 2 : 1;
-    if (const int v = knob(KNOB_SKINNY_NW); v == 1 || v == 2 || v == 4) nw = v;     // tuning override
-    const int64_t groups = ((int64_t)N + 16 * nw - 1) / (16 * nw);
-    // split K over the wavefronts of a workgroup until about 2048 wavefronts stream B
-    int ks = 1;
-    while (ks < 4 && groups * ks < 2048 && K / (ks * 2) >= 512) ks *= 2;
-    const int64_t grid = (groups + (4 / ks) - 1) / (4 / ks);
+    const int v = knob(KNOB_SKINNY_NW);           // (tuning override)
+    const auto [nw, ks, grid, deep] = few_row_form(M, N, K, v == 1 || v == 2 || v == 4 ? v : 0, compute_units() > 0 ? compute_units() : 256);
     if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
     // LDS-DMA form when the 32-bit buffer offsets suffice (FP8MI355_SKINNY_DMA=0 / 1 overrides; not with 33-64 rows
     // against 64 columns per wavefront, which only the override SKINNY_NW asks for: the slots would not fit the LDS)
     const bool fits = lda < (1 << 23) && ldb < (1 << 23) && (mt <= 2 || nw <= 2);
     if (fits && knob(KNOB_SKINNY_DMA) != 0) {
-        if (M <= 8 && ks == 4 && nw == 1 && K > 10240 && grid <= 128)
+        if (deep)
             return launch_sk_dma<FA, FB, 1, 4, 1, true>(a, lda, sa, row_a, b, ldb, sb, row_b, M, N, K, out, ld_out, out_f32, grid, st);
 #define FP8K_SKD(MT_, KS_, NW_)                                                                               \
     if (mt == MT_ && ks == KS_ && nw == NW_)                                                                  \

@@ -214,6 +214,29 @@ hipError_t launch_gemm_fp8_stream(const uint8_t* a, int64_t lda, int fmt_a, cons
                                   int64_t M, int64_t N, int64_t K, void* out, int64_t ld_out, int64_t units, int tile_m,
                                   hipStream_t st);
 
+// Split of a few-row product (gemm_fp8_skinny.hip).  nw: groups of 16 columns per wavefront; ks: wavefronts of a workgroup that share K; deep: five K steps in
+// flight in place of three.  nw_forced: 0, or the switch's value.
+struct FewRowForm { int nw, ks; int64_t grid; bool deep; };
+inline FewRowForm few_row_form(int64_t M, int64_t N, int64_t K, int nw_forced, int64_t cus) {
+    // columns per wavefront: 16 or 32 (64 through the override).  Wider groups reuse every fragment of A
+    // for two or four MFMAs but shorten the ring of K steps in flight, narrower ones give more wavefronts;
+    // measured: 32 wins or ties from N = 6144 on, 64 never beats 32 (28672 x 8192: 5 % slower)
+    const int nw = nw_forced ? nw_forced : N >= 6144 ? 2 : 1;
+    const int64_t groups = (N + 16 * nw - 1) / (16 * nw);
+    // split K over the wavefronts of a workgroup until about 2048 wavefronts stream B
+    int ks = 1;
+    while (ks < 4 && groups * ks < 2048 && K / (ks * 2) >= 512) ks *= 2;
+    const int64_t grid = (groups + (4 / ks) - 1) / (4 / ks);
+    // up to 8 rows on at most half of the CUs a long contraction keeps five (us, three / five at 2 rows: 1024 x 14336 7.50 / 7.21,
+    // x 28672 11.39 / 10.70, 2048 x 28672 11.96 / 11.71; x 8192 5.44 / 5.61; 16 rows, 1024 x 28672 12.71 / 12.99)
+    return {nw, ks, grid, M <= 8 && ks == 4 && nw == 1 && K > 10240 && 2 * grid <= cus};
+}
+
+// columns of a strip (quant_strips.hip) for tensors of at most tall rows, load strips of 32 columns.  16 where 32 would keep half of the CUs busy,
+// unless the strips are short (us, 32 / 16 columns: gradient 4096 x 1024 20.9 / 14.9, x 4096 27.3 / 26.4, x 6144 31.8 / 36.0; 2048 x 1024
+// 12.8 / 10.2, x 4096 15.3 / 14.7, x 6144 16.5 / 20.7; 1024 x 1024 8.7 / 9.3, x 4096 10.8 / 12.5); beyond 4096 rows 32 do not fit.
+inline int strip_columns(int64_t tall, double load, int64_t cus) { return tall > 4096 || (tall > 1024 && 2.0 * load <= (double)cus) ? 16 : 32; }
+
 // few rows of A (M <= 64, the decode shape of inference): B is streamed once
 // from HBM by wavefronts that load their MFMA operands straight from global
 // memory; same contract otherwise.

@@ -237,10 +237,8 @@ hipError_t launch_quant_strips(const StripOperand* ops, int n, int flags, hipStr
     // codes (us a step, hint / plain: 1024x2048x1024 34.4 / 30.3, 2048^3 58.0 / 52.7, 2048x4096x4096 with dW in bfloat16, 24 Mi, 153.1 / 150.8, 4096^3
     // 215.9 / 217.1, 600x14336x4096 238 / 246, 4096x14336x2048 416 / 428).
     a.hint = hint_inputs(by_rows, HINT_PAIR);
-    // Width: load = strips of 32 columns, in units of the tallest tensor's, a tensor without strips half.  16 columns where 32 would
-    // keep half of the CUs busy, unless the strips are short (us, 32 / 16 columns: gradient 4096 x 1024 20.9 / 14.9, x 4096 27.3 / 26.4,
-    // x 6144 31.8 / 36.0; 2048 x 1024 12.8 / 10.2, x 4096 15.3 / 14.7, x 6144 16.5 / 20.7; 1024 x 1024 8.7 / 9.3, x 4096 10.8 / 12.5).
-    const int lpr = tall > 4096 ? 2 : v == 2 || v == 4 ? v : tall > 1024 && load <= 128.0 ? 2 : 4;
+    // load: strips of 32 columns, in units of the tallest tensor's, a tensor without strips half
+    const int lpr = tall <= 4096 && (v == 2 || v == 4) ? v : strip_columns(tall, load, compute_units() > 0 ? compute_units() : 256) / 8;
     const int threads = tall * lpr <= 4096 ? 256 : tall * lpr <= 8192 ? 512 : 1024;
     // workgroups hold the tallest tensor's strip; of a shorter one each takes several
     const int nv = wide <= 2048 ? 1 : wide <= 4096 ? 2 : wide <= 8192 ? 4 : 8;

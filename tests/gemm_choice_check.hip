@@ -7,6 +7,8 @@
 //     mx M N K                    the same, block-scaled; mxrows: with plain rows of scales
 //     own M N K                   the same, its weight written by the same call
 //     act M N K                   the same with the sigmoid
+//     few M N K                   the split of a few-row product
+//     cols rows load              columns of a strip of the shared quantization (the third number is not used)
 //     two M1 N1 K1 M2 N2 K2       the pair of a backward step
 // Arguments: CUs=<n>, <switch number>=<value>.
 #include "../paper_2507_16099_amd/csrc/launchers.hpp"
@@ -65,6 +67,11 @@ int main(int argc, char** argv) {
             const int tile = gemm_mxfp8_ring_choice(g, plain);
             if (tile < 0) std::printf("256x256\n");
             else std::printf("ring %s %d\n", names[tile], ring_waves(tile, g, nullptr, true, plain));
+        } else if (std::strcmp(kind, "few") == 0) {
+            const FewRowForm f = few_row_form(M, N, K, 0, g_cus);
+            std::printf("%d %d %lld %s\n", f.nw, f.ks, (long long)f.grid, f.deep ? "deep" : "");
+        } else if (std::strcmp(kind, "cols") == 0) {
+            std::printf("%d\n", strip_columns(M, (double)N, g_cus));
         } else if (std::strcmp(kind, "act") == 0) {
             std::printf("%s\n", gemm_fp8_ring_choice(g) >= 0 ? "ring" : "256x256");
         } else if (launch_gemm_fp8(g.a, g.lda, 0, nullptr, 1, g.b, g.ldb, 0, nullptr, 1, M, N, K, nullptr, N, 0, nullptr, std::strcmp(kind, "own") == 0) != hipSuccess) {

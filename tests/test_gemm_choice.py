@@ -99,3 +99,11 @@ def test_wavefronts_of_the_widest_tiles(choose, tile):
     assert choose("mx 256 28672 4096", GEMM_RING=tile)[0].endswith(f" {wide}")
     assert f" together 4 " in choose("two 400 400 6144 400 400 6272", GEMM_RING=tile)[0]
     assert f" together {wide} " in choose("two 400 400 6144 400 400 6128", GEMM_RING=tile)[0]
+
+
+@pytest.mark.parametrize("cus", [64, 256])
+def test_half_of_the_cus_is_that_of_the_device(choose, cus):
+    """The deeper ring of few rows and narrow strips are for grids of at most half of the CUs, on a partition of the device too."""
+    deep = choose(f"few 2 {8 * cus} 14336", f"few 2 {8 * cus + 8} 14336", f"few 8 {8 * cus} 14336", f"few 9 {8 * cus} 14336", cus=cus)
+    assert [a.endswith("deep") for a in deep] == [True, False, True, False]
+    assert choose(f"cols 2048 {cus // 2} 0", f"cols 2048 {cus // 2 + 1} 0", f"cols 1024 1 0", f"cols 4097 {cus} 0", cus=cus) == ["16", "32", "32", "16"]

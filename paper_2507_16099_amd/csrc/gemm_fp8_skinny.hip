@@ -419,12 +419,17 @@ static hipError_t launch_sk_dma(const uint8_t* a, int64_t lda, const float* sa, 
     // DEEP: five, where few_row_form says so
     constexpr int R = DEEP ? 5 : SLOT <= 6144 && NW == 1 ? 3 : 2;
     constexpr int lds = 4 * R * SLOT;
-    const bool hint = stream_weight(b, ldb, N, K);
-    auto kern = hint ? gemm_fp8_skinny_dma_kernel<FA, FB, MT, KS, NW, R, true> : gemm_fp8_skinny_dma_kernel<FA, FB, MT, KS, NW, R, false>;
-    static DynamicLdsOnce attr[2];
-    if (hipError_t e = attr[hint].ensure(reinterpret_cast<const void*>(kern), lds); e != hipSuccess) return e;
-    kern<<<dim3((unsigned)grid), dim3(256), lds, st>>>(a, lda, b, ldb, sa, row_a, sb, row_b, M, N, K, out, ld_out, out_f32);
-    return hipGetLastError();
+    auto launch = [&](auto kern, DynamicLdsOnce& attr) {
+        if (hipError_t e = attr.ensure(reinterpret_cast<const void*>(kern), lds); e != hipSuccess) return e;
+        kern<<<dim3((unsigned)grid), dim3(256), lds, st>>>(a, lda, b, ldb, sa, row_a, sb, row_b, M, N, K, out, ld_out, out_f32);
+        return hipGetLastError();
+    };
+    if constexpr (few_row_hint(MT, NW, KS)) {
+        static DynamicLdsOnce attr;
+        if (stream_weight(b, ldb, N, K)) return launch(gemm_fp8_skinny_dma_kernel<FA, FB, MT, KS, NW, R, true>, attr);
+    }
+    static DynamicLdsOnce attr;
+    return launch(gemm_fp8_skinny_dma_kernel<FA, FB, MT, KS, NW, R, false>, attr);
 }
 
 template <int FA, int FB>

@@ -217,6 +217,9 @@ hipError_t launch_gemm_fp8_stream(const uint8_t* a, int64_t lda, int fmt_a, cons
 // Split of a few-row product (gemm_fp8_skinny.hip).  nw: groups of 16 columns per wavefront; ks: wavefronts of a workgroup that share K; deep: five K steps in
 // flight in place of three.  nw_forced: 0, or the switch's value.
 struct FewRowForm { int nw, ks; int64_t grid; bool deep; };
+// Forms of mt tiles of 16 rows that a weight which stream_weight accepts can come to, and which so exist with the streaming hint: against one group of
+// columns N < 6144 and so K > 16384; with 33 rows and more the choice of kernel leaves N <= 8192 and so K >= 12288, always four parts of K.
+constexpr bool few_row_hint(int mt, int nw, int ks) { return nw == 2 ? mt <= 2 || ks == 4 : nw == 1 && ks == 4; }
 inline FewRowForm few_row_form(int64_t M, int64_t N, int64_t K, int nw_forced, int64_t cus) {
     // columns per wavefront: 16 or 32 (64 through the override).  Wider groups reuse every fragment of A
     // for two or four MFMAs but shorten the ring of K steps in flight, narrower ones give more wavefronts;

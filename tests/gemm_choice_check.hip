@@ -69,7 +69,8 @@ int main(int argc, char** argv) {
             else std::printf("ring %s %d\n", names[tile], ring_waves(tile, g, nullptr, true, plain));
         } else if (std::strcmp(kind, "few") == 0) {
             const FewRowForm f = few_row_form(M, N, K, 0, g_cus);
-            std::printf("%d %d %lld %s\n", f.nw, f.ks, (long long)f.grid, f.deep ? "deep" : "");
+            std::printf("%d %d %lld %s%s\n", f.nw, f.ks, (long long)f.grid, f.deep ? "deep" : "",
+                        few_row_hint((int)(M + 15) / 16, f.nw, f.ks) ? " hint" : "");
         } else if (std::strcmp(kind, "cols") == 0) {
             std::printf("%d\n", strip_columns(M, (double)N, g_cus));
         } else if (std::strcmp(kind, "act") == 0) {

@@ -105,5 +105,16 @@ def test_wavefronts_of_the_widest_tiles(choose, tile):
 def test_half_of_the_cus_is_that_of_the_device(choose, cus):
     """The deeper ring of few rows and narrow strips are for grids of at most half of the CUs, on a partition of the device too."""
     deep = choose(f"few 2 {8 * cus} 14336", f"few 2 {8 * cus + 8} 14336", f"few 8 {8 * cus} 14336", f"few 9 {8 * cus} 14336", cus=cus)
-    assert [a.endswith("deep") for a in deep] == [True, False, True, False]
+    assert ["deep" in a for a in deep] == [True, False, True, False]
     assert choose(f"cols 2048 {cus // 2} 0", f"cols 2048 {cus // 2 + 1} 0", f"cols 1024 1 0", f"cols 4097 {cus} 0", cus=cus) == ["16", "32", "32", "16"]
+
+
+def test_every_few_row_form_of_a_streamed_weight_has_the_hint(choose):
+    """Weights of 96 MiB and more, of every width that the choice leaves to the few-row kernel."""
+    shapes = [(M, N, -(-(96 << 20) // (16 * N)) * 16) for M in (1, 8, 16, 17, 32, 33, 48, 49, 64)
+              for N in (16, 512, 3072, 6128, 6144, 8192, 8200, 10176, 16384, 65536, 262144, 1 << 20)]
+    answers = choose(*[f"one {M} {N} {K}" for M, N, K in shapes])
+    few = [s for s, a in zip(shapes, answers) if a == "few-row"]
+    assert {M for M, _, _ in few} == {1, 8, 16, 17, 32, 33, 48, 49, 64}
+    for s, a in zip(few, choose(*["few %d %d %d" % s for s in few])):
+        assert a.endswith("hint"), (s, a)

@@ -230,9 +230,12 @@ inline FewRowForm few_row_form(int64_t M, int64_t N, int64_t K, int nw_forced, i
     int ks = 1;
     while (ks < 4 && groups * ks < 2048 && K / (ks * 2) >= 512) ks *= 2;
     const int64_t grid = (groups + (4 / ks) - 1) / (4 / ks);
-    // up to 8 rows on at most half of the CUs a long contraction keeps five (us, three / five at 2 rows: 1024 x 14336 7.50 / 7.21,
-    // x 28672 11.39 / 10.70, 2048 x 28672 11.96 / 11.71; x 8192 5.44 / 5.61; 16 rows, 1024 x 28672 12.71 / 12.99)
-    return {nw, ks, grid, M <= 8 && ks == 4 && nw == 1 && K > 10240 && 2 * grid <= cus};
+    // a long contraction keeps five up to 8 rows on at most half of the CUs, up to 4 rows on three quarters (us from HBM, three / five at 1, 4, 8, 12
+    // rows: 1024 x 11008 8.0 8.0 8.3 8.8 / 7.5 7.7 8.4 9.0, x 28672 16.1 16.4 17.0 18.2 / 14.5 15.3 16.6 18.4; 2560 x 14336 10.5 10.6 10.9 11.6 / 9.9 10.2
+    // 10.9 11.8, 3072 x 28672 19.3 19.7 20.4 / 18.5 19.0 20.2; 4096 x 14336 12.7 12.7 12.8 / 12.8 12.9 13.1).  Three weights in turn, from the cache: 1024
+    // x 14336 7.2 7.2 7.2 / 7.0 7.0 7.1, 2560 x 14336 8.1 8.2 8.3 / 8.3 8.4 8.5; shorter ones lose there what they gain from HBM (1024 x 8192 HBM 6.6 6.7 7.0
+    // / 6.4 6.5 6.9, cache 5.0 5.1 5.2 / 5.3 5.3 5.4)
+    return {nw, ks, grid, ks == 4 && nw == 1 && K > 10240 && ((M <= 8 && 2 * grid <= cus) || (M <= 4 && 4 * grid <= 3 * cus))};
 }
 
 // columns of a strip (quant_strips.hip) for tensors of at most tall rows, load strips of 32 columns.  16 where 32 would keep half of the CUs busy,

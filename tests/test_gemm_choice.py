@@ -103,9 +103,10 @@ def test_wavefronts_of_the_widest_tiles(choose, tile):
 
 @pytest.mark.parametrize("cus", [64, 256])
 def test_half_of_the_cus_is_that_of_the_device(choose, cus):
-    """The deeper ring of few rows and narrow strips are for grids of at most half of the CUs, on a partition of the device too."""
-    deep = choose(f"few 2 {8 * cus} 14336", f"few 2 {8 * cus + 8} 14336", f"few 8 {8 * cus} 14336", f"few 9 {8 * cus} 14336", cus=cus)
-    assert ["deep" in a for a in deep] == [True, False, True, False]
+    """The deeper ring of few rows and narrow strips are for grids of a part of the CUs, on a partition of the device too."""
+    deep = choose(f"few 8 {8 * cus} 14336", f"few 8 {8 * cus + 8} 14336", f"few 9 {8 * cus} 14336", f"few 4 {12 * cus} 14336", f"few 4 {12 * cus + 8} 14336",
+                  f"few 5 {12 * cus} 14336", f"few 4 {8 * cus} 10240", cus=cus)
+    assert ["deep" in a for a in deep] == [True, False, False, True, False, False, False]
     assert choose(f"cols 2048 {cus // 2} 0", f"cols 2048 {cus // 2 + 1} 0", f"cols 1024 1 0", f"cols 4097 {cus} 0", cus=cus) == ["16", "32", "32", "16"]
 
 

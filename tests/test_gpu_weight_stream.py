@@ -63,8 +63,8 @@ def test_rows_between_the_few_row_and_the_ring_kernel(M, N):
         assert torch.equal(_mm(a, E5, b, E4), want), K
 
 
-@pytest.mark.parametrize("M", [1, 8, 9])
-@pytest.mark.parametrize("N,K", [(1024, 10240), (1024, 10256), (2048, 11024), (2056, 11024), (24, 28672)])
+@pytest.mark.parametrize("M", [1, 4, 5, 8, 9])
+@pytest.mark.parametrize("N,K", [(1024, 10240), (1024, 10256), (2048, 11024), (2056, 11024), (3072, 11024), (3080, 10256), (24, 28672)])
 def test_both_sides_of_the_longer_ring_of_few_rows(M, N, K):
     a, b = _ints(M, K, M, E4), _ints(N, K, 2, E5)
     with knobs(GEMM_VARIANT=4):

@@ -11,7 +11,8 @@ pytestmark = pytest.mark.gpu
 import paper_2507_16099_amd as fp8  # noqa: E402
 
 
-@pytest.mark.parametrize("M,K,N", [(32, 128, 32), (160, 256, 2112), (2080, 384, 96), (128, 2176, 128), (2176, 128, 2304), (384, 640, 512)])
+@pytest.mark.parametrize("M,K,N", [(32, 128, 32), (160, 256, 2112), (2080, 384, 96), (128, 2176, 128), (2176, 128, 2304), (384, 640, 512),
+                                   (2048, 2048, 2048), (2048, 2048, 2176)])      # (the last two: on and beyond the 8 Mi elements of plain loads)
 @pytest.mark.parametrize("kind", ["mx", "block"])
 def test_one_launch_changes_no_bit(M, K, N, kind):
     if kind == "block" and (M % 128 or N % 128):

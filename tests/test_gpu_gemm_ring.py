@@ -122,3 +122,35 @@ def test_backward_of_few_tokens_in_one_launch(M, K, N):
     with knobs(PAIRS=0):
         dx0, dw0 = fp8.fp8_linear_bwd(dy, x, w, r)
     assert torch.equal(dx.view(torch.int16), dx0.view(torch.int16)) and torch.equal(dw.view(torch.int16), dw0.view(torch.int16))
+
+
+@pytest.mark.parametrize("tile", ["128x256", "256x128"])
+@pytest.mark.parametrize("M,N,K", [(1, 8, 6160), (130, 264, 6272), (257, 520, 6400), (300, 392, 6144)])
+def test_widest_tiles_on_either_side_of_their_short_contractions(tile, M, N, K):
+    """Eight wavefronts up to K = 6144, four beyond: odd and even counts of steps, a K that ends inside a step, ragged rows and columns; all
+    outputs, and the sigmoid as the large-product kernel gives it."""
+    rng = np.random.default_rng(K + M)
+    ai, bi = _ints((M, K), rng), _ints((N, K), rng)
+    sa, sb = (2.0 ** rng.integers(-3, 4, size=M)).astype(np.float32), (2.0 ** rng.integers(-3, 4, size=N)).astype(np.float32)
+    want = (ai @ bi.T).astype(np.float32) / sa[:, None] / sb[None, :]
+    with knobs(GEMM_RING=TILES[tile]):
+        for fa, fb in ((0, 0), (0, 1), (1, 0), (1, 1)):
+            args = (dev_u8(orc.encode_array(ai, fa)), fa, dev_f32(sa), fp8.FP8_ROW, dev_u8(orc.encode_array(bi, fb)), fb, dev_f32(sb), fp8.FP8_ROW)
+            assert (host_f32(fp8.fp8_scaled_mm(*args, fp8.FP8_OUT_FP32)) == want).all(), (fa, fb)
+            assert (host_bf16_bits(fp8.fp8_scaled_mm(*args)) == orc.f32_to_bf16(want)).all(), (fa, fb)
+        got = host_bf16_bits(fp8.fp8_scaled_mm(*args, fp8.FP8_EPILOGUE_SIGMOID))
+    with knobs(GEMM_VARIANT=4):
+        assert (got == host_bf16_bits(fp8.fp8_scaled_mm(*args, fp8.FP8_EPILOGUE_SIGMOID))).all()
+
+
+@pytest.mark.parametrize("tile", ["128x256", "256x128"])
+@pytest.mark.parametrize("M,K,N", [(272, 144, 6272), (6272, 144, 272), (6160, 80, 6400)])
+def test_two_products_of_which_one_or_both_are_long(tile, M, K, N):
+    rng = np.random.default_rng(M)
+    dy, x, w = (torch.from_numpy(_ints(s, rng)).cuda().to(torch.bfloat16) for s in ((M, N), (M, K), (N, K)))
+    r = fp8.Recipe(gran=fp8.FP8_ROW, flags=fp8.FP8_POW2_SCALE)
+    with knobs(GEMM_RING=TILES[tile]):
+        dx, dw = fp8.fp8_linear_bwd(dy, x, w, r)
+    with knobs(GEMM_RING=0, PAIRS=0, GEMM_VARIANT=4):
+        dx0, dw0 = fp8.fp8_linear_bwd(dy, x, w, r)
+    assert torch.equal(dx.view(torch.int16), dx0.view(torch.int16)) and torch.equal(dw.view(torch.int16), dw0.view(torch.int16))

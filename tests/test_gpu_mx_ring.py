@@ -82,3 +82,19 @@ def test_partly_filled_slabs(M, K, N, variant):
         want = run()
     for a, b in zip(got, want):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("tile", ["128x256", "256x128"])
+@pytest.mark.parametrize("M,N,K", [(70, 72, 3072), (130, 264, 3200), (257, 520, 6144), (65, 264, 6272), (300, 392, 6656)])
+def test_widest_tiles_on_either_side_of_their_short_contractions(tile, M, N, K):
+    """Eight wavefronts up to K = 3072 with plain scale rows and 6144 with slabs, four beyond: bit for bit the 256 x 256 kernel's result."""
+    x, w = dev_bf16(si.normal_bf16((M, K), 1.0, 1, M)), dev_bf16(si.normal_bf16((N, K), 0.02, 2, N))
+    for fa, fb in ((0, 0), (1, 0), (0, 1), (1, 1)):
+        for slabs in (False, True) if K % 512 == 0 else (False,):
+            args = (fp8.fp8_mx_quantize(x, fa, slabs=slabs), fp8.fp8_mx_quantize(w, fb, slabs=slabs))
+            for flags in (0, fp8.FP8_OUT_FP32):
+                run = lambda: fp8.fp8_mx_scaled_mm(args[0][0], fa, args[0][1], args[1][0], fb, args[1][1], flags)      # noqa: E731
+                with knobs(MX_VARIANT=1):
+                    want = run()
+                with knobs(GEMM_RING=TILES[tile]):
+                    assert torch.equal(run(), want), (fa, fb, slabs, flags)

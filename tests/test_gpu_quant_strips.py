@@ -90,3 +90,25 @@ def test_one_gradient_wanted(M, K, N, want):
     for strips in (None, 2, 4):
         with knobs(STRIPS=strips):
             assert torch.equal(run(), ref)
+
+
+@pytest.mark.parametrize("M,K,N", [(2048, 4096, 4096), (2064, 4096, 4096), (4096, 2056 * 2, 2048), (592, 16384, 1008)])
+def test_rows_of_large_steps_are_read_with_the_hint(M, K, N):
+    """Both sides of 24 Mi elements by rows, whose loads carry the streaming hint beyond."""
+    x, w, dy = _inputs(M, K, N, False)
+    for flags in (0, fp8.FP8_GRAD_WEIGHT_HP):
+        r = fp8.Recipe(gran=fp8.FP8_ROW, flags=flags | fp8.FP8_SAVE_FOR_BWD)
+
+        def run():
+            ws = torch.full((fp8.fp8_linear_workspace_bytes(M, K, N, r, True),), 0x7F, dtype=torch.uint8, device="cuda")
+            outs = [fp8.fp8_linear_fwd(x, w, r, workspace=ws)]
+            outs += list(fp8.fp8_linear_bwd(dy, x, w, r, workspace=ws))
+            return [o.view(torch.int16).clone() for o in outs]
+
+        with knobs(PAIRS=0):
+            want = run()
+        for strips in (None, 2, 4):
+            with knobs(STRIPS=strips):
+                got = run()
+            for a, b in zip(got, want):
+                assert torch.equal(a, b), (strips, flags)

@@ -25,16 +25,16 @@ def _mm(a, fa, b, fb):
     return fp8.fp8_scaled_mm(a, fa, sa, ROW, b, fb, sb, ROW).view(torch.int16)
 
 
-@pytest.mark.parametrize("N,K", [(16384, 6144), (16376, 6144), (16400, 6160)])      # 96 MiB exactly, less, ragged
+@pytest.mark.parametrize("N,K", [(16384, 6144), (16376, 6144), (16400, 6160), (16128, 6400)])      # 96 MiB exactly, less, ragged, a longer contraction
 @pytest.mark.parametrize("fb", [E4, E5])
 def test_both_sides_of_the_size_of_a_streamed_weight(N, K, fb):
     b = _ints(N, K, 1, fb)
-    for M in (3, 16, 31, 64, 65, 128, 129, 255):
+    for M in (3, 16, 31, 64, 65, 128, 129, 192, 255):
         a = _ints(M, K, M, E4)
         with knobs(GEMM_VARIANT=4):
             want = _mm(a, E4, b, fb)
         assert torch.equal(_mm(a, E4, b, fb), want), M
-        for tile in (1, 3, 4, 5):
+        for tile in (1, 3, 4, 5, 6):
             with knobs(GEMM_RING=tile):
                 assert torch.equal(_mm(a, E4, b, fb), want), (M, tile)
 

@@ -236,24 +236,23 @@ static hipError_t launch_tn(const GemmOperands& g, int row_a, int row_b, hipStre
 }
 
 // ---- kernel choice.  Up to 16 rows: the few-row kernel of gemm_fp8_skinny.hip (it streams B once).  17 to 32 rows: the same where
-// there are 64 x 64 ring tiles for less than five eighths of the CUs, else those tiles (us, few-row / ring at 32 rows, weights from HBM:
-// 4096 x 4096 7.1 / 11.2, 8192 x 4096 10.2 / 12.0; 11008 x 4096 15.1 / 13.4, 14336 x 4096 16.2 / 15.3; with the streaming hint 28672 x 4096
-// 27.5 / 26.6, 28672 x 8192 47.3 / 43.6).  Up to 64 rows the few-row kernel where
-// there are too few 64 x 64 tiles for the CUs, N <= 8192, and the contraction is long enough for its wavefronts to share
-// (us, few-row / best ring tile, N x K at 33, 40, 48, 64 rows, weights from HBM: 4096 x 4096 7.8 / 11.2, 8.0 / 11.5,
-// 8.5 / 12.0, 9.5 / 12.8; 8192 x 4096 11.1 / 12.1, 11.5 / 12.4, 11.9 / 12.9, 13.0 / 13.9; 4096 x 14336 18.3 / 30.3 .. 23.6 / 36.9; 4096 x
-// 2048 4.9 / 6.1 .. 5.8 / 6.3.  Beyond the lines: 11008 x 4096 18.8 / 13.1 .. 22.3 / 14.8, 14336 x 4096 20.4 / 15.3 .. 23.6 / 16.0,
-// 28672 x 8192 60.7 / 50.1 .. 71.8 / 52.1, 8192 x 1024 6.1 / 5.1 .. 6.8 / 5.2.  On them it is close: 8192 x 2048 7.8 / 7.8 .. 9.2 / 8.7,
-// 4096 x 1024 4.7 / 4.9 .. 5.3 / 5.1.)
-// More than one round of 256 x 256 tiles (one per CU): the large-product kernels of gemm_fp8_snake.hip /
-// gemm_fp8_stream.hip.  In between the cheapest of the ring kernel's tiles (gemm_fp8_ring.hip) and one round of
-// 256 x 256 tiles by this estimate, in us (one launch; rounds of 256 workgroups, K steps of 128 bytes):
+// there are 64 x 64 ring tiles for less than five eighths of the CUs, else those tiles (us, few-row / ring at 32 rows, weights from
+// HBM: 4096 x 4096 7.1 / 11.2, 8192 x 4096 10.2 / 12.0; 11008 x 4096 15.1 / 13.4, 14336 x 4096 16.2 / 15.3; with the streaming hint
+// 28672 x 4096 27.5 / 26.6, 28672 x 8192 47.3 / 43.6).  Up to 64 rows the few-row kernel where there are too few 64 x 64 tiles for
+// the CUs, N <= 8192, and the contraction is long enough for its wavefronts to share (us, few-row / best ring tile, N x K at 33,
+// 40, 48, 64 rows, weights from HBM: 4096 x 4096 7.8 / 11.2, 8.0 / 11.5, 8.5 / 12.0, 9.5 / 12.8; 8192 x 4096 11.1 / 12.1, 11.5 /
+// 12.4, 11.9 / 12.9, 13.0 / 13.9; 4096 x 14336 18.3 / 30.3 .. 23.6 / 36.9; 4096 x 2048 4.9 / 6.1 .. 5.8 / 6.3.  Beyond the lines:
+// 11008 x 4096 18.8 / 13.1 .. 22.3 / 14.8, 14336 x 4096 20.4 / 15.3 .. 23.6 / 16.0, 28672 x 8192 60.7 / 50.1 .. 71.8 / 52.1, 8192 x
+// 1024 6.1 / 5.1 .. 6.8 / 5.2.  On them it is close: 8192 x 2048 7.8 / 7.8 .. 9.2 / 8.7, 4096 x 1024 4.7 / 4.9 .. 5.3 / 5.1.) More
+// than one round of 256 x 256 tiles (one per CU): the large-product kernels of gemm_fp8_snake.hip / gemm_fp8_stream.hip.  In
+// between the cheapest of the ring kernel's tiles (gemm_fp8_ring.hip) and one round of 256 x 256 tiles by this estimate, in us (one
+// launch; rounds of 256 workgroups, K steps of 128 bytes):
 //     3 + rounds * (a + steps * b);  256 x 256 tiles: 10 + 1.2 * steps, at most half of the CUs busy (half tiles) 7.2 + 0.91 * steps.
 // a: prologue and epilogue of a tile; b: a K step with every CU busy (some 460 / 670 / 970 / 1600 cycles for the tiles below; their
-// matrix instructions take 128 / 256 / 512 / 1024, the fragment reads and LDS-DMA writes at 128 bytes a cycle 384 / 576 / 768 / 1152).
-// No unit is full: 128 x 128 tiles at 777 x 4096 x 14336 keep the matrix units busy 42 % of the time and the LDS's reads 22 %.
-// Measured (a HIP graph of twelve, operands alternating; us; K = 1024 / 4096 / 16384; since then 128 x 64 tiles take 0.4 us less, 128 x 256
-// tiles 0.7 up to K = 6144):
+// matrix instructions take 128 / 256 / 512 / 1024, the fragment reads and LDS-DMA writes at 128 bytes a cycle 384 / 576 / 768 /
+// 1152). No unit is full: 128 x 128 tiles at 777 x 4096 x 14336 keep the matrix units busy 42 % of the time and the LDS's reads 22
+// %. Measured (a HIP graph of twelve, operands alternating; us; K = 1024 / 4096 / 16384; since then 128 x 64 tiles take 0.4 us
+// less, 128 x 256 tiles 0.7 up to K = 6144):
 //                        64x64              128x64             128x128            128x256            before (other kernels)
 //     1024 x 1024     6.0 / 10.5 / 29     7.4 / 13.2 / 36     8.3 / 16.0 / 46    11.3 / 23.9 / 73      7.8 / 14.8 / 45
 //     1024 x 2048     9.6 / 18.3 / 66     7.9 / 14.2 / 50     8.6 / 17.2 / 64    11.6 / 24.8 / 99     10.3 / 21.8 / 74
@@ -265,9 +264,10 @@ static hipError_t launch_tn(const GemmOperands& g, int row_a, int row_b, hipStre
 // GEMM_BIG_FROM: number of 128 x 128 tiles from which the 256 x 256 kernels are taken; GEMM_VARIANT forces a kernel:
 // 0 = the fallback above, 4 = 256 x 256, 5 = few-row kernel (only where M <= 64), 6 / 7 = ring kernel, 64 x 64 / 128 x 128 tiles.
 namespace {
-// a of the widest tiles is that of eight wavefronts also beyond K = 6144, where four take 0.7 us more: it decides there only between a shared launch
-// of two products on these tiles and other forms, of which the shared launch is the faster (us a backward step, 6.3 / 7.0: 2215 x 2048 x 7936
-// 110.8 / 124.3 on 128 x 128 tiles, 4743 x 896 x 16000 272.5 / 300.3; apart 2091 x 2048 x 7168 93.3 / 101.9, 3729 x 1152 x 11648 173.0 / 182.6).
+// a of the widest tiles is that of eight wavefronts also beyond K = 6144, where four take 0.7 us more: it decides there only
+// between a shared launch of two products on these tiles and other forms, of which the shared launch is the faster (us a backward
+// step, 6.3 / 7.0: 2215 x 2048 x 7936 110.8 / 124.3 on 128 x 128 tiles, 4743 x 896 x 16000 272.5 / 300.3; apart 2091 x 2048 x 7168
+// 93.3 / 101.9, 3729 x 1152 x 11648 173.0 / 182.6).
 struct RingCost { int tm, tn; double a, b; };
 constexpr RingCost kRing[RING_TILES] = {{64, 64, 1.0, 0.20},   {128, 64, 1.9, 0.29},  {64, 128, 1.9, 0.29},
                                         {128, 128, 4.0, 0.42}, {128, 256, 6.3, 0.70}, {256, 128, 6.3, 0.70}};
@@ -281,8 +281,8 @@ double ring_cost(int tile, const GemmOperands& g, const GemmOperands* g2, int64_
     const int64_t n1 = tiles(g), n2 = g2 ? tiles(*g2) : 0;
     const double operands = 1e-5 * (double)(n1 + n2) * (c.tm + c.tn);      // (equal otherwise: fewer operand bytes)
     if (n1 + n2 <= cus) return 3.0 + (per1 > per2 ? per1 : per2) + operands;
-    // beside a product of up to 32 rows the lowest tiles' later rounds cost more than the first (us a backward step apart / together:
-    // 32 x 14336 x 256 14.3 / 64x64 17.7, 64x128 15.1, 128x256 12.1; 32 x 11008 x 128 12.4 / 64x64 12.6, 128x128 9.9)
+    // beside a product of up to 32 rows the lowest tiles' later rounds cost more than the first (us a backward step apart /
+    // together: 32 x 14336 x 256 14.3 / 64x64 17.7, 64x128 15.1, 128x256 12.1; 32 x 11008 x 128 12.4 / 64x64 12.6, 128x128 9.9)
     const double later = tile <= RING_64x128 && g2 && g.M <= 32 ? 0.8 * (double)(cdiv(n1 + n2, cus) - 1) : 0.0;
     const double rounds = (double)cdiv(n1 + n2, cus) * ((double)n1 * per1 + (double)n2 * per2) / (double)(n1 + n2) + later;
     return 3.0 + (rounds > per1 + per2 ? rounds : per1 + per2) + operands;     // (two unequal products: at least one tile of each in turn)
@@ -355,6 +355,9 @@ hipError_t launch_gemm_fp8(const uint8_t* a, int64_t lda, int fmt_a, const float
 // else 10 + 1.25 * steps (there are no half tiles).  Measured (us, slabs / plain, before: 256 x 256 or register-staged tiles):
 //     1024 x 1024 x 4096  64x64 12.6 / 14.3, before 40.7 / 77.2     2048 x 2048 x 4096  128x128 21.7 / 26.5, before 41.1 / 76.9
 //     2048 x 4096 x 4096  128x256 34.8 / 39.6, before 42.6 / 43.6   3072 x 4096 x 4096  128x256 59.5 / 67.4, 256x256 48.7 / 46.4
+// With the shorter rings and eight wavefronts since, over 300 x 14336 .. 4096 x 4096 and K = 1024 .. 14336 (130 shapes), the tile
+// taken is on average 1.2 % (slabs) and 3.0 % (plain rows) behind the best one, at most 40 %, where 256 x 256 tiles are taken for
+// K = 1024; plain products 1.8 %.
 int gemm_mxfp8_ring_choice(const GemmOperands& g, bool plain_scales) {
     if (const int r = knob(KNOB_GEMM_RING); r >= 0 && r <= RING_TILES) return r - 1;
     const int64_t cus = compute_units() > 0 ? compute_units() : 256;

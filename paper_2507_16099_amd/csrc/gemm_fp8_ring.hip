@@ -476,10 +476,10 @@ static hipError_t launch_ring_t(const GemmOperands& g1, const GemmOperands* g2, 
     return hipGetLastError();
 }
 
-// stages: 128 x 64 and 64 x 128 tiles take four, though six fit: filling them is the longer part of a short product (us, six / four:
-// 1024 x 2048 x 1024 6.3 / 6.0, 72 x 14336 x 4096 13.8 / 12.8, 512 x 4096 x 4096 13.4 / 13.0, 256 x 4096 x 14336 32.6 / 31.9).  Otherwise what the LDS holds;
-// rows of tiles walked together: close to square patches.  64 x 64: five stages, which with the
-// table of reciprocals is one workgroup per CU; four, for two of them (as in the MX form), cost a long contraction more than
+// stages: 128 x 64 and 64 x 128 tiles take four, though six fit: filling them is the longer part of a short product (us, six /
+// four: 1024 x 2048 x 1024 6.3 / 6.0, 72 x 14336 x 4096 13.8 / 12.8, 512 x 4096 x 4096 13.4 / 13.0, 256 x 4096 x 14336 32.6 /
+// 31.9; block-scaled 1024 x 2048 x 1024 7.4 / 6.9, x 8192 33.7 / 33.1, 72 x 14336 x 4096 17.4 / 17.0).  Otherwise what the LDS holds; rows of tiles walked together: close to square patches.  64 x 64: five stages, which with
+// the table of reciprocals is one workgroup per CU; four, for two of them (as in the MX form), cost a long contraction more than
 // they give a short one or a second round (us, five / four stages: 1000 x 1000 x 14336 25.2 / 27.1, 512 x 512 x 28672 40.5 / 43.0,
 // 1024 x 1024 x 4096 10.5 / 10.5, x 1024 6.0 / 5.8; several rounds, where larger tiles are taken: 2048 x 2048 x 1024 16.3 / 12.9).
 template <int FA, int FB, bool MX>

@@ -412,14 +412,14 @@ static hipError_t launch_sk_dma(const uint8_t* a, int64_t lda, const float* sa, 
                                 const float* sb, int row_b, int M, int N, int K, void* out, int64_t ld_out, int out_f32,
                                 int64_t grid, hipStream_t st) {
     constexpr int SLOT = (NW + MT) * 2048;
-    // Short rings, whose LDS leaves room for three workgroups per CU (up to 16 rows) or two (one at 49 to 64 rows against 32 columns per
-    // wavefront), rather than long ones: a workgroup streams nothing while its ring fills and while its K parts are summed.
-    // (us, weights from HBM: five steps / three at 16 x 4096 x 4096 6.2 / 5.9; three / two at 16 x 28672 x 4096 25.9 / 25.0, 2 x 14336 x 4096 13.5 /
-    // 13.1, 16 x 11008 x 4096 13.3 / 12.7, 64 x 8192 x 8192 19.9 / 19.5, 64 x 4096 x 4096 9.6 / 9.3, 48 x 1024 x 8192 11.9 / 11.6, 33 x 2048 x 11008 +2 %.
-    // One or two tiles of 16 rows against one of 16 columns keep three: 2 x 4096 x 8192 8.2 / 9.3, 32 x 1024 x 8192 9.7 / 9.8.  Two lose at 33 to 36
-    // rows against few columns where K is a multiple of 8192: 33 x 512 x 8192 7.4 / 7.7, 33 x 1024 x 16384 17.0 / 17.3, x 28672 28.9 / 29.0, 36 x 1024 x
-    // 16384 -1 %; at 40 rows and more they are equal or ahead there too)
-    // DEEP: five, where few_row_form says so
+    // Short rings, whose LDS leaves room for three workgroups per CU (up to 16 rows) or two (one at 49 to 64 rows against 32
+    // columns per wavefront), rather than long ones: a workgroup streams nothing while its ring fills and while its K parts are
+    // summed. (us, weights from HBM: five steps / three at 16 x 4096 x 4096 6.2 / 5.9; three / two at 16 x 28672 x 4096 25.9 /
+    // 25.0, 2 x 14336 x 4096 13.5 / 13.1, 16 x 11008 x 4096 13.3 / 12.7, 64 x 8192 x 8192 19.9 / 19.5, 64 x 4096 x 4096 9.6 / 9.3,
+    // 48 x 1024 x 8192 11.9 / 11.6, 33 x 2048 x 11008 +2 %. One or two tiles of 16 rows against one of 16 columns keep three: 2 x
+    // 4096 x 8192 8.2 / 9.3, 32 x 1024 x 8192 9.7 / 9.8.  Two lose at 33 to 36 rows against few columns where K is a multiple of
+    // 8192: 33 x 512 x 8192 7.4 / 7.7, 33 x 1024 x 16384 17.0 / 17.3, x 28672 28.9 / 29.0, 36 x 1024 x 16384 -1 %; at 40 rows and
+    // more they are equal or ahead there too) DEEP: five, where few_row_form says so
     constexpr int R = DEEP ? 5 : SLOT <= 6144 && NW == 1 ? 3 : 2;
     constexpr int lds = 4 * R * SLOT;
     auto launch = [&](auto kern, DynamicLdsOnce& attr) {

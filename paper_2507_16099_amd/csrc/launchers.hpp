@@ -7,12 +7,13 @@
 namespace fp8k {
 
 // Whether a quantization of this many elements, all tensors of the launch together, reads its bfloat16 input with the streaming
-// hint.  The hint makes a load slower by itself (a strip of 4096 rows arrives in 17 instead of 10 us), but its data does not displace what
-// the product reads next (us, hint / plain: see each launcher's lines).
+// hint.  The hint makes a load slower by itself (a strip of 4096 rows arrives in 17 instead of 10 us), but its data does not
+// displace what the product reads next (us, hint / plain: see each launcher's lines).
 inline bool hint_inputs(int64_t elements, int64_t line) { return elements > line; }
-// One tensor before its product: what plain loads gain is small (1 to 3 %), what they cost is large where the weights in turn just fit
-// the last-level cache and the input no longer does beside them (us, hint / plain, three weights in turn: 712 x 7840 x 8080 65.0 / 81.4,
-// 512 x 14336 x 4096 42.3 / 53.2; six: 1900 x 4096 x 4096 36.3 / 40.0).  So only inputs that are a small part of that cache, 4 MB.
+// One tensor before its product: what plain loads gain is small (1 to 3 %), what they cost is large where the weights in turn just
+// fit the last-level cache and the input no longer does beside them (us, hint / plain, three weights in turn: 712 x 7840 x 8080
+// 65.0 / 81.4, 512 x 14336 x 4096 42.3 / 53.2; six: 1900 x 4096 x 4096 36.3 / 40.0).  So only inputs that are a small part of that
+// cache, 4 MB.
 constexpr int64_t HINT_ALONE = (int64_t)2 << 20;
 constexpr int64_t HINT_BLOCKS = (int64_t)8 << 20;    // the tensors of an MX or blockwise step
 constexpr int64_t HINT_PAIR = (int64_t)24 << 20;     // X and W of a step, whose codes are all that the product reads
@@ -74,14 +75,15 @@ struct GemmOperands {
 hipError_t launch_gemm_fp8_pair(const GemmOperands& g1, const GemmOperands& g2, int fmt_a, int fmt_b, int row_a, int row_b,
                                 hipStream_t st);
 
-// Whether the rows of a product's weight [N, K] are requested with the streaming hint: from 96 MiB on, for a served model, whose layers
-// between two calls push such a weight out of the 256 MB last-level cache.  From HBM it then passes at 5.9 instead of 5.2 TB/s (us without /
-// with, three weights in turn: 16 x 28672 x 4096 25.3 / 22.0, x 8192 45.8 / 40.2; 64 x 16384 x 8192 32.6 / 28.2).  What that costs: a weight called
-// again and again with nothing in between, or just written, is in the cache and comes slower with the hint (the same with one
-// weight: 19.9 / 21.1, 36.7 / 39.4, 23.2 / 27.2; 128 x 28672 x 4096 22.8 / 27.4, x 8192 39.3 / 53.4, 72 x 16512 x 6528 22.9 / 33.1).  Smaller weights gain as much from HBM (16 x
-// 14336 x 4096 13.6 / 12.6), but more of them fit the cache between the calls, and lose there (the same, three weights in turn: 11.1 / 12.2).
-// Rows have to be whole lines of 128 bytes: a line that two rows or two stages share is fetched twice with the hint (1 x 28672 x 4112 24.8 /
-// 36.5, x 8224 52.0 / 62.9, x 8256 53.6 / 60.1; 128 x 28672 x 8224 72.8 / 86.7; x 8320, whole lines, 49.3 / 45.0).
+// Whether the rows of a product's weight [N, K] are requested with the streaming hint: from 96 MiB on, for a served model, whose
+// layers between two calls push such a weight out of the 256 MB last-level cache.  From HBM it then passes at 5.9 instead of 5.2
+// TB/s (us without / with, three weights in turn: 16 x 28672 x 4096 25.3 / 22.0, x 8192 45.8 / 40.2; 64 x 16384 x 8192 32.6 /
+// 28.2).  What that costs: a weight called again and again with nothing in between, or just written, is in the cache and comes
+// slower with the hint (the same with one weight: 19.9 / 21.1, 36.7 / 39.4, 23.2 / 27.2; 128 x 28672 x 4096 22.8 / 27.4, x 8192
+// 39.3 / 53.4, 72 x 16512 x 6528 22.9 / 33.1).  Smaller weights gain as much from HBM (16 x 14336 x 4096 13.6 / 12.6), but more of
+// them fit the cache between the calls, and lose there (the same, three weights in turn: 11.1 / 12.2). Rows have to be whole lines
+// of 128 bytes: a line that two rows or two stages share is fetched twice with the hint (1 x 28672 x 4112 24.8 / 36.5, x 8224 52.0
+// / 62.9, x 8256 53.6 / 60.1; 128 x 28672 x 8224 72.8 / 86.7; x 8320, whole lines, 49.3 / 45.0).
 inline bool stream_weight(const uint8_t* b, int64_t ldb, int64_t N, int64_t K) {
     return N * K >= (int64_t)96 << 20 && (((uintptr_t)b | (uint64_t)ldb) & 127) == 0;
 }
@@ -89,13 +91,15 @@ inline bool stream_weight(const uint8_t* b, int64_t ldb, int64_t N, int64_t K) {
 // products of few to middling size on smaller tiles with a deep LDS ring (gemm_fp8_ring.hip); g2: a second product in
 // the same launch, or nullptr; mode 0 = bfloat16, 1 = fp32, 2 = bfloat16 of the sigmoid.  _fits: 32-bit offsets reach
 enum RingTile { RING_64x64 = 0, RING_128x64, RING_64x128, RING_128x128, RING_128x256, RING_256x128, RING_TILES };
-// Its form for a tile: whether B is read with the streaming hint.  One row of tiles against a weight that stream_weight accepts reads it once (us,
-// weights from HBM, without / with: 64 x 28672 x 8192 51.5 / 47.0, 128 rows 56.1 / 53.2, x 4096 32.8 / 30.5).  Not two rows of 128 x 256 tiles: they
-// read it side by side, but fall out of step where the second is not full, and lines are fetched twice (129 rows, x 8192 61.2 / 66.2, x 6144
-// 47.8 / 53.5, x 3584 28.9 / 32.5; 160 rows 63.7 / 64.6, 50.1 / 52.3, 30.5 / 31.7; 256 rows 68.4 / 65.7, 56.7 / 54.3, 34.5 / 33.8); one_row below is
-// for them.  Where the same call has quantized B, its codes are in the last-level cache: the taller tiles then read them plainly (forward of 128 rows, N x K
-// 28672 x 4096 73.9 / 75.6, x 8192 140.3 / 141.7; dX against W^T 28672 x 4096 112.3 / 114.5), low ones with the hint (forward 64 rows 72.0 / 72.4, 136.8 /
-// 137.7, 16384 x 8192 82.0 / 82.3; dX 64 rows 106.8 / 105.0, 271.4 / 268.8, 163.8 / 162.1, 16 rows 104.3 / 100.2, 268.8 / 263.7, 156.3 / 154.8).
+// Its form for a tile: whether B is read with the streaming hint.  One row of tiles against a weight that stream_weight accepts
+// reads it once (us, weights from HBM, without / with: 64 x 28672 x 8192 51.5 / 47.0, 128 rows 56.1 / 53.2, x 4096 32.8 / 30.5).
+// Not two rows of 128 x 256 tiles: they read it side by side, but fall out of step where the second is not full, and lines are
+// fetched twice (129 rows, x 8192 61.2 / 66.2, x 6144 47.8 / 53.5, x 3584 28.9 / 32.5; 160 rows 63.7 / 64.6, 50.1 / 52.3, 30.5 /
+// 31.7; 256 rows 68.4 / 65.7, 56.7 / 54.3, 34.5 / 33.8); one_row below is for them.  Where the same call has quantized B, its codes
+// are in the last-level cache: the taller tiles then read them plainly (forward of 128 rows, N x K 28672 x 4096 73.9 / 75.6, x 8192
+// 140.3 / 141.7; dX against W^T 28672 x 4096 112.3 / 114.5), low ones with the hint (forward 64 rows 72.0 / 72.4, 136.8 / 137.7,
+// 16384 x 8192 82.0 / 82.3; dX 64 rows 106.8 / 105.0, 271.4 / 268.8, 163.8 / 162.1, 16 rows 104.3 / 100.2, 268.8 / 263.7, 156.3 /
+// 154.8).
 inline bool ring_hint(int tile, const GemmOperands& g, const GemmOperands* g2) {
     if (g2 || !stream_weight(g.b, g.ldb, g.N, g.K)) return false;
     switch (tile) {
@@ -104,18 +108,20 @@ inline bool ring_hint(int tile, const GemmOperands& g, const GemmOperands* g2) {
     }
     return false;
 }
-// 129 to 256 rows against such a weight: one row of 256 x 128 tiles in place of two of 128 x 256, which fetches it once (us from HBM, 129 / 193 / 256
-// rows, 128 x 256 plain, with the hint, 256 x 128: 28672 x 8192 61.5 66.2 69.9, 65.3 63.1 65.4, 58.0 62.6 67.1; x 6144 47.6 52.6 57.2, 53.6 51.4 54.3, 46.3
-// 50.0 52.7; x 3584 29.2 32.1 34.5, 33.0 32.1 34.0, 28.7 31.6 34.8; 24576 x 4608 34.7 38.3 42.0, 39.8 38.2 40.3, 33.5 37.3 38.2).  From the cache the two
-// are close (28672 x 6144 36.1 39.7 40.2 / 35.2 38.8 43.2): where the same call has quantized the weight nothing changes.
+// 129 to 256 rows against such a weight: one row of 256 x 128 tiles in place of two of 128 x 256, which fetches it once (us from
+// HBM, 129 / 193 / 256 rows, 128 x 256 plain, with the hint, 256 x 128: 28672 x 8192 61.5 66.2 69.9, 65.3 63.1 65.4, 58.0 62.6
+// 67.1; x 6144 47.6 52.6 57.2, 53.6 51.4 54.3, 46.3 50.0 52.7; x 3584 29.2 32.1 34.5, 33.0 32.1 34.0, 28.7 31.6 34.8; 24576 x 4608
+// 34.7 38.3 42.0, 39.8 38.2 40.3, 33.5 37.3 38.2).  From the cache the two are close (28672 x 6144 36.1 39.7 40.2 / 35.2 38.8
+// 43.2): where the same call has quantized the weight nothing changes.
 inline bool one_row(const GemmOperands& g) { return g.M > 128 && g.M <= 256 && !g.b_written && stream_weight(g.b, g.ldb, g.N, g.K); }
-// Wavefronts of a workgroup: four, one per SIMD, or eight on 128 x 256 and 256 x 128 tiles of short contractions, K <= 6144 (us, four / eight: 2048 x 4096 x
-// 1024 14.5 / 13.4, 3001 x 2048 x 4096 26.0 / 25.1, 2048 x 4096 x 4096 29.6 / 28.7, 1000 x 4096 x 6144 34.2 / 32.7, 4096 x 4096 x 6144 79.5 / 77.1, with the
-// hint 72 x 28672 x 4096 35.8 / 34.7; x 8192 99.6 / 99.2, 2048 x 4096 x 8192 50.3 / 51.0, x 14336 +2 %).  Not where a row of full 256 x 128 tiles fetches a
-// large weight (160 / 193 / 224 / 256 rows, 24576 x 4608 36.7 37.3 37.8 38.2 / 35.8 37.2 39.0 41.7, 28672 x 6144 50.0 50.0 51.1 52.7 / 48.4 49.0 51.9
-// 55.7, 20480 x 5120 42.1 42.6 42.4 44.1 / 41.5 43.9 43.8 47.9).  Block-scaled: the same with slabs of scales (1000 x 4096 x 4096 -7 %, 2048 x 4096 x
-// 6144 -1 %), with plain rows of them up to K = 3072 (3001 x 2048 x 1024 14.2 / 13.0, x 3072 -2 %, x 4096 34.2 /
-// 35.4, x 6144 49.4 / 50.2; 1000 x 4096 x 4096 32.4 / 33.4; 4096 x 4096 x 6144 104.0 / 103.6).
+// Wavefronts of a workgroup: four, one per SIMD, or eight on 128 x 256 and 256 x 128 tiles of short contractions, K <= 6144 (us,
+// four / eight: 2048 x 4096 x 1024 14.5 / 13.4, 3001 x 2048 x 4096 26.0 / 25.1, 2048 x 4096 x 4096 29.6 / 28.7, 1000 x 4096 x 6144
+// 34.2 / 32.7, 4096 x 4096 x 6144 79.5 / 77.1, with the hint 72 x 28672 x 4096 35.8 / 34.7; x 8192 99.6 / 99.2, 2048 x 4096 x 8192
+// 50.3 / 51.0, x 14336 +2 %).  Not where a row of full 256 x 128 tiles fetches a large weight (160 / 193 / 224 / 256 rows, 24576 x
+// 4608 36.7 37.3 37.8 38.2 / 35.8 37.2 39.0 41.7, 28672 x 6144 50.0 50.0 51.1 52.7 / 48.4 49.0 51.9 55.7, 20480 x 5120 42.1 42.6
+// 42.4 44.1 / 41.5 43.9 43.8 47.9).  Block-scaled: the same with slabs of scales (1000 x 4096 x 4096 -7 %, 2048 x 4096 x 6144 -1
+// %), with plain rows of them up to K = 3072 (3001 x 2048 x 1024 14.2 / 13.0, x 3072 -2 %, x 4096 34.2 / 35.4, x 6144 49.4 / 50.2;
+// 1000 x 4096 x 4096 32.4 / 33.4; 4096 x 4096 x 6144 104.0 / 103.6).
 inline int ring_waves(int tile, const GemmOperands& g, const GemmOperands* g2, bool mx, bool plain_scales = false) {
     const int64_t line = plain_scales ? 3072 : 6144;
     if (tile != RING_128x256 && tile != RING_256x128) return 4;
@@ -178,8 +184,8 @@ hipError_t launch_quant_row_pair(const void* x1, int64_t rows1, int64_t ld1, uin
 hipError_t launch_quant_row_col_pair(const RowColOperand& a, const RowColOperand* b, int64_t cols, int fmt, int flags, hipStream_t st);
 // two tensors of the same width and format per column, transposed: one launch, or three (instead of six)
 hipError_t launch_quant_col_t_pair(const ColOperand& a, const ColOperand& b, int64_t cols, int fmt, int flags, hipStream_t st);
-// the backward of the rowwise recipe: the gradient g along both axes, W and X per column: one launch (strips), else five (instead of
-// nine), four with folding.  Without g.q_row, g.q_col_t, w.x or x.x (nullptr) what is left: strips or hipErrorNotSupported
+// the backward of the rowwise recipe: the gradient g along both axes, W and X per column: one launch (strips), else five (instead
+// of nine), four with folding.  Without g.q_row, g.q_col_t, w.x or x.x (nullptr) what is left: strips or hipErrorNotSupported
 hipError_t launch_quant_bwd_rowwise(const RowColOperand& g, int64_t cols_g, int fmt_g, const ColOperand& w, const ColOperand& x,
                                     int64_t cols_wx, int fmt_wx, int flags, hipStream_t st);
 
@@ -214,11 +220,12 @@ hipError_t launch_gemm_fp8_stream(const uint8_t* a, int64_t lda, int fmt_a, cons
                                   int64_t M, int64_t N, int64_t K, void* out, int64_t ld_out, int64_t units, int tile_m,
                                   hipStream_t st);
 
-// Split of a few-row product (gemm_fp8_skinny.hip).  nw: groups of 16 columns per wavefront; ks: wavefronts of a workgroup that share K; deep: five K steps in
-// flight in place of three.  nw_forced: 0, or the switch's value.
+// Split of a few-row product (gemm_fp8_skinny.hip).  nw: groups of 16 columns per wavefront; ks: wavefronts of a workgroup that
+// share K; deep: five K steps in flight in place of three.  nw_forced: 0, or the switch's value.
 struct FewRowForm { int nw, ks; int64_t grid; bool deep; };
-// Forms of mt tiles of 16 rows that a weight which stream_weight accepts can come to, and which so exist with the streaming hint: against one group of
-// columns N < 6144 and so K > 16384; with 33 rows and more the choice of kernel leaves N <= 8192 and so K >= 12288, always four parts of K.
+// Forms of mt tiles of 16 rows that a weight which stream_weight accepts can come to, and which so exist with the streaming hint:
+// against one group of columns N < 6144 and so K > 16384; with 33 rows and more the choice of kernel leaves N <= 8192 and so K >=
+// 12288, always four parts of K.
 constexpr bool few_row_hint(int mt, int nw, int ks) { return nw == 2 ? mt <= 2 || ks == 4 : nw == 1 && ks == 4; }
 inline FewRowForm few_row_form(int64_t M, int64_t N, int64_t K, int nw_forced, int64_t cus) {
     // columns per wavefront: 16 or 32 (64 through the override).  Wider groups reuse every fragment of A
@@ -230,17 +237,19 @@ inline FewRowForm few_row_form(int64_t M, int64_t N, int64_t K, int nw_forced, i
     int ks = 1;
     while (ks < 4 && groups * ks < 2048 && K / (ks * 2) >= 512) ks *= 2;
     const int64_t grid = (groups + (4 / ks) - 1) / (4 / ks);
-    // a long contraction keeps five up to 8 rows on at most half of the CUs, up to 4 rows on three quarters (us from HBM, three / five at 1, 4, 8, 12
-    // rows: 1024 x 11008 8.0 8.0 8.3 8.8 / 7.5 7.7 8.4 9.0, x 28672 16.1 16.4 17.0 18.2 / 14.5 15.3 16.6 18.4; 2560 x 14336 10.5 10.6 10.9 11.6 / 9.9 10.2
-    // 10.9 11.8, 3072 x 28672 19.3 19.7 20.4 / 18.5 19.0 20.2; 4096 x 14336 12.7 12.7 12.8 / 12.8 12.9 13.1).  Three weights in turn, from the cache: 1024
-    // x 14336 7.2 7.2 7.2 / 7.0 7.0 7.1, 2560 x 14336 8.1 8.2 8.3 / 8.3 8.4 8.5; shorter ones lose there what they gain from HBM (1024 x 8192 HBM 6.6 6.7 7.0
-    // / 6.4 6.5 6.9, cache 5.0 5.1 5.2 / 5.3 5.3 5.4)
+    // a long contraction keeps five up to 8 rows on at most half of the CUs, up to 4 rows on three quarters (us from HBM, three /
+    // five at 1, 4, 8, 12 rows: 1024 x 11008 8.0 8.0 8.3 8.8 / 7.5 7.7 8.4 9.0, x 28672 16.1 16.4 17.0 18.2 / 14.5 15.3 16.6 18.4;
+    // 2560 x 14336 10.5 10.6 10.9 11.6 / 9.9 10.2 10.9 11.8, 3072 x 28672 19.3 19.7 20.4 / 18.5 19.0 20.2; 4096 x 14336 12.7 12.7
+    // 12.8 / 12.8 12.9 13.1).  Three weights in turn, from the cache: 1024 x 14336 7.2 7.2 7.2 / 7.0 7.0 7.1, 2560 x 14336 8.1 8.2
+    // 8.3 / 8.3 8.4 8.5; shorter ones lose there what they gain from HBM (1024 x 8192 HBM 6.6 6.7 7.0 / 6.4 6.5 6.9, cache 5.0 5.1
+    // 5.2 / 5.3 5.3 5.4)
     return {nw, ks, grid, ks == 4 && nw == 1 && K > 10240 && ((M <= 8 && 2 * grid <= cus) || (M <= 4 && 4 * grid <= 3 * cus))};
 }
 
-// columns of a strip (quant_strips.hip) for tensors of at most tall rows, load strips of 32 columns.  16 where 32 would keep half of the CUs busy,
-// unless the strips are short (us, 32 / 16 columns: gradient 4096 x 1024 20.9 / 14.9, x 4096 27.3 / 26.4, x 6144 31.8 / 36.0; 2048 x 1024
-// 12.8 / 10.2, x 4096 15.3 / 14.7, x 6144 16.5 / 20.7; 1024 x 1024 8.7 / 9.3, x 4096 10.8 / 12.5); beyond 4096 rows 32 do not fit.
+// columns of a strip (quant_strips.hip) for tensors of at most tall rows, load strips of 32 columns.  16 where 32 would keep half
+// of the CUs busy, unless the strips are short (us, 32 / 16 columns: gradient 4096 x 1024 20.9 / 14.9, x 4096 27.3 / 26.4, x 6144
+// 31.8 / 36.0; 2048 x 1024 12.8 / 10.2, x 4096 15.3 / 14.7, x 6144 16.5 / 20.7; 1024 x 1024 8.7 / 9.3, x 4096 10.8 / 12.5); beyond
+// 4096 rows 32 do not fit.
 inline int strip_columns(int64_t tall, double load, int64_t cus) { return tall > 4096 || (tall > 1024 && 2.0 * load <= (double)cus) ? 16 : 32; }
 
 // few rows of A (M <= 64, the decode shape of inference): B is streamed once
@@ -296,9 +305,10 @@ hipError_t launch_mx_quant(const void* x, int64_t rows, int64_t cols, int64_t ld
 hipError_t launch_mx_quant_t(const void* x, int64_t rows, int64_t cols, int64_t ld, int fmt, uint8_t* qt, int64_t ld_t,
                              uint8_t* et, int64_t ld_e, uint8_t* q_row, int64_t ld_row, uint8_t* e_row, int64_t ld_er,
                              hipStream_t st);
-// The tensors of a block-scaled linear layer in one launch, all in one format (else, and where a tensor does not suit, hipErrorNotSupported
-// and nothing launched).  Two: X and W of a forward, dense rows, MX blocks along them or tiles of 1 x 128 (X) and blocks of 128 x 128 (W).
-// Three: dY, W and X of a backward, transposed as by launch_mx_quant_t / launch_block_quant_t (W in blocks of 128 x 128), dY with q_row.
+// The tensors of a block-scaled linear layer in one launch, all in one format (else, and where a tensor does not suit,
+// hipErrorNotSupported and nothing launched).  Two: X and W of a forward, dense rows, MX blocks along them or tiles of 1 x 128 (X)
+// and blocks of 128 x 128 (W). Three: dY, W and X of a backward, transposed as by launch_mx_quant_t / launch_block_quant_t (W in
+// blocks of 128 x 128), dY with q_row.
 struct BlockOperand {
     const void* x; int64_t rows, cols; int fmt;
     uint8_t* q; int64_t ld_q; uint8_t* e; int64_t ld_e;

@@ -1105,7 +1105,8 @@ hipError_t launch_quant_row_colmax(const void* x, int64_t rows, int64_t cols, in
 // Side storage for first-level column maxima: with it they stay out of the transposed output, so the transposing cast
 // can fold them itself and the second-level launch falls away.  Worth it for small tensors only: every block of the
 // cast reads all the maxima of its 128 columns, and the first level must make do with FOLD_ROWS blocks (measured:
-// 3-8 us less per forward + backward step with tensors of 1024 rows, 3-5 us more with 4096).  0 for the others.
+// 3-8 us less per forward + backward step with tensors of 1024 rows, 3-5 us more with 4096).  0 for the others.  Tensors of up to
+// 4096 rows take column strips where all of a launch can: this is for a small tensor beside a taller one.
 int64_t quant_fold_bytes(int64_t rows, int64_t cols) {
     if (rows < 256 || rows > 2048 || cols < 8 || cols % 8 != 0 || rows * cols > ((int64_t)4 << 20)) return 0;
     return FOLD_ROWS * ((cols + 7) / 8 * 8) * 2;
@@ -1260,7 +1261,8 @@ hipError_t launch_quant_row_pair(const void* x1, int64_t rows1, int64_t ld1, uin
     if (rows1 == 0 || rows2 == 0) return hipErrorNotSupported;
     const int64_t nvec = cols / 8;
     const uint16_t *a = static_cast<const uint16_t*>(x1), *b = static_cast<const uint16_t*>(x2);
-    // (us a step, hint / plain: 1024x2048x1024 28.7 / 26.1, 3001x4096x2048 115.0 / 111.3; 8192x4096x6144 541 / 546)
+    // (us a step, hint / plain: 1024x2048x1024 28.7 / 26.1, 3001x4096x2048 115.0 / 111.3; 8192x4096x6144 541 / 546; from HBM, by Mi
+    // elements of X and W: 16 81.7 / 77.7, 24 132.7 / 127.6, 32 203.7 / 200.8, 40 260.8 / 255.6)
     const int hint = hint_inputs((rows1 + rows2) * cols, HINT_PAIR);
 #define FP8K_QRP(FMT, TX, NV)                                                                                     \
     do {                                                                                                          \
@@ -1655,11 +1657,11 @@ hipError_t launch_block_quant(const void* x, int64_t rows, int64_t cols, int64_t
     return hipGetLastError();
 }
 
-// How the one-pass quantizers into both orientations store their codes, two bytes an element: through the L2, except where
-// the call is a quantization alone (FMT_ALONE) and the codes are half as much again as the last-level cache holds.  There the
-// hint is mostly faster (us, hint / through: 180 Mi elements 172 / 171, 192 Mi 181 / 183, 224 Mi 200 / 213 - 8192 x 28672 210 / 204 -,
-// 256 Mi 222 / 240; below, 112 Mi 105 / 91), but the products behind it lose more (MX steps of 16384 x 2048 x 16384 1530 / 1516,
-// 32768 x 2048 x 8192 1552 / 1531).
+// How the one-pass quantizers into both orientations store their codes, two bytes an element: through the L2, except where the call
+// is a quantization alone (FMT_ALONE) and the codes are half as much again as the last-level cache holds.  There the hint is mostly
+// faster (us, hint / through: 180 Mi elements 172 / 171, 192 Mi 181 / 183, 224 Mi 200 / 213 - 8192 x 28672 210 / 204 -, 256 Mi 222
+// / 240; below, 112 Mi 105 / 91), but the products behind it lose more (MX steps of 16384 x 2048 x 16384 1530 / 1516, 32768 x 2048
+// x 8192 1552 / 1531).
 static bool keep_both_codes(int fmt, int64_t rows, int64_t cols) { return !(fmt & FMT_ALONE) || rows * cols <= (int64_t)192 << 20; }
 
 // MX block quantization with the blocks running DOWN the columns of x and the
@@ -1875,7 +1877,8 @@ __device__ __forceinline__ void block_quant_t_tile(int bid, bool hint, uint8_t* 
             uint32_t byte;
             const float sr = pow2_block_scale<FMT>(mr, byte);
             const int64_t r = r0 + ty * 8 + j;
-            store_vec(q_row + r * ld_row + c, mr >= INF_MAG ? cast8_own<FMT, true>(v[j], sr) : cast8_own<FMT, false>(v[j], sr), ROWS_TOO != 2);                   // cols % 128 == 0: inside
+            const uint2 codes = mr >= INF_MAG ? cast8_own<FMT, true>(v[j], sr) : cast8_own<FMT, false>(v[j], sr);
+            store_vec(q_row + r * ld_row + c, codes, ROWS_TOO != 2);                   // cols % 128 == 0: inside
             if (tx == 0) *reinterpret_cast<uint32_t*>(e_row + e8_off(r, c0 >> 5, ld_er)) = byte * 0x01010101u;
         }
     }
@@ -2003,7 +2006,8 @@ hipError_t launch_mx_quant_t(const void* x, int64_t rows, int64_t cols, int64_t 
 
 // The quantizations of a block-scaled linear layer in one launch: X and W of a forward (rows), or dY, W and X of a backward
 // (transposed, dY along its rows too).  Each tensor's workgroups are those of its own kernel; what is saved are the start and the
-// end of a launch, 3-5 us each (us, separate / together: blockwise 2048 x 4096 x 4096 forward 19.2 / 15.2, backward 31.6 / 24.8; MX 4096 x 4096 x 14336 42.4 / 41.9, 98.9 / 88.4).
+// end of a launch, 3-5 us each (us, separate / together: blockwise 2048 x 4096 x 4096 forward 19.2 / 15.2, backward 31.6 / 24.8; MX
+// 4096 x 4096 x 14336 42.4 / 41.9, 98.9 / 88.4).
 struct BlockSeg {
     const uint16_t* x; int64_t rows, cols;
     uint8_t* q; int64_t ld_q; uint8_t* e; int64_t ld_e;                  // rows: codes and scale bytes; backward: of the transposed tensor
@@ -2026,19 +2030,29 @@ __global__ __launch_bounds__(256) void quant_blocks_bwd_kernel(BlockSeg g, Block
     __shared__ __attribute__((aligned(16))) uint8_t lds[TILE_LDS];
     int bid = blockIdx.x;
     if (bid < g.blocks) {
-        if constexpr (MX) mx_quant_t_tile<FMT, 1>(bid, hint, lds, g.x, g.rows, g.cols, g.cols, g.q, g.ld_q, g.e, g.ld_e, g.q_row, g.ld_row, g.e_row, g.ld_er, g.nx, g.ny);
-        else block_quant_t_tile<FMT, false, 1>(bid, hint, lds, g.x, g.rows, g.cols, g.cols, g.q, g.ld_q, g.e, g.ld_e, g.nx, g.ny, g.q_row, g.ld_row, g.e_row, g.ld_er);
+        if constexpr (MX)
+            mx_quant_t_tile<FMT, 1>(bid, hint, lds, g.x, g.rows, g.cols, g.cols, g.q, g.ld_q, g.e, g.ld_e, g.q_row, g.ld_row, g.e_row,
+                                    g.ld_er, g.nx, g.ny);
+        else
+            block_quant_t_tile<FMT, false, 1>(bid, hint, lds, g.x, g.rows, g.cols, g.cols, g.q, g.ld_q, g.e, g.ld_e, g.nx, g.ny, g.q_row,
+                                              g.ld_row, g.e_row, g.ld_er);
         return;
     }
     bid -= g.blocks;
     if (bid < w.blocks) {
-        if constexpr (MX) mx_quant_t_tile<FMT, 0>(bid, hint, lds, w.x, w.rows, w.cols, w.cols, w.q, w.ld_q, w.e, w.ld_e, nullptr, 0, nullptr, 0, w.nx, w.ny);
-        else block_quant_t_tile<FMT, true, 0>(bid, hint, lds, w.x, w.rows, w.cols, w.cols, w.q, w.ld_q, w.e, w.ld_e, w.nx, w.ny, nullptr, 0, nullptr, 0);
+        if constexpr (MX)
+            mx_quant_t_tile<FMT, 0>(bid, hint, lds, w.x, w.rows, w.cols, w.cols, w.q, w.ld_q, w.e, w.ld_e, nullptr, 0, nullptr, 0, w.nx, w.ny);
+        else
+            block_quant_t_tile<FMT, true, 0>(bid, hint, lds, w.x, w.rows, w.cols, w.cols, w.q, w.ld_q, w.e, w.ld_e, w.nx, w.ny, nullptr, 0,
+                                             nullptr, 0);
         return;
     }
     bid -= w.blocks;
-    if constexpr (MX) mx_quant_t_tile<FMT, 0>(bid, hint, lds, x.x, x.rows, x.cols, x.cols, x.q, x.ld_q, x.e, x.ld_e, nullptr, 0, nullptr, 0, x.nx, x.ny);
-    else block_quant_t_tile<FMT, false, 0>(bid, hint, lds, x.x, x.rows, x.cols, x.cols, x.q, x.ld_q, x.e, x.ld_e, x.nx, x.ny, nullptr, 0, nullptr, 0);
+    if constexpr (MX)
+        mx_quant_t_tile<FMT, 0>(bid, hint, lds, x.x, x.rows, x.cols, x.cols, x.q, x.ld_q, x.e, x.ld_e, nullptr, 0, nullptr, 0, x.nx, x.ny);
+    else
+        block_quant_t_tile<FMT, false, 0>(bid, hint, lds, x.x, x.rows, x.cols, x.cols, x.q, x.ld_q, x.e, x.ld_e, x.nx, x.ny, nullptr, 0,
+                                          nullptr, 0);
 }
 
 hipError_t launch_quant_blocks(const BlockOperand* ops, int n, bool mx, hipStream_t st) {
@@ -2064,8 +2078,12 @@ hipError_t launch_quant_blocks(const BlockOperand* ops, int n, bool mx, hipStrea
         elements += o.rows * o.cols;
         if (total > 0x7FFFFFFF) return hipErrorNotSupported;
     }
-    // (us a step, hint / plain: MX 512x1024x1024 28.6 / 27.6, 1024x2048x1024 35.7 / 34.4, 2048x4096x4096 135.2 / 136.3; blockwise 27.2 / 25.9,
-    // 34.8 / 32.8, 133.5 / 133.9)
+    // us, hint / plain.  Tensors from the last-level cache: MX steps 512x1024x1024 28.6 / 27.6, 1024x2048x1024 35.7 / 34.4,
+    // 2048x4096x4096 135.2 / 136.3, blockwise 27.2 / 25.9, 34.8 / 32.8, 133.5 / 133.9; MX backward 1024x2048x2048 (8 Mi) 30.5 /
+    // 30.1, 2048^3 (12 Mi) 37.7 / 36.8.  All from HBM plain ones lose: the same steps 29.4 / 30.5, 38.9 / 40.1, backward 30.0 /
+    // 30.7, 37.4 / 37.9.  W from HBM, X and dY just written, as in training: forward 1024x2048x1024 14.4 / 14.4, 1024x2048x2048
+    // 18.4 / 18.7, 1024x4096x1024 (8 Mi) 23.1 / 21.1, 2048^3 (8 Mi) 22.2 / 22.6, 2048x4096x4096 46.9 / 47.2; backward 24.4 / 24.9,
+    // 30.3 / 30.7, 2048^3 37.5 / 37.6, 2048x4096x4096 86.2 / 86.7.  The line lies where the three together are even.
     const int hint = hint_inputs(elements, HINT_BLOCKS);
     const dim3 grid((unsigned)total), block(256);
 #define FP8K_QB(FMT, MX)                                                                \

@@ -7,14 +7,14 @@
 // maxima across its wavefronts, derives the scales and writes the transposed codes: one launch, no scratch, no order among
 // workgroups.  The rowwise codes that the same step needs are made by further workgroups of the same launch.
 //
-// What bounds it: up to some 64 strips the time of one strip on its CU - a CU takes in a row's piece every five cycles or
-// so, 32 or 128 bytes alike (measured; 2 KB pitch and more), so 4096 rows take 10 us to arrive, and conversion and stores follow; that is why strips
-// are 16 columns wide where 32 would leave CUs idle, why the loads are plain ones (17 us with the streaming hint) and why the
-// conversion carries no clamp.  With more strips HBM: X and W of 4096 x 4096, both orientations, 201 MB in 38 us = 5.3 TB/s.
+// What bounds it: up to some 64 strips the time of one strip on its CU - a CU takes in a row's piece every five cycles or so, 32 or
+// 128 bytes alike (measured; 2 KB pitch and more), so 4096 rows take 10 us to arrive, and conversion and stores follow; that is why
+// strips are 16 columns wide where 32 would leave CUs idle, why the loads are plain ones (17 us with the streaming hint) and why
+// the conversion carries no clamp.  With more strips HBM: X and W of 4096 x 4096, both orientations, 201 MB in 38 us = 5.3 TB/s.
 // Before / now (us, first kernel's start to last one's end): X and W of 1024 x 1024 20.3 / 9.5, of 4096 x 1024 25.0 / 20.1; the
-// gradient 1024 x 8192 33.7 / 10.4, 2048 x 4096 39.4 / 14.7, 3072 x 8192 42.3 / 29.9, 4096 x 8192 48.1 / 39.9.
-// Steps: 1024 x 2048 x 1024 41.7 / 29.1 (33 before its rows were read plainly), 1024^3 41.1 / 24.5, 3001 x 4096 x 2048 140 / 113, 4096^3
-// 231 / 205 (the last three stateless).
+// gradient 1024 x 8192 33.7 / 10.4, 2048 x 4096 39.4 / 14.7, 3072 x 8192 42.3 / 29.9, 4096 x 8192 48.1 / 39.9. Steps: 1024 x 2048 x
+// 1024 41.7 / 29.1 (33 before its rows were read plainly), 1024^3 41.1 / 24.5, 3001 x 4096 x 2048 140 / 113, 4096^3 231 / 205 (the
+// last three stateless).
 #include "fp8_device.hpp"
 #include "launchers.hpp"
 #include "tuning.hpp"
@@ -220,8 +220,9 @@ hipError_t launch_quant_strips(const StripOperand* ops, int n, int flags, hipStr
     const int v = knob(KNOB_STRIPS);     // 2, 4: wherever they fit, 16 / 32 columns wide
     if (tall == 0 || tall > (v == 4 ? 4096 : 8192) || wide > 16384) return hipErrorNotSupported;
     // Up to 4096 rows always ahead of the separate launches; beyond, strips are 16 columns wide (32-byte requests), which pays
-    // where three tensors share the launch, the stateless backward (us, step before / with: 5000x4096x4096 292 / 272, 8192x4096x4096 397 /
-    // 383, 8192^3 1284 / 1287), but not for one or two (8192x2048 gradient 31 / 33, W and X of the 8192x4096x4096 LayerNorm step 458 / 466).
+    // where three tensors share the launch, the stateless backward (us, step before / with: 5000x4096x4096 292 / 272,
+    // 8192x4096x4096 397 / 383, 8192^3 1284 / 1287), but not for one or two (8192x2048 gradient 31 / 33, W and X of the
+    // 8192x4096x4096 LayerNorm step 458 / 466).
     if (v < 0 && tall > 4096 && n < 3) return hipErrorNotSupported;
     // A tensor wanted in both orientations is read twice, the second time from the 256 MB last-level cache if all of them fit it
     // (X and W of 4096 x 14336, 235 MB: 654 -> 643 us a step; of 4096 x 16384, 268 MB: 756 -> 778).
@@ -233,9 +234,11 @@ hipError_t launch_quant_strips(const StripOperand* ops, int n, int flags, hipStr
         load += (ops[i].q_col_t ? 1.0 : 0.5) * (double)((ops[i].cols + 31) / 32) * (double)ops[i].rows / (double)tall;
     }
     if (twice > (int64_t)120 << 20) return hipErrorNotSupported;
-    // Rows with the streaming hint beyond 24 Mi elements: the loads are slower by themselves, but what they read does not displace the
-    // codes (us a step, hint / plain: 1024x2048x1024 34.4 / 30.3, 2048^3 58.0 / 52.7, 2048x4096x4096 with dW in bfloat16, 24 Mi, 153.1 / 150.8, 4096^3
-    // 215.9 / 217.1, 600x14336x4096 238 / 246, 4096x14336x2048 416 / 428).
+    // Rows with the streaming hint beyond 24 Mi elements: the loads are slower by themselves, but what they read does not displace
+    // the codes (us a step, hint / plain: 1024x2048x1024 34.4 / 30.3, 2048^3 58.0 / 52.7, 2048x4096x4096 with dW in bfloat16, 24
+    // Mi, 153.1 / 150.8, 4096^3 215.9 / 217.1, 600x14336x4096 238 / 246, 4096x14336x2048 416 / 428; all tensors from HBM, 12 Mi
+    // 65.5 / 65.5, 16 84.0 / 84.0, 20 95.8 / 92.5, 24 Mi 134.1 / 132.8 and 149.8 / 150.2, 28 177.8 / 179.1 and 191.4 / 193.7, 32
+    // 206.2 / 207.5, 40 262.1 / 263.1: even from 24 to 28 Mi).
     a.hint = hint_inputs(by_rows, HINT_PAIR);
     // load: strips of 32 columns, in units of the tallest tensor's, a tensor without strips half
     const int lpr = tall <= 4096 && (v == 2 || v == 4) ? v : strip_columns(tall, load, compute_units() > 0 ? compute_units() : 256) / 8;

@@ -23,7 +23,8 @@ enum Knob {
     KNOB_GEMM_TILE_M,       // persistent kernel: 256, 224 or 192 forces the tile height
     KNOB_GEMM_BIG_FROM,     // number of 128 x 128 tiles from which a product goes to the 256 x 256 kernels
     KNOB_PAIRS,             // 0 = no shared launches: every tensor of a linear step quantized, every product launched, by itself
-    KNOB_DECODE_FUSED,      // few tokens against a quantized weight: 0 = activation quantization always a launch of its own, 2 = inside the product wherever that kernel applies
+    KNOB_DECODE_FUSED,      // few tokens against a quantized weight: 0 = activation quantization always a launch of its own,
+                            // 2 = inside the product wherever that kernel applies
     KNOB_GEMM_RING,         // small and middling products: 0 = never the ring kernel, 1 + tile = always that tile of it
     KNOB_STRIPS,            // rowwise steps: 0 = never column strips, 2 / 4 = wherever they fit, 16 / 32 columns wide
     KNOB_COUNT

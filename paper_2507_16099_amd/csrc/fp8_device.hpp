@@ -37,8 +37,21 @@ __device__ __forceinline__ uint4 load_stream(const void* p) {
     return make_uint4(t[0], t[1], t[2], t[3]);
 }
 
-// hint: as above; else a plain load.  Small tensors are read plainly (hint_inputs in launchers.hpp says where the line lies).
-__device__ __forceinline__ uint4 load_in(const void* p, bool hint) { return hint ? load_stream(p) : *static_cast<const uint4*>(p); }
+// HINT: as above; else a plain load.  Small tensors are read plainly (hint_inputs in launchers.hpp says where the line lies).  Known at
+// compile time, or one branch around all loads of a thread: a branch at each of them costs 1-2 % of the kernels that stream a
+// tensor by rows or transpose it (casts per tensor 42.0 -> 42.8 us, maxima 18.0 -> 18.2; 777 x 14336 by rows 29.2 -> 30.2).  Not so
+// in the shared launches of MX and blockwise tensors, which measured equal or 2 % ahead with it (15.5 / 15.8 us).
+template <bool HINT>
+__device__ __forceinline__ uint4 load_in(const void* p) {
+    if constexpr (HINT) return load_stream(p);
+    else return *static_cast<const uint4*>(p);
+}
+__device__ __forceinline__ uint4 load_in(const void* p, bool hint) { return hint ? load_in<true>(p) : load_in<false>(p); }
+template <class Fetch>
+__device__ __forceinline__ void with_loads(bool hint, Fetch&& fetch) {
+    if (hint) fetch([](const void* p) { return load_in<true>(p); });
+    else fetch([](const void* p) { return load_in<false>(p); });
+}
 
 // Codes are stored through the L2 (system scope): they are in the 256 MB last-level cache when the product reads them, and
 // no dirty lines are left that the end of the kernel has to wait for.  Measured (us; streaming hint / plain store / this):

@@ -96,11 +96,13 @@ __global__ __launch_bounds__(256) void amax_flat_kernel(const uint16_t* __restri
     for (int64_t chunk = blockIdx.x; chunk * (256 * 8) < nvec; chunk += gridDim.x) {
         const int64_t base = chunk * (256 * 8) + threadIdx.x;
         uint4 v[8];
+        with_loads(hint, [&](auto load) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int64_t i = base + j * 256;
-            v[j] = i < nvec ? load_in(xv + i, hint) : make_uint4(0, 0, 0, 0);
-        }
+            for (int j = 0; j < 8; ++j) {
+                const int64_t i = base + j * 256;
+                v[j] = i < nvec ? load(xv + i) : make_uint4(0, 0, 0, 0);
+            }
+        });
 #pragma unroll
         for (int j = 0; j < 8; ++j) acc = pk_absmax4(acc, v[j]);
     }
@@ -439,8 +441,10 @@ __global__ __launch_bounds__(256) void cast_kernel(const uint16_t* __restrict__ 
     uint4 v0 = make_uint4(0, 0, 0, 0), v1 = v0;
     if constexpr (GRAN == GRAN_TENSOR) {
         if (r < rows && c + 16 <= cols) {       // the first row is under way while the scale is derived (777 x 14336: 9.4 -> 8.7 us)
-            v0 = load_in(x + r * ld + c, hint);
-            v1 = load_in(x + r * ld + c + 8, hint);
+            with_loads(hint, [&](auto load) {
+                v0 = load(x + r * ld + c);
+                v1 = load(x + r * ld + c + 8);
+            });
         }
         // n_part > 0: scale points at the per-block maxima of the amax pass instead of at the scale
         if (n_part > 0)
@@ -456,8 +460,10 @@ __global__ __launch_bounds__(256) void cast_kernel(const uint16_t* __restrict__ 
         if constexpr (GRAN == GRAN_ROW) s_t = scale[r];
         if (c + 16 <= cols) {
             if (!first) {
-                v0 = load_in(src, hint);
-                v1 = load_in(src + 8, hint);
+                with_loads(hint, [&](auto load) {
+                    v0 = load(src);
+                    v1 = load(src + 8);
+                });
             }
             uint2 lo, hi;
             if constexpr (GRAN == GRAN_COL) {
@@ -497,7 +503,7 @@ __global__ __launch_bounds__(256) void cast_kernel(const uint16_t* __restrict__ 
 // FOLD (per-column scales only): the scales may come from first-level column maxima, see below.
 // pad: the output rows are padded to whole 16-byte pieces that belong to this call (a workspace): their last bytes are
 // written too, as zero codes, so nobody has to clear the buffer first and no piece is stored byte by byte.
-template <int FMT, int GRAN, int TR, bool ACT = false, bool FOLD = false>
+template <int FMT, int GRAN, int TR, bool ACT = false, bool FOLD = false, bool HINT = true>
 __global__ __launch_bounds__(256) void cast_transpose_kernel(const uint16_t* __restrict__ x, int64_t rows,
                                                               int64_t cols, int64_t ld,
                                                               const float* __restrict__ scale,
@@ -513,7 +519,7 @@ __global__ __launch_bounds__(256) void cast_transpose_kernel(const uint16_t* __r
                                                               int64_t ld_part = 0, int n_part2 = 0,
                                                               float* __restrict__ scale_out2 = nullptr,
                                                               uint8_t* __restrict__ q_plain2 = nullptr, int64_t ld_plain2 = 0,
-                                                              int pad = 0, int hint = 1) {
+                                                              int pad = 0) {
     int bid = blockIdx.x;
     if (bid >= split) {
         bid -= split; x = x2; rows = rows2; ld = ld2; scale = scale2; qt = qt2; ld_t = ld_t2; nx = nx2;
@@ -563,7 +569,7 @@ __global__ __launch_bounds__(256) void cast_transpose_kernel(const uint16_t* __r
             } else if (r < rows) {
                 const uint16_t* src = x + r * ld + c;
                 if (c + 8 <= cols) {
-                    v = load_in(src, hint);
+                    v = load_in<HINT>(src);
                     if constexpr (ACT) v = sigmoid_bwd8(v, load_stream(yact + r * ld + c));
                 } else if (c < cols) {
                     uint32_t t[4] = {0, 0, 0, 0};
@@ -702,9 +708,12 @@ static hipError_t launch_cast_t(const uint16_t* x, int64_t rows, int64_t cols, i
         const int64_t gx = (cols + 127) / 128, gy = (rows + 127) / 128;
         const int64_t total = ((gy + 15) / 16) * ((gx + 15) / 16) * 256;
         if (total > 0x7FFFFFFF) return hipErrorInvalidValue;
-        cast_transpose_kernel<FMT, GRAN, 128><<<dim3((unsigned)total), dim3(256), 0, st>>>(
+        auto kern = cast_transpose_kernel<FMT, GRAN, 128>;
+        if constexpr (GRAN == GRAN_TENSOR)
+            if (!hint) kern = cast_transpose_kernel<FMT, GRAN, 128, false, false, false>;
+        kern<<<dim3((unsigned)total), dim3(256), 0, st>>>(
             x, rows, cols, ld, scale, q, ld_out, q_plain, ld_plain, (int)gy, (int)gx, nullptr, n_part, sflags, scale_out, NO_TWIN,
-            nullptr, 0, 0, nullptr, nullptr, 0, 0, 0, 0, nullptr, nullptr, 0, pad, hint);
+            nullptr, 0, 0, nullptr, nullptr, 0, 0, 0, 0, nullptr, nullptr, 0, pad);
         return hipGetLastError();
     }
     const int64_t items = (cols + 15) / 16;
@@ -767,10 +776,11 @@ static hipError_t quant_tensor_pair(const TensorOperand& a, const TensorOperand&
         const int64_t gx = (cols + 127) / 128, gya = (a.rows + 127) / 128, gyb = (b.rows + 127) / 128;
         const int64_t ta = ((gya + 15) / 16) * ((gx + 15) / 16) * 256, tb = ((gyb + 15) / 16) * ((gx + 15) / 16) * 256;
         if (ta + tb > 0x7FFFFFFF) return hipErrorInvalidValue;
-        cast_transpose_kernel<FMT, GRAN_TENSOR, 128><<<dim3((unsigned)(ta + tb)), dim3(256), 0, st>>>(
+        auto kern = hint ? cast_transpose_kernel<FMT, GRAN_TENSOR, 128> : cast_transpose_kernel<FMT, GRAN_TENSOR, 128, false, false, false>;
+        kern<<<dim3((unsigned)(ta + tb)), dim3(256), 0, st>>>(
             xa, a.rows, cols, cols, a.part, a.q, a.ld_out, a.q_plain, a.ld_plain, (int)gya, (int)gx, nullptr, (int)blocks, sfl,
             a.scale_out, (int)ta, xb, b.rows, cols, b.part, b.q, b.ld_out, (int)gyb, 0, (int)blocks, b.scale_out, b.q_plain,
-            b.ld_plain, owns_padding(a.rows, a.ld_out) | owns_padding(b.rows, b.ld_out), hint);
+            b.ld_plain, owns_padding(a.rows, a.ld_out) | owns_padding(b.rows, b.ld_out));
         return hipGetLastError();
     }
     if (a.ld_out != b.ld_out) return hipErrorInvalidValue;
@@ -836,11 +846,13 @@ __global__ __launch_bounds__(256) void quant_row_kernel(const uint16_t* __restri
 
     uint4 v[NV];
     uint32_t acc = 0;
+    with_loads(hint, [&](auto load) {
 #pragma unroll
-    for (int j = 0; j < NV; ++j) {
-        const int64_t vi = tx + (int64_t)j * TX;
-        v[j] = (live && vi < nvec) ? load_in(rv + vi, hint) : make_uint4(0, 0, 0, 0);
-    }
+        for (int j = 0; j < NV; ++j) {
+            const int64_t vi = tx + (int64_t)j * TX;
+            v[j] = (live && vi < nvec) ? load(rv + vi) : make_uint4(0, 0, 0, 0);
+        }
+    });
     uint32_t tail = 0;
     if (live && tx < ntail) tail = row[(nvec << 3) + tx];
 #pragma unroll
@@ -1180,7 +1192,7 @@ hipError_t cast_t_col(const ColOperand& a, const Partials& pa, int64_t Ga, const
         nullptr, pa.folded ? (int)Ga : 0, flags & 1, a.scale_col,
         b ? (int)ta : NO_TWIN, b ? static_cast<const uint16_t*>(b->x) : nullptr, b ? b->rows : 0, b ? b->ld : 0, sb,
         b ? b->q_col_t : nullptr, b ? b->ld_col_t : 0, (int)gyb, ld_part, b && pb.folded ? (int)Gb : 0, b ? b->scale_col : nullptr,
-        nullptr, 0, owns_padding(a.rows, a.ld_col_t) | (b ? owns_padding(b->rows, b->ld_col_t) : 0), 1);
+        nullptr, 0, owns_padding(a.rows, a.ld_col_t) | (b ? owns_padding(b->rows, b->ld_col_t) : 0));
     return hipGetLastError();
 }
 hipError_t cast_t_col(int fmt, const ColOperand& a, const Partials& pa, int64_t Ga, const ColOperand* b, const Partials& pb,

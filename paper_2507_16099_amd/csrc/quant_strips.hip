@@ -147,8 +147,7 @@ __device__ __forceinline__ void quant_rows(const StripRows& s, int b, int flags,
             for (int j = 0; j < NV; ++j) v[k][j] = tx + j * 256 < nvec ? load(rv + tx + j * 256) : make_uint4(0, 0, 0, 0);
         }
     };
-    if (hint) request([](const uint4* p) { return load_stream(p); });
-    else request([](const uint4* p) { return *p; });
+    with_loads(hint, request);
 #pragma unroll
     for (int k = 0; k < RW; ++k) {
         uint32_t acc = 0;

@@ -236,17 +236,16 @@ static hipError_t launch_tn(const GemmOperands& g, int row_a, int row_b, hipStre
 }
 
 // ---- kernel choice.  Up to 16 rows: the few-row kernel of gemm_fp8_skinny.hip (it streams B once).  17 to 32 rows: the same where
-// there are 64 x 64 ring tiles for less than five eighths of the CUs, else those tiles (us, few-row / ring at 32 rows, weights from
-// HBM: 4096 x 4096 7.1 / 11.2, 8192 x 4096 10.2 / 12.0; 11008 x 4096 15.1 / 13.4, 14336 x 4096 16.2 / 15.3; with the streaming hint
-// 28672 x 4096 27.5 / 26.6, 28672 x 8192 47.3 / 43.6).  Up to 64 rows the few-row kernel where there are too few 64 x 64 tiles for
-// the CUs, N <= 8192, and the contraction is long enough for its wavefronts to share (us, few-row / best ring tile, N x K at 33,
-// 40, 48, 64 rows, weights from HBM: 4096 x 4096 7.8 / 11.2, 8.0 / 11.5, 8.5 / 12.0, 9.5 / 12.8; 8192 x 4096 11.1 / 12.1, 11.5 /
-// 12.4, 11.9 / 12.9, 13.0 / 13.9; 4096 x 14336 18.3 / 30.3 .. 23.6 / 36.9; 4096 x 2048 4.9 / 6.1 .. 5.8 / 6.3.  Beyond the lines:
-// 11008 x 4096 18.8 / 13.1 .. 22.3 / 14.8, 14336 x 4096 20.4 / 15.3 .. 23.6 / 16.0, 28672 x 8192 60.7 / 50.1 .. 71.8 / 52.1, 8192 x
-// 1024 6.1 / 5.1 .. 6.8 / 5.2.  On them it is close: 8192 x 2048 7.8 / 7.8 .. 9.2 / 8.7, 4096 x 1024 4.7 / 4.9 .. 5.3 / 5.1.) More
-// than one round of 256 x 256 tiles (one per CU): the large-product kernels of gemm_fp8_snake.hip / gemm_fp8_stream.hip.  In
-// between the cheapest of the ring kernel's tiles (gemm_fp8_ring.hip) and one round of 256 x 256 tiles by this estimate, in us (one
-// launch; rounds of 256 workgroups, K steps of 128 bytes):
+// there are 64 x 64 ring tiles for less than five eighths of the CUs (us, few-row / ring at 32 rows, weights from HBM: 4096 x 4096
+// 7.1 / 11.2, 8192 x 4096 10.2 / 12.0; 11008 x 4096 15.1 / 13.4), else by few_rows_tile below.  Up to 64 rows the few-row kernel
+// where there are too few 64 x 64 tiles for the CUs, N <= 8192, and the contraction is long enough for its wavefronts to share (us,
+// few-row / best ring tile, N x K at 33, 40, 48, 64 rows, weights from HBM: 4096 x 4096 7.8 / 11.2, 8.0 / 11.5, 8.5 / 12.0, 9.5 /
+// 12.8; 8192 x 4096 11.1 / 12.1, 11.5 / 12.4, 11.9 / 12.9, 13.0 / 13.9; 4096 x 14336 18.3 / 30.3 .. 23.6 / 36.9; 4096 x 2048 4.9 /
+// 6.1 .. 5.8 / 6.3.  Beyond the lines: 11008 x 4096 18.8 / 13.1 .. 22.3 / 14.8, 14336 x 4096 20.4 / 15.3 .. 23.6 / 16.0, 28672 x
+// 8192 60.7 / 50.1 .. 71.8 / 52.1, 8192 x 1024 6.1 / 5.1 .. 6.8 / 5.2.  On them it is close: 8192 x 2048 7.8 / 7.8 .. 9.2 / 8.7,
+// 4096 x 1024 4.7 / 4.9 .. 5.3 / 5.1.) More than one round of 256 x 256 tiles (one per CU): the large-product kernels of
+// gemm_fp8_snake.hip / gemm_fp8_stream.hip.  In between the cheapest of the ring kernel's tiles (gemm_fp8_ring.hip) and one round
+// of 256 x 256 tiles by this estimate, in us (one launch; rounds of 256 workgroups, K steps of 128 bytes):
 //     3 + rounds * (a + steps * b);  256 x 256 tiles: 10 + 1.2 * steps, at most half of the CUs busy (half tiles) 7.2 + 0.91 * steps.
 // a: prologue and epilogue of a tile; b: a K step with every CU busy (some 460 / 670 / 970 / 1600 cycles for the tiles below; their
 // matrix instructions take 128 / 256 / 512 / 1024, the fragment reads and LDS-DMA writes at 128 bytes a cycle 384 / 576 / 768 /
@@ -296,6 +295,22 @@ int best_ring(const GemmOperands& g, const GemmOperands* g2, int64_t cus, double
     }
     return best;
 }
+// 17 to 32 rows against a wide weight: the ring kernel's tile, or -1 for the few-row kernel, which has no rounds to fill.  64 x 64
+// tiles over one round at most, 64 x 128 ones where those fit one and the contraction pays for them, else 64 x 64 ones where it is
+// long enough to make up for a last round that is not full.  (us at 17 rows from HBM, few-row / 64 x 64 / 64 x 128; N x K: 16384 x
+// 1024 6.7 / 6.5 / 7.4; 20480 x 512 6.1 / 7.9 / 6.1, x 1024 8.9 / 10.0 / 7.9, x 2048 13.8 / 14.2 / 11.3; 28672 x 512 6.5 / 8.3 /
+// 6.9, x 4096 26.3 / 25.1 / 24.3, 32768 x 8192 58.4 / 53.8 / 58.7; 36864 x 2048 20.5 / 21.4 / 22.4, x 8192 72.4 / 65.8 / 79.0;
+// 65536 x 3072 36.8 / 39.5 / 37.3, 128256 x 4096 107.2 / 95.6 / 97.8.  On a chip just full of 64 x 128 tiles whose rows lie a
+// multiple of 4096 bytes apart the few-row kernel is ahead: 32768 x 4096 27.9 / 30.3 / 32.4)
+int few_rows_tile(const GemmOperands& g, int64_t cus) {
+    const int64_t tiles = cdiv(g.N, 64), K = g.K;
+    if (tiles <= cus) return RING_64x64;
+    if (tiles <= 2 * cus) {
+        if (K < 1024 || (g.ldb % 4096 == 0 && K < 8192 && 8 * tiles > 15 * cus)) return -1;
+        return K >= 8192 && 5 * tiles >= 8 * cus ? RING_64x64 : RING_64x128;
+    }
+    return K >= 6144 || (K >= 4096 && tiles >= 4 * cus) ? RING_64x64 : -1;
+}
 // kernel for one product; *cost: its estimate (large where there is none)
 int pick_path(const GemmOperands& g, double* cost) {
     *cost = 1e30;
@@ -305,11 +320,12 @@ int pick_path(const GemmOperands& g, double* cost) {
     if (v == 0 || v == 4 || v == 5) return v;
     if (v == 6 || v == 7) return fits ? kPathRing + (v == 6 ? RING_64x64 : RING_128x128) : 0;
     const int64_t cus = compute_units() > 0 ? compute_units() : 256;
-    if (g.M <= 16 || (g.M <= 32 && (8 * cdiv(g.N, 64) < 5 * cus || !ring)) ||
-        (g.M <= 64 && g.N <= 8192 && g.K >= 2048 && gemm_fp8_snake_fits(g.lda, g.ldb))) return 5;
+    if (g.M <= 16 || (g.M > 32 && g.M <= 64 && g.N <= 8192 && g.K >= 2048 && gemm_fp8_snake_fits(g.lda, g.ldb))) return 5;
     if (g.M <= 32) {
-        *cost = ring_cost(RING_64x64, g, nullptr, cus);
-        return kPathRing + RING_64x64;
+        if (!ring || 8 * cdiv(g.N, 64) < 5 * cus) return 5;
+        const int tile = few_rows_tile(g, cus);
+        *cost = ring_cost(tile < 0 ? RING_64x64 : tile, g, nullptr, cus);      // (what the few-row kernel takes too where the contraction is short)
+        return tile < 0 ? 5 : kPathRing + tile;
     }
     const int64_t big = cdiv(g.M, 256) * cdiv(g.N, 256);
     if (const int b = knob(KNOB_GEMM_BIG_FROM); b > 0 && cdiv(g.M, 128) * cdiv(g.N, 128) >= b) return 4;

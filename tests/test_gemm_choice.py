@@ -119,3 +119,15 @@ def test_every_few_row_form_of_a_streamed_weight_has_the_hint(choose):
     assert {M for M, _, _ in few} == {1, 8, 16, 17, 32, 33, 48, 49, 64}
     for s, a in zip(few, choose(*["few %d %d %d" % s for s in few])):
         assert a.endswith("hint"), (s, a)
+
+
+def test_rounds_of_tiles_of_17_to_32_rows(choose):
+    """A second round of 64 x 64 tiles that is hardly filled costs as much as a full one: wider tiles in one round, or the few-row kernel."""
+    want = {(10176, 2048): "few-row", (10184, 512): "64x64", (16384, 8192): "64x64", (16392, 1008): "few-row", (16392, 1024): "64x128", (26176, 8192): "64x128",
+            (26184, 8192): "64x64", (32768, 8176): "64x128", (32768, 4096): "few-row", (30720, 4096): "64x128", (32776, 4096): "few-row", (32776, 6144): "64x64", (65472, 4096): "few-row", (65536, 4096): "64x64",
+            (128256, 2048): "few-row"}
+    for M in (17, 32):
+        for (N, K), w in want.items():
+            answer, = choose(f"one {M} {N} {K}")
+            assert w in answer, (M, N, K, answer)
+    assert "64x128" in choose("one 20 8192 2048", cus=64)[0] and "64x64" in choose("one 20 4096 2048", cus=64)[0]

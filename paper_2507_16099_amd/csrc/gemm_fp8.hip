@@ -298,10 +298,11 @@ int best_ring(const GemmOperands& g, const GemmOperands* g2, int64_t cus, double
 // 17 to 32 rows against a wide weight: the ring kernel's tile, or -1 for the few-row kernel, which has no rounds to fill.  64 x 64
 // tiles over one round at most, 64 x 128 ones where those fit one and the contraction pays for them, else 64 x 64 ones where it is
 // long enough to make up for a last round that is not full.  (us at 17 rows from HBM, few-row / 64 x 64 / 64 x 128; N x K: 16384 x
-// 1024 6.7 / 6.5 / 7.4; 20480 x 512 6.1 / 7.9 / 6.1, x 1024 8.9 / 10.0 / 7.9, x 2048 13.8 / 14.2 / 11.3; 28672 x 512 6.5 / 8.3 /
-// 6.9, x 4096 26.3 / 25.1 / 24.3, 32768 x 8192 58.4 / 53.8 / 58.7; 36864 x 2048 20.5 / 21.4 / 22.4, x 8192 72.4 / 65.8 / 79.0;
-// 65536 x 3072 36.8 / 39.5 / 37.3, 128256 x 4096 107.2 / 95.6 / 97.8.  On a chip just full of 64 x 128 tiles whose rows lie a
-// multiple of 4096 bytes apart the few-row kernel is ahead: 32768 x 4096 27.9 / 30.3 / 32.4)
+// 1024 6.7 / 6.5 / 7.4; 20480 x 512 6.1 / 7.9 / 6.1, x 1024 8.9 / 10.0 / 7.9, x 2048 13.8 / 14.2 / 11.3, x 4096 21.8 / 25.8 / 21.6;
+// 28672 x 512 6.5 / 8.3 / 6.9, x 4096 26.3 / 25.1 / 24.3, 32768 x 8192 58.4 / 53.8 / 58.7; 36864 x 2048 20.5 / 21.4 / 22.4, x 8192
+// 72.4 / 65.8 / 79.0; 65536 x 2048 25.3 / 31.5 / 25.5, x 3072 36.8 / 39.5 / 37.3, 128256 x 4096 107.2 / 95.6 / 97.8.  On a chip
+// just full of 64 x 128 tiles whose rows lie a multiple of 4096 bytes apart the few-row kernel is ahead: 32768 x 4096 27.9 / 30.3 /
+// 32.4)
 int few_rows_tile(const GemmOperands& g, int64_t cus) {
     const int64_t tiles = cdiv(g.N, 64), K = g.K;
     if (tiles <= cus) return RING_64x64;

@@ -280,10 +280,14 @@ double ring_cost(int tile, const GemmOperands& g, const GemmOperands* g2, int64_
     const int64_t n1 = tiles(g), n2 = g2 ? tiles(*g2) : 0;
     const double operands = 1e-5 * (double)(n1 + n2) * (c.tm + c.tn);      // (equal otherwise: fewer operand bytes)
     if (n1 + n2 <= cus) return 3.0 + (per1 > per2 ? per1 : per2) + operands;
-    // beside a product of up to 32 rows the lowest tiles' later rounds cost more than the first (us a backward step apart /
-    // together: 32 x 14336 x 256 14.3 / 64x64 17.7, 64x128 15.1, 128x256 12.1; 32 x 11008 x 128 12.4 / 64x64 12.6, 128x128 9.9)
-    const double later = tile <= RING_64x128 && g2 && g.M <= 32 ? 0.8 * (double)(cdiv(n1 + n2, cus) - 1) : 0.0;
-    const double rounds = (double)cdiv(n1 + n2, cus) * ((double)n1 * per1 + (double)n2 * per2) / (double)(n1 + n2) + later;
+    // The low tiles' a is that of one round.  In several 128 x 64 and 64 x 128 tiles take 0.4 us more each (one product, us, 64 x
+    // 128 as priced by one round / as now: 319 x 24064 x 10240 160 / 105 on 256 x 256 tiles, 289 x 23680 x 9216 126 / 92, 182 x
+    // 34048 x 10368 154 / 115; 35 x 35328 x 5760 51 / 45 on 64 x 64), and beside another product all three 0.8 after the first (a
+    // backward step, us: 317 x 6144 x 704 41.1 / 34.0 on 128 x 128 tiles, 2063 x 608 x 14640 117.1 / 109.5; 32 x 14336 x 256 apart
+    // 14.3, 64x64 17.7, 64x128 15.1, 128x256 12.1; 84 x 3328 x 2560 128x64 41.8, 64x64 49.2).
+    const int64_t r = cdiv(n1 + n2, cus);
+    const double later = tile > RING_64x128 ? 0.0 : g2 ? 0.8 * (double)(r - 1) : tile == RING_64x64 ? 0.0 : 0.4 * (double)r;
+    const double rounds = (double)r * ((double)n1 * per1 + (double)n2 * per2) / (double)(n1 + n2) + later;
     return 3.0 + (rounds > per1 + per2 ? rounds : per1 + per2) + operands;     // (two unequal products: at least one tile of each in turn)
 }
 // the cheapest ring tile for one product, or two in one launch

@@ -131,3 +131,13 @@ def test_rounds_of_tiles_of_17_to_32_rows(choose):
             answer, = choose(f"one {M} {N} {K}")
             assert w in answer, (M, N, K, answer)
     assert "64x128" in choose("one 20 8192 2048", cus=64)[0] and "64x64" in choose("one 20 4096 2048", cus=64)[0]
+
+
+def test_low_tiles_over_several_rounds(choose):
+    """What a low tile costs by itself in one round is not what it costs in several: wide products of a few hundred rows stay on 256 x 256 tiles, and pairs
+    take larger tiles."""
+    assert choose("one 319 24064 10240", "one 447 17280 12672", "one 182 34048 10368", "one 702 11264 10112") == ["256x256"] * 4
+    assert choose("one 512 4096 8192")[0].split()[1] in ("128x64", "64x128")      # (one round)
+    for M, K, N, tile in ((1286, 1024, 5120, "128x128"), (730, 6912, 656, "128x128"), (93, 14080, 256, "128x256"), (2048, 768, 11008, "128x128")):
+        answer, = choose(f"two {M} {K} {N} {N} {K} {(M + 15) // 16 * 16}")
+        assert answer.startswith(f"ring {tile} together"), (M, K, N, answer)

@@ -119,11 +119,12 @@ inline bool one_row(const GemmOperands& g) { return g.M > 128 && g.M <= 256 && !
 // 34.2 / 32.7, 4096 x 4096 x 6144 79.5 / 77.1, with the hint 72 x 28672 x 4096 35.8 / 34.7; x 8192 99.6 / 99.2, 2048 x 4096 x 8192
 // 50.3 / 51.0, x 14336 +2 %).  Not where a row of full 256 x 128 tiles fetches a large weight (160 / 193 / 224 / 256 rows, 24576 x
 // 4608 36.7 37.3 37.8 38.2 / 35.8 37.2 39.0 41.7, 28672 x 6144 50.0 50.0 51.1 52.7 / 48.4 49.0 51.9 55.7, 20480 x 5120 42.1 42.6
-// 42.4 44.1 / 41.5 43.9 43.8 47.9).  Block-scaled: the same with slabs of scales (1000 x 4096 x 4096 -7 %, 2048 x 4096 x 6144 -1
-// %), with plain rows of them up to K = 3072 (3001 x 2048 x 1024 14.2 / 13.0, x 3072 -2 %, x 4096 34.2 / 35.4, x 6144 49.4 / 50.2;
-// 1000 x 4096 x 4096 32.4 / 33.4; 4096 x 4096 x 6144 104.0 / 103.6).
+// 42.4 44.1 / 41.5 43.9 43.8 47.9). Block-scaled: the same with slabs of scales (1000 x 4096 x 4096 -7 %, 2048 x 4096 x 6144 -1 %).
+// Up to K = 1536 with plain rows of scales (from the cache 1000 x 4096 x 1024 / 2048 / 3072 / 4096 -11 / -8 / -3 / +2 %, from HBM
+// -13 / +4 / +3 / +11 %), and of 256 x 128 tiles whose B rows are no whole lines (690 x 5968 x 1040 / 2256 / 3088 / 6128 from the
+// cache -8 / -4 / -1 / +2 %, from HBM -3 / +4 / +5 / +8 %).
 inline int ring_waves(int tile, const GemmOperands& g, const GemmOperands* g2, bool mx, bool plain_scales = false) {
-    const int64_t line = plain_scales ? 3072 : 6144;
+    const int64_t line = plain_scales || (tile == RING_256x128 && ((g.ldb | (g2 ? g2->ldb : 0)) & 127)) ? 1536 : 6144;
     if (tile != RING_128x256 && tile != RING_256x128) return 4;
     if (tile == RING_256x128 && !mx && !g2 && g.M > 192 && one_row(g)) return 4;
     return g.K <= line && (!g2 || g2->K <= line) ? 8 : 4;

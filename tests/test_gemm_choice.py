@@ -93,12 +93,16 @@ def test_wavefronts_of_the_widest_tiles(choose, tile):
         for kind in ("one", "mx"):
             a = choose(*[f"{kind} {M} {N} {K}" for K in (128, 6144, 6272)], GEMM_RING=tile)
             assert [re.search(r" (\d)(?: K=|$)", x)[1] for x in a] == (["8", "8", "4"] if tile >= 5 else ["4"] * 3), a
-        a = choose(*[f"mxrows {M} {N} {K}" for K in (128, 3072, 3200)], GEMM_RING=tile)
+        a = choose(*[f"mxrows {M} {N} {K}" for K in (128, 1536, 1664)], GEMM_RING=tile)
         assert [x[-1] for x in a] == (["8", "8", "4"] if tile >= 5 else ["4"] * 3), a
     wide = 8 if tile >= 5 else 4
     assert choose("mx 256 28672 4096", GEMM_RING=tile)[0].endswith(f" {wide}")
-    assert f" together 4 " in choose("two 400 400 6144 400 400 6272", GEMM_RING=tile)[0]
-    assert f" together {wide} " in choose("two 400 400 6144 400 400 6128", GEMM_RING=tile)[0]
+    assert " together 4 " in choose("two 400 400 6144 400 400 6272", GEMM_RING=tile)[0]
+    assert f" together {wide} " in choose("two 400 400 6144 400 400 6016", GEMM_RING=tile)[0]
+    # rows of B that are no whole lines
+    for K, waves in ((1520, wide), (1552, 4 if tile == 6 else wide)):
+        assert f" alone {waves} " in choose(f"one 690 5968 {K}", GEMM_RING=tile)[0]
+        assert f" together {waves} " in choose(f"two 690 5968 1024 690 5968 {K}", GEMM_RING=tile)[0]
 
 
 @pytest.mark.parametrize("cus", [64, 256])

@@ -213,9 +213,10 @@ int grad_gemms(const fp8_recipe* r, int row, const uint8_t* gq, const float* sg,
         if (e == hipSuccess) return FP8_OK;
         if (e != hipErrorNotSupported) return hip_fail(e, "gemm_fp8_pair");
     }
-    const bool fresh = !(r->flags & FP8_SAVE_FOR_BWD);     // codes of W and X written by this call, not by the forward
-    if (dx) FP8_TRY(fp8k::launch_gemm_fp8(gq, ld.n, r->fmt_dy, sg, row, wt, ld.n, r->fmt_w, swt, row, M, K, N, dx, K, 0, st, fresh));
-    if (dw) FP8_TRY(fp8k::launch_gemm_fp8(gqt, ld.m, r->fmt_dy, sgt, row, xt, ld.m, r->fmt_x, sxt, row, N, K, Mp, dw, K, 0, st, fresh));
+    // codes of W and X: written by this call, mostly in strips where by column, or by the forward
+    const fp8k::BFrom from = r->flags & FP8_SAVE_FOR_BWD ? fp8k::B_AT_REST : row ? fp8k::B_WRITTEN_IN_STRIPS : fp8k::B_WRITTEN;
+    if (dx) FP8_TRY(fp8k::launch_gemm_fp8(gq, ld.n, r->fmt_dy, sg, row, wt, ld.n, r->fmt_w, swt, row, M, K, N, dx, K, 0, st, from));
+    if (dw) FP8_TRY(fp8k::launch_gemm_fp8(gqt, ld.m, r->fmt_dy, sgt, row, xt, ld.m, r->fmt_x, sxt, row, N, K, Mp, dw, K, 0, st, from));
     return FP8_OK;
 }
 
@@ -416,7 +417,7 @@ int fp8_linear_fwd(const void* x, const void* w, int64_t M, int64_t K, int64_t N
                 if (int rc = quantize_impl(x, M, K, K, FP8_TENSOR, recipe->fmt_x, fl | FP8_TRANSPOSE_OUT, wsb + b.xt, ld.m, wsf + p.xq, ld.k, sxt, st, part)) return rc;
                 if (int rc = quantize_impl(w, N, K, K, FP8_TENSOR, recipe->fmt_w, fl | FP8_TRANSPOSE_OUT, wsb + b.wt, ld.n, wsf + p.wq, ld.k, swt, st, part)) return rc;
             }
-            FP8_TRY(fp8k::launch_gemm_fp8(wsf + p.xq, ld.k, recipe->fmt_x, sxt, 0, wsf + p.wq, ld.k, recipe->fmt_w, swt, 0, M, N, K, y, N, 0, st, true));
+            FP8_TRY(fp8k::launch_gemm_fp8(wsf + p.xq, ld.k, recipe->fmt_x, sxt, 0, wsf + p.wq, ld.k, recipe->fmt_w, swt, 0, M, N, K, y, N, 0, st, fp8k::B_WRITTEN));
             return FP8_OK;
         }
         float *sx = reinterpret_cast<float*>(wsf + p.sx), *sw = reinterpret_cast<float*>(wsf + p.sw);
@@ -440,7 +441,8 @@ int fp8_linear_fwd(const void* x, const void* w, int64_t M, int64_t K, int64_t N
             }
             if (int rc = quantize_row_col_impl(w, N, K, K, recipe->fmt_w, fl, wsf + p.wq, ld.k, sw, wsb + b.wt, ld.n, swt, st, true)) return rc;
         }
-        FP8_TRY(fp8k::launch_gemm_fp8(wsf + p.xq, ld.k, recipe->fmt_x, sx, 1, wsf + p.wq, ld.k, recipe->fmt_w, sw, 1, M, N, K, y, N, 0, st, true));
+        FP8_TRY(fp8k::launch_gemm_fp8(wsf + p.xq, ld.k, recipe->fmt_x, sx, 1, wsf + p.wq, ld.k, recipe->fmt_w, sw, 1, M, N, K, y, N, 0, st,
+                                      fp8k::B_WRITTEN_IN_STRIPS));
         return FP8_OK;
     }
     if (workspace_bytes < p.total)
@@ -467,7 +469,7 @@ int fp8_linear_fwd(const void* x, const void* w, int64_t M, int64_t K, int64_t N
         if (int rc = quantize_impl(w, N, K, K, g, recipe->fmt_w, fl, wq, ld.k, nullptr, 0, sw, st, part)) return rc;
     }
     FP8_TRY(fp8k::launch_gemm_fp8(xq, ld.k, recipe->fmt_x, sx, g == FP8_ROW, wq, ld.k, recipe->fmt_w, sw, g == FP8_ROW, M, N, K,
-                                  y, N, 0, st, true));
+                                  y, N, 0, st, fp8k::B_WRITTEN));
     return FP8_OK;
 }
 

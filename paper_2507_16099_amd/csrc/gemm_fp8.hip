@@ -328,6 +328,11 @@ int pick_path(const GemmOperands& g, double* cost) {
     if (g.M <= 16 || (g.M > 32 && g.M <= 64 && g.N <= 8192 && g.K >= 2048 && gemm_fp8_snake_fits(g.lda, g.ldb))) return 5;
     if (g.M <= 32) {
         if (!ring || 8 * cdiv(g.N, 64) < 5 * cus) return 5;
+        // Codes that the ring kernel has read take longer to be written anew by the next call's quantization, unless in strips (us
+        // a call, few-row / ring: forward by rows 17 x 12288 x 2048 23.9 / 32.3, 32 x 16384 x 1536 25.1 / 29.8, 32 x 14336 x 4096
+        // 40.1 / 43.3, per tensor 34.7 / 38.4, 35.7 / 39.8, 66.3 / 66.2, 17 x 28672 x 8192 239.5 / 237.2; dX per tensor 32 x 16384
+        // x 1536 40.1 / 43.9, by strips 32 x 20480 x 2048 44.6 / 43.3).
+        if (g.b_from == B_WRITTEN && !stream_weight(g.b, g.ldb, g.N, g.K)) return 5;
         const int tile = few_rows_tile(g, cus);
         *cost = ring_cost(tile < 0 ? RING_64x64 : tile, g, nullptr, cus);      // (what the few-row kernel takes too where the contraction is short)
         return tile < 0 ? 5 : kPathRing + tile;
@@ -348,9 +353,9 @@ int pick_path(const GemmOperands& g, double* cost) {
 hipError_t launch_gemm_fp8(const uint8_t* a, int64_t lda, int fmt_a, const float* scale_a, int row_a,
                            const uint8_t* b, int64_t ldb, int fmt_b, const float* scale_b, int row_b,
                            int64_t M, int64_t N, int64_t K, void* out, int64_t ld_out, int out_f32,
-                           hipStream_t st, bool b_written) {
+                           hipStream_t st, BFrom b_from) {
     if (M == 0 || N == 0) return hipSuccess;
-    const GemmOperands g{a, lda, scale_a, b, ldb, scale_b, M, N, K, out, ld_out, b_written};
+    const GemmOperands g{a, lda, scale_a, b, ldb, scale_b, M, N, K, out, ld_out, b_from};
     double cost;
     const int v = pick_path(g, &cost);
     if (v >= kPathRing) return launch_gemm_fp8_ring(v - kPathRing, g, nullptr, fmt_a, fmt_b, row_a, row_b, out_f32 ? 1 : 0, st);

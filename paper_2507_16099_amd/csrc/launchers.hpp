@@ -59,17 +59,19 @@ hipError_t launch_quant_row(const void* x, int64_t rows, int64_t cols, int64_t l
                             int64_t ld_out, float* scale_out, hipStream_t st);
 
 // out[M,N] = (a[M,K] . b[N,K]^T) / (sa * sb); scale_a/scale_b have one entry
-// (row_a / row_b == 0) or one per row.  b_written: the same call has just written b (see ring_hint).
+// (row_a / row_b == 0) or one per row.
+// b_from: who wrote the codes of b, an earlier call or the same one, and then whether as column strips (see ring_hint).
+enum BFrom { B_AT_REST = 0, B_WRITTEN, B_WRITTEN_IN_STRIPS };
 hipError_t launch_gemm_fp8(const uint8_t* a, int64_t lda, int fmt_a, const float* scale_a, int row_a,
                            const uint8_t* b, int64_t ldb, int fmt_b, const float* scale_b, int row_b,
                            int64_t M, int64_t N, int64_t K, void* out, int64_t ld_out, int out_f32,
-                           hipStream_t st, bool b_written = false);
+                           hipStream_t st, BFrom b_from = B_AT_REST);
 // one scaled product out[M, N] = A[M, K] . B[N, K]^T / (scale_a * scale_b), operands as for launch_gemm_fp8
 struct GemmOperands {
     const uint8_t* a; int64_t lda; const float* scale_a;
     const uint8_t* b; int64_t ldb; const float* scale_b;
     int64_t M, N, K; void* out; int64_t ld_out;
-    bool b_written = false;
+    BFrom b_from = B_AT_REST;
 };
 // two small products (bfloat16 results) in one launch; hipErrorNotSupported, with nothing launched, where that does not pay
 hipError_t launch_gemm_fp8_pair(const GemmOperands& g1, const GemmOperands& g2, int fmt_a, int fmt_b, int row_a, int row_b,
@@ -80,10 +82,11 @@ hipError_t launch_gemm_fp8_pair(const GemmOperands& g1, const GemmOperands& g2, 
 // TB/s (us without / with, three weights in turn: 16 x 28672 x 4096 25.3 / 22.0, x 8192 45.8 / 40.2; 64 x 16384 x 8192 32.6 /
 // 28.2).  What that costs: a weight called again and again with nothing in between, or just written, is in the cache and comes
 // slower with the hint (the same with one weight: 19.9 / 21.1, 36.7 / 39.4, 23.2 / 27.2; 128 x 28672 x 4096 22.8 / 27.4, x 8192
-// 39.3 / 53.4, 72 x 16512 x 6528 22.9 / 33.1).  Smaller weights gain as much from HBM (16 x 14336 x 4096 13.6 / 12.6), but more of
-// them fit the cache between the calls, and lose there (the same, three weights in turn: 11.1 / 12.2). Rows have to be whole lines
-// of 128 bytes: a line that two rows or two stages share is fetched twice with the hint (1 x 28672 x 4112 24.8 / 36.5, x 8224 52.0
-// / 62.9, x 8256 53.6 / 60.1; 128 x 28672 x 8224 72.8 / 86.7; x 8320, whole lines, 49.3 / 45.0).
+// 39.3 / 53.4, 72 x 16512 x 6528 22.9 / 33.1, 113 x 20992 x 6656 27.5 / 43.1).  Smaller weights gain as much from HBM (16 x 14336 x
+// 4096 13.6 / 12.6), but more of them fit the cache between the calls, and lose there (the same, three weights in turn: 11.1 /
+// 12.2). Rows have to be whole lines of 128 bytes: a line that two rows or two stages share is fetched twice with the hint (1 x
+// 28672 x 4112 24.8 / 36.5, x 8224 52.0 / 62.9, x 8256 53.6 / 60.1; 128 x 28672 x 8224 72.8 / 86.7; x 8320, whole lines, 49.3 /
+// 45.0).
 inline bool stream_weight(const uint8_t* b, int64_t ldb, int64_t N, int64_t K) {
     return N * K >= (int64_t)96 << 20 && (((uintptr_t)b | (uint64_t)ldb) & 127) == 0;
 }
@@ -104,7 +107,7 @@ inline bool ring_hint(int tile, const GemmOperands& g, const GemmOperands* g2) {
     if (g2 || !stream_weight(g.b, g.ldb, g.N, g.K)) return false;
     switch (tile) {
         case RING_64x64: case RING_64x128: return g.M <= 64;
-        case RING_128x128: case RING_128x256: return g.M <= 128 && !g.b_written;
+        case RING_128x128: case RING_128x256: return g.M <= 128 && g.b_from == B_AT_REST;
     }
     return false;
 }
@@ -113,7 +116,7 @@ inline bool ring_hint(int tile, const GemmOperands& g, const GemmOperands* g2) {
 // 67.1; x 6144 47.6 52.6 57.2, 53.6 51.4 54.3, 46.3 50.0 52.7; x 3584 29.2 32.1 34.5, 33.0 32.1 34.0, 28.7 31.6 34.8; 24576 x 4608
 // 34.7 38.3 42.0, 39.8 38.2 40.3, 33.5 37.3 38.2).  From the cache the two are close (28672 x 6144 36.1 39.7 40.2 / 35.2 38.8
 // 43.2): where the same call has quantized the weight nothing changes.
-inline bool one_row(const GemmOperands& g) { return g.M > 128 && g.M <= 256 && !g.b_written && stream_weight(g.b, g.ldb, g.N, g.K); }
+inline bool one_row(const GemmOperands& g) { return g.M > 128 && g.M <= 256 && g.b_from == B_AT_REST && stream_weight(g.b, g.ldb, g.N, g.K); }
 // Wavefronts of a workgroup: four, one per SIMD, or eight on 128 x 256 and 256 x 128 tiles of short contractions, K <= 6144 (us,
 // four / eight: 2048 x 4096 x 1024 14.5 / 13.4, 3001 x 2048 x 4096 26.0 / 25.1, 2048 x 4096 x 4096 29.6 / 28.7, 1000 x 4096 x 6144
 // 34.2 / 32.7, 4096 x 4096 x 6144 79.5 / 77.1, with the hint 72 x 28672 x 4096 35.8 / 34.7; x 8192 99.6 / 99.2, 2048 x 4096 x 8192

@@ -26,7 +26,7 @@ hipError_t launch_block_quant_t(const void*, int64_t, int64_t, int64_t, int, int
 hipError_t launch_scale(const float*, int64_t, int, int, float*, hipStream_t) STUB
 hipError_t launch_cast(const void*, int64_t, int64_t, int64_t, const float*, int, int, int, uint8_t*, int64_t, uint8_t*, int64_t, hipStream_t) STUB
 hipError_t launch_quant_row(const void*, int64_t, int64_t, int64_t, int, int, uint8_t*, int64_t, float*, hipStream_t) STUB
-hipError_t launch_gemm_fp8(const uint8_t*, int64_t, int, const float*, int, const uint8_t*, int64_t, int, const float*, int, int64_t, int64_t, int64_t, void*, int64_t, int, hipStream_t, bool) STUB
+hipError_t launch_gemm_fp8(const uint8_t*, int64_t, int, const float*, int, const uint8_t*, int64_t, int, const float*, int, int64_t, int64_t, int64_t, void*, int64_t, int, hipStream_t, BFrom) STUB
 hipError_t launch_quant_row_colmax(const void*, int64_t, int64_t, int64_t, int, int, uint8_t*, int64_t, float*, float*, void*, size_t, hipStream_t) { ++g_launches; return hipErrorNotSupported; }
 bool gemm_fp8_snake_fits(int64_t lda, int64_t ldb) { return lda < (1 << 23) && ldb < (1 << 23); }
 hipError_t launch_gemm_fp8_snake(const uint8_t*, int64_t, int, const float*, int, const uint8_t*, int64_t, int, const float*, int, int64_t, int64_t, int64_t, void*, int64_t, int, hipStream_t, int) STUB

@@ -5,7 +5,7 @@
 // input is a query, each line of the output its answer:
 //     one M N K                   a product
 //     mx M N K                    the same, block-scaled; mxrows: with plain rows of scales
-//     own M N K                   the same, its weight written by the same call
+//     own M N K                   the same, its weight written by the same call; strips: in column strips
 //     act M N K                   the same with the sigmoid
 //     few M N K                   the split of a few-row product
 //     cols rows load              columns of a strip of the shared quantization (the third number is not used)
@@ -75,7 +75,8 @@ int main(int argc, char** argv) {
             std::printf("%d\n", strip_columns(M, (double)N, g_cus));
         } else if (std::strcmp(kind, "act") == 0) {
             std::printf("%s\n", gemm_fp8_ring_choice(g) >= 0 ? "ring" : "256x256");
-        } else if (launch_gemm_fp8(g.a, g.lda, 0, nullptr, 1, g.b, g.ldb, 0, nullptr, 1, M, N, K, nullptr, N, 0, nullptr, std::strcmp(kind, "own") == 0) != hipSuccess) {
+        } else if (launch_gemm_fp8(g.a, g.lda, 0, nullptr, 1, g.b, g.ldb, 0, nullptr, 1, M, N, K, nullptr, N, 0, nullptr,
+                                   std::strcmp(kind, "own") == 0 ? B_WRITTEN : std::strcmp(kind, "strips") == 0 ? B_WRITTEN_IN_STRIPS : B_AT_REST) != hipSuccess) {
             return 3;
         }
     }

@@ -72,7 +72,8 @@ def test_no_streaming_hint_on_tall_tiles_behind_the_weights_own_quantization(cho
     """The codes are in the last-level cache."""
     for M in (33, 64, 65, 128, 193, 256):
         for tile in range(1, 7):
-            one, own = choose(f"one {M} {N} {K}", f"own {M} {N} {K}", GEMM_RING=tile)
+            one, own, strips = choose(f"one {M} {N} {K}", f"own {M} {N} {K}", f"strips {M} {N} {K}", GEMM_RING=tile)
+            assert own == strips
             assert one.split()[1] == own.split()[1]
             assert ("hint" in own) == ("hint" in one and M <= 64 and tile <= 3), (M, tile, one, own)
 
@@ -145,3 +146,12 @@ def test_low_tiles_over_several_rounds(choose):
     for M, K, N, tile in ((1286, 1024, 5120, "128x128"), (730, 6912, 656, "128x128"), (93, 14080, 256, "128x256"), (2048, 768, 11008, "128x128")):
         answer, = choose(f"two {M} {K} {N} {N} {K} {(M + 15) // 16 * 16}")
         assert answer.startswith(f"ring {tile} together"), (M, K, N, answer)
+
+
+def test_few_rows_behind_the_weights_own_quantization(choose):
+    """17 to 32 rows: codes just written go to the few-row kernel, unless in strips or beyond the size of a streamed weight."""
+    for M in (17, 32):
+        for N, K in ((10240, 4096), (16384, 1536), (20480, 2048)):
+            assert choose(f"own {M} {N} {K}", f"strips {M} {N} {K}", f"one {M} {N} {K}")[0] == "few-row"
+            assert choose(f"strips {M} {N} {K}") == choose(f"one {M} {N} {K}") != ["few-row"]
+        assert choose(f"own {M} 28672 4096")[0].startswith("ring")

@@ -244,9 +244,10 @@ static hipError_t launch_tn(const GemmOperands& g, int row_a, int row_b, hipStre
 // 6.1 .. 5.8 / 6.3.  Beyond the lines: 11008 x 4096 18.8 / 13.1 .. 22.3 / 14.8, 14336 x 4096 20.4 / 15.3 .. 23.6 / 16.0, 28672 x
 // 8192 60.7 / 50.1 .. 71.8 / 52.1, 8192 x 1024 6.1 / 5.1 .. 6.8 / 5.2.  On them it is close: 8192 x 2048 7.8 / 7.8 .. 9.2 / 8.7,
 // 4096 x 1024 4.7 / 4.9 .. 5.3 / 5.1.) More than one round of 256 x 256 tiles (one per CU): the large-product kernels of
-// gemm_fp8_snake.hip / gemm_fp8_stream.hip.  In between the cheapest of the ring kernel's tiles (gemm_fp8_ring.hip) and one round
+// gemm_fp8_snake.hip / gemm_fp8_stream.hip.  In between the cheapest of the ring kernel's tiles (gemm_fp8_ring.hpp) and one round
 // of 256 x 256 tiles by this estimate, in us (one launch; rounds of 256 workgroups, K steps of 128 bytes):
-//     3 + rounds * (a + steps * b);  256 x 256 tiles: 10 + 1.2 * steps, at most half of the CUs busy (half tiles) 7.2 + 0.91 * steps.
+//     3 + rounds * (a + steps * b);  256 x 256 tiles: 10 + 1.2 * steps, at most half of the CUs busy (half tiles) 7.2 + 0.91 * steps,
+//     one round of 224 x 256 tiles 9.6 + 1.085 * steps, of 192 x 256 ones 9 + 0.97 * steps (one_round_height).
 // a: prologue and epilogue of a tile; b: a K step with every CU busy (some 460 / 670 / 970 / 1600 cycles for the tiles below; their
 // matrix instructions take 128 / 256 / 512 / 1024, the fragment reads and LDS-DMA writes at 128 bytes a cycle 384 / 576 / 768 /
 // 1152). No unit is full: 128 x 128 tiles at 777 x 4096 x 14336 keep the matrix units busy 42 % of the time and the LDS's reads 22
@@ -259,6 +260,13 @@ static hipError_t launch_tn(const GemmOperands& g, int row_a, int row_b, hipStre
 //     2048 x 4096    29.9 / 62.1 / 242   22.8 / 49.2 / 176   17.9 / 38.2 / 131   17.6 / 32.7 / 109    14.5 / 36.4 / 157
 //     3072 x 4096    43.0 / 100          32.4 / 76           25.6 / 58           23.9 / 56            19.0 / 46.1
 //     4096 x 4096    57.8 / 136          43.3 / 113          31.7 / 83           31.7 / 68            20.8 / 53.3
+// The tiles between these sizes, one round exactly full of them (16 rows of tiles by 16; us, K = 1024 / 4096 / 8192 / 16384, and what
+// the six above and 256 x 256 ones take): 96x64 5.6 / 11.6 / 18.9 / 32.7, before 6.6 / 12.8 / 20.8 / 36.7; 64x192 8.5 / 16.9 /
+// 28.1 / 50.2, 8.9 / 17.9 / 29.2 / 51.8; 160x64 7.3 / 15.4 / 24.9 / 44.6, 8.4 / 16.6 / 27.3 / 48.7; 96x128 8.0 / 17.1 / 26.8 /
+// 48.0, 8.6 / 17.0 / 28.0 / 50.5; 160x128 10.7 / 22.3 / 37.9 / 69.1, 13.2 / 26.4 / 44.5 / 80.0; 192x128 and 128x192 11.9 / 25.2 /
+// 42.9 / 78.9, 13.3 / 27.5 / 47.3 / 85.5; 160x192 16.0 / 29.7 / 50.4 / 99.6, 13.0 / 29.9 / 52.0 / 105.8; 192x192 15.2 / 33.2 / 57.0
+// / 111, 17.8 / 41.3 / 69.7 / 150; 160x256 16.6 / 36.3 / 65.4 / 125, 18.3 / 42.1 / 71.8 / 153; 224x192 16.9 / 37.5 / 64.7 / 126,
+// 18.5 / 43.3 / 74.4 / 153.
 // Switches (tuning and test aid): GEMM_RING = 0 takes the ring kernel out of the choice, 1 + tile forces one of its tiles;
 // GEMM_BIG_FROM: number of 128 x 128 tiles from which the 256 x 256 kernels are taken; GEMM_VARIANT forces a kernel:
 // 0 = the fallback above, 4 = 256 x 256, 5 = few-row kernel (only where M <= 64), 6 / 7 = ring kernel, 64 x 64 / 128 x 128 tiles.
@@ -268,8 +276,10 @@ namespace {
 // step, 6.3 / 7.0: 2215 x 2048 x 7936 110.8 / 124.3 on 128 x 128 tiles, 4743 x 896 x 16000 272.5 / 300.3; apart 2091 x 2048 x 7168
 // 93.3 / 101.9, 3729 x 1152 x 11648 173.0 / 182.6).
 struct RingCost { int tm, tn; double a, b; };
-constexpr RingCost kRing[RING_TILES] = {{64, 64, 1.0, 0.20},   {128, 64, 1.9, 0.29},  {64, 128, 1.9, 0.29},
-                                        {128, 128, 4.0, 0.42}, {128, 256, 6.3, 0.70}, {256, 128, 6.3, 0.70}};
+constexpr RingCost kRing[RING_TILES] = {{64, 64, 1.0, 0.20},   {128, 64, 1.9, 0.29},  {64, 128, 1.9, 0.29},  {128, 128, 4.0, 0.42}, {128, 256, 6.3, 0.70},
+                                        {256, 128, 6.3, 0.70}, {96, 64, 1.3, 0.235},  {64, 192, 2.7, 0.35},  {160, 64, 2.5, 0.31},  {96, 128, 3.2, 0.34},
+                                        {160, 128, 4.2, 0.485}, {192, 128, 4.2, 0.56}, {128, 192, 4.2, 0.56}, {160, 192, 5.9, 0.65}, {192, 192, 6.5, 0.75},
+                                        {160, 256, 6.1, 0.86}, {224, 192, 7.1, 0.86}};
 constexpr int kPathRing = 100;       // + tile: the ring kernel; otherwise a GEMM_VARIANT number
 
 int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -293,11 +303,32 @@ double ring_cost(int tile, const GemmOperands& g, const GemmOperands* g2, int64_
 // the cheapest ring tile for one product, or two in one launch
 int best_ring(const GemmOperands& g, const GemmOperands* g2, int64_t cus, double* cost) {
     int best = 0;
-    for (int t = 0; t < RING_TILES; ++t) {
+    for (int t = 0; t < RING_ANY_ROUNDS; ++t) {
         const double c = ring_cost(t, g, g2, cus);
         if (t == 0 || c < *cost) { best = t; *cost = c; }
     }
     return best;
+}
+// Of the tiles [from, to) between those sizes, which make a round fuller: the cheapest that covers the product in one round, if
+// it is cheaper than *cost, else -1.  Over several rounds they are behind (two full ones of 192 x 192 tiles, K = 4096, 65.8 against
+// 66.9 us on 256 x 256, three 96.6 / 87.2; of 96 x 64 21.1 / 17.0).  Not against a weight that is streamed for up to 256 rows:
+// there the number of times it is fetched counts (ring_hint, one_row).
+int best_one_round(const GemmOperands& g, int from, int to, int64_t cus, double* cost) {
+    int best = -1;
+    if (g.M <= 256 && stream_weight(g.b, g.ldb, g.N, g.K)) return best;
+    for (int t = from; t < to; ++t) {
+        if (cdiv(g.M, kRing[t].tm) * cdiv(g.N, kRing[t].tn) > cus) continue;
+        const double c = ring_cost(t, g, nullptr, cus);
+        if (c < *cost) { best = t; *cost = c; }
+    }
+    return best;
+}
+// one round of the 256 x 256 kernels (half tiles, the lower tiles of the persistent one)
+double large_cost(const GemmOperands& g, bool bf16, int64_t cus) {
+    const double steps = (double)cdiv(g.K, BK);
+    if (2 * cdiv(g.M, 256) * cdiv(g.N, 256) <= cus) return 7.2 + 0.91 * steps;
+    const int h = bf16 ? one_round_height(g.M, g.N, g.K, cus) : 256;
+    return h == 192 ? 9.0 + 0.97 * steps : h == 224 ? 9.6 + 1.085 * steps : 10.0 + 1.2 * steps;
 }
 // 17 to 32 rows against a wide weight: the ring kernel's tile, or -1 for the few-row kernel, which has no rounds to fill.  64 x 64
 // tiles over one round at most, 64 x 128 ones where those fit one and the contraction pays for them, else 64 x 64 ones where it is
@@ -316,8 +347,8 @@ int few_rows_tile(const GemmOperands& g, int64_t cus) {
     }
     return K >= 6144 || (K >= 4096 && tiles >= 4 * cus) ? RING_64x64 : -1;
 }
-// kernel for one product; *cost: its estimate (large where there is none)
-int pick_path(const GemmOperands& g, double* cost) {
+// kernel for one product; *cost: its estimate (large where there is none); any_rounds: only of the tiles that pairs can take too
+int pick_path(const GemmOperands& g, double* cost, bool any_rounds = false) {
     *cost = 1e30;
     const bool fits = gemm_fp8_ring_fits(g), ring = fits && knob(KNOB_GEMM_RING) != 0;
     if (const int r = knob(KNOB_GEMM_RING); r >= 1 && r <= RING_TILES && fits) return kPathRing + r - 1;
@@ -340,10 +371,13 @@ int pick_path(const GemmOperands& g, double* cost) {
     const int64_t big = cdiv(g.M, 256) * cdiv(g.N, 256);
     if (const int b = knob(KNOB_GEMM_BIG_FROM); b > 0 && cdiv(g.M, 128) * cdiv(g.N, 128) >= b) return 4;
     if (big > cus || !ring) return 4;
-    const double steps = (double)cdiv(g.K, BK);
-    const double cost_big = 2 * big <= cus ? 7.2 + 0.91 * steps : 10.0 + 1.2 * steps;
+    double cost_big = large_cost(g, !any_rounds, cus);
     int tile = best_ring(g, nullptr, cus, cost);
     if (tile == RING_128x256 && one_row(g)) tile = RING_256x128;
+    if (!any_rounds) {
+        best_one_round(g, RING_WIDE, RING_TILES, cus, &cost_big);
+        if (const int t = best_one_round(g, RING_ANY_ROUNDS, RING_WIDE, cus, cost); t >= 0) tile = t;
+    }
     if (*cost <= cost_big) return kPathRing + tile;
     *cost = cost_big;
     return 4;
@@ -385,12 +419,13 @@ hipError_t launch_gemm_fp8(const uint8_t* a, int64_t lda, int fmt_a, const float
 // taken is on average 1.2 % (slabs) and 3.0 % (plain rows) behind the best one, at most 40 %, where 256 x 256 tiles are taken for
 // K = 1024; plain products 1.8 %.
 int gemm_mxfp8_ring_choice(const GemmOperands& g, bool plain_scales) {
-    if (const int r = knob(KNOB_GEMM_RING); r >= 0 && r <= RING_TILES) return r - 1;
+    if (const int r = knob(KNOB_GEMM_RING); r >= 0 && r <= RING_MX_TILES) return r - 1;
     const int64_t cus = compute_units() > 0 ? compute_units() : 256;
     const int64_t big = cdiv(g.M, 256) * cdiv(g.N, 256);
     if (big > cus) return -1;
     double cost = 0.0;
-    const int tile = best_ring(g, nullptr, cus, &cost);
+    int tile = best_ring(g, nullptr, cus, &cost);
+    if (const int t = best_one_round(g, RING_ANY_ROUNDS, RING_MX_TILES, cus, &cost); t >= 0) tile = t;
     const double steps = (double)cdiv(g.K, BK);
     const double cost_big = 2 * big <= cus ? 9.0 + 1.05 * steps : 10.0 + 1.25 * steps;
     return 3.0 + (cost - 3.0) * (plain_scales ? 1.25 : 1.1) <= cost_big ? tile : -1;
@@ -404,6 +439,15 @@ int gemm_fp8_ring_choice(const GemmOperands& g) {
     return best_ring(g, nullptr, compute_units() > 0 ? compute_units() : 256, &cost);
 }
 
+int gemm_fp8_wide_choice(const GemmOperands& g, bool bf16) {
+    if (knob(KNOB_GEMM_RING) >= 0 || knob(KNOB_GEMM_VARIANT) >= 0 || knob(KNOB_GEMM_BIG_FROM) > 0 || knob(KNOB_GEMM_STREAM) >= 0 || knob(KNOB_GEMM_TILE_M) >= 0)
+        return -1;      // a form is forced
+    if (!gemm_fp8_ring_fits(g)) return -1;
+    const int64_t cus = compute_units() > 0 ? compute_units() : 256;
+    double cost = large_cost(g, bf16, cus);
+    return best_one_round(g, RING_WIDE, RING_TILES, cus, &cost);
+}
+
 // Two products of the same formats and kinds of scale (bfloat16 results) in ONE launch, for the pair dX, dW of a
 // backward step whose products are too small to fill the chip one at a time.  hipErrorNotSupported (nothing launched)
 // where one launch each is estimated to be as fast: the caller then launches them one after the other.
@@ -412,7 +456,7 @@ hipError_t launch_gemm_fp8_pair(const GemmOperands& g1, const GemmOperands& g2, 
     if (g1.M == 0 || g1.N == 0 || g2.M == 0 || g2.N == 0 || knob(KNOB_PAIRS) == 0) return hipErrorNotSupported;
     if (!gemm_fp8_ring_fits(g1) || !gemm_fp8_ring_fits(g2)) return hipErrorNotSupported;
     double c1, c2, both = 0.0;
-    const int v1 = pick_path(g1, &c1), v2 = pick_path(g2, &c2);
+    const int v1 = pick_path(g1, &c1, true), v2 = pick_path(g2, &c2, true);
     if (c1 > 1e29 || c2 > 1e29) {      // no estimate: forced, few rows, or large
         if (v1 < kPathRing || v1 != v2) return hipErrorNotSupported;
         return launch_gemm_fp8_ring(v1 - kPathRing, g1, &g2, fmt_a, fmt_b, row_a, row_b, 0, st);

@@ -478,6 +478,9 @@ static hipError_t launch_sn(const uint8_t* a, int64_t lda, const float* sa, int 
         return launch_sn_part<FA, FB, OUT_F32, ACT, false>(a, lda, sa, row_a, b, ldb, sb, row_b, M, N, K, out, ld_out, tiles_m, tiles_n,
                                                           0, count, st);
     };
+    const int low = sw < 0 && ntiles <= compute_units() ? one_round_height(M, N, K, compute_units()) : 256;
+    if (stream_ok && low != 256 && knob(KNOB_GEMM_TILE_M) < 0)
+        return launch_gemm_fp8_stream(a, lda, FA, sa, row_a, b, ldb, FB, sb, row_b, M, N, K, out, ld_out, (int64_t)((M + low - 1) / low) * tiles_n, low, st);
     if (stream_ok && (sw >= 2 || ntiles > compute_units())) {
         // a lower tile (224 or 192 rows) when its tile count fills whole rounds of workgroups better than 256-row
         // tiles with their partly filled last round do: then the persistent kernel takes every tile
@@ -520,11 +523,11 @@ hipError_t launch_gemm_fp8_snake(const uint8_t* a, int64_t lda, int fmt_a, const
                                  hipStream_t st, int act) {
     if (M == 0 || N == 0) return hipSuccess;
     if (act && out_f32) return hipErrorInvalidValue;
-    if (act) {      // the fused activation of a product of less than a round of these tiles: the ring kernel's epilogue has it too
-        const GemmOperands g{a, lda, scale_a, b, ldb, scale_b, M, N, K, out, ld_out};
-        if (const int tile = gemm_fp8_ring_choice(g); tile >= 0)
-            return launch_gemm_fp8_ring(tile, g, nullptr, fmt_a, fmt_b, row_a, row_b, 2, st);
-    }
+    // one round of the ring kernel's wide tiles in place of a partly filled one; with the fused activation any of its tiles
+    const GemmOperands g{a, lda, scale_a, b, ldb, scale_b, M, N, K, out, ld_out};
+    int tile = act ? gemm_fp8_ring_choice(g) : -1;
+    if (tile < 0) tile = gemm_fp8_wide_choice(g, !act && !out_f32);
+    if (tile >= 0) return launch_gemm_fp8_ring(tile, g, nullptr, fmt_a, fmt_b, row_a, row_b, act ? 2 : out_f32 ? 1 : 0, st);
     const int m = (int)M, n = (int)N, k = (int)K;
 #define FP8K_SNA(FA_, FB_)                                                                                 \
     if (act && fmt_a == FA_ && fmt_b == FB_)                                                               \

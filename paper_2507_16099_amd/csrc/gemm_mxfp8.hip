@@ -239,7 +239,7 @@ static hipError_t launch_mx_t(const uint8_t* a, int64_t lda, const uint8_t* ea, 
 
 // K must be a multiple of 128 and ld_ea, ld_eb multiples of 4 (a K step reads one aligned
 // dword of scales per row); checked by the caller
-// large problems: the 256 x 256 LDS-DMA kernel; less than a round of its tiles: mostly the ring kernel (gemm_fp8_ring.hip), in
+// large problems: the 256 x 256 LDS-DMA kernel; less than a round of its tiles: mostly the ring kernel (gemm_fp8_ring.hpp), in
 // launch_gemm_mxfp8 (the switch MX_VARIANT = 0 forces this file's kernel, 1 the 256 x 256 one)
 static bool mx_snake_possible(int64_t lda, int64_t ldb, int64_t K) { return K > 0 && gemm_fp8_snake_fits(lda, ldb); }
 static bool mx_takes_snake(int64_t lda, int64_t ldb, int64_t M, int64_t N, int64_t K) {

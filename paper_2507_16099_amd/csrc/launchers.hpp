@@ -91,9 +91,13 @@ inline bool stream_weight(const uint8_t* b, int64_t ldb, int64_t N, int64_t K) {
     return N * K >= (int64_t)96 << 20 && (((uintptr_t)b | (uint64_t)ldb) & 127) == 0;
 }
 
-// products of few to middling size on smaller tiles with a deep LDS ring (gemm_fp8_ring.hip); g2: a second product in
+// products of few to middling size on smaller tiles with a deep LDS ring (gemm_fp8_ring.hpp); g2: a second product in
 // the same launch, or nullptr; mode 0 = bfloat16, 1 = fp32, 2 = bfloat16 of the sigmoid.  _fits: 32-bit offsets reach
-enum RingTile { RING_64x64 = 0, RING_128x64, RING_64x128, RING_128x128, RING_128x256, RING_256x128, RING_TILES };
+// The tiles up to RING_256x128 are taken over any number of rounds and by pairs of products, those behind only by one product that
+// they cover in one round; the last two have no block-scaled form.
+enum RingTile { RING_64x64 = 0, RING_128x64, RING_64x128, RING_128x128, RING_128x256, RING_256x128, RING_96x64, RING_64x192, RING_160x64, RING_96x128,
+                RING_160x128, RING_192x128, RING_128x192, RING_160x192, RING_192x192, RING_160x256, RING_224x192, RING_TILES };
+constexpr int RING_ANY_ROUNDS = RING_256x128 + 1, RING_WIDE = RING_160x192, RING_MX_TILES = RING_160x256;
 // Its form for a tile: whether B is read with the streaming hint.  One row of tiles against a weight that stream_weight accepts
 // reads it once (us, weights from HBM, without / with: 64 x 28672 x 8192 51.5 / 47.0, 128 rows 56.1 / 53.2, x 4096 32.8 / 30.5).
 // Not two rows of 128 x 256 tiles: they read it side by side, but fall out of step where the second is not full, and lines are
@@ -126,14 +130,28 @@ inline bool one_row(const GemmOperands& g) { return g.M > 128 && g.M <= 256 && g
 // Up to K = 1536 with plain rows of scales (from the cache 1000 x 4096 x 1024 / 2048 / 3072 / 4096 -11 / -8 / -3 / +2 %, from HBM
 // -13 / +4 / +3 / +11 %), and of 256 x 128 tiles whose B rows are no whole lines (690 x 5968 x 1040 / 2256 / 3088 / 6128 from the
 // cache -8 / -4 / -1 / +2 %, from HBM -3 / +4 / +5 / +8 %).
+// 192 x 128 tiles: eight up to K = 4096 (3072 x 2048 x 1024 11.9 / 11.5, x 4096 25.2 / 25.1, 1400 x 4096 x 4096 24.8 / 24.2; x 8192 42.9 /
+// 43.5, x 16384 78.9 / 80.6).
 inline int ring_waves(int tile, const GemmOperands& g, const GemmOperands* g2, bool mx, bool plain_scales = false) {
     const int64_t line = plain_scales || (tile == RING_256x128 && ((g.ldb | (g2 ? g2->ldb : 0)) & 127)) ? 1536 : 6144;
+    if (tile == RING_192x128) return g.K <= (plain_scales ? 1536 : 4096) && (!g2 || g2->K <= 4096) ? 8 : 4;
     if (tile != RING_128x256 && tile != RING_256x128) return 4;
     if (tile == RING_256x128 && !mx && !g2 && g.M > 192 && one_row(g)) return 4;
     return g.K <= line && (!g2 || g2->K <= line) ? 8 : 4;
 }
 bool gemm_fp8_ring_fits(const GemmOperands& g);
 int gemm_fp8_ring_choice(const GemmOperands& g);      // its tile where a 256 x 256 tile per workgroup is not the better form, else -1
+int gemm_fp8_wide_choice(const GemmOperands& g, bool bf16);      // of a product sent to the 256 x 256 kernels: its wide tile that is the better form, or -1
+// Height of the 256 x 256 kernel's tiles where lower ones cover the product in one round on more than half of the CUs: 192 or 224
+// rows on the persistent kernel, else 256 (us, 256 rows / 224 / 192: 3001 x 4096 x 2048 26.9 / 24.6 / 23.8; 3072 x 4096 x 1024
+// 17.9 / 16.4 / 16.2, x 4096 42.0 / 40.1 / 39.3, x 8192 75.3 / 73.7 / 70.3; 3584 x 4096 x 4096 45.8 / 44.7, x 8192 84.3 / 79.2, of
+// a short contraction equal: x 1024 18.2 / 18.7).
+inline int one_round_height(int64_t M, int64_t N, int64_t K, int64_t cus) {
+    const int64_t cols = (N + 255) / 256;
+    if (2 * ((M + 255) / 256) * cols <= cus || N % 8 || K <= 256) return 256;
+    if ((M + 191) / 192 * cols <= cus) return 192;
+    return (M + 223) / 224 * cols <= cus && K > 1024 ? 224 : 256;
+}
 hipError_t launch_gemm_fp8_ring(int tile, const GemmOperands& g1, const GemmOperands* g2, int fmt_a, int fmt_b, int row_a,
                                 int row_b, int mode, hipStream_t st);
 

@@ -19,7 +19,8 @@
 #include <cstring>
 
 namespace fp8k {
-static const char* const names[RING_TILES] = {"64x64", "128x64", "64x128", "128x128", "128x256", "256x128"};
+static const char* const names[RING_TILES] = {"64x64", "128x64", "64x128", "128x128", "128x256", "256x128", "96x64", "64x192", "160x64", "96x128",
+                                                "160x128", "192x128", "128x192", "160x192", "192x192", "160x256", "224x192"};
 static int g_cus = 256, g_knobs[KNOB_COUNT];
 int knob(Knob k) { return g_knobs[k]; }
 int compute_units() { return g_cus; }

@@ -1,0 +1,36 @@
+"""The choice of tiles between the usual sizes, without a device: one product in one round, never pairs or several rounds."""
+import re
+
+import pytest
+
+from tests.test_gemm_choice import choose, pytestmark  # noqa: F401
+
+SIZES = [(M, N) for M in (65, 96, 160, 300, 777, 1400, 2500, 3001, 3072, 5000) for N in (64, 512, 1000, 2048, 3072, 4096, 6144, 11008, 28672)]
+NEW = {"96x64", "64x192", "160x64", "96x128", "160x128", "192x128", "128x192", "160x192", "192x192", "160x256", "224x192"}
+
+
+@pytest.mark.parametrize("kind", ["one", "own", "mx", "mxrows"])
+@pytest.mark.parametrize("cus", [64, 256])
+def test_only_in_one_round(choose, kind, cus):  # noqa: F811
+    seen = set()
+    for K in (128, 1024, 4096, 10240):
+        for (M, N), a in zip(SIZES, choose(*[f"{kind} {M} {N} {K}" for M, N in SIZES], cus=cus)):
+            m = re.match(r"ring (\d+)x(\d+)", a)
+            if m and f"{m[1]}x{m[2]}" in NEW:
+                seen.add(f"{m[1]}x{m[2]}")
+                assert -(-M // int(m[1])) * -(-N // int(m[2])) <= cus, (M, N, K, a)
+                assert "hint" not in a and not (M <= 256 and N * K >= 96 << 20)
+    assert len(seen) >= 5, seen
+
+
+def test_never_for_pairs(choose):  # noqa: F811
+    for K in (256, 1024, 4096):
+        for a in choose(*[f"two {M} {K} {N} {N} {K} {(M + 15) // 16 * 16}" for M, N in SIZES]):
+            m = re.match(r"ring (\S+) together", a)
+            assert a == "apart" or m[1] not in NEW, a
+
+
+@pytest.mark.parametrize("M,N,K,tile", [(72, 14336, 4096, "96x64"), (3001, 2048, 4096, "192x128"), (2500, 2048, 8192, "160x128"), (1500, 2048, 4096, "96x128"),
+                                        (1500, 4096, 2048, "192x128"), (2048, 3072, 4096, "128x192"), (512, 4096, 4096, "128x64"), (2048, 4096, 4096, "128x256")])
+def test_the_tile_that_fills_the_round(choose, M, N, K, tile):  # noqa: F811
+    assert choose(f"one {M} {N} {K}")[0].split()[1] == tile

@@ -230,7 +230,11 @@ hipError_t launch_gemm_fp8_snake(const uint8_t* a, int64_t lda, int fmt_a, const
                                  int64_t M, int64_t N, int64_t K, void* out, int64_t ld_out, int out_f32,
                                  hipStream_t st, int act = 0);
 
-// persistent form of the same kernel (gemm_fp8_stream.hip): one workgroup per CU walks many tiles, the epilogue of a
+// its block-scaled form, scales in slabs of slab_a / slab_b rows, in tiles of 256, 224 or 192 rows
+bool gemm_mxfp8_stream_fits(const GemmOperands& g, int64_t slab_a, int64_t slab_b, int out_f32);
+hipError_t launch_gemm_mxfp8_stream(const GemmOperands& g, int fmt_a, const uint8_t* ea, int64_t slab_a, int fmt_b, const uint8_t* eb, int64_t slab_b,
+                                    int tile_m, hipStream_t st);
+// persistent form of the same kernel (gemm_fp8_stream.hpp): one workgroup per CU walks many tiles, the epilogue of a
 // tile is drained inside the K steps of the next.  bfloat16 output, whole tiles [0, units) of the snake kernel's tile
 // order; _fits: shapes it takes (N % 8 == 0, more than two K steps, 32-bit offsets reach)
 bool gemm_fp8_stream_fits(int64_t lda, int64_t ldb, int64_t ld_out, int64_t N, int64_t K, int out_f32, int act);

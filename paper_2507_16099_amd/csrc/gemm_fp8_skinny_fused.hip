@@ -10,7 +10,7 @@
 // R steps of 128 bytes ahead, no barriers in the main loop.  What differs:
 //  * a workgroup is eight wavefronts (one per CU: X is read and converted once per CU) where that makes one
 //    round of workgroups over most CUs, else four (two per CU);
-//  * before the main loop the workgroup reads all of X (at most 32768 elements: 8 or 16 loads of 16 bytes
+//  * before the main loop the workgroup reads all of X (at most 32768 elements: 2 to 16 loads of 16 bytes
 //    per lane, requested ahead of the first ring fill and waited for by count, so they arrive while the
 //    weight's first bytes are still on their way), reduces the row maxima (lane maxima folded within rows
 //    of 16 lanes by DPP rotations, then through scalar registers, then one LDS word per row), derives the
@@ -22,6 +22,8 @@
 #include "fp8_device.hpp"
 #include "launchers.hpp"
 #include "tuning.hpp"
+
+#include <type_traits>
 
 namespace fp8k {
 
@@ -64,8 +66,12 @@ __device__ __forceinline__ void skf_load16(v4i_q& dst, v4i_q rsrc, uint32_t voff
 // wait until at most N_ loads are in flight; the registers are operands so that no use of them moves above the wait
 template <int N_, int U>
 __device__ __forceinline__ void skf_wait_x(v4i_q (&x)[U]) {
-    static_assert(U == 8 || U == 16, "8 or 16 register sets");
-    if constexpr (U == 8) {
+    static_assert(U == 2 || U == 4 || U == 8 || U == 16, "2 to 16 register sets");
+    if constexpr (U == 2) {
+        asm volatile("s_waitcnt vmcnt(%2)" : "+v"(x[0]), "+v"(x[1]) : "n"(N_) : "memory");
+    } else if constexpr (U == 4) {
+        asm volatile("s_waitcnt vmcnt(%4)" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]) : "n"(N_) : "memory");
+    } else if constexpr (U == 8) {
         asm volatile("s_waitcnt vmcnt(%8)"
                      : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7])
                      : "n"(N_)
@@ -82,20 +88,26 @@ template <int N_>
 __device__ __forceinline__ void skf_wait_vmem() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N_) : "memory"); }
 
 namespace skf {
-constexpr int MAX_X = 32768;       // elements of X a workgroup holds in registers: 8 (16) loads of 8 per lane of its 512 (256) threads
+constexpr int MAX_X = 32768;       // elements of X a workgroup holds in registers: up to 8 (16) loads of 8 per lane of its 512 (256) threads
 constexpr int ROW_PAD = 64;        // bytes between the rows of codes in LDS beyond K: consecutive rows start 16 banks apart
+constexpr int steps_ahead(int waves, int nw) { return waves == 8 ? (nw == 1 ? 6 : 3) : (nw == 1 ? 5 : 3); }
+constexpr int64_t lds_bytes(int waves, int nw, int64_t M, int64_t K) { return waves * steps_ahead(waves, nw) * nw * 2048 + M * (K + ROW_PAD) + 128 + 512; }
 }  // namespace skf
 
-template <int FX, int FB, int KS, int NW, int WAVES, int R, bool HINT>
+// U: pieces of X per wavefront, 512 elements and a load of 16 bytes per lane each.  Only as many as X has: what stands in front of the
+// first weight request is time in which nothing streams, and sixteen loads with their row and column (of which one token of 4096
+// needs two) were 500 instructions.
+template <int FX, int FB, int KS, int NW, int WAVES, int R, int U, bool HINT>
 __global__ __launch_bounds__(64 * WAVES) void gemm_fp8_skinny_fused_kernel(
     const uint16_t* __restrict__ X, int64_t ldx, int row_x, int flags, const uint8_t* __restrict__ B, int64_t ldb,
-    const float* __restrict__ scale_b, int row_b, int M, int N, int K, uint16_t* __restrict__ out, int64_t ld_out) {
+    const float* __restrict__ scale_b, int row_b, int M, int N, int K, uint32_t inv_cpr, uint16_t* __restrict__ out, int64_t ld_out) {
     using namespace skf;
     constexpr int NTW = WAVES / KS;
     constexpr int SLOT = NW * 2048;              // weight bytes of one K step of this wavefront
     constexpr int LB = 2 * NW;                   // LDS-DMA loads per step
     static_assert((R - 1) * LB <= 63 && R * LB <= 63, "vmcnt range");
-    // dynamic LDS: WAVES rings of R slots; then the codes of X, row r at r * (K + ROW_PAD); then 128 bytes of zeros
+    // dynamic LDS: WAVES rings of R slots; then the codes of X, row r at r * (K + ROW_PAD); then 128 bytes of zeros; then 512 bytes
+    // that take the codes of pieces past the end
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     __shared__ uint32_t amax_bits[8];
     __shared__ float scale_x[8];
@@ -132,16 +144,15 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_fp8_skinny_fused_kernel(
     const v4i_q rsrc_x = {(int)(uint32_t)px, (int)(uint32_t)(px >> 32), (int)(((int64_t)(M - 1) * ldx + K) * 2), 0x00020000};
     constexpr uint32_t OOB = 0x80000000u;
 
-    // ---- X: wavefront w takes the pieces w, w + 8, ... of 512 elements (piece q = 512 elements from column
-    //      512 (q % cpr) of row q / cpr); a piece past the end is not fetched (zeros)
-    constexpr int U = 64 / WAVES;                // pieces per wavefront: 8 or 16 loads of 16 bytes per lane
-    const int cpr = K / 512, pieces = M * cpr;
+    // ---- X: wavefront w takes the pieces U w .. U w + U - 1 of 512 elements (piece q = 512 elements from column
+    //      512 (q % cpr) of row q / cpr), so mostly of one row; a piece past the end is not fetched (zeros)
+    const int cpr = K / 512, pieces = M * cpr;   // (inv_cpr: 2^32 / cpr rounded up, exact for these; 0 stands for cpr == 1)
     v4i_q xv[U];
     int prow[U], pcol[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const int q = wave + WAVES * u;
-        prow[u] = q / cpr;
+        const int q = wave * U + u;
+        prow[u] = inv_cpr ? (int)__umulhi((uint32_t)q, inv_cpr) : q;
         pcol[u] = q - prow[u] * cpr;
         skf_load16(xv[u], rsrc_x, q < pieces ? (uint32_t)((prow[u] * (int)ldx + pcol[u] * 512 + lane * 8) * 2) : OOB);
     }
@@ -168,26 +179,34 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_fp8_skinny_fused_kernel(
     __syncthreads();                              // amax_bits and zeros are set
     skf_wait_x<R * LB, U>(xv);                       // X is there; the first ring fill may still be under way
     auto as_u4 = [](const v4i_q& a) { return make_uint4((uint32_t)a[0], (uint32_t)a[1], (uint32_t)a[2], (uint32_t)a[3]); };
+    uint32_t pm[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        if (wave + WAVES * u < pieces) {
-            const uint32_t m = wave_max_u32<64>(pk_fold(pk_absmax4(0u, as_u4(xv[u]))));
-            if (lane == 0) atomicMax(&amax_bits[prow[u]], m);
+    for (int u = 0; u < U; ++u) pm[u] = pk_absmax4(0u, as_u4(xv[u]));
+    const int last = wave * U + U <= pieces ? prow[U - 1] : M - 1;
+    for (int r = prow[0]; r <= last; ++r) {       // the rows of this wavefront's pieces, one as a rule: one reduction each
+        uint32_t m = 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) m = pk_absmax(m, prow[u] == r ? pm[u] : 0u);
+        const uint32_t w = wave_max_u32<64>(pk_fold(m));
+        if (lane == 0) atomicMax(&amax_bits[r], w);
+    }
+    __syncthreads();
+    // every wavefront derives the scales for itself, that of row m in lane m
+    uint32_t mag = amax_bits[lane & 7];           // (rows from M on: 0)
+    if (!row_x)
+        for (int m = 0; m < M; ++m) mag = amax_bits[m] > mag ? amax_bits[m] : mag;
+    const float sc_x = scale_from_amax(mag_to_float(mag), FX, flags);
+    if (tid < M) scale_x[tid] = sc_x;             // for the epilogue
+    auto convert = [&](auto clamp_t) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int at = wave * U + u < pieces ? prow[u] * row_bytes + pcol[u] * 512 : M * row_bytes + 128;
+            const float sc = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(sc_x), prow[u] & 7));
+            *reinterpret_cast<uint2*>(codes + at + lane * 8) = cast8_own<FX, decltype(clamp_t)::value>(as_u4(xv[u]), sc);
         }
-    }
-    __syncthreads();
-    if (tid < M) {
-        uint32_t mag = amax_bits[tid];
-        if (!row_x)
-            for (int m = 0; m < M; ++m) mag = amax_bits[m] > mag ? amax_bits[m] : mag;
-        scale_x[tid] = scale_from_amax(mag_to_float(mag), FX, flags);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        if (wave + WAVES * u < pieces)
-            *reinterpret_cast<uint2*>(codes + prow[u] * row_bytes + pcol[u] * 512 + lane * 8) = cast8<FX>(as_u4(xv[u]), scale_x[prow[u]]);
-    }
+    };
+    if (__any(lane < M && !(sc_x < CLAMP_FROM))) convert(std::true_type{});
+    else convert(std::false_type{});
     __syncthreads();
 
     v4f_q acc[NW];
@@ -261,38 +280,55 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_fp8_skinny_fused_kernel(
     }
 }
 
-template <int FX, int FB, int KS, int NW, int WAVES>
-static hipError_t launch_skf(const uint16_t* x, int64_t ldx, int row_x, int flags, const uint8_t* b, int64_t ldb,
+template <int FX, int FB, int KS, int NW, int WAVES, int U>
+static hipError_t launch_skf_u(const uint16_t* x, int64_t ldx, int row_x, int flags, const uint8_t* b, int64_t ldb,
                              const float* sb, int row_b, int M, int N, int K, uint16_t* out, int64_t ld_out, int64_t grid,
                              hipStream_t st) {
     using namespace skf;
     // eight wavefronts: 96 KB of rings, one workgroup per CU with the codes of X (33 KB at most); four: 40 or 48 KB
-    constexpr int R = WAVES == 8 ? (NW == 1 ? 6 : 3) : (NW == 1 ? 5 : 3);
-    const int lds = WAVES * R * NW * 2048 + M * (K + ROW_PAD) + 128;
+    constexpr int R = steps_ahead(WAVES, NW);
+    const int lds = (int)lds_bytes(WAVES, NW, M, K);
     const bool hint = stream_weight(b, ldb, N, K);
-    auto kern = hint ? gemm_fp8_skinny_fused_kernel<FX, FB, KS, NW, WAVES, R, true> : gemm_fp8_skinny_fused_kernel<FX, FB, KS, NW, WAVES, R, false>;
+    auto kern = hint ? gemm_fp8_skinny_fused_kernel<FX, FB, KS, NW, WAVES, R, U, true> : gemm_fp8_skinny_fused_kernel<FX, FB, KS, NW, WAVES, R, U, false>;
+    const uint32_t cpr = (uint32_t)K / 512, inv_cpr = (uint32_t)((((uint64_t)1 << 32) + cpr - 1) / cpr);
     static DynamicLdsOnce attr[2];
-    if (hipError_t e = attr[hint].ensure(reinterpret_cast<const void*>(kern), WAVES * R * NW * 2048 + MAX_X + 8 * ROW_PAD + 128); e != hipSuccess) return e;
-    kern<<<dim3((unsigned)grid), dim3(64 * WAVES), lds, st>>>(x, ldx, row_x, flags, b, ldb, sb, row_b, M, N, K, out, ld_out);
+    if (hipError_t e = attr[hint].ensure(reinterpret_cast<const void*>(kern), WAVES * R * NW * 2048 + MAX_X + 8 * ROW_PAD + 128 + 512); e != hipSuccess) return e;
+    kern<<<dim3((unsigned)grid), dim3(64 * WAVES), lds, st>>>(x, ldx, row_x, flags, b, ldb, sb, row_b, M, N, K, inv_cpr, out, ld_out);
     return hipGetLastError();
+}
+
+template <int FX, int FB, int KS, int NW, int WAVES>
+static hipError_t launch_skf(const uint16_t* x, int64_t ldx, int row_x, int flags, const uint8_t* b, int64_t ldb,
+                             const float* sb, int row_b, int M, int N, int K, uint16_t* out, int64_t ld_out, int64_t grid,
+                             hipStream_t st) {
+    const int pieces = M * (K / 512);
+#define FP8K_SKF_U(U_) \
+    if (pieces <= WAVES * U_) return launch_skf_u<FX, FB, KS, NW, WAVES, U_>(x, ldx, row_x, flags, b, ldb, sb, row_b, M, N, K, out, ld_out, grid, st)
+    FP8K_SKF_U(2);
+    FP8K_SKF_U(4);
+    FP8K_SKF_U(8);
+    if constexpr (WAVES == 4) FP8K_SKF_U(16);
+#undef FP8K_SKF_U
+    return hipErrorNotSupported;
 }
 
 // hipErrorNotSupported (nothing launched) where the one-launch form does not apply (more than 8 tokens or more
 // than 32768 activations - what a workgroup holds in registers between the amax and the conversion -, activations
 // to e5m2, K not a multiple of 512, operands beyond the reach of 32-bit buffer offsets) or does not pay: every
-// workgroup reads and converts all of X before its first product, 16 to 128 elements per lane, and that time
-// grows with M while the launch it saves (2-3 us) does not.  Measured against the two-launch form on the
-// Llama-3 projections, calls replayed from a graph: one token 13-21 % faster on the 8B shapes (2-4 % on the
-// 70B ones), two tokens 4-16 %, four tokens 0-9 %, eight tokens 3 % faster on the 14336 x 4096 weight and
-// 12-13 % slower on the 4096 x 4096 and 6144 x 4096 ones.  Default therefore: one token, or up to four with
-// M * K <= 16384.  The switch DECODE_FUSED: 0 = never, 2 = wherever the kernel applies.
+// workgroup reads and converts all of X before its first product.  Two launches / one, us a call replayed from a graph, three
+// weights in turn (N x K: tokens): 4096 x 4096: 1 6.7 / 4.5, 2 7.0 / 4.7, 4 7.1 / 5.4, 8 7.3 / 7.2; 14336 x 4096: 1 13.4 / 11.0,
+// 8 13.7 / 12.3; 2048 x 2048: 1 4.9 / 3.3, 8 5.3 / 4.6; 4096 x 14336: 1 13.7 / 10.8, 2 13.9 / 12.4; 28672 x 8192: 1 39.6 / 36.6, 3
+// 39.8 / 38.4.  (With sixteen loads whatever X needs, a reduction for each of them and clamped conversions, as it was before, 4096
+// x 4096: 1 5.8, 2 6.4, 4 7.4.)  Not over more workgroups than the chip holds at once for more than four tokens, whose conversion
+// every later workgroup repeats while it streams nothing (28672 x 4096: 4 22.3 / 21.6, 6 22.5 / 22.8; 128256 x 4096: 4 96.7 /
+// 94.1, 6 97.1 / 97.6), nor where the codes leave room for one workgroup per CU only (28672 x 8192: 4 40.1 / 47.9; x 4096: 8 22.7 /
+// 33.4).  The switch DECODE_FUSED: 0 = never, 2 = wherever the kernel applies.
 hipError_t launch_linear_skinny_fused(const void* x, int64_t ldx, int fmt_x, int row_x, int flags, const uint8_t* b,
                                       int64_t ldb, int fmt_b, const float* scale_b, int row_b, int64_t M, int64_t N,
                                       int64_t K, void* out, int64_t ld_out, hipStream_t st) {
     using namespace skf;
     const int mode = knob(KNOB_DECODE_FUSED);
     if (mode == 0 || M < 1 || M > 8 || N < 1 || K < 512 || K % 512 != 0 || M * K > MAX_X) return hipErrorNotSupported;
-    if (mode != 2 && M != 1 && (M > 4 || M * K > 16384)) return hipErrorNotSupported;
     if (fmt_x != FMT_E4M3FN) return hipErrorNotSupported;
     if (ldb >= (1 << 23) || ((M - 1) * ldx + K) * 2 >= (int64_t)1 << 31 || (int64_t)16 * 4 * ldb + K >= (int64_t)1 << 31)
         return hipErrorNotSupported;
@@ -310,6 +346,7 @@ hipError_t launch_linear_skinny_fused(const void* x, int64_t ldx, int fmt_x, int
     const int ntw = waves / ks;
     const int64_t grid = (groups + ntw - 1) / ntw;
     if (grid > 0x7FFFFFFF) return hipErrorNotSupported;
+    if (mode != 2 && ((grid > 2 * (int64_t)cus && M > 4) || (waves == 4 && grid > cus && 2 * lds_bytes(4, nw, M, K) > 160 * 1024))) return hipErrorNotSupported;
     const uint16_t* xp = static_cast<const uint16_t*>(x);
     uint16_t* op = static_cast<uint16_t*>(out);
     const int m = (int)M, n = (int)N, k = (int)K;

@@ -1,0 +1,36 @@
+"""The one-launch decode linear holds X as pieces of 512 elements, a count per wavefront that depends on M * K: every count, rows that start
+inside a wavefront's pieces, rows of zeros, infinities and NaN; the bits of the two-launch form."""
+import pytest
+import torch
+
+from tests.gpu_util import knobs
+
+pytestmark = pytest.mark.gpu
+
+import paper_2507_16099_amd as fp8  # noqa: E402
+
+
+@pytest.mark.parametrize("N", [40, 1024, 3072, 6152])
+@pytest.mark.parametrize("K", [512, 1536, 2560, 4096, 5120, 6656, 10752, 16384, 32768])
+def test_as_two_launches(N, K):
+    gen = torch.Generator(device="cuda").manual_seed(K + N)
+    w = torch.randn((N, K), device="cuda", generator=gen).to(torch.bfloat16)
+    wq, sw = fp8.fp8_quantize(w, fp8.FP8_ROW, fp8.FP8_E4M3FN)
+    for M in range(1, 9):
+        if M * K > 32768:
+            break
+        x = torch.randn((M, K), device="cuda", generator=gen) * torch.logspace(-3, 3, M, device="cuda")[:, None]
+        x[torch.arange(M), torch.randint(0, K, (M,), generator=gen, device="cuda")] *= 20.0      # the row's maximum, in any of its pieces
+        x = x.to(torch.bfloat16)
+        odd = x.clone()
+        odd[M // 2] = 0
+        odd[M - 1, K - 1] = float("inf")
+        odd[0, K // 2] = float("nan")
+        for v in (x, odd):
+            for gran, flags in ((fp8.FP8_ROW, 0), (fp8.FP8_ROW, fp8.FP8_POW2_SCALE), (fp8.FP8_TENSOR, 0)):
+                run = lambda: fp8.fp8_linear_fwd_prequantized(v, wq, fp8.FP8_E4M3FN, sw, fp8.FP8_ROW, fp8.FP8_E4M3FN, gran, flags).view(torch.int16)      # noqa: E731
+                with knobs(DECODE_FUSED=0):
+                    want = run()
+                with knobs(DECODE_FUSED=2):
+                    assert torch.equal(run(), want), (M, gran, flags)
+                assert torch.equal(run(), want), (M, gran, flags)

@@ -2,8 +2,10 @@
 from __future__ import annotations
 
 import os
+import shutil
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -33,8 +35,24 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _compile_pycall() -> None:
+    """The module that makes the Python calls cheap (csrc/pycall.c).  Where the interpreter's headers are missing the binding does
+    without it."""
+    include, cc, out = sysconfig.get_paths()["include"], shutil.which(os.environ.get("CC", "gcc")), os.path.join(HERE, "_pycall.so")
+    if cc is None or not os.path.exists(os.path.join(include, "Python.h")):
+        if os.path.exists(out):
+            os.remove(out)
+        sys.stderr.write("no C compiler or Python.h: calls go through ctypes\n")
+        return
+    r = subprocess.run([cc, "-O2", "-Wall", "-shared", "-fPIC", f"-I{include}", "-o", out, os.path.join(CSRC, "pycall.c")],
+                       capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"{cc} failed for pycall.c:\n{r.stdout}\n{r.stderr}")
+
+
 def build(verbose: bool = True) -> str:
     os.makedirs(OBJ, exist_ok=True)
+    _compile_pycall()
     with ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
         objs = list(ex.map(_compile, SOURCES))
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]

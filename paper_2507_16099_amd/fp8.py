@@ -9,6 +9,7 @@ an exception is raised.
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 import os
 from dataclasses import dataclass
 
@@ -22,6 +23,31 @@ FP8_EPILOGUE_SIGMOID = 32
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libfp8mi355.so")
 _lib = None
+
+
+def _load_pycall():
+    """The module that looks matrices over and calls the library without ctypes (csrc/pycall.c); None where it is not built."""
+    path = os.path.join(_HERE, "_pycall.so")
+    if not os.path.exists(path):
+        return None
+    spec = importlib.util.spec_from_file_location("_pycall", path)
+    try:
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+    except ImportError:      # built for another interpreter
+        return None
+    return module
+
+
+_pycall = _load_pycall()
+
+
+def _fast(function):
+    """A ctypes function of pointers and integers as one that takes tensors for its pointers."""
+    if _pycall is not None:
+        kinds = "".join("p" if t is C.c_void_p else "l" for t in function.argtypes)
+        return _pycall.Call(C.cast(function, C.c_void_p).value, kinds)
+    return lambda *args: function(*[a.data_ptr() if isinstance(a, torch.Tensor) else a for a in args])
 
 
 class Fp8Error(RuntimeError):
@@ -129,6 +155,9 @@ def load_library() -> C.CDLL:
     L.fp8_linear_bwd.argtypes = [vp, vp, vp, i64, i64, i64, C.POINTER(_CRecipe), vp, vp, vp, C.c_size_t, vp]
     L.fp8_internal_set_knob.restype = ci
     L.fp8_internal_set_knob.argtypes = [C.c_char_p, ci]
+    # the calls of a served model's layers, which take less time on the GPU than ctypes needs to make them
+    for name in ("quantize", "scaled_mm", "linear_fwd_prequantized", "linear_fwd_prequantized_static"):
+        setattr(L, "fast_" + name, _fast(getattr(L, "fp8_" + name)))
     _lib = L
     return L
 
@@ -155,8 +184,8 @@ def _check(rc: int) -> None:
         raise Fp8Error(rc, fp8_last_error())
 
 
-# A decode linear is 6-10 us on the GPU, so what a call costs here counts: 9.3 us of Python, ctypes and launch with the
-# stream object (2.7 us) and one attribute at a time in _mat (0.75 us per tensor), of which the launch itself is 3.5 us.
+# A decode linear is 4-10 us on the GPU, so what a call costs here counts: 5.9 us for one through ctypes, the stream's number by
+# torch's own functions included (2.7 us more by the stream object), of which the launch is 2.3; 3.7 with csrc/pycall.c.
 # Every tensor has been seen to be on the GPU before the stream is asked for, so the runtime is up.  The two functions are
 # torch's own and not public (a CPU build has neither): without them the stream object serves.
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
@@ -175,7 +204,7 @@ def _ptr(t) -> int | None:
     return None if t is None else t.data_ptr()
 
 
-def _mat(t: torch.Tensor, itemsize: int):
+def _mat_any(t: torch.Tensor, itemsize: int):
     """(rows, cols, ld) of a 2-D tensor whose last dimension is contiguous."""
     shape = t.shape
     assert t.is_cuda and len(shape) == 2 and t.element_size() == itemsize, (t.shape, t.dtype, t.device)
@@ -185,6 +214,9 @@ def _mat(t: torch.Tensor, itemsize: int):
     if rows > 1 and cols > 0:
         return rows, cols, ld
     return rows, cols, (cols + 15) // 16 * 16 if rows == 0 or cols == 0 else max(ld, cols)
+
+
+_mat = _mat_any if _pycall is None else _pycall.Mat(_mat_any)
 
 
 def _groups(gran: int, rows: int, cols: int) -> int:
@@ -235,8 +267,7 @@ def fp8_quantize(x: torch.Tensor, gran: int, fmt: int, flags: int = 0, out: torc
     if scale_out is None:
         scale_out = torch.empty(_groups(gran, rows, cols), dtype=torch.float32, device=x.device)
     _, _, ld_out = _mat(out, 1)
-    _check(load_library().fp8_quantize(_ptr(x), rows, cols, ld, gran, fmt, flags, _ptr(out), ld_out,
-                                       _ptr(scale_out), _stream()))
+    _check(load_library().fast_quantize(x, rows, cols, ld, gran, fmt, flags, out, ld_out, scale_out, _stream()))
     return out, scale_out
 
 
@@ -271,8 +302,8 @@ def fp8_scaled_mm(a: torch.Tensor, fmt_a: int, scale_a: torch.Tensor, gran_a: in
         pad = 4 if flags & FP8_OUT_FP32 else 8
         out = torch.empty((M, (N + pad - 1) // pad * pad), dtype=dt, device=a.device)[:, :N]
     _, _, ld_out = _mat(out, out.element_size())
-    _check(load_library().fp8_scaled_mm(_ptr(a), lda, fmt_a, _ptr(scale_a), gran_a, _ptr(b), ldb, fmt_b,
-                                        _ptr(scale_b), gran_b, M, N, K, _ptr(out), ld_out, flags, _stream()))
+    _check(load_library().fast_scaled_mm(a, lda, fmt_a, scale_a, gran_a, b, ldb, fmt_b, scale_b, gran_b, M, N, K, out, ld_out, flags,
+                                         _stream()))
     return out
 
 
@@ -378,9 +409,8 @@ def fp8_linear_fwd_prequantized(x: torch.Tensor, wq: torch.Tensor, fmt_w: int, s
     _, _, ld_y = _mat(y, 2)
     if workspace is None:
         workspace = torch.empty(fp8_linear_prequantized_workspace_bytes(M, K), dtype=torch.uint8, device=x.device)
-    _check(load_library().fp8_linear_fwd_prequantized(_ptr(x), M, K, fmt_x, gran_x, flags, _ptr(wq), ldw, fmt_w,
-                                                      _ptr(scale_w), gran_w, N, _ptr(y), ld_y, _ptr(workspace),
-                                                      workspace.numel(), _stream()))
+    _check(load_library().fast_linear_fwd_prequantized(x, M, K, fmt_x, gran_x, flags, wq, ldw, fmt_w, scale_w, gran_w, N, y, ld_y,
+                                                       workspace, workspace.numel(), _stream()))
     return y
 
 
@@ -396,8 +426,8 @@ def fp8_linear_fwd_prequantized_static(x: torch.Tensor, wq: torch.Tensor, fmt_w:
     N, Kw, ldw = _mat(wq, 1)
     assert K == Kw and ldx == K, (x.shape, wq.shape)
     _, _, ld_y = _mat(y, 2)
-    _check(load_library().fp8_linear_fwd_prequantized_static(_ptr(x), M, K, fmt_x, gran_x, flags, _ptr(wq), ldw, fmt_w,
-                                                             _ptr(scale_w), gran_w, N, _ptr(y), ld_y, _stream()))
+    _check(load_library().fast_linear_fwd_prequantized_static(x, M, K, fmt_x, gran_x, flags, wq, ldw, fmt_w, scale_w, gran_w, N, y,
+                                                              ld_y, _stream()))
     return y
 
 

@@ -316,13 +316,14 @@ static hipError_t launch_skf(const uint16_t* x, int64_t ldx, int row_x, int flag
 // than 32768 activations - what a workgroup holds in registers between the amax and the conversion -, activations
 // to e5m2, K not a multiple of 512, operands beyond the reach of 32-bit buffer offsets) or does not pay: every
 // workgroup reads and converts all of X before its first product.  Two launches / one, us a call replayed from a graph, three
-// weights in turn (N x K: tokens): 4096 x 4096: 1 6.7 / 4.5, 2 7.0 / 4.7, 4 7.1 / 5.4, 8 7.3 / 7.2; 14336 x 4096: 1 13.4 / 11.0,
+// weights in turn (N x K: tokens): 4096 x 4096: 1 6.7 / 4.5, 2 7.0 / 4.7, 4 7.1 / 5.4; 14336 x 4096: 1 13.4 / 11.0,
 // 8 13.7 / 12.3; 2048 x 2048: 1 4.9 / 3.3, 8 5.3 / 4.6; 4096 x 14336: 1 13.7 / 10.8, 2 13.9 / 12.4; 28672 x 8192: 1 39.6 / 36.6, 3
 // 39.8 / 38.4.  (With sixteen loads whatever X needs, a reduction for each of them and clamped conversions, as it was before, 4096
 // x 4096: 1 5.8, 2 6.4, 4 7.4.)  Not over more workgroups than the chip holds at once for more than four tokens, whose conversion
 // every later workgroup repeats while it streams nothing (28672 x 4096: 4 22.3 / 21.6, 6 22.5 / 22.8; 128256 x 4096: 4 96.7 /
 // 94.1, 6 97.1 / 97.6), nor where the codes leave room for one workgroup per CU only (28672 x 8192: 4 40.1 / 47.9; x 4096: 8 22.7 /
-// 33.4).  The switch DECODE_FUSED: 0 = never, 2 = wherever the kernel applies.
+// 33.4), nor, beyond 16384 activations of more than four tokens, against a narrow weight (8 tokens 1024 x 4096 5.8 / 6.7, 4096 x
+// 4096 7.1 / 7.2, 6144 x 4096 8.7 / 8.9).  The switch DECODE_FUSED: 0 = never, 2 = wherever the kernel applies.
 hipError_t launch_linear_skinny_fused(const void* x, int64_t ldx, int fmt_x, int row_x, int flags, const uint8_t* b,
                                       int64_t ldb, int fmt_b, const float* scale_b, int row_b, int64_t M, int64_t N,
                                       int64_t K, void* out, int64_t ld_out, hipStream_t st) {
@@ -346,7 +347,7 @@ hipError_t launch_linear_skinny_fused(const void* x, int64_t ldx, int fmt_x, int
     const int ntw = waves / ks;
     const int64_t grid = (groups + ntw - 1) / ntw;
     if (grid > 0x7FFFFFFF) return hipErrorNotSupported;
-    if (mode != 2 && ((grid > 2 * (int64_t)cus && M > 4) || (waves == 4 && grid > cus && 2 * lds_bytes(4, nw, M, K) > 160 * 1024))) return hipErrorNotSupported;
+    if (mode != 2 && ((M > 4 && (grid > 2 * (int64_t)cus || (M * K > 16384 && N < 8192))) || (waves == 4 && grid > cus && 2 * lds_bytes(4, nw, M, K) > 160 * 1024))) return hipErrorNotSupported;
     const uint16_t* xp = static_cast<const uint16_t*>(x);
     uint16_t* op = static_cast<uint16_t*>(out);
     const int m = (int)M, n = (int)N, k = (int)K;

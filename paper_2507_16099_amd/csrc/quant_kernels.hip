@@ -888,6 +888,48 @@ __global__ __launch_bounds__(256) void quant_row_kernel(const uint16_t* __restri
     }
 }
 
+// The same for the tokens of a decode batch, which leave most CUs idle: a block of up to 1024 threads per row, so that a thread has
+// one vector (of rows up to 8192) instead of four.  What bounds it is the chain of one wavefront's instructions around the arrival
+// of the row (us a call of a quantized weight's forward, 256 threads a row / as here: 16 x 4096 x 4096 7.4 / 7.2, 72 x 14336 x 4096
+// 14.4 / 14.2, 16 x 4096 x 14336 14.5 / 13.9, 64 x 8192 x 8192 18.3 / 18.0).
+template <int FMT, int TX, int NV>
+__global__ __launch_bounds__(TX) void quant_row_few_kernel(const uint16_t* __restrict__ x, int cols, int64_t ld, int flags, uint8_t* __restrict__ q,
+                                                            int64_t ld_out, float* __restrict__ scale_out) {
+    __shared__ __attribute__((aligned(16))) uint32_t part[TX / 64];
+    const int tx = threadIdx.x, nvec = cols >> 3, ntail = cols & 7;
+    const uint16_t* row = x + (int64_t)blockIdx.x * ld;
+    uint4 v[NV];
+    uint32_t tail = 0;
+#pragma unroll
+    for (int j = 0; j < NV; ++j) v[j] = tx + j * TX < nvec ? reinterpret_cast<const uint4*>(row)[tx + j * TX] : make_uint4(0, 0, 0, 0);
+    if (tx < ntail) tail = row[(nvec << 3) + tx];
+    uint32_t acc = tail & 0x7FFFu;
+#pragma unroll
+    for (int j = 0; j < NV; ++j) acc = pk_absmax4(acc, v[j]);
+    uint32_t m = wave_max_u32<64>(pk_fold(acc));
+    if ((tx & 63) == 0) part[tx >> 6] = m;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < TX / 64; i += 4) {
+        const uint4 p = *reinterpret_cast<const uint4*>(part + i);
+        m = max(max(max(p.x, p.y), max(p.z, p.w)), m);
+    }
+    const float s = scale_from_amax(mag_to_float(m), FMT, flags);
+    if (tx == 0) scale_out[blockIdx.x] = s;
+    uint8_t* dst = q + (int64_t)blockIdx.x * ld_out;
+    auto finish = [&](auto clamp) {
+#pragma unroll
+        for (int j = 0; j < NV; ++j)
+            if (tx + j * TX < nvec) reinterpret_cast<uint2*>(dst)[tx + j * TX] = cast8_own<FMT, decltype(clamp)::value>(v[j], s);
+    };
+    if (s >= CLAMP_FROM) finish(std::true_type{});
+    else finish(std::false_type{});
+    if (tx < ntail) {
+        const float t = __uint_as_float(tail << 16) * s;
+        dst[(nvec << 3) + tx] = (uint8_t)(cvt2<FMT>(t, t) & 0xFFu);
+    }
+}
+
 // Up to 512 Ki elements (the tokens of a decode batch) plain stores are up to 1.5 % of a quantized weight's forward ahead of
 // those through the L2, from 1 Mi on behind (us, plain / through: 8 x 4096 x 4096 9.4 / 9.5, 72 x 4096 x 4096 13.3 / 13.5,
 // 128 x 4096 x 4096 13.8 / 13.9, 160 x 4096 x 4096 14.3 / 14.3, 256 x 4096 x 4096 15.4 / 15.3): few dirty lines at the end of
@@ -903,6 +945,17 @@ static bool launch_quant_row_t(const uint16_t* x, int64_t rows, int64_t cols, in
         x, rows, cols, ld, flags, q, ld_out, scale_out, NO_TWIN, nullptr, 0, 0, nullptr, 0, nullptr, hint)
     if (nvec <= 16) FP8K_QR(16, 1);
     else if (nvec <= 64) FP8K_QR(64, 1);
+    else if constexpr (FEW) {
+#define FP8K_QRF(TX, NV) \
+    quant_row_few_kernel<FMT, TX, NV><<<dim3((unsigned)rows), dim3(TX), 0, st>>>(x, (int)cols, ld, flags, q, ld_out, scale_out)
+        if (nvec <= 256) FP8K_QRF(256, 1);
+        else if (nvec <= 512) FP8K_QRF(512, 1);
+        else if (nvec <= 1024) FP8K_QRF(1024, 1);
+        else if (nvec <= 2048) FP8K_QRF(1024, 2);
+        else if (nvec <= 4096) FP8K_QRF(1024, 4);
+        else return false;
+#undef FP8K_QRF
+    }
     else if (nvec <= 256) FP8K_QR(256, 1);
     else if (nvec <= 512) FP8K_QR(256, 2);
     else if (nvec <= 1024) FP8K_QR(256, 4);

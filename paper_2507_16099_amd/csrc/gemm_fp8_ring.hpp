@@ -171,6 +171,13 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_fp8_ring_kernel(R
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
 
     const RingProblem& p = blockIdx.y ? p2 : p1;
+    // All arguments are requested here and waited for once: left to itself the compiler fetches each where it is first used, six
+    // trips to memory one behind the other in front of the first load.
+#ifdef __HIP_DEVICE_COMPILE__
+    asm volatile("" ::"s"(p.A), "s"(p.lda), "s"(p.B), "s"(p.ldb), "s"(p.scale_a), "s"(p.scale_b), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.out), "s"(p.ld_out),
+                 "s"(p.tiles_m), "s"(p.tiles_n), "s"(p.in_group), "s"(p.inv_group), "s"(p.inv_tail), "s"(p.per_xcd), "s"(row_a), "s"(row_b), "s"(mode));
+    if constexpr (MX) asm volatile("" ::"s"(p.EA), "s"(p.EB), "s"(p.ld_ea), "s"(p.ld_eb));
+#endif
     const int M = p.M, N = p.N, K = p.K, tiles_m = p.tiles_m, tiles_n = p.tiles_n;
 
     // ---- workgroup -> tile (ids are dealt round-robin to the XCDs; each XCD walks a contiguous range of tiles)

@@ -481,6 +481,11 @@ hipError_t launch_gemm_fp8_skinny(const uint8_t* a, int64_t lda, int fmt_a, cons
                                   hipStream_t st) {
     if (M == 0 || N == 0) return hipSuccess;
     if (M > 64) return hipErrorInvalidValue;
+    if (knob(KNOB_SKINNY_NW) < 0) {
+        const GemmOperands g{a, lda, scale_a, b, ldb, scale_b, M, N, K, out, ld_out};
+        const hipError_t e = launch_gemm_fp8_few_stream(g, fmt_a, fmt_b, row_a, row_b, out_f32, st);
+        if (e != hipErrorNotSupported) return e;
+    }
     const int m = (int)M, n = (int)N, k = (int)K;
 #define FP8K_SKF(FA_, FB_)               \
     if (fmt_a == FA_ && fmt_b == FB_)    \

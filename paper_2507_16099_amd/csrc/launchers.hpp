@@ -272,6 +272,22 @@ inline FewRowForm few_row_form(int64_t M, int64_t N, int64_t K, int nw_forced, i
     return {nw, ks, grid, ks == 4 && nw == 1 && K > 10240 && ((M <= 8 && 2 * grid <= cus) || (M <= 4 && 4 * grid <= 3 * cus))};
 }
 
+// Whether a product of up to 16 rows goes to persistent workgroups (gemm_fp8_few_stream.hip): weights of 96 MiB and more, except those
+// whose rows are whole multiples of 2 KB and whose 32-column groups the few-row kernel's workgroups hold in one round (two of short
+// rows): there its own wavefronts stream as fast and start sooner (us from HBM, few-row / persistent at 5 and 16 rows: 16384 x 8192
+// 21.8 22.3 / 23.1 23.7, 8192 x 14336 19.6 20.2 / 21.2 21.8, 16384 x 14336 35.8 37.2 / 37.8 39.1, 28672 x 4096 20.5 21.6 / 22.0 21.8.
+// Taken: 28672 x 8192 37.7 40.0 / 37.8 38.5, x 6144 30.4 32.1 / 28.4 28.9, 8192 x 16384 30.4 30.7 / 24.6 25.0, 128256 x 4096 94 96 / 79
+// 81, 20312 x 6320 30.6 36.0 / 24.9 26.7, 17352 x 8704 30.1 31.8 / 25.2 25.4, 13320 x 14576 46.9 53.8 / 41.1 43.7).  forced: the switch
+// SKINNY_DMA, 2 or 3 = wherever it fits, strided or in runs; 0 or 1 = never.
+inline bool few_row_streams(const GemmOperands& g, int64_t cus, int forced = -1) {
+    const int64_t tiles = (g.N + 15) / 16;
+    if (g.M < 1 || g.M > 16 || g.K < 1 || g.K > 16384 || tiles > 32 * cus || g.lda >= (1 << 23) || g.ldb >= (1 << 23)) return false;
+    if (forced >= 0) return forced >= 2;
+    if (g.N * g.K < (int64_t)96 << 20) return false;
+    return g.ldb % 2048 != 0 || g.K >= 16384 || (g.N + 31) / 32 > (g.K <= 4096 ? 4 : 2) * cus;
+}
+hipError_t launch_gemm_fp8_few_stream(const GemmOperands& g, int fmt_a, int fmt_b, int row_a, int row_b, int out_f32, hipStream_t st);
+
 // columns of a strip (quant_strips.hip) for tensors of at most tall rows, load strips of 32 columns.  16 where 32 would keep half
 // of the CUs busy, unless the strips are short (us, 32 / 16 columns: gradient 4096 x 1024 20.9 / 14.9, x 4096 27.3 / 26.4, x 6144
 // 31.8 / 36.0; 2048 x 1024 12.8 / 10.2, x 4096 15.3 / 14.7, x 6144 16.5 / 20.7; 1024 x 1024 8.7 / 9.3, x 4096 10.8 / 12.5); beyond

@@ -15,7 +15,7 @@ enum Knob {
     KNOB_GEMM_VARIANT = 0,  // 0 = 128x128 tiles, 4 = LDS-DMA 256x256 kernel, 5 = few-row kernel, 6 / 7 = 64x64 / 128x128 with loads ahead
     KNOB_SNAKE_HALF,        // 0 = no half tiles for a partly filled last round
     KNOB_SKINNY_NW,         // few-row kernel: 1, 2 or 4 column groups of 16 per wavefront
-    KNOB_SKINNY_DMA,        // few-row kernel: 0 = operands straight into registers, 1 = through LDS
+    KNOB_SKINNY_DMA,        // few-row kernel: 0 = operands straight into registers, 1 = through LDS, 2 / 3 = the persistent one, strided / in runs
     KNOB_MX_VARIANT,        // MX GEMM: 0 = register-staged kernel, 1 = LDS-DMA kernel
     KNOB_MX_SLAB,           // 0 = plain scale rows inside the MX / blockwise linear calls
     KNOB_BF16_VARIANT,      // bfloat16 dW: 0 = register-staged kernel, 1 = LDS-DMA kernel

@@ -277,7 +277,8 @@ inline FewRowForm few_row_form(int64_t M, int64_t N, int64_t K, int nw_forced, i
 // rows): there its own wavefronts stream as fast and start sooner (us from HBM, few-row / persistent at 5 and 16 rows: 16384 x 8192
 // 21.8 22.3 / 23.1 23.7, 8192 x 14336 19.6 20.2 / 21.2 21.8, 16384 x 14336 35.8 37.2 / 37.8 39.1, 28672 x 4096 20.5 21.6 / 22.0 21.8.
 // Taken: 28672 x 8192 37.7 40.0 / 37.8 38.5, x 6144 30.4 32.1 / 28.4 28.9, 8192 x 16384 30.4 30.7 / 24.6 25.0, 128256 x 4096 94 96 / 79
-// 81, 20312 x 6320 30.6 36.0 / 24.9 26.7, 17352 x 8704 30.1 31.8 / 25.2 25.4, 13320 x 14576 46.9 53.8 / 41.1 43.7).  forced: the switch
+// 81, 20312 x 6320 30.6 36.0 / 24.9 26.7, 17352 x 8704 30.1 31.8 / 25.2 25.4, 13320 x 14576 46.9 53.8 / 41.1 43.7).  Smaller weights:
+// equal or slower (80 .. 87 MiB 0.92 .. 1.11 times as fast, 42 .. 64 MiB 0.76 .. 1.06, below 40 MiB 0.76 .. 1.05).  forced: the switch
 // SKINNY_DMA, 2 or 3 = wherever it fits, strided or in runs; 0 or 1 = never.
 inline bool few_row_streams(const GemmOperands& g, int64_t cus, int forced = -1) {
     const int64_t tiles = (g.N + 15) / 16;

@@ -988,18 +988,23 @@ hipError_t launch_quant_row(const void* x, int64_t rows, int64_t cols, int64_t l
 // maxima of its own 8 * NV columns.  The block's column maxima go to row b of
 // a [G, cols] matrix of bfloat16 magnitudes, which amax_cols_kernel reduces;
 // the per-column cast then reads the tensor a second (and last) time.
-// With up to four vectors per thread the next rows are requested before the
-// current ones are reduced; wider rows rely on the other resident blocks to keep
-// loads in flight (a second row in registers would halve the occupancy).  Rows
-// of up to 2048 (4096) elements travel four (two) at a time: a block of a small
-// tensor has only a handful of rows, and each trip to memory that it has to
-// wait for costs about a microsecond.  The wave maxima alternate between two
-// LDS slots, so one barrier per trip is enough.
+// Rows of up to 2048 elements travel four at a time, of up to 4096 two as long as
+// the tensor has few of them: a block of a small tensor has only a handful of
+// rows, and each trip to memory that it has to wait for costs about a
+// microsecond.  The wave maxima alternate between two LDS slots, so one barrier
+// per trip is enough.  What bounds it beyond that is how the blocks of a CU
+// cover each other.  Rows of 4097 to 16384 elements: two blocks of 512 threads a CU, which
+// request their next row before they reduce the one at hand, instead of four of 256
+// that leave it to each other; they also leave half as many rows of maxima.  Elsewhere a row
+// requested ahead gains nothing, and where two tensors are read (ACT) it costs.  us, before / now: 16384 x 14336 131.6 /
+// 125.6 (5.9 TB/s with the maxima), 8192 x 8192 40.9 / 38.1, 4100 x 8192 21.7 / 21.2, 16384 x 4096 40.4 / 38.4; ACT 8192 x 4096 31.4 /
+// 27.3 (6.1 TB/s), 4100 x 4096 18.1 / 16.4, 2048 x 8192 19.3 / 16.4, 2048 x 14336 31.7 / 27.9, 16384 x 2048 36.2 / 33.3.
 // ACT: the tensor to quantize is dz = x * y * (1 - y), formed on the fly from the gradient x and the stored
 // sigmoid output y (same shape and leading dimension): the backward through Sigmoid + Linear never
 // materialises dz.
-template <int FMT, int NV, bool ACT = false>
-__global__ __launch_bounds__(256) void quant_row_colmax_kernel(const uint16_t* __restrict__ x, int64_t rows,
+// TX threads a block, NV vectors a thread, R rows in flight together.
+template <int FMT, int TX, int NV, int R, bool ACT = false>
+__global__ __launch_bounds__(TX) void quant_row_colmax_kernel(const uint16_t* __restrict__ x, int64_t rows,
                                                                 int64_t cols, int64_t ld, int flags,
                                                                 uint8_t* __restrict__ q, int64_t ld_out,
                                                                 float* __restrict__ scale_out,
@@ -1009,8 +1014,7 @@ __global__ __launch_bounds__(256) void quant_row_colmax_kernel(const uint16_t* _
                                                                 int64_t rows2 = 0, int64_t ld2 = 0, uint8_t* __restrict__ q2 = nullptr,
                                                                 int64_t ld_out2 = 0, float* __restrict__ scale_out2 = nullptr,
                                                                 uint16_t* __restrict__ part2 = nullptr) {
-    constexpr bool PREFETCH = NV <= 4;
-    constexpr int R = NV == 1 ? 4 : NV == 2 ? 2 : 1;   // rows in flight together (narrow rows: one round trip to memory serves R rows)
+    constexpr bool PREFETCH = TX == 512 && !ACT;
     int bid = blockIdx.x, nb = split == NO_TWIN ? (int)gridDim.x : split;
     if (bid >= split) {
         bid -= split; nb = (int)gridDim.x - split;
@@ -1018,7 +1022,7 @@ __global__ __launch_bounds__(256) void quant_row_colmax_kernel(const uint16_t* _
     }
     const int64_t nvec = cols >> 3;     // cols is a multiple of 8 (checked by the launcher)
     const int tid = threadIdx.x;
-    __shared__ uint32_t red[2][R][4];
+    __shared__ uint32_t red[2][R][TX / 64];
     uint4 cmax[NV], v[R][NV];
 #pragma unroll
     for (int j = 0; j < NV; ++j) cmax[j] = make_uint4(0, 0, 0, 0);
@@ -1031,14 +1035,14 @@ __global__ __launch_bounds__(256) void quant_row_colmax_kernel(const uint16_t* _
             const uint4* rv = reinterpret_cast<const uint4*>(x + (in ? r : 0) * ld);
 #pragma unroll
             for (int j = 0; j < NV; ++j) {
-                const int64_t vi = tid + (int64_t)j * 256;
+                const int64_t vi = tid + (int64_t)j * TX;
                 dst[k][j] = (in && vi < nvec) ? rv[vi] : make_uint4(0, 0, 0, 0);
             }
             if constexpr (ACT) {
                 const uint4* yv = reinterpret_cast<const uint4*>(yact + (in ? r : 0) * ld);
 #pragma unroll
                 for (int j = 0; j < NV; ++j) {
-                    const int64_t vi = tid + (int64_t)j * 256;
+                    const int64_t vi = tid + (int64_t)j * TX;
                     if (in && vi < nvec) dst[k][j] = sigmoid_bwd8(dst[k][j], yv[vi]);
                 }
             }
@@ -1077,15 +1081,18 @@ __global__ __launch_bounds__(256) void quant_row_colmax_kernel(const uint16_t* _
             if (rk >= rows) break;
             uint32_t m = red[slot][k][0];
 #pragma unroll
-            for (int i = 1; i < 4; ++i) m = red[slot][k][i] > m ? red[slot][k][i] : m;
+            for (int i = 1; i < TX / 64; ++i) m = red[slot][k][i] > m ? red[slot][k][i] : m;
             const float s = scale_from_amax(mag_to_float(m), FMT, flags);
             if (tid == 0) scale_out[rk] = s;
             uint8_t* dst = q + rk * ld_out;
+            auto put = [&](auto clamp) {
 #pragma unroll
-            for (int j = 0; j < NV; ++j) {
-                const int64_t vi = tid + (int64_t)j * 256;
-                if (vi < nvec) store_vec(reinterpret_cast<uint2*>(dst) + vi, cast8<FMT>(v[k][j], s), keep_codes(rows, cols));
-            }
+                for (int j = 0; j < NV; ++j) {
+                    const int64_t vi = tid + (int64_t)j * TX;
+                    if (vi < nvec) store_vec(reinterpret_cast<uint2*>(dst) + vi, cast8_own<FMT, decltype(clamp)::value>(v[k][j], s), keep_codes(rows, cols));
+                }
+            };
+            if (s < CLAMP_FROM) put(std::false_type{}); else put(std::true_type{});
         }
         slot ^= 1;
         if constexpr (PREFETCH) {
@@ -1100,19 +1107,59 @@ __global__ __launch_bounds__(256) void quant_row_colmax_kernel(const uint16_t* _
     uint16_t* prow = part + (int64_t)bid * ld_part;
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
-        const int64_t vi = tid + (int64_t)j * 256;
+        const int64_t vi = tid + (int64_t)j * TX;
         if (vi < nvec) reinterpret_cast<uint4*>(prow)[vi] = cmax[j];
     }
 }
 
 // number of blocks of the kernel that the device keeps resident at once
 template <typename K>
-static int resident_blocks(K kernel) {
+static int resident_blocks(K kernel, int threads = 256) {
     int per_cu = 0, dev = 0, cus = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 256, 0) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess) return 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
     return per_cu * cus;
+}
+
+// blocks of quant_row_colmax_kernel (of tx threads) for a tensor, given how many the device keeps resident for it (0: not suited): all
+// resident at once (a second, partly filled round of blocks would idle most of the chip), each with at least 8 rows (fewer where that
+// would leave CUs without a block: a 1024 x 16384 tensor took 24 us with 128 blocks), one row of scratch each
+static int64_t row_colmax_blocks(int64_t rows, int64_t cols, int64_t scratch_bytes, int64_t resident, int tx) {
+    int64_t G = resident < 262144 / tx ? resident : 262144 / tx;
+    int64_t cap = rows / 8;
+    if (cap < 256) cap = rows / 2 < 256 ? rows / 2 : 256;
+    const int64_t room = scratch_bytes / (cols * 2);
+    if (G < 32768 / tx || cap < 128 || room < 128) return 0;
+    if (G > cap) G = cap;
+    return G > room ? room : G;
+}
+// f(threads, vectors a thread, rows in flight) for rows of nvec 16-byte vectors.  From 6144 rows on the blocks of a CU cover each other
+// and fewer rows in flight leave room for more of them (us, two rows / one: 4100 x 4096 11.1 / 11.6, 9000 x 4096 23.7 / 21.9; with a
+// second tensor 2048 x 4096 10.9 / 11.9, 4100 x 4096 16.4 / 16.5, 8192 x 4096 29.2 / 27.3; four / two: 16384 x 2048 33.3 / 27.8).
+template <class F>
+static auto row_colmax_form(int64_t nvec, int64_t rows, F&& f) {
+    using std::integral_constant;
+    const bool tall = rows >= 6144;
+    if (nvec <= 256) return tall ? f(integral_constant<int, 256>{}, integral_constant<int, 1>{}, integral_constant<int, 2>{})
+                                 : f(integral_constant<int, 256>{}, integral_constant<int, 1>{}, integral_constant<int, 4>{});
+    if (nvec <= 512) return tall ? f(integral_constant<int, 256>{}, integral_constant<int, 2>{}, integral_constant<int, 1>{})
+                                 : f(integral_constant<int, 256>{}, integral_constant<int, 2>{}, integral_constant<int, 2>{});
+    if (nvec <= 1024) return f(integral_constant<int, 512>{}, integral_constant<int, 2>{}, integral_constant<int, 1>{});
+    if (nvec <= 2048) return f(integral_constant<int, 512>{}, integral_constant<int, 4>{}, integral_constant<int, 1>{});
+    return f(integral_constant<int, 256>{}, integral_constant<int, 16>{}, integral_constant<int, 1>{});
+}
+template <int FMT, bool ACT>
+static hipError_t launch_row_colmax(const uint16_t* x, const uint16_t* y, int64_t rows, int64_t cols, int64_t ld, int flags, uint8_t* q,
+                                    int64_t ld_out, float* scale_out, uint16_t* part, size_t scratch_bytes, int64_t* G, hipStream_t st) {
+    return row_colmax_form(cols / 8, rows, [&](auto tx, auto nv, auto r) {
+        constexpr auto kern = quant_row_colmax_kernel<FMT, decltype(tx)::value, decltype(nv)::value, decltype(r)::value, ACT>;
+        static CachedInt resident_c;   // per kernel
+        *G = row_colmax_blocks(rows, cols, (int64_t)scratch_bytes, resident_c.get([&] { return resident_blocks(kern, tx); }), tx);
+        if (*G == 0) return hipErrorNotSupported;
+        kern<<<dim3((unsigned)*G), dim3(tx), 0, st>>>(x, rows, cols, ld, flags, q, ld_out, scale_out, part, cols, y, NO_TWIN, nullptr, 0, 0, nullptr, 0, nullptr, nullptr);
+        return hipGetLastError();
+    });
 }
 
 // Rowwise codes + scales of x, and the per-column scales scale_cols[c] =
@@ -1124,41 +1171,13 @@ hipError_t launch_quant_row_colmax(const void* x, int64_t rows, int64_t cols, in
                                    size_t scratch_bytes, hipStream_t st) {
     const int64_t nvec = cols / 8;
     if (cols % 8 != 0 || nvec > 256 * 16 || nvec < 64) return hipErrorNotSupported;
-    const int64_t ld_part = cols;
     const uint16_t* xp = static_cast<const uint16_t*>(x);
     uint16_t* part = static_cast<uint16_t*>(scratch);
-    // G blocks, all resident at once (a second, partly filled round of blocks would
-    // idle most of the chip), each with at least 8 rows (fewer where that would leave CUs without a block:
-    // a 1024 x 16384 tensor took 24 us with 128 blocks), G rows of scratch
     int64_t G = 0;
-#define FP8K_QRC(FMT, NV)                                                                                     \
-    do {                                                                                                      \
-        static CachedInt resident_c;   /* per kernel */                                                       \
-        const int resident = resident_c.get([] { return resident_blocks(quant_row_colmax_kernel<FMT, NV>); }); \
-        G = resident < 1024 ? resident : 1024;                                                                \
-        { /* at least 8 rows per block, but not fewer than 256 blocks while each still has 2 rows */          \
-            int64_t cap = rows / 8;                                                                           \
-            if (cap < 256) cap = rows / 2 < 256 ? rows / 2 : 256;                                             \
-            if (G > cap) G = cap;                                                                             \
-        }                                                                                                     \
-        if ((size_t)(G * ld_part * 2) > scratch_bytes) G = (int64_t)(scratch_bytes / (size_t)(ld_part * 2));  \
-        if (G < 128) return hipErrorNotSupported;                                                             \
-        quant_row_colmax_kernel<FMT, NV><<<dim3((unsigned)G), dim3(256), 0, st>>>(xp, rows, cols, ld, flags, q, ld_out, \
-                                                                                  scale_out, part, ld_part);  \
-    } while (0)
-#define FP8K_QRC_NV(FMT)                 \
-    if (nvec <= 256) FP8K_QRC(FMT, 1);   \
-    else if (nvec <= 512) FP8K_QRC(FMT, 2);  \
-    else if (nvec <= 1024) FP8K_QRC(FMT, 4); \
-    else if (nvec <= 2048) FP8K_QRC(FMT, 8); \
-    else FP8K_QRC(FMT, 16)
-    if (fmt == FMT_E4M3FN) { FP8K_QRC_NV(FMT_E4M3FN); }
-    else { FP8K_QRC_NV(FMT_E5M2); }
-#undef FP8K_QRC_NV
-#undef FP8K_QRC
-    hipError_t e = hipGetLastError();
+    const auto launch = fmt == FMT_E4M3FN ? launch_row_colmax<FMT_E4M3FN, false> : launch_row_colmax<FMT_E5M2, false>;
+    hipError_t e = launch(xp, nullptr, rows, cols, ld, flags, q, ld_out, scale_out, part, scratch_bytes, &G, st);
     if (e != hipSuccess) return e;
-    return launch_colmax_final_scale(part, G, cols, ld_part, fmt, flags, scale_cols, st);
+    return launch_colmax_final_scale(part, G, cols, cols, fmt, flags, scale_cols, st);
 }
 
 
@@ -1188,16 +1207,6 @@ Partials partials_of(void* fold, int64_t rows, int64_t cols, uint8_t* q_col_t, i
     const int64_t fb = fold ? quant_fold_bytes(rows, cols) : 0;
     if (fb) return Partials{static_cast<uint16_t*>(fold), fb, true};
     return Partials{reinterpret_cast<uint16_t*>(q_col_t), cols * ld_col_t, false};
-}
-
-// blocks of quant_row_colmax_kernel for a tensor, given how many the device keeps resident for it (0: not suited)
-int64_t row_colmax_blocks(int64_t rows, int64_t cols, int64_t scratch_bytes, int64_t resident) {
-    int64_t G = resident < 1024 ? resident : 1024;
-    int64_t cap = rows / 8;                       // at least 8 rows per block, but not fewer than 256 blocks while each still has 2 rows
-    if (cap < 256) cap = rows / 2 < 256 ? rows / 2 : 256;
-    if (G > cap) G = cap;
-    if (G * cols * 2 > scratch_bytes) G = scratch_bytes / (cols * 2);
-    return G < 128 ? 0 : G;
 }
 
 // blocks of colmax_partial_kernel for a tensor (0: not suited)
@@ -1272,39 +1281,35 @@ hipError_t colmax_partial_pair(const ColOperand& a, uint16_t* pa, int64_t Ga, co
 // rowwise codes + first-level column maxima of one tensor (b == nullptr) or two of the same width and format in one
 // launch, the maxima going to pa / pb.  Ga / Gb receive the numbers of blocks = rows of partials; 0 blocks: not suited
 // (nothing launched).
-template <int FMT, int NV>
+template <int FMT>
 hipError_t row_colmax_first_level(const RowColOperand& a, const Partials& pa, const RowColOperand* b, const Partials& pb,
                                   int64_t cols, int flags, int64_t* Ga, int64_t* Gb, hipStream_t st) {
-    static CachedInt resident_c;
-    const int64_t resident = resident_c.get([] { return resident_blocks(quant_row_colmax_kernel<FMT, NV>); });
-    // two tensors share the resident blocks in proportion to their rows
-    const int64_t ra = b ? resident * a.rows / (a.rows + b->rows) : resident;
-    *Ga = row_colmax_blocks(a.rows, cols, pa.room, ra);
-    *Gb = b ? row_colmax_blocks(b->rows, cols, pb.room, resident - ra) : 0;
-    if (*Ga == 0 || (b && *Gb == 0)) return hipErrorNotSupported;
-    if (b)
-        quant_row_colmax_kernel<FMT, NV><<<dim3((unsigned)(*Ga + *Gb)), dim3(256), 0, st>>>(
-            static_cast<const uint16_t*>(a.x), a.rows, cols, a.ld, flags, a.q_row, a.ld_row, a.scale_row, pa.at, cols, nullptr,
-            (int)*Ga, static_cast<const uint16_t*>(b->x), b->rows, b->ld, b->q_row, b->ld_row, b->scale_row, pb.at);
-    else
-        quant_row_colmax_kernel<FMT, NV><<<dim3((unsigned)*Ga), dim3(256), 0, st>>>(
-            static_cast<const uint16_t*>(a.x), a.rows, cols, a.ld, flags, a.q_row, a.ld_row, a.scale_row, pa.at, cols);
-    return hipGetLastError();
+    return row_colmax_form(cols / 8, a.rows + (b ? b->rows : 0), [&](auto tx, auto nv, auto r) {
+        constexpr auto kern = quant_row_colmax_kernel<FMT, decltype(tx)::value, decltype(nv)::value, decltype(r)::value>;
+        static CachedInt resident_c;
+        const int64_t resident = resident_c.get([&] { return resident_blocks(kern, tx); });
+        // two tensors share the resident blocks in proportion to their rows
+        const int64_t ra = b ? resident * a.rows / (a.rows + b->rows) : resident;
+        *Ga = row_colmax_blocks(a.rows, cols, pa.room, ra, tx);
+        *Gb = b ? row_colmax_blocks(b->rows, cols, pb.room, resident - ra, tx) : 0;
+        if (*Ga == 0 || (b && *Gb == 0)) return hipErrorNotSupported;
+        if (b)
+            kern<<<dim3((unsigned)(*Ga + *Gb)), dim3(tx), 0, st>>>(
+                static_cast<const uint16_t*>(a.x), a.rows, cols, a.ld, flags, a.q_row, a.ld_row, a.scale_row, pa.at, cols, nullptr,
+                (int)*Ga, static_cast<const uint16_t*>(b->x), b->rows, b->ld, b->q_row, b->ld_row, b->scale_row, pb.at);
+        else
+            kern<<<dim3((unsigned)*Ga), dim3(tx), 0, st>>>(static_cast<const uint16_t*>(a.x), a.rows, cols, a.ld, flags, a.q_row, a.ld_row,
+                                                           a.scale_row, pa.at, cols, nullptr, NO_TWIN, nullptr, 0, 0, nullptr, 0, nullptr, nullptr);
+        return hipGetLastError();
+    });
 }
 
 hipError_t row_colmax_first_level(const RowColOperand& a, const Partials& pa, const RowColOperand* b, const Partials& pb,
                                   int64_t cols, int fmt, int flags, int64_t* Ga, int64_t* Gb, hipStream_t st) {
     const int64_t nvec = cols / 8;
     if (cols % 8 != 0 || nvec > 256 * 16 || nvec < 64) return hipErrorNotSupported;
-#define FP8K_RCF(FMT)                                                                                     \
-    if (nvec <= 256) return row_colmax_first_level<FMT, 1>(a, pa, b, pb, cols, flags, Ga, Gb, st);        \
-    if (nvec <= 512) return row_colmax_first_level<FMT, 2>(a, pa, b, pb, cols, flags, Ga, Gb, st);        \
-    if (nvec <= 1024) return row_colmax_first_level<FMT, 4>(a, pa, b, pb, cols, flags, Ga, Gb, st);       \
-    if (nvec <= 2048) return row_colmax_first_level<FMT, 8>(a, pa, b, pb, cols, flags, Ga, Gb, st);       \
-    return row_colmax_first_level<FMT, 16>(a, pa, b, pb, cols, flags, Ga, Gb, st)
-    if (fmt == FMT_E4M3FN) { FP8K_RCF(FMT_E4M3FN); }
-    FP8K_RCF(FMT_E5M2);
-#undef FP8K_RCF
+    return fmt == FMT_E4M3FN ? row_colmax_first_level<FMT_E4M3FN>(a, pa, b, pb, cols, flags, Ga, Gb, st)
+                             : row_colmax_first_level<FMT_E5M2>(a, pa, b, pb, cols, flags, Ga, Gb, st);
 }
 
 StripOperand strips_of(const RowColOperand& o, int64_t cols, int fmt) {
@@ -1436,38 +1441,13 @@ hipError_t launch_quant_row_col_sigmoid_bwd(const void* dy, const void* y, int64
     if (cols % 8 != 0 || nvec > 256 * 16 || nvec < 64) return hipErrorNotSupported;
     const uint16_t* xp = static_cast<const uint16_t*>(dy);
     const uint16_t* yp = static_cast<const uint16_t*>(y);
-    const int64_t ld_part = cols;
     uint16_t* part = reinterpret_cast<uint16_t*>(q_col_t);          // overwritten by the transposed codes afterwards
     const size_t scratch_bytes = (size_t)cols * (size_t)ld_col_t;   // (the output lies in a workspace, padding included)
     int64_t G = 0;
-#define FP8K_QRCA(FMT, NV)                                                                                    \
-    do {                                                                                                      \
-        static CachedInt resident_c;                                                                          \
-        const int resident = resident_c.get([] { return resident_blocks(quant_row_colmax_kernel<FMT, NV, true>); }); \
-        G = resident < 1024 ? resident : 1024;                                                                \
-        { /* at least 8 rows per block, but not fewer than 256 blocks while each still has 2 rows */          \
-            int64_t cap = rows / 8;                                                                           \
-            if (cap < 256) cap = rows / 2 < 256 ? rows / 2 : 256;                                             \
-            if (G > cap) G = cap;                                                                             \
-        }                                                                                                     \
-        if ((size_t)(G * ld_part * 2) > scratch_bytes) G = (int64_t)(scratch_bytes / (size_t)(ld_part * 2));  \
-        if (G < 128) return hipErrorNotSupported;                                                             \
-        quant_row_colmax_kernel<FMT, NV, true><<<dim3((unsigned)G), dim3(256), 0, st>>>(                       \
-            xp, rows, cols, ld, flags, q_row, ld_row, scale_row, part, ld_part, yp);                          \
-    } while (0)
-#define FP8K_QRCA_NV(FMT)                 \
-    if (nvec <= 256) FP8K_QRCA(FMT, 1);   \
-    else if (nvec <= 512) FP8K_QRCA(FMT, 2);  \
-    else if (nvec <= 1024) FP8K_QRCA(FMT, 4); \
-    else if (nvec <= 2048) FP8K_QRCA(FMT, 8); \
-    else FP8K_QRCA(FMT, 16)
-    if (fmt == FMT_E4M3FN) { FP8K_QRCA_NV(FMT_E4M3FN); }
-    else { FP8K_QRCA_NV(FMT_E5M2); }
-#undef FP8K_QRCA_NV
-#undef FP8K_QRCA
-    hipError_t e = hipGetLastError();
+    const auto launch = fmt == FMT_E4M3FN ? launch_row_colmax<FMT_E4M3FN, true> : launch_row_colmax<FMT_E5M2, true>;
+    hipError_t e = launch(xp, yp, rows, cols, ld, flags, q_row, ld_row, scale_row, part, scratch_bytes, &G, st);
     if (e != hipSuccess) return e;
-    e = launch_colmax_final_scale(part, G, cols, ld_part, fmt, flags, scale_col, st);
+    e = launch_colmax_final_scale(part, G, cols, cols, fmt, flags, scale_col, st);
     if (e != hipSuccess) return e;
     const int64_t gx = (cols + 127) / 128, gy = (rows + 127) / 128;
     const int64_t total = ((gy + 15) / 16) * ((gx + 15) / 16) * 256;

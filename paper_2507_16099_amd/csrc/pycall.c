@@ -3,9 +3,9 @@
  * A decode linear takes 4.5 us on the GPU; its call cost 5.9 us on the host, of which 2.3 are the launch, 1.0 ctypes' conversion of
  * seventeen arguments, 1.0 the shapes and strides of three matrices and 0.4 five addresses.  With this module 3.7 us in all.
  *
- *   Call(address, signature)       callable; signature: one letter per argument, 'p' = pointer (None, an int, or an object with
- *                                  data_ptr()), 'l' = integer (passed in 64 bits); returns the C function's int.  The interpreter
- *                                  lock is released during the call.
+ *   Call(address, signature)       callable; signature: one letter per argument, 't' = tensor (None or an object with data_ptr(): a
+ *                                  number in its place is refused), 'l' = integer (passed in 64 bits); returns the C function's
+ *                                  int.  The interpreter lock is released during the call.
  *   Mat(other)                     callable: (tensor, itemsize) -> (rows, cols, ld) of a 2-D tensor on the GPU that is not empty, with
  *                                  elements of that size and a contiguous last dimension; anything else is left to
  *                                  other(tensor, itemsize).
@@ -82,11 +82,11 @@ static PyObject* call_vectorcall(PyObject* self, PyObject* const* args, size_t n
         return PyErr_Format(PyExc_TypeError, "this function takes %d positional arguments", c->n);
     for (int i = 0; i < c->n; ++i) {
         PyObject* o = args[i];
-        if (PyLong_Check(o)) {
-            a[i] = (L)PyLong_AsUnsignedLongLongMask(o);
-        } else if (c->kind[i] == 'p' && o == Py_None) {
+        if (c->kind[i] == 't' && o == Py_None) {
             a[i] = 0;
-        } else if (c->kind[i] == 'p') {
+        } else if (c->kind[i] == 'l' && PyLong_Check(o)) {
+            a[i] = (L)PyLong_AsUnsignedLongLongMask(o);
+        } else if (c->kind[i] == 't') {
             PyObject* p = PyObject_CallMethodNoArgs(o, s_data_ptr);
             if (!p) return NULL;
             a[i] = (L)PyLong_AsUnsignedLongLongMask(p);
@@ -110,7 +110,7 @@ static PyObject* call_new(PyTypeObject* type, PyObject* args, PyObject* kw) {
     if (!PyArg_ParseTuple(args, "Ks#", &address, &kinds, &n)) return NULL;
     if (address == 0 || n < 1 || n > MAX_ARGS) return PyErr_Format(PyExc_ValueError, "an address and 1 to %d arguments", MAX_ARGS);
     for (Py_ssize_t i = 0; i < n; ++i)
-        if (kinds[i] != 'p' && kinds[i] != 'l') return PyErr_Format(PyExc_ValueError, "argument kinds are 'p' and 'l'");
+        if (kinds[i] != 't' && kinds[i] != 'l') return PyErr_Format(PyExc_ValueError, "argument kinds are 't' and 'l'");
     Call* c = (Call*)type->tp_alloc(type, 0);
     if (!c) return NULL;
     c->vectorcall = call_vectorcall;

@@ -43,11 +43,11 @@ _pycall = _load_pycall()
 
 
 def _fast(function):
-    """A ctypes function of pointers and integers as one that takes tensors for its pointers."""
+    """A ctypes function of pointers and integers, the last pointer a stream, as one that takes tensors (or None) for the others."""
+    kinds = "".join("t" if t is C.c_void_p else "l" for t in function.argtypes[:-1]) + "l"
     if _pycall is not None:
-        kinds = "".join("p" if t is C.c_void_p else "l" for t in function.argtypes)
         return _pycall.Call(C.cast(function, C.c_void_p).value, kinds)
-    return lambda *args: function(*[a.data_ptr() if isinstance(a, torch.Tensor) else a for a in args])
+    return lambda *args: function(*[_ptr(a) if k == "t" else a for k, a in zip(kinds, args)])
 
 
 class Fp8Error(RuntimeError):

@@ -24,7 +24,7 @@ def test_every_argument_arrives(n):
     values = [(-1) ** i * (1 << 40) + i for i in range(n)]
     call = fp8._pycall.Call(C.cast(f, C.c_void_p).value, "l" * n)
     assert call(*values) == -7 and got == [tuple(values)]
-    assert fp8._pycall.Call(C.cast(f, C.c_void_p).value, "p" * n)(*[Pointer(0x7FFF00000000 + i) if i % 3 else None for i in range(n)]) == -7
+    assert fp8._pycall.Call(C.cast(f, C.c_void_p).value, "t" * n)(*[Pointer(0x7FFF00000000 + i) if i % 3 else None for i in range(n)]) == -7
     assert got[1] == tuple(0x7FFF00000000 + i if i % 3 else 0 for i in range(n))
     for wrong in (values + [0], values[:-1], [1.5] * n, ["a"] * n, [None] * n):
         with pytest.raises(TypeError):
@@ -38,11 +38,14 @@ def test_narrow_arguments_and_results_of_the_library():
     for bad in (dict(M=-1), dict(gran=5), dict(fmt=9), dict(ldw=3)):
         M, fmt, gran, ldw = bad.get("M", 2), bad.get("fmt", 0), bad.get("gran", 1), bad.get("ldw", 16)
         args = (4096, M, 16, fmt, gran, 0, 4096, ldw, 0, 4096, 1, 8, 4096, 8, 4096, 16, 0)
+        tensors = [Pointer(a) if a == 4096 else a for a in args]
         want = L.fp8_linear_fwd_prequantized(*args), fp8.fp8_last_error()
         assert want[0] != 0
-        assert (L.fast_linear_fwd_prequantized(*args), fp8.fp8_last_error()) == want, bad
-    with pytest.raises(AttributeError):
-        L.fast_linear_fwd_prequantized(object(), *args[1:])
+        assert (L.fast_linear_fwd_prequantized(*tensors), fp8.fp8_last_error()) == want, bad
+    for i in (0, 6, 9, 12, 14):
+        for wrong in (object(), 4096, 1, True, 1.0):      # a number is no tensor, although it would pass for an address
+            with pytest.raises(AttributeError):
+                L.fast_linear_fwd_prequantized(*tensors[:i], wrong, *tensors[i + 1:])
 
 
 class Tensor:
@@ -85,11 +88,14 @@ def test_without_the_module(monkeypatch):
     seen = []
 
     class Function:
-        argtypes = [C.c_void_p, C.c_int64]
+        argtypes = [C.c_void_p, C.c_int64, C.c_void_p, C.c_void_p]
 
         def __call__(self, *a):
             seen.append(a)
             return 0
 
     t = torch.zeros(3)
-    assert fp8._fast(Function())(t, 5) == 0 and seen == [(t.data_ptr(), 5)]
+    call = fp8._fast(Function())
+    assert call(t, 5, None, 9) == 0 and seen == [(t.data_ptr(), 5, None, 9)]
+    with pytest.raises(AttributeError):
+        call(4096, 5, None, 9)

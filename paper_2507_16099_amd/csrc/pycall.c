@@ -3,9 +3,12 @@
  * A decode linear takes 4.5 us on the GPU; its call cost 5.9 us on the host, of which 2.3 are the launch, 1.0 ctypes' conversion of
  * seventeen arguments, 1.0 the shapes and strides of three matrices and 0.4 five addresses.  With this module 3.7 us in all.
  *
- *   Call(address, signature)       callable; signature: one letter per argument, 't' = tensor (None or an object with data_ptr(): a
- *                                  number in its place is refused), 'l' = integer (passed in 64 bits); returns the C function's
- *                                  int.  The interpreter lock is released during the call.
+ *   Call(address, signature[, other])
+ *                                  callable; signature: one letter per argument, 't' = tensor (None or an object with data_ptr(): a
+ *                                  number in its place is refused), 'l' = integer (an int, passed in 64 bits); returns the C
+ *                                  function's int.  The interpreter lock is released during the call.  Where an integer is not
+ *                                  an int (NumPy's, a 0-d tensor, what else ctypes takes or refuses) the call is left to
+ *                                  other(*arguments); without one it is refused.
  *   Mat(other)                     callable: (tensor, itemsize) -> (rows, cols, ld) of a 2-D tensor on the GPU that is not empty, with
  *                                  elements of that size and a contiguous last dimension; anything else is left to
  *                                  other(tensor, itemsize).
@@ -24,6 +27,7 @@ typedef struct {
     PyObject_HEAD
     vectorcallfunc vectorcall;
     void* address;
+    PyObject* other; /* NULL: none */
     int n;
     char kind[MAX_ARGS];
 } Call;
@@ -80,6 +84,8 @@ static PyObject* call_vectorcall(PyObject* self, PyObject* const* args, size_t n
     int rc;
     if (PyVectorcall_NARGS(nargsf) != c->n || (kwnames && PyTuple_GET_SIZE(kwnames) != 0))
         return PyErr_Format(PyExc_TypeError, "this function takes %d positional arguments", c->n);
+    for (int i = 0; c->other && i < c->n; ++i)
+        if (c->kind[i] == 'l' && !PyLong_Check(args[i])) return PyObject_Vectorcall(c->other, args, (size_t)c->n, NULL);
     for (int i = 0; i < c->n; ++i) {
         PyObject* o = args[i];
         if (c->kind[i] == 't' && o == Py_None) {
@@ -106,8 +112,10 @@ static PyObject* call_new(PyTypeObject* type, PyObject* args, PyObject* kw) {
     unsigned long long address;
     const char* kinds;
     Py_ssize_t n;
+    PyObject* other = NULL;
     if (kw && PyDict_GET_SIZE(kw) != 0) return PyErr_Format(PyExc_TypeError, "Call() takes no keyword arguments");
-    if (!PyArg_ParseTuple(args, "Ks#", &address, &kinds, &n)) return NULL;
+    if (!PyArg_ParseTuple(args, "Ks#|O", &address, &kinds, &n, &other)) return NULL;
+    if (other && !PyCallable_Check(other)) return PyErr_Format(PyExc_TypeError, "a callable is required");
     if (address == 0 || n < 1 || n > MAX_ARGS) return PyErr_Format(PyExc_ValueError, "an address and 1 to %d arguments", MAX_ARGS);
     for (Py_ssize_t i = 0; i < n; ++i)
         if (kinds[i] != 't' && kinds[i] != 'l') return PyErr_Format(PyExc_ValueError, "argument kinds are 't' and 'l'");
@@ -115,9 +123,16 @@ static PyObject* call_new(PyTypeObject* type, PyObject* args, PyObject* kw) {
     if (!c) return NULL;
     c->vectorcall = call_vectorcall;
     c->address = (void*)(uintptr_t)address;
+    Py_XINCREF(other);
+    c->other = other;
     c->n = (int)n;
     for (Py_ssize_t i = 0; i < n; ++i) c->kind[i] = kinds[i];
     return (PyObject*)c;
+}
+
+static void call_dealloc(PyObject* self) {
+    Py_XDECREF(((Call*)self)->other);
+    Py_TYPE(self)->tp_free(self);
 }
 
 static PyTypeObject CallType = {
@@ -127,6 +142,7 @@ static PyTypeObject CallType = {
     .tp_vectorcall_offset = offsetof(Call, vectorcall),
     .tp_call = PyVectorcall_Call,
     .tp_new = call_new,
+    .tp_dealloc = call_dealloc,
 };
 
 /* the two entries of a tuple of two ints */

@@ -45,9 +45,11 @@ _pycall = _load_pycall()
 def _fast(function):
     """A ctypes function of pointers and integers, the last pointer a stream, as one that takes tensors (or None) for the others."""
     kinds = "".join("t" if t is C.c_void_p else "l" for t in function.argtypes[:-1]) + "l"
-    if _pycall is not None:
-        return _pycall.Call(C.cast(function, C.c_void_p).value, kinds)
-    return lambda *args: function(*[_ptr(a) if k == "t" else a for k, a in zip(kinds, args)])
+
+    def through_ctypes(*args):
+        return function(*[_ptr(a) if k == "t" else a for k, a in zip(kinds, args)])
+
+    return through_ctypes if _pycall is None else _pycall.Call(C.cast(function, C.c_void_p).value, kinds, through_ctypes)
 
 
 class Fp8Error(RuntimeError):

@@ -1,6 +1,7 @@
 """The calls without ctypes (csrc/pycall.c): arguments arrive as through ctypes, matrices are looked over as in Python."""
 import ctypes as C
 
+import numpy as np
 import pytest
 import torch
 
@@ -46,6 +47,45 @@ def test_narrow_arguments_and_results_of_the_library():
         for wrong in (object(), 4096, 1, True, 1.0):      # a number is no tensor, although it would pass for an address
             with pytest.raises(AttributeError):
                 L.fast_linear_fwd_prequantized(*tensors[:i], wrong, *tensors[i + 1:])
+
+
+class Index:
+    def __init__(self, value):
+        self.value = value
+
+    def __index__(self):
+        return self.value
+
+
+class Parameter:
+    def __init__(self, value):
+        self._as_parameter_ = value
+
+
+@pytest.mark.parametrize("number", [np.int64, np.int32, np.uint8, torch.tensor, Index, Parameter, bool, lambda v: v + (1 << 32)], ids=lambda f: getattr(f, "__name__", "f"))
+def test_whatever_ctypes_takes_for_an_integer(number):
+    """Sizes, formats, granularities and flags that are no ints: the code and the message that the same numbers give as ints (calls that
+    the library refuses before any device; the refused argument comes last, so that the others have been read)."""
+    L = fp8.load_library()
+    args = [Pointer(4096), 2, 16, 0, 1, 0, Pointer(4096), 16, 0, Pointer(4096), 1, 8, Pointer(4096), 8, Pointer(4096 + 64), 16, 0]      # (workspace not on 256 bytes)
+    want = L.fast_linear_fwd_prequantized(*args), fp8.fp8_last_error()
+    assert want[0] != 0 and "256" in want[1]
+    plain = [a.address if isinstance(a, Pointer) else a for a in args]
+    wide = number is not bool and number(1) == (1 << 32) + 1
+    for i in (1, 2, 3, 4, 5, 7, 8, 10, 11, 13, 15):
+        if isinstance(args[i], Pointer) or (number is bool and args[i] > 1) or (wide and i not in (3, 4, 5, 8, 10)):
+            continue
+        values = [number(a) if k == i else a for k, a in enumerate(args)]
+        assert (L.fp8_linear_fwd_prequantized(*[number(a) if k == i else a for k, a in enumerate(plain)]), fp8.fp8_last_error()) == want, i
+        assert (L.fast_linear_fwd_prequantized(*values), fp8.fp8_last_error()) == want, i
+    for i in (1, 3, 15):
+        for wrong in (1.0, np.float32(1), "1", None, torch.tensor(1.5)):
+            errors = []
+            for call, rest in ((L.fp8_linear_fwd_prequantized, plain), (L.fast_linear_fwd_prequantized, args)):
+                with pytest.raises(Exception) as e:
+                    call(*rest[:i], wrong, *rest[i + 1:])
+                errors.append((e.type, str(e.value)))
+            assert errors[0] == errors[1], (i, wrong)
 
 
 class Tensor:

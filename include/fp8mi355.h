@@ -257,7 +257,9 @@ int fp8_grad_weight_hp(const void* dy, const void* x, int64_t M, int64_t K, int6
  * GEMM streams wq once and is bound by that HBM read.  For a single token (and
  * up to four with M * K <= 16384; K a multiple of 512 and at most 32768, fmt_x
  * e4m3) the activation scales and codes are formed inside that GEMM's launch:
- * one launch instead of two, the same bits, and the workspace is not written.
+ * one launch instead of two, the same codes and scales, and the workspace is not
+ * written.  Up to eight tokens with M * K <= 32768 may take one launch too, where
+ * that is the faster form; whether theirs is written is not part of the contract.
  */
 size_t fp8_linear_prequantized_workspace_bytes(int64_t M, int64_t K);
 int fp8_linear_fwd_prequantized(const void* x, int64_t M, int64_t K, int fmt_x, int gran_x, int flags,

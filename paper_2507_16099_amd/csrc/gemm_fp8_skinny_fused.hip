@@ -323,7 +323,10 @@ static hipError_t launch_skf(const uint16_t* x, int64_t ldx, int row_x, int flag
 // every later workgroup repeats while it streams nothing (28672 x 4096: 4 22.3 / 21.6, 6 22.5 / 22.8; 128256 x 4096: 4 96.7 /
 // 94.1, 6 97.1 / 97.6), nor where the codes leave room for one workgroup per CU only (28672 x 8192: 4 40.1 / 47.9; x 4096: 8 22.7 /
 // 33.4), nor, beyond 16384 activations of more than four tokens, against a narrow weight (8 tokens 1024 x 4096 5.8 / 6.7, 4096 x
-// 4096 7.1 / 7.2, 6144 x 4096 8.7 / 8.9).  The switch DECODE_FUSED: 0 = never, 2 = wherever the kernel applies.
+// 4096 7.1 / 7.2, 6144 x 4096 8.7 / 8.9).  One token, and up to four of 16384 activations together, take one launch whatever the weight:
+// the header promises that their workspace is not written, and programs may share it between streams for that (the longest of them
+// would be as fast or faster in two: 1 token 16384 x 32768 112 / 104, 28672 x 31744 145 / 139, x 32768 180 / 185).  The switch DECODE_FUSED:
+// 0 = never, 2 = wherever the kernel applies.
 hipError_t launch_linear_skinny_fused(const void* x, int64_t ldx, int fmt_x, int row_x, int flags, const uint8_t* b,
                                       int64_t ldb, int fmt_b, const float* scale_b, int row_b, int64_t M, int64_t N,
                                       int64_t K, void* out, int64_t ld_out, hipStream_t st) {
@@ -347,7 +350,9 @@ hipError_t launch_linear_skinny_fused(const void* x, int64_t ldx, int fmt_x, int
     const int ntw = waves / ks;
     const int64_t grid = (groups + ntw - 1) / ntw;
     if (grid > 0x7FFFFFFF) return hipErrorNotSupported;
-    if (mode != 2 && ((M > 4 && (grid > 2 * (int64_t)cus || (M * K > 16384 && N < 8192))) || (waves == 4 && grid > cus && 2 * lds_bytes(4, nw, M, K) > 160 * 1024))) return hipErrorNotSupported;
+    const bool promised = M == 1 || (M <= 4 && M * K <= 16384);
+    const bool later_rounds = M > 4 && (grid > 2 * (int64_t)cus || (M * K > 16384 && N < 8192)), one_a_cu = waves == 4 && grid > cus && 2 * lds_bytes(4, nw, M, K) > 160 * 1024;
+    if (mode != 2 && !promised && (later_rounds || one_a_cu)) return hipErrorNotSupported;
     const uint16_t* xp = static_cast<const uint16_t*>(x);
     uint16_t* op = static_cast<uint16_t*>(out);
     const int m = (int)M, n = (int)N, k = (int)K;

@@ -34,3 +34,18 @@ def test_as_two_launches(N, K):
                 with knobs(DECODE_FUSED=2):
                     assert torch.equal(run(), want), (M, gran, flags)
                 assert torch.equal(run(), want), (M, gran, flags)
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 40, 512), (1, 4096, 4096), (1, 6152, 31744), (1, 16384, 32256), (1, 16384, 32768), (1, 28672, 32768), (2, 6152, 8192), (4, 28672, 4096),
+                                   (3, 1024, 5120)])
+def test_the_workspace_is_not_written(M, N, K):
+    """One token, and up to four of 16384 activations together: programs may hand the same workspace, or none of their own, to
+    calls on several streams."""
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    x = torch.randn((M, K), device="cuda", generator=gen).to(torch.bfloat16)
+    wq = torch.randint(0, 0x70, (N, K), dtype=torch.uint8, device="cuda", generator=gen)
+    sw = torch.ones(N, device="cuda")
+    ws = torch.full((fp8.fp8_linear_prequantized_workspace_bytes(M, K),), 0x5A, dtype=torch.uint8, device="cuda")
+    for gran in (fp8.FP8_ROW, fp8.FP8_TENSOR):
+        fp8.fp8_linear_fwd_prequantized(x, wq, fp8.FP8_E4M3FN, sw, fp8.FP8_ROW, fp8.FP8_E4M3FN, gran, workspace=ws)
+        assert bool((ws == 0x5A).all())

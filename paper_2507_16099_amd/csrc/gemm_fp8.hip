@@ -323,6 +323,22 @@ int best_one_round(const GemmOperands& g, int from, int to, int64_t cus, double*
     }
     return best;
 }
+// Two products in one launch, tile by tile: those of the longer contraction first (long / short: number and us of its tiles), each
+// CU taking the next one that is left.  (ring_cost's whole rounds of an average tile are up to a quarter more where a few long tiles
+// precede many short ones: 4864 x 1024 x 14336 143 / 123 us, 1286 x 1024 x 5120 33 / 25.)
+double tiles_in_turn(int64_t n_long, double t_long, int64_t n_short, double t_short, int64_t cus) {
+    const int64_t q = n_long / cus, r = n_long % cus;
+    const double level[2] = {(double)q * t_long, (double)(q + (r > 0)) * t_long};      // when the CUs are done with the long ones: cus - r, r of them
+    const double ideal = ((double)n_long * t_long + (double)n_short * t_short) / (double)cus;
+    auto fit = [&](double end, double from) { return end < from ? (int64_t)0 : (int64_t)((end - from) / t_short + 1e-6); };
+    double end = 1e30;
+    for (const double from : level) {      // the end lies a whole number of short tiles behind one of the levels
+        double k = ideal > from ? (double)(int64_t)((ideal - from) / t_short) : 0.0;
+        while ((cus - r) * fit(from + k * t_short, level[0]) + r * fit(from + k * t_short, level[1]) < n_short) k += 1.0;
+        if (from + k * t_short < end) end = from + k * t_short;
+    }
+    return end > level[1] ? end : level[1];
+}
 // one round of the 256 x 256 kernels (half tiles, the lower tiles of the persistent one)
 double large_cost(const GemmOperands& g, bool bf16, int64_t cus) {
     const double steps = (double)cdiv(g.K, BK);
@@ -371,6 +387,8 @@ int pick_path(const GemmOperands& g, double* cost, bool any_rounds = false) {
     const int64_t big = cdiv(g.M, 256) * cdiv(g.N, 256);
     if (const int b = knob(KNOB_GEMM_BIG_FROM); b > 0 && cdiv(g.M, 128) * cdiv(g.N, 128) >= b) return 4;
     if (big > cus || !ring) return 4;
+    // (fp32 results are priced as bfloat16 ones are, although they have no lower tiles: without those a sum of less than 512 elements
+    // would go to 128 x 256 tiles more often, 588 x 13024 x 272 19.5 -> 17.8 us, but 3032 x 2592 x 496 15.0 -> 19.2, 875 x 8264 x 416 16.4 -> 19.5)
     double cost_big = large_cost(g, !any_rounds, cus);
     int tile = best_ring(g, nullptr, cus, cost);
     if (tile == RING_128x256 && one_row(g)) tile = RING_256x128;
@@ -450,7 +468,8 @@ int gemm_fp8_wide_choice(const GemmOperands& g, bool bf16) {
 
 // Two products of the same formats and kinds of scale (bfloat16 results) in ONE launch, for the pair dX, dW of a
 // backward step whose products are too small to fill the chip one at a time.  hipErrorNotSupported (nothing launched)
-// where one launch each is estimated to be as fast: the caller then launches them one after the other.
+// where one launch each is estimated to be as fast, on the same kinds of tile, or clearly faster on those that only single products
+// take: the caller then launches them one after the other.
 hipError_t launch_gemm_fp8_pair(const GemmOperands& g1, const GemmOperands& g2, int fmt_a, int fmt_b, int row_a, int row_b,
                                 hipStream_t st) {
     if (g1.M == 0 || g1.N == 0 || g2.M == 0 || g2.N == 0 || knob(KNOB_PAIRS) == 0) return hipErrorNotSupported;
@@ -464,8 +483,25 @@ hipError_t launch_gemm_fp8_pair(const GemmOperands& g1, const GemmOperands& g2, 
     const int64_t cus = compute_units() > 0 ? compute_units() : 256;
     const int tile = best_ring(g1, &g2, cus, &both);
     if (both >= c1 + c2) return hipErrorNotSupported;
+    // Against the tiles that only single products take (one round of them, or of the persistent kernel's lower ones) estimates do not
+    // compare as like with like: a shared launch is up to a fifth faster than its own - no gap between the products, tiles of both to
+    // fill the last round.  Beyond that the two go apart, unless a short contraction leaves mostly prologue and epilogue.  (Backward steps,
+    // us, shared / apart, by estimated ratio.  From 1.2 on, 91 steps, 4 to 16 % faster apart: 3072 x 3072 x 3072 86 / 78, 4352 x 2048 x
+    // 5120 132 / 122, 6144 x 1504 x 5472 163 / 148, 7973 x 1040 x 7984 236 / 203, 1280 x 2048 x 6880 77 / 72.  1.1 .. 1.2: 6144 x 2048 x
+    // 6144 183 / 169, 2560 x 2048 x 8192 119 / 114, but 2048 x 5744 x 1904 67 / 75, 3072 x 3728 x 3024 90 / 97, 1170 x 4016 x 2048 40 / 44.
+    // Below, 50 of 64 faster shared, by up to 15 %.  Up to 1024 tokens or features: 1012 x 4112 x 2848 58.8 / 63.7, 875 x 2656 x 5120 58.3
+    // / 58.4, 768 x 3072 x 4496 53.7 / 51.4.)
     const bool swap = g2.K > g1.K;     // the workgroups of the longer contraction first
-    return launch_gemm_fp8_ring(tile, swap ? g2 : g1, swap ? &g1 : &g2, fmt_a, fmt_b, row_a, row_b, 0, st);
+    const GemmOperands &first = swap ? g2 : g1, &second = swap ? g1 : g2;
+    if (second.K > 1024) {
+        const RingCost& c = kRing[tile];
+        auto tiles = [&](const GemmOperands& g) { return cdiv(g.M, c.tm) * cdiv(g.N, c.tn); };
+        auto each = [&](const GemmOperands& g) { return c.a + (double)cdiv(g.K, BK) * c.b; };
+        pick_path(g1, &c1);      // what they take by themselves
+        pick_path(g2, &c2);
+        if (3.0 + tiles_in_turn(tiles(first), each(first), tiles(second), each(second), cus) > 1.2 * (c1 + c2)) return hipErrorNotSupported;
+    }
+    return launch_gemm_fp8_ring(tile, first, &second, fmt_a, fmt_b, row_a, row_b, 0, st);
 }
 
 }  // namespace fp8k

@@ -343,7 +343,7 @@ double tiles_in_turn(int64_t n_long, double t_long, int64_t n_short, double t_sh
 double large_cost(const GemmOperands& g, bool bf16, int64_t cus) {
     const double steps = (double)cdiv(g.K, BK);
     if (2 * cdiv(g.M, 256) * cdiv(g.N, 256) <= cus) return 7.2 + 0.91 * steps;
-    const int h = bf16 ? one_round_height(g.M, g.N, g.K, cus) : 256;
+    const int h = bf16 ? one_round_height(g, cus) : 256;
     return h == 192 ? 9.0 + 0.97 * steps : h == 224 ? 9.6 + 1.085 * steps : 10.0 + 1.2 * steps;
 }
 // 17 to 32 rows against a wide weight: the ring kernel's tile, or -1 for the few-row kernel, which has no rounds to fill.  64 x 64
@@ -447,6 +447,35 @@ int gemm_mxfp8_ring_choice(const GemmOperands& g, bool plain_scales) {
     const double steps = (double)cdiv(g.K, BK);
     const double cost_big = 2 * big <= cus ? 9.0 + 1.05 * steps : 10.0 + 1.25 * steps;
     return 3.0 + (cost - 3.0) * (plain_scales ? 1.25 : 1.1) <= cost_big ? tile : -1;
+}
+
+// Height of the persistent kernel's tiles for a product whose scales lie in slabs, or 0: one 256 x 256 tile per workgroup.  Over
+// several rounds the height with the least sum of round lengths, a tile of h rows taking a time like h + 100, a last round of up to
+// half of the CUs 0.85 of a full one (us, tile per workgroup / 256 / 224 / 192: 14336 x 4096 x 4096 188 / 184 / 175 / 189; 4096 x
+// 14336 x 4096 189 / 183 / 202 / 194; 8192 x 6144 x 4096 152 / 149 / 166 / 181; 6144 x 4096 x 8192 167 / 165 / 156 / 150; 5000 x
+// 8192 x 2048 83 / 76 / 73 / 82).  256 rows only up to K = 6144, where the tile boundaries count (us, tile per workgroup / 256:
+// 8192 x 16384 x 2048 229 / 211, x 4096 394 / 383, x 8192 760 / 767; 16384 x 16384 x 1024 277 / 243; 16384 x 4096 x 14336 657 / 658).
+// In one round only the lower tiles, where they fill it better (3072 x 4096 x 4096 46.5 / 46.2 / 44.1 / 42.9).  Rows of the output that
+// start between sectors: from K = 8192 on only (us, tile per workgroup / persistent: 8192 x 8184 x 1024 83 / 109, x 4096 219 / 232, 6144 x
+// 4080 x 1024 39 / 51, x 2048 58 / 68, x 4096 98 / 99, x 8192 180 / 174; 5000 x 8184 x 2048 90 / 100, x 8192 288 / 276).
+int gemm_mxfp8_stream_height(const GemmOperands& g) {
+    const int64_t M = g.M, N = g.N, K = g.K;
+    const int sw = knob(KNOB_GEMM_STREAM), forced = knob(KNOB_GEMM_TILE_M);
+    if (forced == 256 || forced == 224 || forced == 192) return forced;
+    const int64_t cus = compute_units() > 0 ? compute_units() : 256, cols = cdiv(N, 256);
+    if (cdiv(M, 256) * cols <= cus && sw < 2) {
+        const int low = one_round_height(g, cus);
+        return low == 256 ? 0 : low;
+    }
+    if (!rows_on_sectors(g) && K < 8192 && sw < 2) return 0;
+    int best = 256;
+    double least = 0.0;
+    for (int tm : {256, 224, 192}) {
+        const int64_t tiles = cdiv(M, tm) * cols, rest = tiles % cus;
+        const double cost = (tm + 100) * ((double)(tiles / cus) + (rest == 0 ? 0.0 : 2 * rest <= cus ? 0.85 : 1.0));
+        if (tm == 256 || cost < least) { best = tm; least = cost; }
+    }
+    return best == 256 && K > 6144 && sw < 2 ? 0 : best;
 }
 
 int gemm_fp8_ring_choice(const GemmOperands& g) {

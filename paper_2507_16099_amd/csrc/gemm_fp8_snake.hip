@@ -478,7 +478,7 @@ static hipError_t launch_sn(const uint8_t* a, int64_t lda, const float* sa, int 
         return launch_sn_part<FA, FB, OUT_F32, ACT, false>(a, lda, sa, row_a, b, ldb, sb, row_b, M, N, K, out, ld_out, tiles_m, tiles_n,
                                                           0, count, st);
     };
-    const int low = sw < 0 && ntiles <= compute_units() ? one_round_height(M, N, K, compute_units()) : 256;
+    const int low = sw < 0 && ntiles <= compute_units() ? one_round_height({a, lda, sa, b, ldb, sb, M, N, K, out, ld_out}, compute_units()) : 256;
     if (stream_ok && low != 256 && knob(KNOB_GEMM_TILE_M) < 0)
         return launch_gemm_fp8_stream(a, lda, FA, sa, row_a, b, ldb, FB, sb, row_b, M, N, K, out, ld_out, (int64_t)((M + low - 1) / low) * tiles_n, low, st);
     if (stream_ok && (sw >= 2 || ntiles > compute_units())) {

@@ -265,31 +265,6 @@ bool gemm_mxfp8_takes_slab_scales(int64_t lda, int64_t ldb, int64_t M, int64_t N
     return mx_slab_possible(lda, ldb, M, N, K);      // both LDS-DMA kernels read them
 }
 
-// Height of the persistent kernel's tiles for a product whose scales lie in slabs, or 0: one 256 x 256 tile per workgroup.  Over
-// several rounds the height with the least sum of round lengths, a tile of h rows taking a time like h + 100, a last round of up to
-// half of the CUs 0.85 of a full one (us, tile per workgroup / 256 / 224 / 192: 14336 x 4096 x 4096 188 / 184 / 175 / 189; 4096 x
-// 14336 x 4096 189 / 183 / 202 / 194; 8192 x 6144 x 4096 152 / 149 / 166 / 181; 6144 x 4096 x 8192 167 / 165 / 156 / 150; 5000 x
-// 8192 x 2048 83 / 76 / 73 / 82).  256 rows only up to K = 6144, where the tile boundaries count (us, tile per workgroup / 256:
-// 8192 x 16384 x 2048 229 / 211, x 4096 394 / 383, x 8192 760 / 767; 16384 x 16384 x 1024 277 / 243; 16384 x 4096 x 14336 657 / 658).
-// In one round only the lower tiles, where they fill it better (3072 x 4096 x 4096 46.5 / 46.2 / 44.1 / 42.9).
-static int mx_stream_height(int64_t M, int64_t N, int64_t K) {
-    const int sw = knob(KNOB_GEMM_STREAM), forced = knob(KNOB_GEMM_TILE_M);
-    if (forced == 256 || forced == 224 || forced == 192) return forced;
-    const int64_t cus = compute_units() > 0 ? compute_units() : 256, cols = (N + 255) / 256;
-    if ((M + 255) / 256 * cols <= cus && sw < 2) {
-        const int low = one_round_height(M, N, K, cus);
-        return low == 256 ? 0 : low;
-    }
-    int best = 256;
-    double least = 0.0;
-    for (int tm : {256, 224, 192}) {
-        const int64_t tiles = (M + tm - 1) / tm * cols, rest = tiles % cus;
-        const double cost = (tm + 100) * ((double)(tiles / cus) + (rest == 0 ? 0.0 : 2 * rest <= cus ? 0.85 : 1.0));
-        if (tm == 256 || cost < least) { best = tm; least = cost; }
-    }
-    return best == 256 && K > 6144 && sw < 2 ? 0 : best;
-}
-
 // ld_ea / ld_eb >= 0: scale rows of that many bytes.  < 0: slabs of sixteen blocks, [K / 512][-ld rows][16 bytes]
 // (for both operands alike; only the LDS-DMA kernels read that layout, so one of them is taken whatever the switches say).
 hipError_t launch_gemm_mxfp8(const uint8_t* a, int64_t lda, int fmt_a, const uint8_t* ea, int64_t ld_ea,
@@ -305,7 +280,7 @@ hipError_t launch_gemm_mxfp8(const uint8_t* a, int64_t lda, int fmt_a, const uin
             return launch_gemm_mxfp8_ring(tile, g, fmt_a, fmt_b, ea, ld_ea, eb, ld_eb, out_f32, st);
     if (slabs) {
         if (knob(KNOB_MX_VARIANT) < 0 && knob(KNOB_GEMM_STREAM) != 0 && gemm_mxfp8_stream_fits(g, -ld_ea, -ld_eb, out_f32))
-            if (const int tm = mx_stream_height(M, N, K); tm > 0) return launch_gemm_mxfp8_stream(g, fmt_a, ea, -ld_ea, fmt_b, eb, -ld_eb, tm, st);
+            if (const int tm = gemm_mxfp8_stream_height(g); tm > 0) return launch_gemm_mxfp8_stream(g, fmt_a, ea, -ld_ea, fmt_b, eb, -ld_eb, tm, st);
         return launch_gemm_mxfp8_snake(a, lda, fmt_a, ea, ld_ea, b, ldb, fmt_b, eb, ld_eb, M, N, K, out, ld_out, out_f32, st);
     }
     if (mx_takes_snake(lda, ldb, M, N, K) && ld_ea < (1 << 23) && ld_eb < (1 << 23))

@@ -142,15 +142,20 @@ inline int ring_waves(int tile, const GemmOperands& g, const GemmOperands* g2, b
 bool gemm_fp8_ring_fits(const GemmOperands& g);
 int gemm_fp8_ring_choice(const GemmOperands& g);      // its tile where a 256 x 256 tile per workgroup is not the better form, else -1
 int gemm_fp8_wide_choice(const GemmOperands& g, bool bf16);      // of a product sent to the 256 x 256 kernels: its wide tile that is the better form, or -1
+// Whether every row of a bfloat16 output starts on 64 bytes.  The persistent kernel writes 64 bytes of a row at a time past the caches;
+// where those straddle two sectors its stores are slower by as much as its tile boundaries gain, and more.
+inline bool rows_on_sectors(const GemmOperands& g) { return (((uintptr_t)g.out | 2 * (uint64_t)g.ld_out) & 63) == 0; }
 // Height of the 256 x 256 kernel's tiles where lower ones cover the product in one round on more than half of the CUs: 192 or 224
 // rows on the persistent kernel, else 256 (us, 256 rows / 224 / 192: 3001 x 4096 x 2048 26.9 / 24.6 / 23.8; 3072 x 4096 x 1024
 // 17.9 / 16.4 / 16.2, x 4096 42.0 / 40.1 / 39.3, x 8192 75.3 / 73.7 / 70.3; 3584 x 4096 x 4096 45.8 / 44.7, x 8192 84.3 / 79.2, of
-// a short contraction equal: x 1024 18.2 / 18.7).
-inline int one_round_height(int64_t M, int64_t N, int64_t K, int64_t cus) {
-    const int64_t cols = (N + 255) / 256;
-    if (2 * ((M + 255) / 256) * cols <= cus || N % 8 || K <= 256) return 256;
-    if ((M + 191) / 192 * cols <= cus) return 192;
-    return (M + 223) / 224 * cols <= cus && K > 1024 ? 224 : 256;
+// a short contraction equal: x 1024 18.2 / 18.7).  Only where rows start on sectors: one round hides nothing of the epilogue, which
+// takes 3 to 10 us longer elsewhere (us, 256 rows / the lower ones, N = 4096, 4064, 4048, 4040: 3072 x N x 1024 18.1 18.9 19.1 18.6 / 15.5
+// 15.5 22.7 24.9, x 4096 44.6 44.0 44.7 42.3 / 38.3 37.6 44.0 47.0; 3584 x N x 2048 26.8 28.8 28.9 29.2 / 26.8 26.4 34.5 38.8).
+inline int one_round_height(const GemmOperands& g, int64_t cus) {
+    const int64_t cols = (g.N + 255) / 256;
+    if (2 * ((g.M + 255) / 256) * cols <= cus || g.N % 8 || !rows_on_sectors(g) || g.K <= 256) return 256;
+    if ((g.M + 191) / 192 * cols <= cus) return 192;
+    return (g.M + 223) / 224 * cols <= cus && g.K > 1024 ? 224 : 256;
 }
 hipError_t launch_gemm_fp8_ring(int tile, const GemmOperands& g1, const GemmOperands* g2, int fmt_a, int fmt_b, int row_a,
                                 int row_b, int mode, hipStream_t st);
@@ -158,6 +163,7 @@ hipError_t launch_gemm_fp8_ring(int tile, const GemmOperands& g1, const GemmOper
 // the block-scaled form (K a multiple of 128; scales as for launch_gemm_mxfp8, g.scale_a / g.scale_b unused)
 bool gemm_mxfp8_ring_fits(const GemmOperands& g, int64_t ld_ea, int64_t ld_eb);
 int gemm_mxfp8_ring_choice(const GemmOperands& g, bool plain_scales);      // a tile, or -1
+int gemm_mxfp8_stream_height(const GemmOperands& g);      // of the persistent kernel's tiles (scales in slabs), or 0: one 256 x 256 tile per workgroup
 hipError_t launch_gemm_mxfp8_ring(int tile, const GemmOperands& g, int fmt_a, int fmt_b, const uint8_t* ea, int64_t ld_ea,
                                   const uint8_t* eb, int64_t ld_eb, int out_f32, hipStream_t st);
 

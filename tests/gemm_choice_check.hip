@@ -9,6 +9,7 @@
 //     act M N K                   the same with the sigmoid
 //     f32 M N K                   the same with fp32 results
 //     large M N K                 of a product sent to the 256 x 256 kernels: its wide tile, or the height of the tiles of one round; large32: fp32 results
+//     slabs M N K                 height of the persistent kernel's tiles for a block-scaled product, 0: one 256 x 256 tile per workgroup
 //     few M N K                   the split of a few-row product
 //     cols rows load              columns of a strip of the shared quantization (the third number is not used)
 //     two M1 N1 K1 M2 N2 K2       the pair of a backward step
@@ -78,11 +79,13 @@ int main(int argc, char** argv) {
             std::printf("%d\n", strip_columns(M, (double)N, g_cus));
         } else if (std::strcmp(kind, "act") == 0) {
             std::printf("%s\n", gemm_fp8_ring_choice(g) >= 0 ? "ring" : "256x256");
+        } else if (std::strcmp(kind, "slabs") == 0) {
+            std::printf("%d rows\n", gemm_mxfp8_stream_height(g));
         } else if (std::strncmp(kind, "large", 5) == 0) {
             const bool bf16 = std::strcmp(kind, "large") == 0;
             const int tile = gemm_fp8_wide_choice(g, bf16);
             if (tile >= 0) std::printf("ring %s\n", names[tile]);
-            else std::printf("%d rows\n", bf16 ? one_round_height(M, N, K, g_cus) : 256);
+            else std::printf("%d rows\n", bf16 ? one_round_height(g, g_cus) : 256);
         } else if (launch_gemm_fp8(g.a, g.lda, 0, nullptr, 1, g.b, g.ldb, 0, nullptr, 1, M, N, K, nullptr, N, std::strcmp(kind, "f32") == 0, nullptr,
                                    std::strcmp(kind, "own") == 0 ? B_WRITTEN : std::strcmp(kind, "strips") == 0 ? B_WRITTEN_IN_STRIPS : B_AT_REST) != hipSuccess) {
             return 3;

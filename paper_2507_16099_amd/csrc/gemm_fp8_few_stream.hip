@@ -214,17 +214,14 @@ static hipError_t launch_fs(const GemmOperands& g, int row_a, int row_b, int out
     return launch(gemm_fp8_few_stream_kernel<FA, FB, PER, false>, attr[0]);
 }
 
-// hipErrorNotSupported (nothing launched) where this form does not apply (few_row_streams).  Each workgroup takes a run of neighbouring
-// tiles where the runs are full on nearly all CUs, rows are whole cache lines and runs do not start whole powers of two apart, else
-// every grid-th tile (us, runs / strided at 16 rows: 28672 x 8192 38.5 / 39.0, 28672 x 4096 21.8 / 23.4, 128256 x 4096 80.6 / 92.4; 8192
-// x 16384 28.5 / 25.0, 11008 x 11008 26.3 / 24.1, 18232 x 15104 52.0 / 45.9, 20312 x 6320 28.3 / 26.6, 24344 x 8112 41.9 / 40.2).
+// hipErrorNotSupported (nothing launched) where this form does not apply (few_row_streams); the order of the tiles: few_row_runs.
 hipError_t launch_gemm_fp8_few_stream(const GemmOperands& g, int fmt_a, int fmt_b, int row_a, int row_b, int out_f32, hipStream_t st) {
     const int64_t cus = compute_units() > 0 ? compute_units() : 256;
     const int forced = knob(KNOB_SKINNY_DMA);
     if (!few_row_streams(g, cus, forced)) return hipErrorNotSupported;
     const int64_t tiles = (g.N + 15) / 16, grid = tiles < cus ? tiles : cus, run = (tiles + grid - 1) / grid;
     const int per = (int)(((g.K + 127) / 128 + fs::WAVES - 1) / fs::WAVES);
-    const bool runs = run > 1 && (forced == 3 || (forced != 2 && 20 * tiles >= 19 * run * grid && g.ldb % 128 == 0 && (run * 16 * g.ldb) % (256 << 10) != 0));
+    const bool runs = few_row_runs(g, cus, forced);
     const int first = runs ? (int)run : 1, step = runs ? 1 : (int)grid;
 #define FP8K_FS(FA_, FB_, PER_) \
     if (fmt_a == FA_ && fmt_b == FB_ && per <= PER_) return launch_fs<FA_, FB_, PER_>(g, row_a, row_b, out_f32, first, step, (int)grid, st)

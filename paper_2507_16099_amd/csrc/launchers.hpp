@@ -278,20 +278,41 @@ inline FewRowForm few_row_form(int64_t M, int64_t N, int64_t K, int nw_forced, i
     return {nw, ks, grid, ks == 4 && nw == 1 && K > 10240 && ((M <= 8 && 2 * grid <= cus) || (M <= 4 && 4 * grid <= 3 * cus))};
 }
 
-// Whether a product of up to 16 rows goes to persistent workgroups (gemm_fp8_few_stream.hip): weights of 96 MiB and more, except those
-// whose rows are whole multiples of 2 KB and whose 32-column groups the few-row kernel's workgroups hold in one round (two of short
-// rows): there its own wavefronts stream as fast and start sooner (us from HBM, few-row / persistent at 5 and 16 rows: 16384 x 8192
-// 21.8 22.3 / 23.1 23.7, 8192 x 14336 19.6 20.2 / 21.2 21.8, 16384 x 14336 35.8 37.2 / 37.8 39.1, 28672 x 4096 20.5 21.6 / 22.0 21.8.
-// Taken: 28672 x 8192 37.7 40.0 / 37.8 38.5, x 6144 30.4 32.1 / 28.4 28.9, 8192 x 16384 30.4 30.7 / 24.6 25.0, 128256 x 4096 94 96 / 79
-// 81, 20312 x 6320 30.6 36.0 / 24.9 26.7, 17352 x 8704 30.1 31.8 / 25.2 25.4, 13320 x 14576 46.9 53.8 / 41.1 43.7).  Smaller weights:
-// equal or slower (80 .. 87 MiB 0.92 .. 1.11 times as fast, 42 .. 64 MiB 0.76 .. 1.06, below 40 MiB 0.76 .. 1.05).  forced: the switch
-// SKINNY_DMA, 2 or 3 = wherever it fits, strided or in runs; 0 or 1 = never.
+// Whether a product of up to 16 rows goes to persistent workgroups (gemm_fp8_few_stream.hip): weights of 96 MiB and more, where the
+// few-row kernel has one of three weaknesses that they have not.  (us from HBM, few-row / persistent, 1 and 16 rows.)
+//  * Rows that are no whole cache lines, of which its short-lived workgroups fetch the shared ones twice: 20000 x 5136 24.6 30.6 / 21.6
+//    23.2, 9728 x 10416 29.6 37.2 / 23.8 25.3, 16384 x 7184 23.7 29.5 / 23.4 24.8, 8192 x 12304 21.3 25.9 / 21.4 23.0.
+//  * Streams that all start a multiple of 4096 bytes apart, rows and parts of K both: they crowd the same channels.  65536 x 4096 57.7
+//    56.3 / 41.9 41.8, 32768 x 8192 57.9 55.1 / 42.9 44.5, 8192 x 16384 30.3 30.7 / 24.8 25.3, 16384 x 16384 57.4 53.7 / 44.8 45.1, 28672 x
+//    16384 92.0 93.6 / 74.5 77.0; with parts of 2048 32768 x 4096 22.3 22.6 / 25.6 26.7, 49152 x 4096 31.6 32.2 / 36.0 37.8.
+//  * A busiest CU with more rows of the weight than the persistent kernel's has, by a fifth (a tenth where K is long enough for the
+//    difference to count): 10240 x 14336 29.0 33.1 / 26.5 27.3, 20480 x 10240 36.0 41.3 / 33.8 34.4, 18432 x 8192 28.0 29.5 / 25.7 25.9,
+//    36864 x 4096 28.3 29.6 / 26.8 26.8; by a seventh 28672 x 6144 29.9 32.2 / 28.8 29.1, x 8192 37.5 40.0 / 37.8 38.9, but x 4096 20.5 21.7
+//    / 22.3 22.4; as many 24576 x 8192 31.4 32.1 / 33.1 34.2, 8192 x 13312 18.5 19.1 / 20.3 20.7, 16384 x 12288 32.7 34.5 / 33.3 34.7.
+// Smaller weights: equal or slower (80 .. 87 MiB 0.92 .. 1.11 times as fast, 42 .. 64 MiB 0.76 .. 1.06, below 40 MiB 0.76 .. 1.05).
+// forced: the switch SKINNY_DMA, 2 or 3 = wherever it fits, strided or in runs; 0 or 1 = never.
 inline bool few_row_streams(const GemmOperands& g, int64_t cus, int forced = -1) {
     const int64_t tiles = (g.N + 15) / 16;
     if (g.M < 1 || g.M > 16 || g.K < 1 || g.K > 16384 || tiles > 32 * cus || g.lda >= (1 << 23) || g.ldb >= (1 << 23)) return false;
     if (forced >= 0) return forced >= 2;
     if (g.N * g.K < (int64_t)96 << 20) return false;
-    return g.ldb % 2048 != 0 || g.K >= 16384 || (g.N + 31) / 32 > (g.K <= 4096 ? 4 : 2) * cus;
+    if (g.ldb % 128 != 0) return true;
+    const FewRowForm f = few_row_form(g.M, g.N, g.K, 0, cus);
+    const int64_t part = ((g.K + 127) / 128 + f.ks - 1) / f.ks * 128;
+    if (g.ldb % 4096 == 0 && part % 4096 == 0) return true;
+    const int64_t few = (f.grid + cus - 1) / cus * (4 / f.ks) * f.nw * 16, persistent = (tiles + cus - 1) / cus * 16;      // rows of the busiest CU
+    return g.K < 6144 ? 5 * few >= 6 * persistent : 10 * few >= 11 * persistent;
+}
+// Which tiles of 16 weight rows a persistent workgroup takes: a run of neighbouring ones, whose loads come from one stretch of the
+// weight, or every grid-th.  Runs where rows are whole cache lines of at most 8 KB and runs do not start multiples of 256 KB apart, with rows of
+// up to 4 KB there too (us, runs / strided at 16 rows: 28672 x 8192 38.9 / 39.3, 28672 x 6144 29.1 / 29.6, 36864 x 4096 26.8 / 29.7, 65536 x
+// 4096 41.8 / 49.2, 128256 x 4096 82.1 / 93.3, 16400 x 8192 23.7 / 25.2; 16384 x 8192 25.0 / 23.9, 8192 x 16384 28.4 / 25.3, 20480 x 10240
+// 35.0 / 34.4, 12288 x 11008 29.4 / 26.6, 28672 x 14336 65.9 / 65.2, 20312 x 6320 28.3 / 26.6, 24344 x 8112 41.9 / 40.2).
+inline bool few_row_runs(const GemmOperands& g, int64_t cus, int forced = -1) {
+    const int64_t tiles = (g.N + 15) / 16, run = (tiles + cus - 1) / cus;
+    if (run < 2) return false;
+    if (forced == 2 || forced == 3) return forced == 3;
+    return g.ldb % 128 == 0 && g.K <= 8192 && (g.K <= 4096 || run * 16 * g.ldb % (256 << 10) != 0);
 }
 hipError_t launch_gemm_fp8_few_stream(const GemmOperands& g, int fmt_a, int fmt_b, int row_a, int row_b, int out_f32, hipStream_t st);
 

@@ -11,6 +11,8 @@
 //     large M N K                 of a product sent to the 256 x 256 kernels: its wide tile, or the height of the tiles of one round; large32: fp32 results
 //     slabs M N K                 height of the persistent kernel's tiles for a block-scaled product, 0: one 256 x 256 tile per workgroup
 //     few M N K                   the split of a few-row product
+//     stream M N K                up to 16 rows: persistent workgroups, strided or in runs, or the few-row kernel; streamld M N K ld: rows of
+//                                 the weight ld bytes apart
 //     cols rows load              columns of a strip of the shared quantization (the third number is not used)
 //     two M1 N1 K1 M2 N2 K2       the pair of a backward step
 // Arguments: CUs=<n>, <switch number>=<value>.
@@ -55,13 +57,13 @@ int main(int argc, char** argv) {
         if (std::strncmp(argv[i], "CUs=", 4) == 0) g_cus = std::atoi(eq + 1);
         else g_knobs[std::atoi(argv[i])] = std::atoi(eq + 1);
     }
-    char kind[8];
+    char kind[16];
     long long M, N, K, M2, N2, K2;
     auto product = [](long long m, long long n, long long k) {
         // (addresses that nothing reads: whole cache lines)
         return GemmOperands{reinterpret_cast<const uint8_t*>(4096), k, nullptr, reinterpret_cast<const uint8_t*>(8192), k, nullptr, m, n, k, nullptr, n};
     };
-    while (std::scanf("%7s %lld %lld %lld", kind, &M, &N, &K) == 4) {
+    while (std::scanf("%15s %lld %lld %lld", kind, &M, &N, &K) == 4) {
         const GemmOperands g = product(M, N, K);
         if (std::strcmp(kind, "two") == 0) {
             if (std::scanf("%lld %lld %lld", &M2, &N2, &K2) != 3) return 2;
@@ -75,6 +77,10 @@ int main(int argc, char** argv) {
             const FewRowForm f = few_row_form(M, N, K, 0, g_cus);
             std::printf("%d %d %lld %s%s\n", f.nw, f.ks, (long long)f.grid, f.deep ? "deep" : "",
                         few_row_hint((int)(M + 15) / 16, f.nw, f.ks) ? " hint" : "");
+        } else if (std::strncmp(kind, "stream", 6) == 0) {
+            GemmOperands w = g;
+            if (std::strcmp(kind, "streamld") == 0 && std::scanf("%lld", &M2) == 1) w.ldb = M2;
+            std::printf("%s\n", !few_row_streams(w, g_cus, g_knobs[KNOB_SKINNY_DMA]) ? "few-row" : few_row_runs(w, g_cus, g_knobs[KNOB_SKINNY_DMA]) ? "runs" : "strided");
         } else if (std::strcmp(kind, "cols") == 0) {
             std::printf("%d\n", strip_columns(M, (double)N, g_cus));
         } else if (std::strcmp(kind, "act") == 0) {

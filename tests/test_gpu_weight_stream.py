@@ -49,7 +49,7 @@ def test_one_launch_decode_of_a_streamed_weight(N, K):
         x = torch.randn((M, K), device="cuda", generator=gen).to(torch.bfloat16)
         run = lambda: fp8.fp8_linear_fwd_prequantized(x, wq, E4, sw, ROW).view(torch.int16)      # noqa: E731
         got = run()
-        with knobs(DECODE_FUSED=0):
+        with knobs(DECODE_FUSED=0, SKINNY_DMA=1):      # (the persistent few-row kernel adds the parts of K in another order)
             assert torch.equal(got, run())
 
 

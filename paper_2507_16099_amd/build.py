@@ -2,16 +2,19 @@
 from __future__ import annotations
 
 import os
+import shlex
 import shutil
 import subprocess
 import sys
 import sysconfig
 from concurrent.futures import ThreadPoolExecutor
+from importlib.machinery import EXTENSION_SUFFIXES
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libfp8mi355.so")
+PYCALL = os.path.join(HERE, "_pycall" + EXTENSION_SUFFIXES[0])      # (names the interpreter that it is for)
 SOURCES = ["quant_kernels.hip", "quant_strips.hip", "tuning.hip", "gemm_fp8.hip", "gemm_fp8_snake.hip", "gemm_fp8_stream.hip", "gemm_fp8_ring.hip", "gemm_mxfp8_ring.hip", "gemm_fp8_skinny.hip", "gemm_fp8_skinny_fused.hip", "gemm_fp8_few_stream.hip", "gemm_bf16_at_b.hip", "gemm_bf16_at_b_snake.hip", "layernorm_quant.hip", "gemm_mxfp8.hip", "gemm_mxfp8_snake.hip", "gemm_mxfp8_stream.hip", "api.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # packed-fp32 instructions are disabled on purpose (the compiler would
@@ -35,19 +38,20 @@ def _compile(src: str) -> str:
     return obj
 
 
-def _compile_pycall() -> None:
-    """The module that makes the Python calls cheap (csrc/pycall.c).  Where the interpreter's headers are missing the binding does
-    without it."""
-    include, cc, out = sysconfig.get_paths()["include"], shutil.which(os.environ.get("CC", "gcc")), os.path.join(HERE, "_pycall.so")
-    if cc is None or not os.path.exists(os.path.join(include, "Python.h")):
-        if os.path.exists(out):
-            os.remove(out)
-        sys.stderr.write("no C compiler or Python.h: calls go through ctypes\n")
-        return
-    r = subprocess.run([cc, "-O2", "-Wall", "-shared", "-fPIC", f"-I{include}", "-o", out, os.path.join(CSRC, "pycall.c")],
-                       capture_output=True, text=True)
-    if r.returncode != 0:
-        raise RuntimeError(f"{cc} failed for pycall.c:\n{r.stdout}\n{r.stderr}")
+def _compile_pycall(out: str = PYCALL) -> None:
+    """The module that makes the Python calls cheap (csrc/pycall.c).  The binding does without it where the interpreter's headers are
+    missing or too old for it."""
+    include, cc = sysconfig.get_paths()["include"], shlex.split(os.environ.get("CC", "gcc"))
+    why = "no C compiler or Python.h"
+    if cc and shutil.which(cc[0]) and os.path.exists(os.path.join(include, "Python.h")):
+        r = subprocess.run([*cc, "-O2", "-Wall", "-shared", "-fPIC", f"-I{include}", "-o", out, os.path.join(CSRC, "pycall.c")],
+                           capture_output=True, text=True)
+        if r.returncode == 0:
+            return
+        why = f"{cc[0]} failed for pycall.c:\n{r.stdout}\n{r.stderr}"
+    if os.path.exists(out):      # of an earlier build
+        os.remove(out)
+    sys.stderr.write(f"{why}: calls go through ctypes\n")
 
 
 def build(verbose: bool = True) -> str:

@@ -9,6 +9,7 @@ an exception is raised.
 from __future__ import annotations
 
 import ctypes as C
+import importlib.machinery
 import importlib.util
 import os
 from dataclasses import dataclass
@@ -26,8 +27,9 @@ _lib = None
 
 
 def _load_pycall():
-    """The module that looks matrices over and calls the library without ctypes (csrc/pycall.c); None where it is not built."""
-    path = os.path.join(_HERE, "_pycall.so")
+    """The module that looks matrices over and calls the library without ctypes (csrc/pycall.c); None where it is not built for this
+    interpreter."""
+    path = os.path.join(_HERE, "_pycall" + importlib.machinery.EXTENSION_SUFFIXES[0])
     if not os.path.exists(path):
         return None
     spec = importlib.util.spec_from_file_location("_pycall", path)

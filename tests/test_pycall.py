@@ -1,10 +1,12 @@
 """The calls without ctypes (csrc/pycall.c): arguments arrive as through ctypes, matrices are looked over as in Python."""
 import ctypes as C
+import sysconfig
 
 import numpy as np
 import pytest
 import torch
 
+import paper_2507_16099_amd.build as build
 import paper_2507_16099_amd.fp8 as fp8
 
 pytestmark = pytest.mark.skipif(fp8._pycall is None, reason="built without the interpreter's headers")
@@ -139,3 +141,17 @@ def test_without_the_module(monkeypatch):
     assert call(t, 5, None, 9) == 0 and seen == [(t.data_ptr(), 5, None, 9)]
     with pytest.raises(AttributeError):
         call(4096, 5, None, 9)
+
+
+def test_built_for_one_interpreter(tmp_path, monkeypatch, capfd):
+    """The file names the interpreter; a build that cannot make it goes on without it and leaves no older one."""
+    assert build.PYCALL.endswith(sysconfig.get_config_var("EXT_SUFFIX")) and fp8._pycall.__file__ == build.PYCALL
+    out = tmp_path / "_pycall.so"
+    for cc in ("false", "no-such-compiler", ""):
+        monkeypatch.setenv("CC", cc)
+        out.write_bytes(b"old")
+        build._compile_pycall(str(out))
+        assert not out.exists() and "calls go through ctypes" in capfd.readouterr().err
+    monkeypatch.setenv("CC", "gcc -g0")
+    build._compile_pycall(str(out))
+    assert out.stat().st_size > 1000

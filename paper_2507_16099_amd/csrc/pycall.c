@@ -84,8 +84,6 @@ static PyObject* call_vectorcall(PyObject* self, PyObject* const* args, size_t n
     int rc;
     if (PyVectorcall_NARGS(nargsf) != c->n || (kwnames && PyTuple_GET_SIZE(kwnames) != 0))
         return PyErr_Format(PyExc_TypeError, "this function takes %d positional arguments", c->n);
-    for (int i = 0; c->other && i < c->n; ++i)
-        if (c->kind[i] == 'l' && !PyLong_Check(args[i])) return PyObject_Vectorcall(c->other, args, (size_t)c->n, NULL);
     for (int i = 0; i < c->n; ++i) {
         PyObject* o = args[i];
         if (c->kind[i] == 't' && o == Py_None) {
@@ -97,6 +95,8 @@ static PyObject* call_vectorcall(PyObject* self, PyObject* const* args, size_t n
             if (!p) return NULL;
             a[i] = (L)PyLong_AsUnsignedLongLongMask(p);
             Py_DECREF(p);
+        } else if (c->other) {
+            return PyObject_Vectorcall(c->other, args, (size_t)c->n, NULL);
         } else {
             return PyErr_Format(PyExc_TypeError, "argument %d: an int is required, not %.100s", i + 1, Py_TYPE(o)->tp_name);
         }

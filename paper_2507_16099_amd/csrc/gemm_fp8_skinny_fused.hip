@@ -322,8 +322,11 @@ static hipError_t launch_skf(const uint16_t* x, int64_t ldx, int row_x, int flag
 // x 4096: 1 5.8, 2 6.4, 4 7.4.)  Not over more workgroups than the chip holds at once for more than four tokens, whose conversion
 // every later workgroup repeats while it streams nothing (28672 x 4096: 4 22.3 / 21.6, 6 22.5 / 22.8; 128256 x 4096: 4 96.7 /
 // 94.1, 6 97.1 / 97.6), nor where the codes leave room for one workgroup per CU only (28672 x 8192: 4 40.1 / 47.9; x 4096: 8 22.7 /
-// 33.4), nor, beyond 16384 activations of more than four tokens, against a narrow weight (8 tokens 1024 x 4096 5.8 / 6.7, 4096 x
-// 4096 7.1 / 7.2, 6144 x 4096 8.7 / 8.9).  One token, and up to four of 16384 activations together, take one launch whatever the weight:
+// 33.4), nor, beyond 16384 activations, against a narrow weight, whose stream is too short for the conversion to hide in: for more than
+// four tokens and up to K = 5120 below 8192 rows of it (8 tokens 1024 x 4096 5.8 / 6.7, 4096 x 4096 7.1 / 7.2, 6144 x 4096 8.7 / 8.9; 4
+// tokens 1024 x 5120 6.3 / 7.1, 3072 x 5120 7.4 / 7.9, 6144 x 4608 -4 %), for up to four below 4096 up to K = 8192 (3 tokens 1024 x 6144 -8 %,
+// 3072 x 6144 -4 %, 4096 x 6144 +1 %, 4 tokens 2048 x 7680 -5 %), below 3072 up to K = 12288 unless rows lie a multiple of 4096 bytes apart,
+// which the two launches take longer for (3 tokens 1024 x 9216 -6 %, 2048 x 10240 -3 %, x 8192 8.0 / 7.6, 2 tokens x 14336 9.9 / 9.7).  One token, and up to four of 16384 activations together, take one launch whatever the weight:
 // the header promises that their workspace is not written, and programs may share it between streams for that (the longest of them
 // would be as fast or faster in two: 1 token 16384 x 32768 112 / 104, 28672 x 31744 145 / 139, x 32768 180 / 185).  The switch DECODE_FUSED:
 // 0 = never, 2 = wherever the kernel applies.
@@ -351,8 +354,10 @@ hipError_t launch_linear_skinny_fused(const void* x, int64_t ldx, int fmt_x, int
     const int64_t grid = (groups + ntw - 1) / ntw;
     if (grid > 0x7FFFFFFF) return hipErrorNotSupported;
     const bool promised = M == 1 || (M <= 4 && M * K <= 16384);
-    const bool later_rounds = M > 4 && (grid > 2 * (int64_t)cus || (M * K > 16384 && N < 8192)), one_a_cu = waves == 4 && grid > cus && 2 * lds_bytes(4, nw, M, K) > 160 * 1024;
-    if (mode != 2 && !promised && (later_rounds || one_a_cu)) return hipErrorNotSupported;
+    const int64_t narrow = M > 4 || K <= 5120 ? 8192 : K < 8192 ? 4096 : K < 12288 && K % 4096 != 0 ? 3072 : 0;
+    const bool later_rounds = M > 4 && grid > 2 * (int64_t)cus, too_narrow = M * K > 16384 && N < narrow;
+    const bool one_a_cu = waves == 4 && grid > cus && 2 * lds_bytes(4, nw, M, K) > 160 * 1024;
+    if (mode != 2 && !promised && (later_rounds || too_narrow || one_a_cu)) return hipErrorNotSupported;
     const uint16_t* xp = static_cast<const uint16_t*>(x);
     uint16_t* op = static_cast<uint16_t*>(out);
     const int m = (int)M, n = (int)N, k = (int)K;

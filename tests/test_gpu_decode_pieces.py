@@ -51,3 +51,18 @@ def test_the_workspace_is_not_written(M, N, K):
     for gran in (fp8.FP8_ROW, fp8.FP8_TENSOR):
         fp8.fp8_linear_fwd_prequantized(x, wq, fp8.FP8_E4M3FN, sw, fp8.FP8_ROW, fp8.FP8_E4M3FN, gran, workspace=ws)
         assert bool((ws == 0x5A).all())
+
+
+@pytest.mark.parametrize("one,M,N,K", [(True, 4, 1024, 4096), (False, 5, 1024, 4096), (False, 4, 1024, 5120), (False, 4, 8184, 5120), (True, 4, 8192, 5120), (False, 3, 4088, 5632),
+                                       (True, 3, 4096, 5632), (True, 3, 2048, 5120), (False, 3, 3064, 9216), (True, 3, 3072, 9216), (True, 3, 1024, 8192), (True, 2, 1024, 12288),
+                                       (False, 2, 1024, 10752), (False, 8, 8184, 4096), (True, 8, 8192, 4096), (False, 5, 32776, 1024), (False, 8, 28672, 4096)])
+def test_one_launch_or_two(one, M, N, K):
+    """Both sides of the lines of the choice: two launches write the workspace."""
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("lines for 256 CUs")
+    gen = torch.Generator(device="cuda").manual_seed(K)
+    x = torch.randn((M, K), device="cuda", generator=gen).to(torch.bfloat16)
+    wq = torch.randint(0, 0x70, (N, K), dtype=torch.uint8, device="cuda", generator=gen)
+    ws = torch.full((fp8.fp8_linear_prequantized_workspace_bytes(M, K),), 0x5A, dtype=torch.uint8, device="cuda")
+    fp8.fp8_linear_fwd_prequantized(x, wq, fp8.FP8_E4M3FN, torch.ones(N, device="cuda"), fp8.FP8_ROW, workspace=ws)
+    assert bool((ws == 0x5A).all()) == one

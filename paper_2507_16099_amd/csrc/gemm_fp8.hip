@@ -309,6 +309,16 @@ int best_ring(const GemmOperands& g, const GemmOperands* g2, int64_t cus, double
     }
     return best;
 }
+// 64 x 192 tiles, which gain least (a twentieth, beyond short contractions), not where a step of them fetches more than one of 96 x 128
+// or 128 x 128 tiles does: beyond K = 1024 where rows are no whole lines, beyond 1536 over an odd number of rows of tiles below 16, of
+// which the last group in the order of tiles holds one or three.  (us from HBM, with these / with the tiles taken instead; partial lines:
+// 172 x 11216 x 5296 42.6 / 35.0, 316 x 8288 x 6944 52.0 / 42.3, 192 x 16024 x 4256 35.6 / 29.5, 105 x 19784 x 2080 19.9 / 18.9, 1222 x 2136
+// x 1264 10.2 / 9.2; odd rows: 900 x 3208 x 12800 54.5 / 46.2, 425 x 6864 x 2688 16.1 / 13.4, 415 x 6056 x 4096 21.3 / 17.7, 576 x 4496 x
+// 2048 11.7 / 9.8, 185 x 12224 x 3072 20.6 / 18.5.)
+bool takes_64x192(const GemmOperands& g) {
+    const int64_t rows = cdiv(g.M, 64);
+    return g.K <= 1024 || (((g.lda | g.ldb) & 127) == 0 && (g.K <= 1536 || rows % 2 == 0 || rows >= 16));
+}
 // Of the tiles [from, to) between those sizes, which make a round fuller: the cheapest that covers the product in one round, if
 // it is cheaper than *cost, else -1.  Over several rounds they are behind (two full ones of 192 x 192 tiles, K = 4096, 65.8 against
 // 66.9 us on 256 x 256, three 96.6 / 87.2; of 96 x 64 21.1 / 17.0).  Not against a weight that is streamed for up to 256 rows:
@@ -318,6 +328,7 @@ int best_one_round(const GemmOperands& g, int from, int to, int64_t cus, double*
     if (g.M <= 256 && stream_weight(g.b, g.ldb, g.N, g.K)) return best;
     for (int t = from; t < to; ++t) {
         if (cdiv(g.M, kRing[t].tm) * cdiv(g.N, kRing[t].tn) > cus) continue;
+        if (t == RING_64x192 && !takes_64x192(g)) continue;
         const double c = ring_cost(t, g, nullptr, cus);
         if (c < *cost) { best = t; *cost = c; }
     }

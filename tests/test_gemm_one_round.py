@@ -34,3 +34,17 @@ def test_never_for_pairs(choose):  # noqa: F811
                                         (1500, 4096, 2048, "192x128"), (2048, 3072, 4096, "128x192"), (512, 4096, 4096, "128x64"), (2048, 4096, 4096, "128x256")])
 def test_the_tile_that_fills_the_round(choose, M, N, K, tile):  # noqa: F811
     assert choose(f"one {M} {N} {K}")[0].split()[1] == tile
+
+
+def test_64x192_tiles_only_where_they_fetch_no_more(choose):  # noqa: F811
+    """Beyond a short contraction not over rows that are no whole cache lines, nor over a few rows of tiles of an odd number."""
+    def tile(kind, M, N, K):
+        return choose(f"{kind} {M} {N} {K}")[0].split()[1]
+
+    for M, N, K in ((172, 11216, 5296), (316, 8288, 6944), (105, 19784, 2080), (1222, 2136, 1264), (425, 6864, 2688), (576, 4496, 2048), (900, 3208, 12800)):
+        assert tile("one", M, N, K) != "64x192", (M, N, K)
+    for kind in ("mx", "mxrows"):
+        for M, N, K in ((425, 6864, 2688), (576, 4496, 2048)):
+            assert "64x192" not in choose(f"{kind} {M} {N} {K}")[0], (kind, M, N, K)
+    for M, N, K in ((1222, 2136, 1024), (576, 4496, 1536), (128, 18776, 2432), (332, 7528, 1920), (1152, 2640, 2432)):
+        assert tile("one", M, N, K) == "64x192", (M, N, K)

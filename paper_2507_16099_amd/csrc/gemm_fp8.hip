@@ -400,14 +400,18 @@ int pick_path(const GemmOperands& g, double* cost, bool any_rounds = false) {
     if (big > cus || !ring) return 4;
     // (fp32 results are priced as bfloat16 ones are, although they have no lower tiles: without those a sum of less than 512 elements
     // would go to 128 x 256 tiles more often, 588 x 13024 x 272 19.5 -> 17.8 us, but 3032 x 2592 x 496 15.0 -> 19.2, 875 x 8264 x 416 16.4 -> 19.5)
-    double cost_big = large_cost(g, !any_rounds, cus);
+    double cost_big = large_cost(g, !any_rounds, cus), operands = 0.0;
     int tile = best_ring(g, nullptr, cus, cost);
     if (tile == RING_128x256 && one_row(g)) tile = RING_256x128;
     if (!any_rounds) {
-        best_one_round(g, RING_WIDE, RING_TILES, cus, &cost_big);
+        // (the lower tiles priced with their operands as ring_cost prices its own: K up to 512 on rather few of them is otherwise left to
+        // them where one round of 128 x 256 tiles is faster; us, lower / 128 x 256: 820 x 8576 x 288 11.0 / 9.2, 329 x 19744 x 384 9.8 / 8.6,
+        // 560 x 12864 x 512 10.2 / 9.3, 834 x 9056 x 448 10.5 / 9.8, 374 x 20576 x 512 9.9 / 9.9)
+        const int h = one_round_height(g, cus);
+        if (best_one_round(g, RING_WIDE, RING_TILES, cus, &cost_big) < 0 && h != 256) operands = 1e-5 * (double)(cdiv(g.M, h) * cdiv(g.N, 256) * (h + 256));
         if (const int t = best_one_round(g, RING_ANY_ROUNDS, RING_WIDE, cus, cost); t >= 0) tile = t;
     }
-    if (*cost <= cost_big) return kPathRing + tile;
+    if (*cost <= cost_big + operands) return kPathRing + tile;
     *cost = cost_big;
     return 4;
 }

@@ -47,3 +47,14 @@ def test_wide_tiles_in_one_round(choose, cus):  # noqa: F811
         assert choose("one 702 11264 10112", "large 702 11264 10112") == ["256x256", "ring 192x192"]
         assert choose("large 782 11008 11920", "large 638 11008 4080") == ["ring 160x256", "ring 160x192"]
     assert not any(a.startswith("ring") for a in choose("large 702 11264 10112", "large 782 11008 11920", GEMM_STREAM=0))
+
+
+def test_short_contractions_priced_with_their_operands(choose):  # noqa: F811
+    """One round of 128 x 256 tiles of a short contraction is not left to rather few lower ones, which are slower there."""
+    slower = ((820, 8576, 288), (329, 19744, 384), (560, 12864, 512), (834, 9056, 448))
+    for kind in ("one", "f32"):
+        for a in choose(*[f"{kind} {M} {N} {K}" for M, N, K in slower]):
+            assert a.startswith(("ring 128x256", "ring 256x128")), (kind, a)
+    faster = ((1294, 6688, 384), (475, 17760, 512), (4671, 2048, 512), (3072, 4096, 1024))
+    assert choose(*[f"one {M} {N} {K}" for M, N, K in faster]) == ["256x256"] * 4
+    assert choose(*[f"large {M} {N} {K}" for M, N, K in faster]) == ["192 rows"] * 4

@@ -322,14 +322,18 @@ static hipError_t launch_skf(const uint16_t* x, int64_t ldx, int row_x, int flag
 // x 4096: 1 5.8, 2 6.4, 4 7.4.)  Not over more workgroups than the chip holds at once for more than four tokens, whose conversion
 // every later workgroup repeats while it streams nothing (28672 x 4096: 4 22.3 / 21.6, 6 22.5 / 22.8; 128256 x 4096: 4 96.7 /
 // 94.1, 6 97.1 / 97.6), nor where the codes leave room for one workgroup per CU only (28672 x 8192: 4 40.1 / 47.9; x 4096: 8 22.7 /
-// 33.4), nor, beyond 16384 activations, against a narrow weight, whose stream is too short for the conversion to hide in: for more than
-// four tokens and up to K = 5120 below 8192 rows of it (8 tokens 1024 x 4096 5.8 / 6.7, 4096 x 4096 7.1 / 7.2, 6144 x 4096 8.7 / 8.9; 4
-// tokens 1024 x 5120 6.3 / 7.1, 3072 x 5120 7.4 / 7.9, 6144 x 4608 -4 %), for up to four below 4096 up to K = 8192 (3 tokens 1024 x 6144 -8 %,
-// 3072 x 6144 -4 %, 4096 x 6144 +1 %, 4 tokens 2048 x 7680 -5 %), below 3072 up to K = 12288 unless rows lie a multiple of 4096 bytes apart,
-// which the two launches take longer for (3 tokens 1024 x 9216 -6 %, 2048 x 10240 -3 %, x 8192 8.0 / 7.6, 2 tokens x 14336 9.9 / 9.7).  One token, and up to four of 16384 activations together, take one launch whatever the weight:
-// the header promises that their workspace is not written, and programs may share it between streams for that (the longest of them
-// would be as fast or faster in two: 1 token 16384 x 32768 112 / 104, 28672 x 31744 145 / 139, x 32768 180 / 185).  The switch DECODE_FUSED:
-// 0 = never, 2 = wherever the kernel applies.
+// 33.4), nor, beyond 16384 activations, against a narrow weight, whose stream is too short for the conversion to hide in:
+//  * more than four tokens below 8192 rows of it (8 tokens 1024 x 4096 5.8 / 6.7, 4096 x 4096 7.1 / 7.2, 6144 x 4096 8.7 / 8.9); below 12288
+//    where a token has less than 3072 activations, a scale each (8 tokens 8624 x 2560 10.1 / 10.9, 10232 x 2560 11.6 / 12.1, 7 tokens 12168
+//    x 2560 11.8 / 12.2, 13584 x 2560 12.4 / 11.2; with one scale for all, which two launches take longer for, 8 tokens 9096 x 2560 13.1 / 11.6);
+//  * up to four tokens below 8192 up to K = 5120 (4 tokens 1024 x 5120 6.3 / 7.1, 3072 x 5120 7.4 / 7.9, 6144 x 4608 -4 %), below 4096 up to
+//    K = 8192 (3 tokens 1024 x 6144 -8 %, 3072 x 6144 -4 %, 4096 x 6144 +1 %, 4 tokens 2048 x 7680 -5 %), below 3072 up to K = 12288 unless
+//    rows lie a multiple of 4096 bytes apart, which the two launches take longer for (3 tokens 1024 x 9216 -6 %, 2048 x 10240 -3 %, x 8192
+//    8.0 / 7.6, 2 tokens x 14336 9.9 / 9.7).
+// One token, and up to four of 16384 activations together, take one launch whatever the weight: the header promises that their
+// workspace is not written, and programs may share it between streams for that (the longest of them would be as fast or faster in
+// two: 1 token 16384 x 32768 112 / 104, 28672 x 31744 145 / 139, x 32768 180 / 185).  The switch DECODE_FUSED: 0 = never, 2 = wherever
+// the kernel applies.
 hipError_t launch_linear_skinny_fused(const void* x, int64_t ldx, int fmt_x, int row_x, int flags, const uint8_t* b,
                                       int64_t ldb, int fmt_b, const float* scale_b, int row_b, int64_t M, int64_t N,
                                       int64_t K, void* out, int64_t ld_out, hipStream_t st) {
@@ -354,7 +358,7 @@ hipError_t launch_linear_skinny_fused(const void* x, int64_t ldx, int fmt_x, int
     const int64_t grid = (groups + ntw - 1) / ntw;
     if (grid > 0x7FFFFFFF) return hipErrorNotSupported;
     const bool promised = M == 1 || (M <= 4 && M * K <= 16384);
-    const int64_t narrow = M > 4 || K <= 5120 ? 8192 : K < 8192 ? 4096 : K < 12288 && K % 4096 != 0 ? 3072 : 0;
+    const int64_t narrow = M > 4 && K < 3072 && row_x ? 12288 : M > 4 || K <= 5120 ? 8192 : K < 8192 ? 4096 : K < 12288 && K % 4096 != 0 ? 3072 : 0;
     const bool later_rounds = M > 4 && grid > 2 * (int64_t)cus, too_narrow = M * K > 16384 && N < narrow;
     const bool one_a_cu = waves == 4 && grid > cus && 2 * lds_bytes(4, nw, M, K) > 160 * 1024;
     if (mode != 2 && !promised && (later_rounds || too_narrow || one_a_cu)) return hipErrorNotSupported;

@@ -281,7 +281,10 @@ inline FewRowForm few_row_form(int64_t M, int64_t N, int64_t K, int nw_forced, i
 // Whether a product of up to 16 rows goes to persistent workgroups (gemm_fp8_few_stream.hip): weights of 96 MiB and more, where the
 // few-row kernel has one of three weaknesses that they have not.  (us from HBM, few-row / persistent, 1 and 16 rows.)
 //  * Rows that are no whole cache lines, of which its short-lived workgroups fetch the shared ones twice: 20000 x 5136 24.6 30.6 / 21.6
-//    23.2, 9728 x 10416 29.6 37.2 / 23.8 25.3, 16384 x 7184 23.7 29.5 / 23.4 24.8, 8192 x 12304 21.3 25.9 / 21.4 23.0.
+//    23.2, 9728 x 10416 29.6 37.2 / 23.8 25.3, 16384 x 7184 23.7 29.5 / 23.4 24.8, 8192 x 12304 21.3 25.9 / 21.4 23.0.  (From the cache,
+//    called again with nothing in between, the few-row kernel is ahead where one round holds the weight: 16384 x 8240 22.1 / 23.5 at 4
+//    rows.)  Not for up to four tokens over two tiles a workgroup, which pass before the ring pays (1, 2, 4 rows from HBM, few-row / persistent:
+//    8192 x 12384 22.9 - 23.5 / 23.5 - 23.5, x 12352 21.1 21.0 - / 22.4 22.4 -, x 16336 - 27.4 - / - 28.9 -; from the cache 16.3 / 18.9).
 //  * Streams that all start a multiple of 4096 bytes apart, rows and parts of K both: they crowd the same channels.  65536 x 4096 57.7
 //    56.3 / 41.9 41.8, 32768 x 8192 57.9 55.1 / 42.9 44.5, 8192 x 16384 30.3 30.7 / 24.8 25.3, 16384 x 16384 57.4 53.7 / 44.8 45.1, 28672 x
 //    16384 92.0 93.6 / 74.5 77.0; with parts of 2048 32768 x 4096 22.3 22.6 / 25.6 26.7, 49152 x 4096 31.6 32.2 / 36.0 37.8.
@@ -296,7 +299,7 @@ inline bool few_row_streams(const GemmOperands& g, int64_t cus, int forced = -1)
     if (g.M < 1 || g.M > 16 || g.K < 1 || g.K > 16384 || tiles > 32 * cus || g.lda >= (1 << 23) || g.ldb >= (1 << 23)) return false;
     if (forced >= 0) return forced >= 2;
     if (g.N * g.K < (int64_t)96 << 20) return false;
-    if (g.ldb % 128 != 0) return true;
+    if (g.ldb % 128 != 0 && (g.M > 4 || tiles > 2 * cus)) return true;
     const FewRowForm f = few_row_form(g.M, g.N, g.K, 0, cus);
     const int64_t part = ((g.K + 127) / 128 + f.ks - 1) / f.ks * 128;
     if (g.ldb % 4096 == 0 && part % 4096 == 0) return true;

@@ -22,6 +22,11 @@ def test_rows_that_are_no_whole_lines(choose):  # noqa: F811
     assert ask(choose, [(16384, 7168), (16384, 7184), (16384, 7168, 7232), (16384, 7168, 7296)]) == ["few-row", "strided", "strided", "few-row"]
 
 
+def test_few_tokens_over_two_tiles_a_workgroup(choose):  # noqa: F811
+    for M, want in ((1, "few-row"), (4, "few-row"), (5, "strided"), (16, "strided")):
+        assert choose(f"stream {M} 8192 12336", f"stream {M} 8200 12336") == [want, "strided"], M
+
+
 def test_streams_a_multiple_of_4096_bytes_apart(choose):  # noqa: F811
     assert ask(choose, [(49152, 4096), (65504, 4096), (65536, 4096)]) == ["few-row", "few-row", "runs"]          # parts of 2048, 4096
     assert ask(choose, [(32736, 8192), (32768, 8192), (24576, 8192)]) == ["few-row", "strided", "few-row"]

@@ -319,16 +319,36 @@ bool takes_64x192(const GemmOperands& g) {
     const int64_t rows = cdiv(g.M, 64);
     return g.K <= 1024 || (((g.lda | g.ldb) & 127) == 0 && (g.K <= 1536 || rows % 2 == 0 || rows >= 16));
 }
+// Tiles that make a round fuller but fetch a weight from HBM more often than those that they replace, one round as well (a served
+// model's weight; what the call itself has quantized comes from the cache, where they are 5 to 15 % ahead).  Over rows that are no whole
+// lines, in place of 256 x 128 ones, 160 x 192 beyond K = 2560 where those are not much fewer, 128 x 192 beyond 6144 unless in two rows of
+// those; 96 x 128 in place of as many 128 x 128 in three rows and more, beyond K = 2048.  (us a forward with the quantization of its
+// activations, the fuller / the others.  160 x 192: 3520 x 1856 x 10416 118 / 102, 448 x 14976 x 7904 81 / 71, 953 x 6784 x 5840 65 / 57, 3502 x
+// 1808 x 4384 55.9 / 49.9, but 2618 x 2312 x 2384 28.2 / 29.7, 972 x 6272 x 3488 36.0 / 37.5; 128 x 192: 976 x 4720 x 10464 94.8 / 88.1, but 409 x
+// 11864 x 4016 39.8 / 42.6, 387 x 11632 x 10448 81 / 88; 96 x 128: 266 x 10280 x 15488 70.9 / 63.2, 279 x 9208 x 7168 36.9 / 34.0, 274 x 8944 x
+// 2688 18.4 / 17.8, but 280 x 9352 x 1648 10 % ahead.)
+bool fetches_more(int t, const GemmOperands& g, int64_t cus) {
+    auto tiles = [&](int i) { return cdiv(g.M, kRing[i].tm) * cdiv(g.N, kRing[i].tn); };
+    const int64_t others = tiles(RING_256x128);
+    switch (t) {
+        case RING_96x128: return g.K > 2048 && g.M > 256 && tiles(t) <= tiles(RING_128x128);
+        case RING_128x192: if (g.K <= 6144 || cdiv(g.M, 256) == 2) return false; break;
+        case RING_160x192: if (g.K <= 2560 || 8 * others < 7 * tiles(t)) return false; break;
+        default: return false;
+    }
+    double cost;
+    return ((g.lda | g.ldb) & 127) != 0 && others <= cus && best_ring(g, nullptr, cus, &cost) == RING_256x128;
+}
 // Of the tiles [from, to) between those sizes, which make a round fuller: the cheapest that covers the product in one round, if
 // it is cheaper than *cost, else -1.  Over several rounds they are behind (two full ones of 192 x 192 tiles, K = 4096, 65.8 against
 // 66.9 us on 256 x 256, three 96.6 / 87.2; of 96 x 64 21.1 / 17.0).  Not against a weight that is streamed for up to 256 rows:
 // there the number of times it is fetched counts (ring_hint, one_row).
-int best_one_round(const GemmOperands& g, int from, int to, int64_t cus, double* cost) {
+int best_one_round(const GemmOperands& g, int from, int to, int64_t cus, double* cost, bool at_rest = false) {
     int best = -1;
     if (g.M <= 256 && stream_weight(g.b, g.ldb, g.N, g.K)) return best;
     for (int t = from; t < to; ++t) {
         if (cdiv(g.M, kRing[t].tm) * cdiv(g.N, kRing[t].tn) > cus) continue;
-        if (t == RING_64x192 && !takes_64x192(g)) continue;
+        if ((t == RING_64x192 && !takes_64x192(g)) || (at_rest && fetches_more(t, g, cus))) continue;
         const double c = ring_cost(t, g, nullptr, cus);
         if (c < *cost) { best = t; *cost = c; }
     }
@@ -408,8 +428,9 @@ int pick_path(const GemmOperands& g, double* cost, bool any_rounds = false) {
         // them where one round of 128 x 256 tiles is faster; us, lower / 128 x 256: 820 x 8576 x 288 11.0 / 9.2, 329 x 19744 x 384 9.8 / 8.6,
         // 560 x 12864 x 512 10.2 / 9.3, 834 x 9056 x 448 10.5 / 9.8, 374 x 20576 x 512 9.9 / 9.9)
         const int h = one_round_height(g, cus);
-        if (best_one_round(g, RING_WIDE, RING_TILES, cus, &cost_big) < 0 && h != 256) operands = 1e-5 * (double)(cdiv(g.M, h) * cdiv(g.N, 256) * (h + 256));
-        if (const int t = best_one_round(g, RING_ANY_ROUNDS, RING_WIDE, cus, cost); t >= 0) tile = t;
+        const bool at_rest = g.b_from == B_AT_REST;
+        if (best_one_round(g, RING_WIDE, RING_TILES, cus, &cost_big, at_rest) < 0 && h != 256) operands = 1e-5 * (double)(cdiv(g.M, h) * cdiv(g.N, 256) * (h + 256));
+        if (const int t = best_one_round(g, RING_ANY_ROUNDS, RING_WIDE, cus, cost, at_rest); t >= 0) tile = t;
     }
     if (*cost <= cost_big + operands) return kPathRing + tile;
     *cost = cost_big;

@@ -48,3 +48,20 @@ def test_64x192_tiles_only_where_they_fetch_no_more(choose):  # noqa: F811
             assert "64x192" not in choose(f"{kind} {M} {N} {K}")[0], (kind, M, N, K)
     for M, N, K in ((1222, 2136, 1024), (576, 4496, 1536), (128, 18776, 2432), (332, 7528, 1920), (1152, 2640, 2432)):
         assert tile("one", M, N, K) == "64x192", (M, N, K)
+
+
+def test_a_weight_at_rest_is_not_fetched_more_often(choose):  # noqa: F811
+    """Both sides of the lines; what the call itself has quantized is in the cache and keeps the fuller round."""
+    def tiles(kind, *shapes):
+        one, large = (choose(*[f"{k} {M} {N} {K}" for M, N, K in shapes]) for k in (kind, "large"))
+        return [(b if a == "256x256" else a).split()[1] for a, b in zip(one, large)]
+
+    slower = ((3520, 1856, 10416), (448, 14976, 7904), (953, 6784, 5840), (3502, 1808, 4384))
+    assert tiles("one", *slower) == ["256x128"] * 4 and tiles("own", *slower) == ["160x192"] * 4
+    # whole lines, a short contraction, clearly fewer tiles
+    assert tiles("one", (3520, 1856, 10496), (448, 14976, 2544), (972, 6272, 3488)) == ["160x192"] * 3
+    assert "128x192" not in tiles("one", (976, 4720, 10464), (4220, 1328, 10448), (975, 5384, 6640))
+    assert tiles("one", (975, 5384, 6128), (975, 5384, 6656), (387, 11632, 10448)) == ["128x192"] * 3
+    assert tiles("one", (279, 9208, 7168), (266, 10280, 15488), (281, 10496, 2064)) == ["128x128"] * 3
+    assert tiles("own", (279, 9208, 7168)) == ["96x128"]
+    assert tiles("one", (280, 9352, 2048), (185, 12224, 3072), (525, 4720, 3712)) == ["96x128"] * 3

@@ -491,9 +491,11 @@ int gemm_mxfp8_ring_choice(const GemmOperands& g, bool plain_scales) {
 // 14336 x 4096 189 / 183 / 202 / 194; 8192 x 6144 x 4096 152 / 149 / 166 / 181; 6144 x 4096 x 8192 167 / 165 / 156 / 150; 5000 x
 // 8192 x 2048 83 / 76 / 73 / 82).  256 rows only up to K = 6144, where the tile boundaries count (us, tile per workgroup / 256:
 // 8192 x 16384 x 2048 229 / 211, x 4096 394 / 383, x 8192 760 / 767; 16384 x 16384 x 1024 277 / 243; 16384 x 4096 x 14336 657 / 658).
-// In one round only the lower tiles, where they fill it better (3072 x 4096 x 4096 46.5 / 46.2 / 44.1 / 42.9).  Rows of the output that
-// start between sectors: from K = 8192 on only (us, tile per workgroup / persistent: 8192 x 8184 x 1024 83 / 109, x 4096 219 / 232, 6144 x
-// 4080 x 1024 39 / 51, x 2048 58 / 68, x 4096 98 / 99, x 8192 180 / 174; 5000 x 8184 x 2048 90 / 100, x 8192 288 / 276).
+// In one round only the lower tiles, where they fill it better (3072 x 4096 x 4096 46.5 / 46.2 / 44.1 / 42.9).  Where rows of the output
+// start between sectors, only lower tiles and from K = 3072 on (us, tile per workgroup / persistent: 8192 x 8184 x 1024 83 / 109, x 4096 219
+// / 232, 6144 x 4080 x 1024 39 / 51, x 2048 58 / 68, x 4096 98 / 99, x 8192 180 / 174; 5000 x 8184 x 2048 90 / 100, x 8192 288 / 276, 6166 x 7856
+// x 3584 175 / 159, 4174 x 2312 x 15872 153 / 136; 350 products over several rounds, relative to a tile per workgroup: of 192 rows K = 2048 ..
+// 2559 +2 %, 3072 .. 3583 -4 %, 4096 .. 8191 -10 %; of 224 rows 2560 .. 3071 +6 %, 3584 .. 8191 -2 to -5 %; of 256 rows +17 %, +8 %, +5 %).
 int gemm_mxfp8_stream_height(const GemmOperands& g) {
     const int64_t M = g.M, N = g.N, K = g.K;
     const int sw = knob(KNOB_GEMM_STREAM), forced = knob(KNOB_GEMM_TILE_M);
@@ -503,7 +505,8 @@ int gemm_mxfp8_stream_height(const GemmOperands& g) {
         const int low = one_round_height(g, cus);
         return low == 256 ? 0 : low;
     }
-    if (!rows_on_sectors(g) && K < 8192 && sw < 2) return 0;
+    const bool sectors = rows_on_sectors(g);
+    if (!sectors && K < 3072 && sw < 2) return 0;
     int best = 256;
     double least = 0.0;
     for (int tm : {256, 224, 192}) {
@@ -511,7 +514,7 @@ int gemm_mxfp8_stream_height(const GemmOperands& g) {
         const double cost = (tm + 100) * ((double)(tiles / cus) + (rest == 0 ? 0.0 : 2 * rest <= cus ? 0.85 : 1.0));
         if (tm == 256 || cost < least) { best = tm; least = cost; }
     }
-    return best == 256 && K > 6144 && sw < 2 ? 0 : best;
+    return best == 256 && (K > 6144 || !sectors) && sw < 2 ? 0 : best;
 }
 
 int gemm_fp8_ring_choice(const GemmOperands& g) {

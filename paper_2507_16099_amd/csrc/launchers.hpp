@@ -148,14 +148,18 @@ inline bool rows_on_sectors(const GemmOperands& g) { return (((uintptr_t)g.out |
 // Height of the 256 x 256 kernel's tiles where lower ones cover the product in one round on more than half of the CUs: 192 or 224
 // rows on the persistent kernel, else 256 (us, 256 rows / 224 / 192: 3001 x 4096 x 2048 26.9 / 24.6 / 23.8; 3072 x 4096 x 1024
 // 17.9 / 16.4 / 16.2, x 4096 42.0 / 40.1 / 39.3, x 8192 75.3 / 73.7 / 70.3; 3584 x 4096 x 4096 45.8 / 44.7, x 8192 84.3 / 79.2, of
-// a short contraction equal: x 1024 18.2 / 18.7).  Only where rows start on sectors: one round hides nothing of the epilogue, which
-// takes 3 to 10 us longer elsewhere (us, 256 rows / the lower ones, N = 4096, 4064, 4048, 4040: 3072 x N x 1024 18.1 18.9 19.1 18.6 / 15.5
-// 15.5 22.7 24.9, x 4096 44.6 44.0 44.7 42.3 / 38.3 37.6 44.0 47.0; 3584 x N x 2048 26.8 28.8 28.9 29.2 / 26.8 26.4 34.5 38.8).
+// a short contraction equal: x 1024 18.2 / 18.7).  One round hides nothing of the epilogue, which takes 3 to 10 us longer where rows do not
+// start on sectors (us, 256 rows / the lower ones, N = 4096, 4064, 4048, 4040: 3072 x N x 1024 18.1 18.9 19.1 18.6 / 15.5 15.5 22.7 24.9, x
+// 4096 44.6 44.0 44.7 42.3 / 38.3 37.6 44.0 47.0; 3584 x N x 2048 26.8 28.8 28.9 29.2 / 26.8 26.4 34.5 38.8).  There 192 rows only from K =
+// 3584 on, 224 from 7168 (200 products, lower ones relative to 256 rows, plain and block-scaled: 192 rows K = 1536 .. 2047 +9 % +15 %, 2560 ..
+// 3071 +1 % +4 %, 3584 .. 4095 -1 % 0, 7168 .. 8191 -2 % -4 %, from 12288 -6 % -7 %; 224 rows 3072 .. 3583 +10 % +16 %, 6144 .. 7167 +2 %
+// +2 %, 8192 .. 12287 -3 % -2 %, from 12288 -4 % -4 %).
 inline int one_round_height(const GemmOperands& g, int64_t cus) {
     const int64_t cols = (g.N + 255) / 256;
-    if (2 * ((g.M + 255) / 256) * cols <= cus || g.N % 8 || !rows_on_sectors(g) || g.K <= 256) return 256;
-    if ((g.M + 191) / 192 * cols <= cus) return 192;
-    return (g.M + 223) / 224 * cols <= cus && g.K > 1024 ? 224 : 256;
+    const bool sectors = rows_on_sectors(g);
+    if (2 * ((g.M + 255) / 256) * cols <= cus || g.N % 8 || g.K <= 256) return 256;
+    if ((g.M + 191) / 192 * cols <= cus) return sectors || g.K >= 3584 ? 192 : 256;
+    return (g.M + 223) / 224 * cols <= cus && g.K > (sectors ? 1024 : 7167) ? 224 : 256;
 }
 hipError_t launch_gemm_fp8_ring(int tile, const GemmOperands& g1, const GemmOperands* g2, int fmt_a, int fmt_b, int row_a,
                                 int row_b, int mode, hipStream_t st);

@@ -10,22 +10,27 @@ ONE_ROUND = [(3072, 4096), (3001, 4096), (2048, 5120), (768, 15104), (1536, 7168
 
 
 def test_lower_tiles_only_where_rows_start_on_sectors(choose):  # noqa: F811
+    """... or where the contraction is long enough for them to pay all the same."""
     for M, N in ONE_ROUND:
-        for K in (512, 1024, 2048, 4096):
-            want = "192 rows" if -(-M // 192) * -(-N // 256) <= 256 else "224 rows" if K > 1024 else "256 rows"
+        low = -(-M // 192) * -(-N // 256) <= 256
+        for K in (512, 1024, 2048, 3456, 3584, 7040, 7168, 12288):
+            want = "192 rows" if low else "224 rows" if K > 1024 else "256 rows"
+            between = want if K >= (3584 if low else 7168) else "256 rows"
             for off, answer in zip((0, 32, 8, 16, 48, 56), choose(*[f"large {M} {N - o} {K}" for o in (0, 32, 8, 16, 48, 56)])):
-                assert answer == (want if off % 32 == 0 else "256 rows"), (M, N - off, K, answer)
-            for q in ("slabs",):
-                a = choose(f"{q} {M} {N} {K}", f"{q} {M} {N - 8} {K}")
-                assert a == [want.replace("256", "0"), "0 rows"], (M, N, K, a)
+                assert answer == (want if off % 32 == 0 else between), (M, N - off, K, answer)
+            a = choose(f"slabs {M} {N} {K}", f"slabs {M} {N - 8} {K}")
+            assert a == [want.replace("256", "0"), between.replace("256", "0")], (M, N, K, a)
 
 
 def test_block_scaled_over_several_rounds(choose):  # noqa: F811
-    for M, N in ((4096, 14336), (8192, 8192), (5000, 8192), (14336, 4096), (6144, 4096)):
-        for K in (1024, 2048, 4096, 6144, 8192):
+    heights = set()
+    for M, N in ((4096, 14336), (8192, 8192), (5000, 8192), (14336, 4096), (6144, 4096), (6166, 7872)):
+        for K in (1024, 2048, 2944, 3072, 4096, 6144, 8192):
             whole, half, odd, odder = (int(a.split()[0]) for a in choose(*[f"slabs {M} {n} {K}" for n in (N, N - 32, N - 8, N - 16)]))
             assert whole == half and (whole > 0 or K > 6144)
-            assert odd == odder == (whole if K >= 8192 else 0), (M, N, K)
+            assert odd == odder == (whole if K >= 3072 and whole != 256 else 0), (M, N, K)
+            heights.add(odd)
+    assert heights == {0, 192, 224}
     # forced forms stay forced
     assert choose("slabs 4096 14328 1024", GEMM_TILE_M=224) == ["224 rows"] and choose("slabs 300 264 1024", GEMM_STREAM=8) != ["0 rows"]
 

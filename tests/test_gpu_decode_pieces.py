@@ -65,5 +65,10 @@ def test_one_launch_or_two(one, M, N, K):
     x = torch.randn((M, K), device="cuda", generator=gen).to(torch.bfloat16)
     wq = torch.randint(0, 0x70, (N, K), dtype=torch.uint8, device="cuda", generator=gen)
     ws = torch.full((fp8.fp8_linear_prequantized_workspace_bytes(M, K),), 0x5A, dtype=torch.uint8, device="cuda")
-    fp8.fp8_linear_fwd_prequantized(x, wq, fp8.FP8_E4M3FN, torch.ones(N, device="cuda"), fp8.FP8_ROW, workspace=ws)
+    sw = torch.ones(N, device="cuda")
+    fp8.fp8_linear_fwd_prequantized(x, wq, fp8.FP8_E4M3FN, sw, fp8.FP8_ROW, workspace=ws)
     assert bool((ws == 0x5A).all()) == one
+    if M <= 4:      # one scale for all tokens, whose two launches are three: always one
+        ws.fill_(0x5A)
+        fp8.fp8_linear_fwd_prequantized(x, wq, fp8.FP8_E4M3FN, sw, fp8.FP8_ROW, fp8.FP8_E4M3FN, fp8.FP8_TENSOR, workspace=ws)
+        assert bool((ws == 0x5A).all())

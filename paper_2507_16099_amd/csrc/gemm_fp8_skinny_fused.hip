@@ -327,10 +327,10 @@ static hipError_t launch_skf(const uint16_t* x, int64_t ldx, int row_x, int flag
 //    where a token has less than 3072 activations, a scale each (8 tokens 8624 x 2560 10.1 / 10.9, 10232 x 2560 11.6 / 12.1, 7 tokens 12168
 //    x 2560 11.8 / 12.2, 13584 x 2560 12.4 / 11.2; with one scale for all, which two launches take longer for, 8 tokens 9096 x 2560 13.1 / 11.6);
 //  * up to four tokens below 8192 up to K = 5120 (4 tokens 1024 x 5120 6.3 / 7.1, 3072 x 5120 7.4 / 7.9, 6144 x 4608 -4 %), below 4096 up to
-//    K = 8192 (3 tokens 1024 x 6144 -8 %, 3072 x 6144 -4 %, 4096 x 6144 +1 %, 4 tokens 2048 x 7680 -5 %), below 3072 up to K = 12288 unless
-//    rows lie a multiple of 4096 bytes apart, which the two launches take longer for (3 tokens 1024 x 9216 -6 %, 2048 x 10240 -3 %, x 8192
-//    8.0 / 7.6, 2 tokens x 14336 9.9 / 9.7); not with one scale for all (4 tokens 3232 x 4608 9.1 / 7.6, 640 x 6144 8.8 / 7.4, 3 tokens 1992 x
-//    6144 9.0 / 7.5, 712 x 8704 10.0 / 7.8).
+//    K = 8192 (3 tokens 1024 x 6144 -8 %, 3072 x 6144 -4 %, 4096 x 6144 +1 %, 4 tokens 2048 x 7680 -5 %), three below 3072 up to K = 10240
+//    unless rows lie a multiple of 4096 bytes apart, which the two launches take longer for (3 tokens 1024 x 9216 -6 %, 2048 x 10240 -3 %, x 8192
+//    8.0 / 7.6, 544 x 10752 8.2 / 8.1, 2 tokens 2112 x 9216 9.4 / 8.9, 2048 x 10752 10.1 / 9.5); not with one scale for all (4 tokens
+//    3232 x 4608 9.1 / 7.6, 640 x 6144 8.8 / 7.4, 3 tokens 1992 x 6144 9.0 / 7.5, 712 x 8704 10.0 / 7.8).
 // One token, and up to four of 16384 activations together, take one launch whatever the weight: the header promises that their
 // workspace is not written, and programs may share it between streams for that (the longest of them would be as fast or faster in
 // two: 1 token 16384 x 32768 112 / 104, 28672 x 31744 145 / 139, x 32768 180 / 185).  The switch DECODE_FUSED: 0 = never, 2 = wherever
@@ -359,7 +359,7 @@ hipError_t launch_linear_skinny_fused(const void* x, int64_t ldx, int fmt_x, int
     const int64_t grid = (groups + ntw - 1) / ntw;
     if (grid > 0x7FFFFFFF) return hipErrorNotSupported;
     const bool promised = M == 1 || (M <= 4 && M * K <= 16384);
-    const int64_t few = !row_x ? 0 : K <= 5120 ? 8192 : K < 8192 ? 4096 : K < 12288 && K % 4096 != 0 ? 3072 : 0;      // for up to four tokens
+    const int64_t few = !row_x ? 0 : K <= 5120 ? 8192 : K < 8192 ? 4096 : M > 2 && K <= 10240 && K % 4096 != 0 ? 3072 : 0;      // for up to four tokens
     const int64_t narrow = M <= 4 ? few : row_x && K < 3072 ? 12288 : 8192;
     const bool later_rounds = M > 4 && grid > 2 * (int64_t)cus, too_narrow = M * K > 16384 && N < narrow;
     const bool one_a_cu = waves == 4 && grid > cus && 2 * lds_bytes(4, nw, M, K) > 160 * 1024;

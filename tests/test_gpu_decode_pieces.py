@@ -55,7 +55,7 @@ def test_the_workspace_is_not_written(M, N, K):
 
 @pytest.mark.parametrize("one,M,N,K", [(True, 4, 1024, 4096), (False, 5, 1024, 4096), (False, 4, 1024, 5120), (False, 4, 8184, 5120), (True, 4, 8192, 5120), (False, 3, 4088, 5632),
                                        (True, 3, 4096, 5632), (True, 3, 2048, 5120), (False, 3, 3064, 9216), (True, 3, 3072, 9216), (True, 3, 1024, 8192), (True, 2, 1024, 12288),
-                                       (False, 2, 1024, 10752), (False, 8, 8184, 4096), (True, 8, 8192, 4096), (False, 5, 32776, 1024), (False, 8, 28672, 4096),
+                                       (True, 2, 1024, 10752), (True, 2, 1024, 9216), (True, 3, 1024, 10752), (False, 8, 8184, 4096), (True, 8, 8192, 4096), (False, 5, 32776, 1024), (False, 8, 28672, 4096),
                                        (False, 8, 12280, 2560), (True, 8, 12288, 2560), (False, 7, 8192, 2560), (True, 6, 8192, 2560), (True, 6, 8192, 3072)])
 def test_one_launch_or_two(one, M, N, K):
     """Both sides of the lines of the choice: two launches write the workspace."""

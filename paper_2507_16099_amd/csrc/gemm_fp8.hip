@@ -322,16 +322,17 @@ bool takes_64x192(const GemmOperands& g) {
 // Tiles that make a round fuller but fetch a weight from HBM more often than those that they replace, one round as well (a served
 // model's weight; what the call itself has quantized comes from the cache, where they are 5 to 15 % ahead).  Over rows that are no whole
 // lines, in place of 256 x 128 ones, 160 x 192 beyond K = 2560 where those are not much fewer, 128 x 192 beyond 6144 unless in two rows of
-// those; 96 x 128 in place of as many 128 x 128 in three rows and more, beyond K = 2048.  (us a forward with the quantization of its
-// activations, the fuller / the others.  160 x 192: 3520 x 1856 x 10416 118 / 102, 448 x 14976 x 7904 81 / 71, 953 x 6784 x 5840 65 / 57, 3502 x
-// 1808 x 4384 55.9 / 49.9, but 2618 x 2312 x 2384 28.2 / 29.7, 972 x 6272 x 3488 36.0 / 37.5; 128 x 192: 976 x 4720 x 10464 94.8 / 88.1, but 409 x
-// 11864 x 4016 39.8 / 42.6, 387 x 11632 x 10448 81 / 88; 96 x 128: 266 x 10280 x 15488 70.9 / 63.2, 279 x 9208 x 7168 36.9 / 34.0, 274 x 8944 x
-// 2688 18.4 / 17.8, but 280 x 9352 x 1648 10 % ahead.)
+// those; in three rows of tiles and more 96 x 128 in place of as many 128 x 128 beyond K = 2048, of nearly as many beyond 4096.  (us a
+// forward with the quantization of its activations, the fuller / the others.  160 x 192: 3520 x 1856 x 10416 118 / 102, 448 x 14976 x 7904
+// 81 / 71, 953 x 6784 x 5840 65 / 57, 3502 x 1808 x 4384 55.9 / 49.9, but 2618 x 2312 x 2384 28.2 / 29.7, 972 x 6272 x 3488 36.0 / 37.5; 128 x 192:
+// 976 x 4720 x 10464 94.8 / 88.1, but 409 x 11864 x 4016 39.8 / 42.6, 387 x 11632 x 10448 81 / 88; 96 x 128: 266 x 10280 x 15488 70.9 / 63.2, 279 x
+// 9208 x 7168 36.9 / 34.0, 274 x 8944 x 2688 18.4 / 17.8, 658 x 4096 x 16064 89 / 79, 644 x 3784 x 8576 41.2 / 37.5, but 280 x 9352 x 1648 10 %
+// ahead, 525 x 4720 x 3712 1 %, 655 x 4480 x 2864 10 %.)
 bool fetches_more(int t, const GemmOperands& g, int64_t cus) {
     auto tiles = [&](int i) { return cdiv(g.M, kRing[i].tm) * cdiv(g.N, kRing[i].tn); };
     const int64_t others = tiles(RING_256x128);
     switch (t) {
-        case RING_96x128: return g.K > 2048 && g.M > 256 && tiles(t) <= tiles(RING_128x128);
+        case RING_96x128: return g.M > 256 && ((g.K > 2048 && tiles(t) <= tiles(RING_128x128)) || (g.K > 4096 && 6 * tiles(t) <= 7 * tiles(RING_128x128)));
         case RING_128x192: if (g.K <= 6144 || cdiv(g.M, 256) == 2) return false; break;
         case RING_160x192: if (g.K <= 2560 || 8 * others < 7 * tiles(t)) return false; break;
         default: return false;

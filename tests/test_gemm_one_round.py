@@ -62,6 +62,6 @@ def test_a_weight_at_rest_is_not_fetched_more_often(choose):  # noqa: F811
     assert tiles("one", (3520, 1856, 10496), (448, 14976, 2544), (972, 6272, 3488)) == ["160x192"] * 3
     assert "128x192" not in tiles("one", (976, 4720, 10464), (4220, 1328, 10448), (975, 5384, 6640))
     assert tiles("one", (975, 5384, 6128), (975, 5384, 6656), (387, 11632, 10448)) == ["128x192"] * 3
-    assert tiles("one", (279, 9208, 7168), (266, 10280, 15488), (281, 10496, 2064)) == ["128x128"] * 3
+    assert tiles("one", (279, 9208, 7168), (266, 10280, 15488), (281, 10496, 2064), (658, 4096, 16064), (644, 3784, 8576)) == ["128x128"] * 5
     assert tiles("own", (279, 9208, 7168)) == ["96x128"]
     assert tiles("one", (280, 9352, 2048), (185, 12224, 3072), (525, 4720, 3712)) == ["96x128"] * 3
